@@ -668,7 +668,8 @@ static RouteScratch route_scratch(int64_t N, int32_t K, int32_t D, moin_dtype dt
     const size_t Kpad = align_up((size_t)K, 256);
     const size_t cn_bytes = align_up(Kpad * 4, 256);
     L.group = route_stream_group(N, K, D, dt == MOIN_BF16);
-    const size_t n_best = L.group > 1 ? (size_t)N : (size_t)ROUTE_SMALL_MAX_N;
+    const size_t n_best = L.group > 1 || dt == MOIN_F32 ? (size_t)std::max<int64_t>(N, ROUTE_SMALL_MAX_N)
+                                                        : (size_t)ROUTE_SMALL_MAX_N;
     L.cnorm = 0;
     L.cinit = cn_bytes;
     L.best = 2 * cn_bytes;
@@ -684,9 +685,10 @@ static int route_launches(moin_ctx *ctx, const void *emb, const void *centroids,
                           int32_t D, moin_dtype dt, const int32_t *slot_of_centroid, uint32_t flags,
                           int32_t *expert_ids, int32_t *centroid_ids, int32_t *counts, char *w,
                           const RouteScratch &L, bool need_cid, bool record, hipStream_t st, int self_clean = 0,
-                          const RoutePlanFuse *fuse = nullptr)
+                          const RoutePlanFuse *fuse = nullptr, void *screen_ws = nullptr)
 {
     RouteArgs a;
+    a.screen_ws = screen_ws;
     a.emb = emb; a.cent = centroids; a.N = N; a.K = K; a.D = D;
     a.is_bf16 = (dt == MOIN_BF16);
     a.slot = slot_of_centroid;
@@ -712,7 +714,7 @@ static int route_launches(moin_ctx *ctx, const void *emb, const void *centroids,
     };
     const bool routed = N > 0 && (a.cid || a.expert_ids);
     if (routed) {
-        if (self_clean != 2 &&
+        if (self_clean != 2 && !screen_ws &&
             run(MOIN_K_ROUTE_AUX, [&] { return launch_centroid_norms(a, st); }) != hipSuccess)
             return MOIN_EHIP;
         if (run(MOIN_K_ROUTE, [&] { return launch_route(a, st); }) != hipSuccess) return MOIN_EHIP;
@@ -807,6 +809,9 @@ static int route_impl(moin_ctx *ctx, const void *emb, const void *centroids, int
                 return MOIN_EHIP;
         }
         if (cap) ctx->route_pinned = 1;
+        if (dt == MOIN_F32)   // distances computed directly: no norms to keep
+            return route_launches(ctx, emb, centroids, N, K, D, dt, slot_of_centroid, flags, expert_ids, centroid_ids,
+                                  counts, static_cast<char *>(ctx->route_buf), L, need_cid, true, st, 2, fuse);
         const int retained = (flags & MOIN_ROUTE_RETAINED_ONLY) ? 1 : 0;
         const bool same = ctx->route_key.valid && ctx->route_key.cent == centroids &&
                           ctx->route_key.slot == (retained ? slot_of_centroid : nullptr) && ctx->route_key.K == K &&
@@ -821,10 +826,21 @@ static int route_impl(moin_ctx *ctx, const void *emb, const void *centroids, int
                               reuse ? 2 : 1, fuse);
     }
     if (fuse) return MOIN_EINVAL;   // (the caller asks for it only where it applies)
-    const int rc = ensure_ws(ctx, L.total, st);
+    // larger fp32 batches: screened by a bf16 product, except where a capture finds the workspace too small
+    size_t screen_at = align_up(L.total, 256), need = L.total;
+    bool screen = dt == MOIN_F32 && route_screen_pays(N, K, D, false);
+    if (screen) {
+        need = screen_at + route_screen_bytes(N, K, D, 0);
+        if (need > ctx->ws_bytes && capturing(st)) {
+            screen = false;
+            need = L.total;
+        }
+    }
+    const int rc = ensure_ws(ctx, need, st);
     if (rc != MOIN_OK) return rc;
-    return route_launches(ctx, emb, centroids, N, K, D, dt, slot_of_centroid, flags, expert_ids,
-                          centroid_ids, counts, static_cast<char *>(ctx->ws), L, need_cid, true, st);
+    char *w = static_cast<char *>(ctx->ws);
+    return route_launches(ctx, emb, centroids, N, K, D, dt, slot_of_centroid, flags, expert_ids, centroid_ids, counts,
+                          w, L, need_cid, true, st, 0, nullptr, screen ? w + screen_at : nullptr);
 }
 
 int moin_route(moin_ctx *ctx, const void *emb, const void *centroids, int64_t N, int32_t K,
@@ -1313,7 +1329,17 @@ int moin_route_topk(moin_ctx *ctx, const void *emb, const void *centroids, int64
     a.retained_only = (flags & MOIN_ROUTE_RETAINED_ONLY) ? 1 : 0;
     a.cid = centroid_ids;
     a.expert_ids = expert_ids;
-    if (timed(ctx, MOIN_K_ROUTE, st, [&] { return launch_route_topk(a, k, dist2, st); }) != hipSuccess)
+    void *ws = nullptr;
+    if (route_screen_pays(N, K, D, true)) {
+        const size_t need = route_screen_bytes(N, K, D, a.is_bf16);
+        // (a capture that finds the workspace too small records the search over all centroids)
+        if (need <= ctx->ws_bytes || !capturing(st)) {
+            const int rc = ensure_ws(ctx, need, st);
+            if (rc != MOIN_OK) return rc;
+            ws = ctx->ws;
+        }
+    }
+    if (timed(ctx, MOIN_K_ROUTE, st, [&] { return launch_route_topk(a, k, dist2, ws, st); }) != hipSuccess)
         return MOIN_EHIP;
     return MOIN_OK;
 }

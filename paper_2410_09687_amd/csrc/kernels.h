@@ -139,17 +139,25 @@ struct RouteArgs {
     const PlanView *plan = nullptr;
     const int *seq_offsets = nullptr, *rank_of_expert = nullptr;
     int *err_word = nullptr;
+    // fp32: route_screen_bytes() of device memory, or null (every distance is then computed directly)
+    void *screen_ws = nullptr;
 };
 constexpr int ROUTE_PLAN_FUSED_MAX_S = 512;  // the grouping rides in the routing launch up to this many queries
 constexpr int ROUTE_SMALL_MAX_N = 4096;  // up to here the K range is split across workgroups
-// true for the batches the small-batch kernel takes (bf16, D a multiple of 64, N <= ROUTE_SMALL_MAX_N)
+// true for the batches that are routed, unpacked and tallied in one launch (N <= ROUTE_SMALL_MAX_N; bf16 with
+// D a multiple of 64, or fp32 with few enough pairs)
 bool route_small_batch(int64_t N, int K, int D, int is_bf16);
 // Workgroups that share one query tile in the large-batch bf16 kernel (1: none).
 int route_stream_group(int64_t N, int K, int D, int is_bf16);
 hipError_t launch_centroid_norms(const RouteArgs &a, hipStream_t stream);
 hipError_t launch_route(const RouteArgs &a, hipStream_t stream);
-// the k (1..8) nearest centroids per query: a.cid / a.expert_ids are [N, k], d2 [N, k] or null
-hipError_t launch_route_topk(const RouteArgs &a, int k, float *d2, hipStream_t stream);
+// Exact nearest centroids behind a bf16 screening product (route_exact.hip): whether it beats computing every
+// distance, and the device memory it needs.
+bool route_screen_pays(int64_t N, int K, int D, bool topk);
+size_t route_screen_bytes(int64_t N, int K, int D, int is_bf16);
+// the k (1..8) nearest centroids per query: a.cid / a.expert_ids are [N, k], d2 [N, k] or null; ws null: every
+// distance is computed
+hipError_t launch_route_topk(const RouteArgs &a, int k, float *d2, void *ws, hipStream_t stream);
 // true when launch_route itself fills a.counts (no histogram launch needed)
 bool route_tallies_counts(const RouteArgs &a);
 hipError_t launch_histogram(const int *ids, int64_t N, int K, int *counts, int zero_first,

@@ -10,41 +10,17 @@
 // ever leaves the workgroup.  A workgroup owns 256 queries and sweeps all
 // centroid tiles in ascending order, which makes "lowest index wins a tie"
 // fall out of a strict '<'.
-// fp32 path: small inputs only; direct sum of squared differences in fp32.
+// fp32 embeddings and the k nearest centroids: route_exact.hip.
 #include <type_traits>
 
 #include "gemm_core.h"
 #include "kernels.h"
-#include "plan_body.h"
+#include "route_finish.h"
 
 namespace moin {
 
 using CfgRoute = GemmCore<256, 256, 64, 4, 2>;      // rows: centroids, cols: queries; any D % 8 == 0
 using CfgRouteSmall = DmaCore<64, 64, 64, 2, 2, 6>;  // small batches: one (centroid chunk, query tile) per workgroup
-
-struct RouteKParams {
-    const char *emb, *cent;
-    const float *cnorm;   // [K padded to a multiple of 256]; +inf for excluded / padding
-    const float *cinit;   // [same]: -||c||^2 / 2, -inf for excluded / padding
-    const int *slot;
-    int *cid;
-    int *expert_ids;
-    unsigned long long *best;
-    int *arrivals;        // small-batch kernel
-    int *counts;          // small batches only: tallied by the finishing workgroup (zeroed beforehand)
-    int64_t N;
-    int K, D;
-    int group;            // streaming kernel: workgroups that share one query tile
-    int64_t n_virtual;    // streaming kernel: work items (query tiles rounded up to 8, times group)
-    int self_clean;       // small-batch kernel: best / arrivals are clean on entry and are left clean
-                          // (the finishing workgroup resets them and zeroes counts before its tally)
-    // small-batch kernel, optional: the finishing workgroup goes on to group the routed batch by
-    // expert (queries = the batch's sequences), so that routing and grouping are one launch
-    int with_plan;
-    PlanView plan;
-    const int *seq_offsets, *rank_of_expert;
-    int *err_word;
-};
 
 __device__ __forceinline__ bool lex_less(float v, int i, float bv, int bi)
 {
@@ -562,7 +538,6 @@ template <class C>
 __global__ __launch_bounds__(C::NT) void route_small_kernel(RouteKParams p, int nqt)
 {
     extern __shared__ __align__(16) char smem[];
-    __shared__ int last_flag;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int wn = wave % C::WN;
@@ -614,36 +589,7 @@ __global__ __launch_bounds__(C::NT) void route_small_kernel(RouteKParams p, int 
             atomicMin(&p.best[q0 + col],
                       ((unsigned long long)float_order_key(bestv[j]) << 32) | (unsigned)besti[j]);
     }
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0)
-        last_flag = (atomicAdd(p.arrivals, 1) == (int)gridDim.x - 1);
-    __syncthreads();
-    if (!last_flag) return;
-    __threadfence();
-    if (p.self_clean && p.counts) {   // (uniform) nobody zeroed the histogram ahead of this launch
-        for (int k = threadIdx.x; k < p.K; k += C::NT) p.counts[k] = 0;
-        __syncthreads();
-    }
-    if (p.self_clean && threadIdx.x == 0) *p.arrivals = 0;
-    for (int q = threadIdx.x; q < (int)p.N; q += C::NT) {
-        const unsigned long long key =
-            __hip_atomic_load(&p.best[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (p.self_clean) p.best[q] = ~0ull;   // ready for the next call
-        const unsigned idx = (unsigned)(key & 0xffffffffu);
-        const int bi = (idx < (unsigned)p.K) ? (int)idx : 0;   // nothing won: centroid 0
-        if (p.cid) p.cid[q] = bi;
-        if (p.expert_ids) p.expert_ids[q] = p.slot ? p.slot[bi] : bi;
-        if (p.counts) atomicAdd(&p.counts[bi], 1);
-    }
-    if constexpr (C::NT == PLAN_THREADS_SMALL) {
-        if (p.with_plan) {
-            // the ids this workgroup has just written are the plan's input
-            __threadfence_block();
-            __syncthreads();
-            plan_body<PLAN_THREADS_SMALL>(p.plan, p.seq_offsets, p.expert_ids, p.rank_of_expert, p.err_word);
-        }
-    }
+    route_finish<C::NT>(p);
 }
 
 // ||c_k||^2 in fp32 (one wave per centroid), +inf for centroids left out of the
@@ -691,39 +637,6 @@ __global__ __launch_bounds__(256) void centroid_norm_kernel(const char *cent, in
     }
 }
 
-// fp32 embeddings: one wave per query, direct sum of squared differences.
-// cnorm is only consulted for its +inf marks (centroids left out of the search).
-__global__ __launch_bounds__(256) void route_f32_kernel(const float *emb, const float *cent,
-                                                        const float *cnorm, int64_t N, int K, int D,
-                                                        const int *slot, int *cid, int *expert_ids)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= N) return;
-    const float *q = emb + i * D;
-    float bv = __builtin_inff();
-    int bi = 0;
-    for (int k = 0; k < K; ++k) {
-        const float *c = cent + (int64_t)k * D;
-        float acc = 0.f;
-        for (int j = lane; j < D; j += 64) {
-            const float d = q[j] - c[j];
-            acc = fmaf(d, d, acc);
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-        if (cnorm[k] == __builtin_inff()) acc = __builtin_inff();
-        if (acc < bv) {
-            bv = acc;
-            bi = k;
-        }
-    }
-    if (lane == 0) {
-        if (cid) cid[i] = bi;
-        if (expert_ids) expert_ids[i] = slot ? slot[bi] : bi;
-    }
-}
-
 // counts[k] = #{i : ids[i] == k}.  Workgroups tally a slice of ids in LDS and
 // flush the non-zero bins with integer atomics (order-independent, exact).
 constexpr int HIST_LDS_BINS = 16384;
@@ -755,154 +668,6 @@ __global__ __launch_bounds__(1024) void histogram_kernel(const int *ids, int64_t
     }
 }
 
-// The k nearest centroids of every query ("Future Works", creating new experts on the
-// fly: a query on the boundary of several clusters may need several adapters).  A
-// request-time call, not the bulk router: one wave per query, the squared distance
-// written out as the sum of squared differences in fp32 (lanes split the dimension; the
-// cross-lane sum ends in a uniform value, so every lane sees the same bits), centroids visited in index
-// order and inserted behind their equals, so equal distances keep index order.
-// Every lane carries the same list of ROUTE_TOPK_MAX entries in registers.
-constexpr int ROUTE_TOPK_MAX = 8;
-constexpr int ROUTE_TOPK_BATCH = 8;
-
-template <bool BF16>
-__global__ __launch_bounds__(256) void route_topk_kernel(const char *__restrict__ emb, const char *__restrict__ cent,
-                                                         int64_t N, int K, int D, int k,
-                                                         const int *__restrict__ slot, int retained_only,
-                                                         int *__restrict__ cid, int *__restrict__ expert_ids,
-                                                         float *__restrict__ d2)
-{
-    constexpr int VPC = BF16 ? 8 : 4;   // values per 16-byte chunk
-    const int lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= N) return;
-    const int64_t row_bytes = (int64_t)D * (16 / VPC);
-    const char *q = emb + i * row_bytes;
-    const int nch = D / VPC;
-    float ld[ROUTE_TOPK_MAX];
-    int li[ROUTE_TOPK_MAX];
-#pragma unroll
-    for (int m = 0; m < ROUTE_TOPK_MAX; ++m) {
-        ld[m] = __builtin_inff();
-        li[m] = -1;
-    }
-    // ROUTE_TOPK_BATCH centroids at a time: their loads are independent and in flight together
-    for (int c0 = 0; c0 < K; c0 += ROUTE_TOPK_BATCH) {
-        float acc[ROUTE_TOPK_BATCH];
-#pragma unroll
-        for (int u = 0; u < ROUTE_TOPK_BATCH; ++u) acc[u] = 0.f;
-        for (int ch = lane; ch < nch; ch += 64) {
-            const uint4 a = *reinterpret_cast<const uint4 *>(q + (int64_t)ch * 16);
-            uint4 b[ROUTE_TOPK_BATCH];
-#pragma unroll
-            for (int u = 0; u < ROUTE_TOPK_BATCH; ++u)   // past the last centroid: the last one again, not inserted
-                b[u] = *reinterpret_cast<const uint4 *>(cent + (int64_t)min(c0 + u, K - 1) * row_bytes + (int64_t)ch * 16);
-            float x[8];
-            if constexpr (BF16) {
-                const uint32_t aw[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    x[2 * t] = bits_f32(aw[t] << 16);
-                    x[2 * t + 1] = bits_f32(aw[t] & 0xFFFF0000u);
-                }
-            } else {
-                x[0] = bits_f32(a.x); x[1] = bits_f32(a.y); x[2] = bits_f32(a.z); x[3] = bits_f32(a.w);
-            }
-#pragma unroll
-            for (int u = 0; u < ROUTE_TOPK_BATCH; ++u) {
-                float y[8];
-                if constexpr (BF16) {
-                    const uint32_t bw[4] = {b[u].x, b[u].y, b[u].z, b[u].w};
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        y[2 * t] = bits_f32(bw[t] << 16);
-                        y[2 * t + 1] = bits_f32(bw[t] & 0xFFFF0000u);
-                    }
-                } else {
-                    y[0] = bits_f32(b[u].x); y[1] = bits_f32(b[u].y); y[2] = bits_f32(b[u].z); y[3] = bits_f32(b[u].w);
-                }
-#pragma unroll
-                for (int t = 0; t < VPC; ++t) {
-                    const float df = x[t] - y[t];
-                    acc[u] += df * df;
-                }
-            }
-        }
-        // The eight sums over the wave in 10 exchanges instead of 48: at distance 32 a lane hands
-        // over the four partial sums its half does not keep, at 16 two, at 8 one; then three plain
-        // butterfly steps.  Lane l ends with the sum of centroid 4 (l / 32) + 2 (l / 16 % 2) + l / 8 % 2,
-        // and a uniform read of one lane of each group gives every lane all eight.
-        static_assert(ROUTE_TOPK_BATCH == 8, "the exchange pattern below is written for eight sums");
-        float v4[4], v2[2], v1;
-        {
-            const bool hi = lane & 32;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float keep = hi ? acc[4 + j] : acc[j], give = hi ? acc[j] : acc[4 + j];
-                v4[j] = keep + __shfl_xor(give, 32);
-            }
-            const bool h16 = lane & 16;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const float keep = h16 ? v4[2 + j] : v4[j], give = h16 ? v4[j] : v4[2 + j];
-                v2[j] = keep + __shfl_xor(give, 16);
-            }
-            const bool h8 = lane & 8;
-            const float keep = h8 ? v2[1] : v2[0], give = h8 ? v2[0] : v2[1];
-            v1 = keep + __shfl_xor(give, 8);
-#pragma unroll
-            for (int off = 4; off > 0; off >>= 1) v1 += __shfl_xor(v1, off);
-        }
-#pragma unroll
-        for (int u = 0; u < ROUTE_TOPK_BATCH; ++u) {
-            acc[u] = bits_f32((uint32_t)__builtin_amdgcn_readlane(
-                (int)__builtin_bit_cast(uint32_t, v1), ((u >> 2) & 1) * 32 + ((u >> 1) & 1) * 16 + (u & 1) * 8));
-            const int c = c0 + u;
-            // (the same for the whole wave) past the end, or a topic left out of the search
-            if (c >= K || (retained_only && slot[c] < 0)) continue;
-            const float d = acc[u];
-            // (every lane holds the same list: the test is the same for the whole wave)
-            if (!(d < ld[ROUTE_TOPK_MAX - 1])) continue;
-            // behind its equals; a NaN compares false and never enters
-#pragma unroll
-            for (int m = ROUTE_TOPK_MAX - 1; m >= 0; --m) {
-                const bool lt = d < ld[m];
-                if (m + 1 < ROUTE_TOPK_MAX) {
-                    ld[m + 1] = lt ? ld[m] : ld[m + 1];
-                    li[m + 1] = lt ? li[m] : li[m + 1];
-                }
-                ld[m] = lt ? d : ld[m];
-                li[m] = lt ? c : li[m];
-            }
-        }
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int m = 0; m < ROUTE_TOPK_MAX; ++m)
-            if (m < k) {
-                const int c = li[m];
-                if (cid) cid[i * k + m] = c;
-                if (expert_ids) expert_ids[i * k + m] = c < 0 ? -1 : (slot ? slot[c] : c);
-                if (d2) d2[i * k + m] = ld[m];
-            }
-    }
-}
-
-hipError_t launch_route_topk(const RouteArgs &a, int k, float *d2, hipStream_t stream)
-{
-    if (a.N <= 0) return hipSuccess;
-    if (k < 1 || k > ROUTE_TOPK_MAX) return hipErrorInvalidValue;
-    const int64_t grid = (a.N + 3) / 4;
-    if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (a.is_bf16)
-        hipLaunchKernelGGL(route_topk_kernel<true>, dim3((unsigned)grid), dim3(256), 0, stream, (const char *)a.emb,
-                           (const char *)a.cent, a.N, a.K, a.D, k, a.slot, a.retained_only, a.cid, a.expert_ids, d2);
-    else
-        hipLaunchKernelGGL(route_topk_kernel<false>, dim3((unsigned)grid), dim3(256), 0, stream, (const char *)a.emb,
-                           (const char *)a.cent, a.N, a.K, a.D, k, a.slot, a.retained_only, a.cid, a.expert_ids, d2);
-    return hipGetLastError();
-}
-
 // Plain fill: a memset node recorded into a captured graph is unreliable on
 // this platform, a kernel is not.
 __global__ __launch_bounds__(256) void fill_i32_kernel(int *dst, int n, int value)
@@ -918,9 +683,15 @@ static hipError_t allow_lds(K kern, int bytes)
                                hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
+hipError_t prepare_route_exact_kernels();
+hipError_t launch_route_direct(const RouteKParams &p, int retained_only, hipStream_t stream);
+hipError_t launch_route_screened(const RouteArgs &a, int k, float *d2, int none_id, void *ws, hipStream_t stream);
+bool route_direct_small(int64_t N, int K, int D, int is_bf16);
+
 hipError_t prepare_route_kernels()
 {
     hipError_t e;
+    if ((e = prepare_route_exact_kernels()) != hipSuccess) return e;
     if ((e = allow_lds(&route_kernel<CfgRoute>, CfgRoute::SMEM_BYTES)) != hipSuccess) return e;
     if ((e = allow_lds(&route_stream4_kernel, r4::SMEM_BYTES)) != hipSuccess) return e;
     return allow_lds(&route_small_kernel<CfgRouteSmall>, CfgRouteSmall::SMEM_BYTES);
@@ -957,20 +728,30 @@ int route_stream_group(int64_t N, int K, int D, int is_bf16)
     return best_g;
 }
 
+// Batches whose routing launch ends in route_finish: request-sized ones, bf16 or -- all distances computed
+// directly -- fp32.
+static bool finishes_itself(const RouteArgs &a)
+{
+    return use_small_route(a) || (!a.is_bf16 && !a.screen_ws && a.N <= ROUTE_SMALL_MAX_N);
+}
+
 bool route_small_batch(int64_t N, int K, int D, int is_bf16)
 {
     RouteArgs a{};
     a.N = N; a.K = K; a.D = D; a.is_bf16 = is_bf16;
-    return use_small_route(a);
+    return use_small_route(a) || route_direct_small(N, K, D, is_bf16);
 }
 
-bool route_tallies_counts(const RouteArgs &a) { return a.N > 0 && a.counts != nullptr && use_small_route(a); }
+bool route_tallies_counts(const RouteArgs &a)
+{
+    return a.N > 0 && a.counts != nullptr && (finishes_itself(a) || (!a.is_bf16 && a.screen_ws));
+}
 
 hipError_t launch_centroid_norms(const RouteArgs &a, hipStream_t stream)
 {
     const int Kpad = (a.K + 255) / 256 * 256;
     // a self-cleaning small-batch call needs the norms only
-    const int64_t nbest = a.self_clean ? 0 : ((use_small_route(a) || a.group > 1) ? a.N : 0);
+    const int64_t nbest = a.self_clean ? 0 : ((finishes_itself(a) || !a.is_bf16 || a.group > 1) ? a.N : 0);
     const int narr = a.self_clean ? 0 : 1;
     hipLaunchKernelGGL(centroid_norm_kernel, dim3((Kpad + 3) / 4), dim3(256), 0, stream,
                        (const char *)a.cent, a.K, Kpad, a.D, a.is_bf16, a.slot, a.retained_only,
@@ -981,37 +762,46 @@ hipError_t launch_centroid_norms(const RouteArgs &a, hipStream_t stream)
 hipError_t launch_route(const RouteArgs &a, hipStream_t stream)
 {
     if (a.N <= 0) return hipSuccess;
-    if (a.is_bf16) {
-        RouteKParams p;
-        p.emb = (const char *)a.emb; p.cent = (const char *)a.cent;
-        p.cnorm = a.cnorm; p.cinit = a.cinit; p.slot = a.slot; p.cid = a.cid; p.expert_ids = a.expert_ids;
-        p.best = a.best; p.arrivals = a.arrivals;
-        p.counts = use_small_route(a) ? a.counts : nullptr;
-        p.N = a.N; p.K = a.K; p.D = a.D;
-        p.group = a.group > 1 ? a.group : 1;
-        p.self_clean = use_small_route(a) ? a.self_clean : 0;
-        static_assert(ROUTE_PLAN_FUSED_MAX_S <= 2 * PLAN_THREADS_SMALL && CfgRouteSmall::NT == PLAN_THREADS_SMALL,
-                      "the grouping that rides in the small-batch launch is the four-wave one");
-        if (a.plan && !(use_small_route(a) && a.self_clean && a.expert_ids && a.seq_offsets && a.err_word &&
-                        a.N <= ROUTE_PLAN_FUSED_MAX_S && a.plan->S == (int)a.N))
-            return hipErrorInvalidValue;
-        p.with_plan = a.plan ? 1 : 0;
-        if (p.with_plan) {
-            p.plan = *a.plan;
-            p.seq_offsets = a.seq_offsets; p.rank_of_expert = a.rank_of_expert; p.err_word = a.err_word;
-        } else {
-            p.plan = PlanView{};
-            p.seq_offsets = p.rank_of_expert = nullptr; p.err_word = nullptr;
-        }
-        if (use_small_route(a)) {
-            using C = CfgRouteSmall;
-            const int nqt = (int)((a.N + C::BN - 1) / C::BN);
-            const int64_t grid = (int64_t)nqt * ((a.K + C::BM - 1) / C::BM);
-            if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-            hipLaunchKernelGGL(route_small_kernel<C>, dim3((unsigned)grid), dim3(C::NT),
-                               C::SMEM_BYTES, stream, p, nqt);
-            return hipGetLastError();
-        }
+    if (!a.is_bf16 && a.screen_ws) return launch_route_screened(a, 1, nullptr, 0, a.screen_ws, stream);
+    RouteKParams p;
+    p.emb = (const char *)a.emb; p.cent = (const char *)a.cent;
+    p.cnorm = a.cnorm; p.cinit = a.cinit; p.slot = a.slot; p.cid = a.cid; p.expert_ids = a.expert_ids;
+    p.best = a.best; p.arrivals = a.arrivals;
+    p.finish = finishes_itself(a) ? 1 : 0;
+    p.counts = p.finish ? a.counts : nullptr;
+    p.N = a.N; p.K = a.K; p.D = a.D;
+    p.group = a.group > 1 ? a.group : 1;
+    p.n_virtual = 0;
+    p.self_clean = p.finish ? a.self_clean : 0;
+    static_assert(ROUTE_PLAN_FUSED_MAX_S <= 2 * PLAN_THREADS_SMALL && CfgRouteSmall::NT == PLAN_THREADS_SMALL,
+                  "the grouping that rides in the small-batch launch is the four-wave one");
+    if (a.plan && !(p.finish && a.self_clean && a.expert_ids && a.seq_offsets && a.err_word &&
+                    a.N <= ROUTE_PLAN_FUSED_MAX_S && a.plan->S == (int)a.N))
+        return hipErrorInvalidValue;
+    p.with_plan = a.plan ? 1 : 0;
+    if (p.with_plan) {
+        p.plan = *a.plan;
+        p.seq_offsets = a.seq_offsets; p.rank_of_expert = a.rank_of_expert; p.err_word = a.err_word;
+    } else {
+        p.plan = PlanView{};
+        p.seq_offsets = p.rank_of_expert = nullptr; p.err_word = nullptr;
+    }
+    auto unpack = [&]() {
+        hipLaunchKernelGGL(route_unpack_kernel, dim3((unsigned)((a.N + 255) / 256)), dim3(256), 0,
+                           stream, p.best, a.N, a.K, a.slot, a.cid, a.expert_ids);
+    };
+    if (!a.is_bf16) {
+        const hipError_t e = launch_route_direct(p, a.retained_only, stream);
+        if (e != hipSuccess) return e;
+        if (!p.finish) unpack();
+    } else if (use_small_route(a)) {
+        using C = CfgRouteSmall;
+        const int nqt = (int)((a.N + C::BN - 1) / C::BN);
+        const int64_t grid = (int64_t)nqt * ((a.K + C::BM - 1) / C::BM);
+        if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(route_small_kernel<C>, dim3((unsigned)grid), dim3(C::NT),
+                           C::SMEM_BYTES, stream, p, nqt);
+    } else {
         const int64_t grid = (a.N + CfgRoute::BN - 1) / CfgRoute::BN;
         if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
         if (a.D % 64 == 0) {
@@ -1029,18 +819,10 @@ hipError_t launch_route(const RouteArgs &a, hipStream_t stream)
 #endif
             p.n_virtual = sgrid;
             hipLaunchKernelGGL(route_stream4_kernel, dim3((unsigned)pgrid), dim3(r4::NT), r4::SMEM_BYTES, stream, p);
-            if (p.group > 1)
-                hipLaunchKernelGGL(route_unpack_kernel, dim3((unsigned)((a.N + 255) / 256)), dim3(256), 0,
-                                   stream, p.best, a.N, a.K, a.slot, a.cid, a.expert_ids);
+            if (p.group > 1) unpack();
         } else
             hipLaunchKernelGGL(route_kernel<CfgRoute>, dim3((unsigned)grid), dim3(CfgRoute::NT),
                                CfgRoute::SMEM_BYTES, stream, p);
-    } else {
-        const int64_t grid = (a.N + 3) / 4;
-        if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(route_f32_kernel, dim3((unsigned)grid), dim3(256), 0, stream,
-                           (const float *)a.emb, (const float *)a.cent, a.cnorm, a.N, a.K, a.D,
-                           a.slot, a.cid, a.expert_ids);
     }
     return hipGetLastError();
 }
