@@ -18,6 +18,7 @@ hipError_t prepare_route_kernels();
 hipError_t prepare_decode_kernels();
 hipError_t prepare_kmeans_kernels();
 hipError_t prepare_mx_kernels();
+hipError_t prepare_plan_kernels();
 hipError_t prepare_kernels()
 {
     hipError_t e = prepare_linear_kernels();
@@ -25,6 +26,7 @@ hipError_t prepare_kernels()
     if ((e = prepare_decode_kernels()) != hipSuccess) return e;
     if ((e = prepare_kmeans_kernels()) != hipSuccess) return e;
     if ((e = prepare_mx_kernels()) != hipSuccess) return e;
+    if ((e = prepare_plan_kernels()) != hipSuccess) return e;
     return prepare_route_kernels();
 }
 }  // namespace moin
@@ -657,6 +659,7 @@ struct RoutePlanFuse {
 };
 
 // Where a routing call keeps its intermediate results inside a block of device memory.
+constexpr size_t ARRIVALS_BYTES = ((size_t)ARRIVAL_WORDS * 4 + 255) / 256 * 256;
 struct RouteScratch {
     size_t cnorm, cinit, best, arrivals, cid, total;
     int group;
@@ -668,13 +671,13 @@ static RouteScratch route_scratch(int64_t N, int32_t K, int32_t D, moin_dtype dt
     const size_t Kpad = align_up((size_t)K, 256);
     const size_t cn_bytes = align_up(Kpad * 4, 256);
     L.group = route_stream_group(N, K, D, dt == MOIN_BF16);
-    const size_t n_best = L.group > 1 || dt == MOIN_F32 ? (size_t)std::max<int64_t>(N, ROUTE_SMALL_MAX_N)
+    const size_t n_best = L.group > 1 || dt == MOIN_F32 || route_pad_pays(N, D, dt == MOIN_BF16) ? (size_t)std::max<int64_t>(N, ROUTE_SMALL_MAX_N)
                                                         : (size_t)ROUTE_SMALL_MAX_N;
     L.cnorm = 0;
     L.cinit = cn_bytes;
     L.best = 2 * cn_bytes;
     L.arrivals = L.best + align_up(n_best * 8, 256);
-    L.cid = L.arrivals + 256;
+    L.cid = L.arrivals + ARRIVALS_BYTES;
     L.total = L.cid + (need_cid ? align_up((size_t)N * 4, 256) : 0);
     return L;
 }
@@ -685,10 +688,10 @@ static int route_launches(moin_ctx *ctx, const void *emb, const void *centroids,
                           int32_t D, moin_dtype dt, const int32_t *slot_of_centroid, uint32_t flags,
                           int32_t *expert_ids, int32_t *centroid_ids, int32_t *counts, char *w,
                           const RouteScratch &L, bool need_cid, bool record, hipStream_t st, int self_clean = 0,
-                          const RoutePlanFuse *fuse = nullptr, void *screen_ws = nullptr)
+                          const RoutePlanFuse *fuse = nullptr, void *extra = nullptr)
 {
     RouteArgs a;
-    a.screen_ws = screen_ws;
+    (dt == MOIN_F32 ? a.screen_ws : a.pad_ws) = extra;
     a.emb = emb; a.cent = centroids; a.N = N; a.K = K; a.D = D;
     a.is_bf16 = (dt == MOIN_BF16);
     a.slot = slot_of_centroid;
@@ -714,7 +717,7 @@ static int route_launches(moin_ctx *ctx, const void *emb, const void *centroids,
     };
     const bool routed = N > 0 && (a.cid || a.expert_ids);
     if (routed) {
-        if (self_clean != 2 && !screen_ws &&
+        if (self_clean != 2 && !a.screen_ws &&
             run(MOIN_K_ROUTE_AUX, [&] { return launch_centroid_norms(a, st); }) != hipSuccess)
             return MOIN_EHIP;
         if (run(MOIN_K_ROUTE, [&] { return launch_route(a, st); }) != hipSuccess) return MOIN_EHIP;
@@ -773,7 +776,7 @@ static int route_impl(moin_ctx *ctx, const void *emb, const void *centroids, int
         const size_t cn_bytes = L.cinit - L.cnorm;
         L.best = 0;
         L.arrivals = (size_t)ROUTE_SMALL_MAX_N * 8;
-        L.cnorm = L.arrivals + 256;
+        L.cnorm = L.arrivals + ARRIVALS_BYTES;
         L.cinit = L.cnorm + cn_bytes;
         L.cid = L.cinit + cn_bytes;
         L.total = L.cid + (need_cid ? align_up((size_t)N * 4, 256) : 0);
@@ -805,7 +808,7 @@ static int route_impl(moin_ctx *ctx, const void *emb, const void *centroids, int
             // minima at "nothing won yet", counter at zero (the kernels keep them so from here on)
             char *b = static_cast<char *>(p);
             if (hipMemsetAsync(b + L.best, 0xFF, L.arrivals - L.best, st) != hipSuccess ||
-                hipMemsetAsync(b + L.arrivals, 0, 256, st) != hipSuccess)
+                hipMemsetAsync(b + L.arrivals, 0, ARRIVALS_BYTES, st) != hipSuccess)
                 return MOIN_EHIP;
         }
         if (cap) ctx->route_pinned = 1;
@@ -826,21 +829,18 @@ static int route_impl(moin_ctx *ctx, const void *emb, const void *centroids, int
                               reuse ? 2 : 1, fuse);
     }
     if (fuse) return MOIN_EINVAL;   // (the caller asks for it only where it applies)
-    // larger fp32 batches: screened by a bf16 product, except where a capture finds the workspace too small
-    size_t screen_at = align_up(L.total, 256), need = L.total;
-    bool screen = dt == MOIN_F32 && route_screen_pays(N, K, D, false);
-    if (screen) {
-        need = screen_at + route_screen_bytes(N, K, D, 0);
-        if (need > ctx->ws_bytes && capturing(st)) {
-            screen = false;
-            need = L.total;
-        }
-    }
+    // larger fp32 batches are screened by a bf16 product, rows that are no whole blocks are padded, except where
+    // a capture finds the workspace too small
+    const size_t extra_at = align_up(L.total, 256);
+    size_t need = L.total;
+    if (dt == MOIN_F32 && route_screen_pays(N, K, D, false)) need = extra_at + route_screen_bytes(N, K, D, 0);
+    else if (route_pad_pays(N, D, dt == MOIN_BF16)) need = extra_at + route_pad_bytes(N, K, D);
+    if (need > L.total && need > ctx->ws_bytes && capturing(st)) need = L.total;
     const int rc = ensure_ws(ctx, need, st);
     if (rc != MOIN_OK) return rc;
     char *w = static_cast<char *>(ctx->ws);
     return route_launches(ctx, emb, centroids, N, K, D, dt, slot_of_centroid, flags, expert_ids, centroid_ids, counts,
-                          w, L, need_cid, true, st, 0, nullptr, screen ? w + screen_at : nullptr);
+                          w, L, need_cid, true, st, 0, nullptr, need > L.total ? w + extra_at : nullptr);
 }
 
 int moin_route(moin_ctx *ctx, const void *emb, const void *centroids, int64_t N, int32_t K,

@@ -115,6 +115,9 @@ hipError_t launch_decode_expand_shared(const PlanView &pv, const DecodeArgs *d, 
 // y = x W^T in one pass (no adapters anywhere in the call)
 hipError_t launch_decode_base_only(const PlanView &pv, const LinearArgs &a, hipStream_t stream);
 
+// Words in which the workgroups of a routing launch report that they are done (route_finish.h), a cache line each
+constexpr int ARRIVAL_FAN = 32, ARRIVAL_STRIDE = 32;
+constexpr int ARRIVAL_WORDS = (ARRIVAL_FAN + 1) * ARRIVAL_STRIDE;
 struct RouteArgs {
     const void *emb, *cent;
     int64_t N;
@@ -129,7 +132,7 @@ struct RouteArgs {
     // small batches: per-query packed (score, index) minimum merged across
     // workgroups, and the arrival counter that elects the finishing workgroup
     unsigned long long *best;  // [ROUTE_SMALL_MAX_N, or N when group > 1] workspace
-    int *arrivals;             // [1] workspace
+    int *arrivals;             // [ARRIVAL_WORDS] workspace
     int *counts;               // [K] or null: zeroed by the norms kernel
     int group;                 // route_stream_group() of the call
     int self_clean = 0;        // small batches: best / arrivals are kept clean between calls by the kernel
@@ -141,7 +144,15 @@ struct RouteArgs {
     int *err_word = nullptr;
     // fp32: route_screen_bytes() of device memory, or null (every distance is then computed directly)
     void *screen_ws = nullptr;
+    // bf16 with D not a multiple of 64: route_pad_bytes() of device memory, or null (the tiled kernel then reads
+    // the rows as they are)
+    void *pad_ws = nullptr;
 };
+// Padded copies pay up to here (2985 centroids of 200 dimensions, us a call as they are / padded: 20 queries 104 /
+// 17, 8192: 110 / 33, 32768: 113 / 90); beyond, the tiled kernel's 256-query workgroups fill the chip (40000: 111).
+constexpr int64_t ROUTE_PAD_MAX_N = 32768;
+bool route_pad_pays(int64_t N, int D, int is_bf16);
+size_t route_pad_bytes(int64_t N, int K, int D);
 constexpr int ROUTE_PLAN_FUSED_MAX_S = 512;  // the grouping rides in the routing launch up to this many queries
 constexpr int ROUTE_SMALL_MAX_N = 4096;  // up to here the K range is split across workgroups
 // true for the batches that are routed, unpacked and tallied in one launch (N <= ROUTE_SMALL_MAX_N; bf16 with

@@ -1,275 +1,297 @@
-// Grouping of a batch by expert, as a device function (see plan.hip for what it computes).
+// Grouping of a batch by expert, as device functions (see plan.hip for what they compute).
 #pragma once
+#include "gemm_core.h"
 #include "kernels.h"
 
 namespace moin {
 
 constexpr int PLAN_THREADS_MAX = 1024;   // large batches
-constexpr int PLAN_THREADS_SMALL = 256;  // up to 512 sequences: four waves meet at a barrier much faster than sixteen
-constexpr int PLAN_LDS_S = 2048;
+constexpr int PLAN_THREADS_SMALL = 256;  // up to PLAN_CAP_SMALL sequences: four waves meet at a barrier much faster than sixteen
+constexpr int PLAN_CAP_SMALL = 512;
+constexpr int PLAN_CAP_MAX = 12288;      // what one compute unit's LDS holds, at 12 bytes a sequence
+constexpr int PLAN_COUNT_S = 128;        // up to here a sequence's place is found by comparing it with all others
 
-// In-place exclusive prefix sum of data[0..n) by one workgroup; returns the total.
-template <int PLAN_THREADS>
-__device__ int block_exclusive_scan(int *data, int n, int *lds /* PLAN_THREADS + 1 ints */)
+// (The arrays are always reached through the struct, never through a pointer that could also be a global one: for
+// such a generic pointer the compiler may form &array[-1] ahead of a loop, and below the start of LDS that is an
+// address outside every segment.)
+template <int PT, int CAP>
+struct PlanLds {
+    unsigned ekey[CAP];          // expert + 1 of each sequence (-1, no adapter, sorts first)
+    int tokbase[CAP];            // per sorted position: tokens before it
+    uint16_t idx[2][CAP];        // sequences in sorted order, and the buffer they are sorted through
+    int hist[PT / 64][128];      // per wave: digit counts, then cursors
+    int sums[3][PT / 64];
+    int bad_offsets, any_long;
+};
+using PlanLdsSmall = PlanLds<PLAN_THREADS_SMALL, PLAN_CAP_SMALL>;
+using PlanLdsMax = PlanLds<PLAN_THREADS_MAX, PLAN_CAP_MAX>;
+
+// Exclusive prefix sums of N values per thread over the workgroup, and the totals.
+template <int PT, int N>
+__device__ __forceinline__ void plan_scan(int (&v)[N], int (&total)[N], int (*sums)[PT / 64])
 {
-    const int tid = threadIdx.x;
-    const int per = (n + PLAN_THREADS - 1) / PLAN_THREADS;
-    const int lo = min(tid * per, n), hi = min(lo + per, n);
-    int sum = 0;
-    for (int i = lo; i < hi; ++i) sum += data[i];
-    lds[tid] = sum;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int own[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) own[k] = v[k];
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1)
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const int y = __shfl_up(v[k], off);
+            if (lane >= off) v[k] += y;
+        }
+    if (lane == 63)
+#pragma unroll
+        for (int k = 0; k < N; ++k) sums[k][wave] = v[k];
     __syncthreads();
-    // Hillis-Steele inclusive scan over the per-thread sums
-    for (int off = 1; off < PLAN_THREADS; off <<= 1) {
-        const int v = (tid >= off) ? lds[tid - off] : 0;
-        __syncthreads();
-        lds[tid] += v;
-        __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        int before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < PT / 64; ++w) {
+            const int s = sums[k][w];
+            before += w < wave ? s : 0;
+            all += s;
+        }
+        v[k] += before - own[k];
+        total[k] = all;
     }
-    const int total = lds[PLAN_THREADS - 1];
-    int run = lds[tid] - sum;
     __syncthreads();
-    for (int i = lo; i < hi; ++i) {
-        const int v = data[i];
-        data[i] = run;
-        run += v;
-    }
-    __syncthreads();
-    return total;
 }
 
-// The whole grouping, by ONE workgroup of PLAN_THREADS threads (all of them must call it).  A device
-// function so that the kernel that routes a request-sized batch can go on to group it in the same launch.
-template <int PLAN_THREADS>
-__device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_offsets, const int *expert_ids,
-                                          const int *rank_of_expert, int *err_word)
+// Rank of adapter slot e ("Future Works": adaptive rank per topic).  Multiples of 8,
+// like the stacks' own rank; anything else is rounded down and raises the sticky fault.
+__device__ __forceinline__ int plan_rank_of(int e, const int *rank_of_expert, int *err_word)
 {
-    // Rank of adapter slot e ("Future Works": adaptive rank per topic).  Multiples of 8,
-    // like the stacks' own rank; anything else is rounded down and raises the sticky fault.
-    auto rank_of = [&](int e) -> int {
-        if (e < 0) return 0;
-        if (!rank_of_expert) return RANK_FULL;
-        int rk = rank_of_expert[e];
-        if (rk < 0 || (rk & 7)) {
-            atomicOr(err_word, ERR_BAD_RANK);
-            rk = rk < 0 ? RANK_FULL : (rk & ~7);
-        }
-        return rk;
-    };
-    __shared__ int lds[PLAN_THREADS + 1];
-    // batches of up to PLAN_LDS_S sequences sort and scan entirely in LDS (a
-    // barrier-separated pass then costs tens of nanoseconds, not a round trip
-    // to L2); larger ones use the plan's global scratch
-    __shared__ unsigned long long lds_keys[PLAN_LDS_S];
-    __shared__ int lds_tmp[4 * (PLAN_LDS_S + 1)];
-    __shared__ int bad_offsets;
-    const int tid = threadIdx.x;
-    const int S = pv.S;
-    const int T = (int)pv.T;
-    int npow2 = 1;
-    while (npow2 < S) npow2 <<= 1;
-    const bool small = npow2 <= PLAN_LDS_S;
-    unsigned long long *keys = small ? lds_keys : pv.keys;
-    int *tmp = small ? lds_tmp : pv.tmp;
-
-    int *lens = tmp;                  // [S]   length of each sequence (by sequence)
-    int *a1 = tmp + (S + 1);          // [S+1] per sorted position: tile count -> tile base
-    int *a2 = tmp + 2 * (S + 1);      // [S+1] per sorted position: length -> token base
-    int *a3 = tmp + 3 * (S + 1);      // [S+1] per sorted position: group head flag -> group id
-
-    // 1. validate, build sort keys (expert + 1 in the high word: -1 sorts first)
-    int err = 0;
-    if (tid == 0) bad_offsets = 0;
-    __syncthreads();
-    if (tid == 0 && (seq_offsets[0] != 0 || seq_offsets[S] != T)) err |= ERR_BAD_OFFSETS;
-    for (int s = tid; s < npow2; s += PLAN_THREADS) {
-        unsigned long long key = ~0ull;
-        if (s < S) {
-            int lo = seq_offsets[s], hi = seq_offsets[s + 1];
-            int e = expert_ids[s];
-            if (lo < 0 || hi > T || hi < lo) {
-                err |= ERR_BAD_OFFSETS;
-                lo = 0;
-                hi = 0;
-            }
-            if (e < -1 || e >= pv.E) {
-                err |= ERR_BAD_EXPERT;
-                e = -1;
-            }
-            lens[s] = hi - lo;
-            key = ((unsigned long long)(unsigned)(e + 1) << 32) | (unsigned)s;
-        }
-        keys[s] = key;
+    if (e < 0) return 0;
+    if (!rank_of_expert) return RANK_FULL;
+    int rk = rank_of_expert[e];
+    if (rk < 0 || (rk & 7)) {
+        atomicOr(err_word, ERR_BAD_RANK);
+        rk = rk < 0 ? RANK_FULL : (rk & ~7);
     }
-    if (err) atomicOr(err_word, err);
-    if (err & ERR_BAD_OFFSETS) bad_offsets = 1;
-    for (int j = tid; j < pv.max_plain; j += PLAN_THREADS) {
-        const int rows = min(TILE_M, T - j * TILE_M);
+    return rk;
+}
+
+// Plain row tiles over all tokens (batches of the gather path).
+__device__ __forceinline__ void plan_plain_tiles(const PlanView &pv, int nt)
+{
+    const int T = (int)pv.T;
+    for (int j = threadIdx.x; j < pv.max_plain; j += nt) {
         pv.plain_row0[j] = j * TILE_M;
-        pv.plain_rows[j] = max(rows, 0);
+        pv.plain_rows[j] = max(min(TILE_M, T - j * TILE_M), 0);
         pv.plain_expert[j] = -1;
         pv.plain_rank[j] = 0;
     }
-    if (tid == 0 && pv.max_plain > 0) *pv.plain_n = min(pv.max_plain, (T + TILE_M - 1) / TILE_M);
-    __syncthreads();
-    if (bad_offsets) {
-        // the sequences do not cover every token exactly once: one base-only
-        // sequence over the whole batch instead
-        const int nt = (T + TILE_M - 1) / TILE_M;   // <= max_tiles
-        for (int j = tid; j < nt; j += PLAN_THREADS) {
-            pv.tile_row0[j] = j * TILE_M;
-            pv.tile_rows[j] = min(TILE_M, T - j * TILE_M);
-            pv.tile_expert[j] = -1;
-            pv.tile_rank[j] = 0;
-        }
-        if (tid == 0) *pv.n_tiles = nt;
-        if (pv.decode) {
-            for (int t = tid; t < T; t += PLAN_THREADS) pv.tok_sorted[t] = t;
-            const int nc = min((T + GROUP_CHUNK - 1) / GROUP_CHUNK, pv.max_groups);
-            if (tid == 0) *pv.n_groups = nc;
-            for (int gi = tid; gi < pv.max_groups; gi += PLAN_THREADS)
-                pv.grp_meta[gi] = gi < nc ? make_int4(-1, gi * GROUP_CHUNK, min(T, (gi + 1) * GROUP_CHUNK), 0)
-                                          : make_int4(-1, 0, 0, 0);
-        }
-        return;
-    }
+    if (threadIdx.x == 0 && pv.max_plain > 0) *pv.plain_n = min(pv.max_plain, (T + TILE_M - 1) / TILE_M);
+}
 
-    // 2. bitonic sort of the keys by the one workgroup.  Element i meets element i ^ j,
-    // ascending where (i & k) == 0.  Up to PLAN_LDS_S keys everything happens in LDS.
-    // Beyond, only the steps whose partners lie PLAN_LDS_S or more apart walk global
-    // memory; all steps with j < PLAN_LDS_S stay inside an aligned chunk of PLAN_LDS_S
-    // keys, which is brought into LDS once for a whole run of them.
-    auto steps_in = [&](unsigned long long *buf, int n, int base, int k, int j_first) {
-        for (int j = j_first; j > 0; j >>= 1) {
-            for (int i = tid; i < n; i += PLAN_THREADS) {
-                const int l = i ^ j;
-                if (l > i) {
-                    const unsigned long long a = buf[i], b = buf[l];
-                    const bool up = ((base + i) & k) == 0;
-                    if ((a > b) == up) {
-                        buf[i] = b;
-                        buf[l] = a;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    };
-    if (small) {
-        for (int k = 2; k <= npow2; k <<= 1) steps_in(keys, npow2, 0, k, k >> 1);
-    } else {
-        auto chunk_run = [&](int c, int k_first, int k_last, int j_first_of_last) {
-            // chunk c through LDS: whole stages k_first..k_last / 2 and, of stage k_last, the steps from j_first_of_last down
-            unsigned long long *g = keys + (size_t)c * PLAN_LDS_S;
-            for (int i = tid; i < PLAN_LDS_S; i += PLAN_THREADS) lds_keys[i] = g[i];
-            __syncthreads();
-            for (int k = k_first; k < k_last; k <<= 1) steps_in(lds_keys, PLAN_LDS_S, c * PLAN_LDS_S, k, k >> 1);
-            steps_in(lds_keys, PLAN_LDS_S, c * PLAN_LDS_S, k_last, j_first_of_last);
-            for (int i = tid; i < PLAN_LDS_S; i += PLAN_THREADS) g[i] = lds_keys[i];
-            __syncthreads();
-        };
-        const int n_chunks = npow2 / PLAN_LDS_S;
-        for (int c = 0; c < n_chunks; ++c) chunk_run(c, 2, PLAN_LDS_S, PLAN_LDS_S >> 1);
-        for (int k = 2 * PLAN_LDS_S; k <= npow2; k <<= 1) {
-            for (int j = k >> 1; j >= PLAN_LDS_S; j >>= 1) {
-                for (int i = tid; i < npow2; i += PLAN_THREADS) {
-                    const int l = i ^ j;
-                    if (l > i) {
-                        const unsigned long long a = keys[i], b = keys[l];
-                        const bool up = (i & k) == 0;
-                        if ((a > b) == up) {
-                            keys[i] = b;
-                            keys[l] = a;
-                        }
-                    }
-                }
-                __syncthreads();
-            }
-            for (int c = 0; c < n_chunks; ++c) chunk_run(c, k, k, PLAN_LDS_S >> 1);
-        }
+// The sequences do not cover every token exactly once: one base-only sequence over the whole batch instead.
+__device__ __forceinline__ void plan_base_only(const PlanView &pv, int nt_threads)
+{
+    const int tid = threadIdx.x, T = (int)pv.T;
+    const int nt = (T + TILE_M - 1) / TILE_M;   // <= max_tiles
+    for (int j = tid; j < nt; j += nt_threads) {
+        pv.tile_row0[j] = j * TILE_M;
+        pv.tile_rows[j] = min(TILE_M, T - j * TILE_M);
+        pv.tile_expert[j] = -1;
+        pv.tile_rank[j] = 0;
     }
-
-    // 3. per sorted position: tile count, token count, group-head flag
-    for (int p = tid; p < S; p += PLAN_THREADS) {
-        const unsigned long long key = keys[p];
-        const int s = (int)(key & 0xffffffffu);
-        const int len = lens[s];
-        a1[p] = (len + TILE_M - 1) / TILE_M;
-        a2[p] = len;
-        const bool head = (p == 0) || ((keys[p - 1] >> 32) != (key >> 32));
-        a3[p] = head ? 1 : 0;
-    }
-    __syncthreads();
-    const int n_tiles = block_exclusive_scan<PLAN_THREADS>(a1, S, lds);
-    if (tid == 0) *pv.n_tiles = min(n_tiles, pv.max_tiles);
-    int n_groups = 0, n_tok = 0;
+    if (tid == 0) *pv.n_tiles = nt;
     if (pv.decode) {
-        n_tok = block_exclusive_scan<PLAN_THREADS>(a2, S, lds);
-        n_groups = block_exclusive_scan<PLAN_THREADS>(a3, S, lds);   // a3[p] = groups before p
-        if (tid == 0) pv.grp_start[n_groups] = min(n_tok, T);
-    }
-
-    // 4. emit
-    for (int p = tid; p < S; p += PLAN_THREADS) {
-        const unsigned long long key = keys[p];
-        const int s = (int)(key & 0xffffffffu);
-        const int e = (int)(key >> 32) - 1;
-        const int lo = seq_offsets[s];
-        const int len = lens[s];
-        const int tb = a1[p];
-        const int rk = rank_of(e);
-        for (int j = 0, left = len; left > 0 && tb + j < pv.max_tiles; ++j, left -= TILE_M) {
-            pv.tile_row0[tb + j] = lo + j * TILE_M;
-            pv.tile_rows[tb + j] = min(left, TILE_M);
-            pv.tile_expert[tb + j] = e;
-            pv.tile_rank[tb + j] = rk;
-        }
-        if (pv.decode) {
-            const int base = min(a2[p], T);
-            const bool head = (p == 0) || ((keys[p - 1] >> 32) != (key >> 32));
-            if (head) {
-                const int gi = a3[p];   // exclusive count of heads before p
-                pv.grp_tmp[gi] = make_int2(e, rk);
-                pv.grp_start[gi] = base;
-            }
-        }
-    }
-    if (pv.decode) {
-        // tokens in sorted order, one per thread and step whatever the sequences' lengths:
-        // position t belongs to the last sorted sequence that starts at or before it
-        for (int t = tid; t < min(n_tok, T); t += PLAN_THREADS) {
-            int first = 0, last = S - 1;
-            while (first < last) {
-                const int mid = (first + last + 1) >> 1;
-                if (a2[mid] <= t) first = mid;
-                else last = mid - 1;
-            }
-            const int s = (int)(keys[first] & 0xffffffffu);
-            pv.tok_sorted[t] = seq_offsets[s] + (t - a2[first]);
-        }
-    }
-    if (pv.decode) {
-        // A group ends where the next one starts.  It is cut into records of at most
-        // GROUP_CHUNK tokens: the decode kernels hand a record to one column of
-        // workgroups, and a hot expert's tokens must not all queue behind one column.
-        __syncthreads();   // grp_start / grp_tmp are complete, a1 is free
-        for (int gi = tid; gi < n_groups; gi += PLAN_THREADS)
-            a1[gi] = (pv.grp_start[gi + 1] - pv.grp_start[gi] + GROUP_CHUNK - 1) / GROUP_CHUNK;
-        __syncthreads();
-        const int n_rec = min(block_exclusive_scan<PLAN_THREADS>(a1, n_groups, lds), pv.max_groups);
-        for (int gi = tid; gi < n_groups; gi += PLAN_THREADS) {
-            const int2 er = pv.grp_tmp[gi];
-            const int ge = pv.grp_start[gi + 1];
-            int rec = a1[gi];
-            for (int t = pv.grp_start[gi]; t < ge && rec < pv.max_groups; t += GROUP_CHUNK, ++rec)
-                pv.grp_meta[rec] = make_int4(er.x, t, min(t + GROUP_CHUNK, ge), er.y);
-        }
-        if (tid == 0) *pv.n_groups = n_rec;
-        // unused records read as empty groups, so the decode kernels need not
-        // fetch the group count before their own record
-        for (int gi = n_rec + tid; gi < pv.max_groups; gi += PLAN_THREADS) pv.grp_meta[gi] = make_int4(-1, 0, 0, 0);
+        for (int t = tid; t < T; t += nt_threads) pv.tok_sorted[t] = t;
+        const int nc = min((T + GROUP_CHUNK - 1) / GROUP_CHUNK, pv.max_groups);
+        if (tid == 0) *pv.n_groups = nc;
+        for (int gi = tid; gi < pv.max_groups; gi += nt_threads)
+            pv.grp_meta[gi] = gi < nc ? make_int4(-1, gi * GROUP_CHUNK, min(T, (gi + 1) * GROUP_CHUNK), 0)
+                                      : make_int4(-1, 0, 0, 0);
     }
 }
 
+// The whole grouping of a batch of at most CAP sequences, by ONE workgroup of PT threads (all of them must
+// call it), in LDS.  A device function so that the kernel that routes a request-sized batch can go on to group
+// it in the same launch; that kernel hands in LDS it has no more use for.
+// Bound by latency: trips to memory, barriers, dependent LDS reads.  The sort is stable and takes the digits
+// of the expert alone: up to PLAN_COUNT_S sequences each finds its place by comparing itself with all others
+// (one barrier), beyond them a radix sort, 7 bits a pass, lanes of a wave that share a digit finding each other
+// with one ballot per bit.  (It was a bitonic sort of 64-bit keys: 36 barriers for 256 sequences, and above
+// 2048 through global memory: 8192 sequences took 230 us.)
+template <int PT, int CAP>
+__device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_offsets, const int *expert_ids,
+                                          const int *rank_of_expert, int *err_word, PlanLds<PT, CAP> &L)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int S = pv.S;
+    const int T = (int)pv.T;
+
+    // 1. validate, fetch the experts
+    if (tid == 0) L.bad_offsets = L.any_long = 0;
+    __syncthreads();
+    int err = 0;
+    if (tid == 0 && (seq_offsets[0] != 0 || seq_offsets[S] != T)) err |= ERR_BAD_OFFSETS;
+    for (int s = tid; s < S; s += PT) {
+        const int lo = seq_offsets[s], hi = seq_offsets[s + 1];
+        int e = expert_ids[s];
+        if (lo < 0 || hi > T || hi < lo) err |= ERR_BAD_OFFSETS;
+        if (e < -1 || e >= pv.E) {
+            err |= ERR_BAD_EXPERT;
+            e = -1;
+        }
+        L.ekey[s] = (unsigned)(e + 1);
+        L.idx[0][s] = (uint16_t)s;
+    }
+    if (err) atomicOr(err_word, err);
+    if (err & ERR_BAD_OFFSETS) L.bad_offsets = 1;
+    plan_plain_tiles(pv, PT);
+    __syncthreads();
+    if (L.bad_offsets) {
+        plan_base_only(pv, PT);
+        return;
+    }
+
+    // 2. sort the sequences by expert, stably
+    int cur = 0;
+    if (S <= PLAN_COUNT_S) {
+        static_assert(PT >= PLAN_COUNT_S && CAP >= PLAN_COUNT_S, "a sequence per thread");
+        if (tid < S) {
+            const unsigned me = L.ekey[tid];
+            int at = 0;
+#pragma unroll 4
+            for (int j = 0; j < S; ++j) {
+                const unsigned o = L.ekey[j];
+                at += (o < me || (o == me && j < tid)) ? 1 : 0;
+            }
+            L.idx[1][at] = (uint16_t)tid;
+        }
+        cur = 1;
+        __syncthreads();
+    } else {
+        constexpr int NW = PT / 64;
+        const int per_wave = ((S + NW - 1) / NW + 63) / 64 * 64;
+        const int w0 = min(wave * per_wave, S), w1 = min(w0 + per_wave, S);
+        const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+        for (int shift = 0; shift == 0 || (shift < 32 && ((unsigned)pv.E >> shift) != 0); shift += 7) {
+            for (int d = lane; d < 128; d += 64) L.hist[wave][d] = 0;
+            for (int i = w0 + lane; i < w1; i += 64)   // (a wave's own row: its LDS operations stay in order)
+                atomicAdd(&L.hist[wave][(L.ekey[L.idx[cur][i]] >> shift) & 127], 1);
+            __syncthreads();
+            // cursors: digits in order, the waves of a digit in order
+            constexpr int PER = 128 * NW / PT;   // 2
+            int c[PER], v[1] = {0}, total[1];
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                const int f = tid * PER + q;
+                c[q] = L.hist[f % NW][f / NW];
+                v[0] += c[q];
+            }
+            plan_scan<PT, 1>(v, total, L.sums);
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                const int f = tid * PER + q;
+                L.hist[f % NW][f / NW] = v[0];
+                v[0] += c[q];
+            }
+            __syncthreads();
+            for (int i = w0 + lane; i - lane < w1; i += 64) {
+                const bool ok = i < w1;
+                const int s = ok ? L.idx[cur][i] : 0;
+                const int d = ok ? (int)((L.ekey[s] >> shift) & 127) : 0;
+                uint64_t m = __ballot(ok);
+#pragma unroll
+                for (int bit = 0; bit < 7; ++bit) {
+                    const bool one = (d >> bit) & 1;
+                    const uint64_t bal = __ballot(one);
+                    m &= one ? bal : ~bal;
+                }
+                const int base = ok ? L.hist[wave][d] : 0;
+                if (ok) {
+                    L.idx[cur ^ 1][base + __popcll(m & below)] = (uint16_t)s;
+                    if ((m & below) == 0) L.hist[wave][d] = base + __popcll(m);   // the first of them moves the cursor
+                }
+            }
+            cur ^= 1;
+            __syncthreads();
+        }
+    }
+    const uint16_t *order = L.idx[cur];
+    uint16_t *head_at = L.idx[cur ^ 1];   // per group: its first sorted position
+
+    // 3. tiles / tokens / groups before each sorted position, a run of positions per thread; emit.  (The decode
+    // kernels know no tiles, the prefill kernels no token order.)
+    const int per = (S + PT - 1) / PT;
+    const int p0 = min(tid * per, S), p1 = min(p0 + per, S);
+    int v[3] = {0, 0, 0}, total[3];
+    for (int p = p0; p < p1; ++p) {
+        const int s = order[p];
+        const int len = seq_offsets[s + 1] - seq_offsets[s];
+        v[0] += (len + TILE_M - 1) / TILE_M;
+        v[1] += len;
+        v[2] += p == 0 || L.ekey[order[p - 1]] != L.ekey[s];
+    }
+    plan_scan<PT, 3>(v, total, L.sums);
+    if (tid == 0) *pv.n_tiles = pv.decode ? 0 : min(total[0], pv.max_tiles);
+    for (int p = p0; p < p1; ++p) {
+        const int s = order[p];
+        const int lo = seq_offsets[s], len = seq_offsets[s + 1] - lo;
+        const int e = (int)L.ekey[s] - 1;
+        if (!pv.decode) {
+            const int rk = plan_rank_of(e, rank_of_expert, err_word);
+            for (int left = len, j = 0; left > 0 && v[0] < pv.max_tiles; ++j, ++v[0], left -= TILE_M) {
+                pv.tile_row0[v[0]] = lo + j * TILE_M;
+                pv.tile_rows[v[0]] = min(left, TILE_M);
+                pv.tile_expert[v[0]] = e;
+                pv.tile_rank[v[0]] = rk;
+            }
+        } else {
+            L.tokbase[p] = v[1];
+            if (p == 0 || L.ekey[order[p - 1]] != L.ekey[s]) head_at[v[2]++] = (uint16_t)p;
+            if (len > 8) L.any_long = 1;
+            else
+                for (int j = 0; j < len && v[1] + j < T; ++j) pv.tok_sorted[v[1] + j] = lo + j;
+            v[1] += len;
+        }
+    }
+    if (!pv.decode) return;
+    __syncthreads();
+    const int n_tok = min(total[1], T), n_groups = total[2];
+    if (L.any_long) {
+        // tokens in sorted order, one per thread and step whatever the sequences' lengths:
+        // position t belongs to the last sorted sequence that starts at or before it
+        for (int t = tid; t < n_tok; t += PT) {
+            int first = 0, last = S - 1;
+            while (first < last) {
+                const int mid = (first + last + 1) >> 1;
+                if (L.tokbase[mid] <= t) first = mid;
+                else last = mid - 1;
+            }
+            pv.tok_sorted[t] = seq_offsets[order[first]] + (t - L.tokbase[first]);
+        }
+    }
+    // 4. A group ends where the next one starts.  It is cut into records of at most GROUP_CHUNK tokens: the
+    // decode kernels hand a record to one column of workgroups, and a hot expert's tokens must not all queue
+    // behind one column.
+    const int gper = (n_groups + PT - 1) / PT;
+    const int g0 = min(tid * gper, n_groups), g1 = min(g0 + gper, n_groups);
+    int n[1] = {0}, n_rec[1];
+    for (int g = g0; g < g1; ++g) {
+        const int gs = L.tokbase[head_at[g]], ge = g + 1 < n_groups ? L.tokbase[head_at[g + 1]] : n_tok;
+        n[0] += (ge - gs + GROUP_CHUNK - 1) / GROUP_CHUNK;
+    }
+    plan_scan<PT, 1>(n, n_rec, L.sums);
+    for (int g = g0; g < g1; ++g) {
+        const int p = head_at[g];
+        const int gs = L.tokbase[p], ge = g + 1 < n_groups ? L.tokbase[head_at[g + 1]] : n_tok;
+        const int e = (int)L.ekey[order[p]] - 1;
+        const int rk = plan_rank_of(e, rank_of_expert, err_word);
+        for (int t = gs; t < ge && n[0] < pv.max_groups; t += GROUP_CHUNK, ++n[0])
+            pv.grp_meta[n[0]] = make_int4(e, t, min(t + GROUP_CHUNK, ge), rk);
+    }
+    const int n_out = min(n_rec[0], pv.max_groups);
+    if (tid == 0) *pv.n_groups = n_out;
+    // unused records read as empty groups, so the decode kernels need not
+    // fetch the group count before their own record
+    for (int gi = n_out + tid; gi < pv.max_groups; gi += PT) pv.grp_meta[gi] = make_int4(-1, 0, 0, 0);
+}
 
 }  // namespace moin

@@ -20,7 +20,11 @@
 namespace moin {
 
 using CfgRoute = GemmCore<256, 256, 64, 4, 2>;      // rows: centroids, cols: queries; any D % 8 == 0
-using CfgRouteSmall = DmaCore<64, 64, 64, 2, 2, 6>;  // small batches: one (centroid chunk, query tile) per workgroup
+// Smaller batches: one (centroid chunk, query tile) per workgroup.  64 x 64 with five blocks in flight where
+// the launch is short of workgroups and latency decides; 128 x 128, two workgroups per compute unit, from about
+// one such tile per compute unit on.
+using CfgRouteSmall = DmaCore<64, 64, 64, 2, 2, 5>;
+using CfgRouteMid = DmaCore<128, 128, 64, 2, 2, 2>;
 
 __device__ __forceinline__ bool lex_less(float v, int i, float bv, int bi)
 {
@@ -589,8 +593,35 @@ __global__ __launch_bounds__(C::NT) void route_small_kernel(RouteKParams p, int 
             atomicMin(&p.best[q0 + col],
                       ((unsigned long long)float_order_key(bestv[j]) << 32) | (unsigned)besti[j]);
     }
-    route_finish<C::NT>(p);
+    if (p.finish) {
+        static_assert(C::SMEM_BYTES >= (int)sizeof(PlanLdsSmall), "the grouping works in the stages");
+        __syncthreads();
+        route_finish<C::NT>(p, smem);
+    }
 }
+
+// Padded copies of bf16 rows whose length is not a multiple of 64 (Dp == 0: none).
+struct PadRows {
+    const char *emb;
+    int64_t N;
+    int Dp;
+    char *cent_p, *emb_p;
+};
+
+static PadRows pad_rows(const RouteArgs &a)
+{
+    PadRows r{};
+    if (!a.is_bf16 || !a.pad_ws || a.D % 64 == 0) return r;
+    r.emb = (const char *)a.emb;
+    r.N = a.N;
+    r.Dp = (a.D + 63) / 64 * 64;
+    r.cent_p = static_cast<char *>(a.pad_ws);
+    r.emb_p = r.cent_p + (size_t)a.K * r.Dp * 2;
+    return r;
+}
+
+bool route_pad_pays(int64_t N, int D, int is_bf16) { return is_bf16 && D % 64 != 0 && N <= ROUTE_PAD_MAX_N; }
+size_t route_pad_bytes(int64_t N, int K, int D) { return (size_t)(N + K) * ((D + 63) / 64 * 64) * 2; }
 
 // ||c_k||^2 in fp32 (one wave per centroid), +inf for centroids left out of the
 // search and for the padding up to a multiple of 256.  The same launch resets
@@ -601,7 +632,7 @@ __global__ __launch_bounds__(256) void centroid_norm_kernel(const char *cent, in
                                                             int retained_only, float *cnorm,
                                                             float *cinit,
                                                             unsigned long long *best, int64_t nbest,
-                                                            int *arrivals, int narrivals, int *counts)
+                                                            int *arrivals, int narrivals, int *counts, PadRows pad)
 {
     const int gid = blockIdx.x * 256 + threadIdx.x;
     const int gsz = gridDim.x * 256;
@@ -611,8 +642,20 @@ __global__ __launch_bounds__(256) void centroid_norm_kernel(const char *cent, in
     for (int i = gid; i < narrivals; i += gsz) arrivals[i] = 0;
 
     const int lane = threadIdx.x & 63;
-    const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (k >= Kpad) return;
+    const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (pad.Dp > 0) {   // waves past the centroids: the queries
+        const bool is_cent = w < Kpad;
+        const int64_t row = is_cent ? w : w - Kpad;
+        if (row < (is_cent ? (int64_t)K : pad.N)) {
+            const char *src = (is_cent ? cent : pad.emb) + row * D * 2;
+            char *dst = (is_cent ? pad.cent_p : pad.emb_p) + row * pad.Dp * 2;
+            for (int ch = lane; ch < pad.Dp / 8; ch += 64)   // D % 8 == 0
+                *reinterpret_cast<uint4 *>(dst + ch * 16) =
+                    ch * 8 < D ? *reinterpret_cast<const uint4 *>(src + ch * 16) : make_uint4(0, 0, 0, 0);
+        }
+    }
+    if (w >= Kpad) return;
+    const int k = (int)w;
     float acc = 0.f;
     if (k < K) {
         if (is_bf16) {
@@ -694,35 +737,43 @@ hipError_t prepare_route_kernels()
     if ((e = prepare_route_exact_kernels()) != hipSuccess) return e;
     if ((e = allow_lds(&route_kernel<CfgRoute>, CfgRoute::SMEM_BYTES)) != hipSuccess) return e;
     if ((e = allow_lds(&route_stream4_kernel, r4::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&route_small_kernel<CfgRouteMid>, CfgRouteMid::SMEM_BYTES)) != hipSuccess) return e;
     return allow_lds(&route_small_kernel<CfgRouteSmall>, CfgRouteSmall::SMEM_BYTES);
 }
 
-static bool use_small_route(const RouteArgs &a)
-{
-    return a.is_bf16 && a.D % 64 == 0 && a.N <= ROUTE_SMALL_MAX_N;
-}
+// (5000 centroids, 768 dimensions, us a call with 64 x 64 / 128 x 128 tiles: 256 queries 22 / -, 512: 28 / 22,
+// 1024: 42 / 25, 4096: 134 / 53)
+constexpr int64_t ROUTE_MID_MIN_TILES = 128;
+
+// Rows of 64-value blocks: as they are, or padded copies.
+static bool whole_blocks(const RouteArgs &a) { return a.is_bf16 && (a.D % 64 == 0 || a.pad_ws); }
+
+static bool use_small_route(const RouteArgs &a) { return whole_blocks(a) && a.N <= ROUTE_SMALL_MAX_N; }
 
 static bool use_stream_route(const RouteArgs &a) { return a.is_bf16 && a.D % 64 == 0 && !use_small_route(a); }
 
-// Workgroups per query tile of the streaming kernel: prefers 4 (eight query
-// tiles per XCD in flight), among the sizes that split the centroid tiles
-// evenly or nearly so; 1 = no sharing (few centroid tiles).
+// Workgroups per query tile of the streaming kernel.  Query tile t lies on XCD t % 8, whose 32 compute units
+// hold 32 / g groups of g workgroups; a workgroup sweeps every g-th centroid tile.  The size with the shortest
+// sweep wins; among equals 4 (eight query tiles per XCD in flight: L2 serves them all), then its neighbours.
+// Few query tiles take large groups: 8192 queries, 5000 centroids (20 tiles of 256): 8 workgroups x 3 tiles
+// instead of 4 x 5, which left half of the chip idle.
 int route_stream_group(int64_t N, int K, int D, int is_bf16)
 {
     RouteArgs a{};
     a.N = N; a.K = K; a.D = D; a.is_bf16 = is_bf16;
     if (!use_stream_route(a)) return 1;
-    const int nct = (K + r4::BT - 1) / r4::BT;
-    const int pref[] = {4, 8, 2, 5, 3, 6, 7};
+    const int64_t nct = (K + r4::BT - 1) / r4::BT;
+    const int64_t per_xcd = ((N + r4::BT - 1) / r4::BT + 7) / 8;
+    const int pref[] = {4, 8, 2, 5, 3, 6, 7, 1, 10, 9, 16, 12, 14, 20, 32};
     int best_g = 1;
-    double best_waste = 1.05;   // accept at most 5 % of idle tile slots over the plain scheme
+    int64_t best = INT64_MAX;
     for (int g : pref) {
         if (g > nct) continue;
-        const double waste = (double)((nct + g - 1) / g * g) / nct;
-        if (waste < best_waste) {
-            best_waste = waste;
+        const int64_t groups = 32 / g;
+        const int64_t sweep = (per_xcd + groups - 1) / groups * ((nct + g - 1) / g);
+        if (sweep < best) {
+            best = sweep;
             best_g = g;
-            if (waste == 1.0) break;
         }
     }
     return best_g;
@@ -751,11 +802,13 @@ hipError_t launch_centroid_norms(const RouteArgs &a, hipStream_t stream)
 {
     const int Kpad = (a.K + 255) / 256 * 256;
     // a self-cleaning small-batch call needs the norms only
-    const int64_t nbest = a.self_clean ? 0 : ((finishes_itself(a) || !a.is_bf16 || a.group > 1) ? a.N : 0);
-    const int narr = a.self_clean ? 0 : 1;
-    hipLaunchKernelGGL(centroid_norm_kernel, dim3((Kpad + 3) / 4), dim3(256), 0, stream,
+    const int64_t nbest = a.self_clean ? 0 : ((finishes_itself(a) || !a.is_bf16 || a.pad_ws || a.group > 1) ? a.N : 0);
+    const int narr = a.self_clean ? 0 : ARRIVAL_WORDS;
+    const PadRows pad = pad_rows(a);
+    const int64_t waves = Kpad + (pad.Dp > 0 ? a.N : 0);
+    hipLaunchKernelGGL(centroid_norm_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, stream,
                        (const char *)a.cent, a.K, Kpad, a.D, a.is_bf16, a.slot, a.retained_only,
-                       a.cnorm, a.cinit, a.best, nbest, a.arrivals, narr, a.self_clean ? nullptr : a.counts);
+                       a.cnorm, a.cinit, a.best, nbest, a.arrivals, narr, a.self_clean ? nullptr : a.counts, pad);
     return hipGetLastError();
 }
 
@@ -773,7 +826,7 @@ hipError_t launch_route(const RouteArgs &a, hipStream_t stream)
     p.group = a.group > 1 ? a.group : 1;
     p.n_virtual = 0;
     p.self_clean = p.finish ? a.self_clean : 0;
-    static_assert(ROUTE_PLAN_FUSED_MAX_S <= 2 * PLAN_THREADS_SMALL && CfgRouteSmall::NT == PLAN_THREADS_SMALL,
+    static_assert(ROUTE_PLAN_FUSED_MAX_S <= PLAN_CAP_SMALL && CfgRouteSmall::NT == PLAN_THREADS_SMALL,
                   "the grouping that rides in the small-batch launch is the four-wave one");
     if (a.plan && !(p.finish && a.self_clean && a.expert_ids && a.seq_offsets && a.err_word &&
                     a.N <= ROUTE_PLAN_FUSED_MAX_S && a.plan->S == (int)a.N))
@@ -794,13 +847,27 @@ hipError_t launch_route(const RouteArgs &a, hipStream_t stream)
         const hipError_t e = launch_route_direct(p, a.retained_only, stream);
         if (e != hipSuccess) return e;
         if (!p.finish) unpack();
-    } else if (use_small_route(a)) {
-        using C = CfgRouteSmall;
-        const int nqt = (int)((a.N + C::BN - 1) / C::BN);
-        const int64_t grid = (int64_t)nqt * ((a.K + C::BM - 1) / C::BM);
-        if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(route_small_kernel<C>, dim3((unsigned)grid), dim3(C::NT),
-                           C::SMEM_BYTES, stream, p, nqt);
+    } else if (use_small_route(a) || a.pad_ws) {
+        const PadRows pad = pad_rows(a);
+        if (pad.Dp > 0) {
+            p.emb = pad.emb_p;
+            p.cent = pad.cent_p;
+            p.D = pad.Dp;
+        }
+        auto launch = [&](auto cfg) {
+            using C = decltype(cfg);
+            const int nqt = (int)((a.N + C::BN - 1) / C::BN);
+            const int64_t grid = (int64_t)nqt * ((a.K + C::BM - 1) / C::BM);
+            if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+            hipLaunchKernelGGL(route_small_kernel<C>, dim3((unsigned)grid), dim3(C::NT),
+                               C::SMEM_BYTES, stream, p, nqt);
+            return hipSuccess;
+        };
+        using M = CfgRouteMid;
+        const int64_t mid_tiles = ((a.N + M::BN - 1) / M::BN) * ((a.K + M::BM - 1) / M::BM);
+        const hipError_t e = mid_tiles >= ROUTE_MID_MIN_TILES ? launch(M{}) : launch(CfgRouteSmall{});
+        if (e != hipSuccess) return e;
+        if (!p.finish) unpack();
     } else {
         const int64_t grid = (a.N + CfgRoute::BN - 1) / CfgRoute::BN;
         if (grid > 0x7fffffffLL) return hipErrorInvalidValue;

@@ -122,6 +122,7 @@ __device__ __forceinline__ u64 readlane64(u64 v, int l)
 __global__ __launch_bounds__(256) void route_direct_kernel(RouteKParams p, int n_runs, int per, int retained_only)
 {
     using V = Vals<false>;
+    extern __shared__ __align__(16) char smem[];   // for the grouping alone
     const int lane = threadIdx.x & 63;
     const int64_t w = (int64_t)blockIdx.x * 4 + uniform(threadIdx.x >> 6);
     const int64_t q0 = w / n_runs * 8;
@@ -180,7 +181,7 @@ __global__ __launch_bounds__(256) void route_direct_kernel(RouteKParams p, int n
         const int64_t qi = q0 + (lane >> 3);
         if ((lane & 7) == 0 && qi < p.N && key != NO_KEY) atomicMin(&p.best[qi], key);
     }
-    if (p.finish) route_finish<256>(p);
+    if (p.finish) route_finish<256>(p, smem);
 }
 
 // ---- screening ---------------------------------------------------------------------------------------------
@@ -615,7 +616,8 @@ hipError_t launch_route_direct(const RouteKParams &p, int retained_only, hipStre
     runs = (ncb + per - 1) / per;
     const int64_t grid = (nqb * runs + 3) / 4;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(route_direct_kernel, dim3((unsigned)grid), dim3(256), 0, stream, p, (int)runs, (int)per,
+    hipLaunchKernelGGL(route_direct_kernel, dim3((unsigned)grid), dim3(256),
+                       p.with_plan ? sizeof(PlanLdsSmall) : 0, stream, p, (int)runs, (int)per,
                        retained_only);
     return hipGetLastError();
 }

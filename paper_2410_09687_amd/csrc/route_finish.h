@@ -15,7 +15,7 @@ struct RouteKParams {
     int *cid;
     int *expert_ids;
     unsigned long long *best;
-    int *arrivals;        // for route_finish
+    int *arrivals;        // ARRIVAL_WORDS, for route_finish
     int *counts;          // batches with a finishing workgroup: tallied by it (zeroed beforehand)
     int64_t N;
     int K, D;
@@ -34,39 +34,67 @@ struct RouteKParams {
 
 // Every workgroup of the launch calls this once its winners are in best[] (device-scope atomics).  The one
 // that arrives last unpacks them: ids, adapter slots, the histogram, and the grouping of the batch where the
-// call asks for it.
+// call asks for it.  What the others leave behind are atomics alone, so a workgroup only waits for its own to
+// be done before it reports; a release fence would write back, and its acquire half invalidate, the XCD's L2
+// once per workgroup.  Reports go to ARRIVAL_FAN words first and from there to one: atomics on one word take
+// turns at about 13 ns.
+// `smem`: sizeof(PlanLdsSmall) bytes of LDS, free by now, when the call asks for the grouping.
 template <int NT>
-__device__ __forceinline__ void route_finish(const RouteKParams &p)
+__device__ __forceinline__ void route_finish(const RouteKParams &p, char *smem)
 {
     __shared__ int last_flag;
-    __threadfence();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0)
-        last_flag = (atomicAdd(p.arrivals, 1) == (int)gridDim.x - 1);
+    if (threadIdx.x == 0) {
+        const unsigned n = gridDim.x, f = blockIdx.x % ARRIVAL_FAN;
+        bool last = true;
+        if (n > ARRIVAL_FAN) {
+            const unsigned mine = (n - f + ARRIVAL_FAN - 1) / ARRIVAL_FAN;   // workgroups that report to word f
+            last = atomicAdd(p.arrivals + (1 + f) * ARRIVAL_STRIDE, 1) == (int)mine - 1;
+        }
+        if (last) last = atomicAdd(p.arrivals, 1) == (int)min(n, (unsigned)ARRIVAL_FAN) - 1;
+        last_flag = last;
+    }
     __syncthreads();
     if (!last_flag) return;
-    __threadfence();
     if (p.self_clean && p.counts) {   // (uniform) nobody zeroed the histogram ahead of this launch
         for (int k = threadIdx.x; k < p.K; k += NT) p.counts[k] = 0;
         __syncthreads();
     }
-    if (p.self_clean && threadIdx.x == 0) *p.arrivals = 0;
-    for (int q = threadIdx.x; q < (int)p.N; q += NT) {
-        const unsigned long long key =
-            __hip_atomic_load(&p.best[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (p.self_clean) p.best[q] = ~0ull;   // ready for the next call
-        const unsigned idx = (unsigned)(key & 0xffffffffu);
-        const int bi = (idx < (unsigned)p.K) ? (int)idx : 0;   // nothing won: centroid 0
-        if (p.cid) p.cid[q] = bi;
-        if (p.expert_ids) p.expert_ids[q] = p.slot ? p.slot[bi] : bi;
-        if (p.counts) atomicAdd(&p.counts[bi], 1);
+    if (p.self_clean && threadIdx.x <= ARRIVAL_FAN) p.arrivals[threadIdx.x * ARRIVAL_STRIDE] = 0;
+    constexpr int UNR = 4;   // the loads of several queries in flight: each is a trip to memory
+    for (int q0 = threadIdx.x; q0 < (int)p.N; q0 += NT * UNR) {
+        int bi[UNR];
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            const int q = min(q0 + u * NT, (int)p.N - 1);
+            const unsigned idx =
+                (unsigned)(__hip_atomic_load(&p.best[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xffffffffu);
+            bi[u] = (idx < (unsigned)p.K) ? (int)idx : 0;   // nothing won: centroid 0
+        }
+        int e[UNR];
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) e[u] = p.slot ? p.slot[bi[u]] : bi[u];
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            const int q = q0 + u * NT;
+            if (q >= (int)p.N) break;
+            if (p.cid) p.cid[q] = bi[u];
+            if (p.expert_ids) p.expert_ids[q] = e[u];
+            if (p.counts) atomicAdd(&p.counts[bi[u]], 1);
+        }
+    }
+    if (p.self_clean) {   // ready for the next call (every thread its own queries, read above; lanes past the end read the last)
+        __syncthreads();
+        for (int q = threadIdx.x; q < (int)p.N; q += NT) p.best[q] = ~0ull;
     }
     if constexpr (NT == PLAN_THREADS_SMALL) {
         if (p.with_plan) {
             // the ids this workgroup has just written are the plan's input
             __threadfence_block();
             __syncthreads();
-            plan_body<PLAN_THREADS_SMALL>(p.plan, p.seq_offsets, p.expert_ids, p.rank_of_expert, p.err_word);
+            plan_body<PLAN_THREADS_SMALL, PLAN_CAP_SMALL>(p.plan, p.seq_offsets, p.expert_ids, p.rank_of_expert, p.err_word,
+                                          *reinterpret_cast<PlanLdsSmall *>(smem));
         }
     }
 }
