@@ -212,9 +212,13 @@ struct PlanLayout {
 PlanLayout plan_layout(int32_t S, int64_t T, int32_t E, bool upper_bound = false)
 {
     PlanLayout L;
-    // one record per distinct expert (and one for "no adapter"), plus what cutting the
-    // groups into chunks of GROUP_CHUNK tokens can add
-    const int64_t groups = std::min<int64_t>(S, (int64_t)E + 1) + T / GROUP_CHUNK + 1;
+    // one record per distinct expert (and one for "no adapter"), plus what cutting the groups can add: between two
+    // sizes of record it grows with T, so the most of any batch of up to T tokens is found at T or at such a step
+    int64_t cut = group_chunk_records(T);
+    if (upper_bound)
+        for (int64_t step : {(int64_t)DECODE_MAX_T, (int64_t)4096, (int64_t)16384})
+            if (T > step) cut = std::max(cut, group_chunk_records(step));
+    const int64_t groups = std::min<int64_t>(S, (int64_t)E + 1) + cut;
     L.decode = upper_bound || ((T <= DECODE_MAX_T || T <= (int64_t)GATHER_MAX_AVG_LEN * S) && groups <= 65535);
     L.max_tiles = (int)(T / TILE_M) + S + 1;
     L.max_groups = L.decode ? (int)std::min<int64_t>(groups, 65535) : 0;
@@ -314,6 +318,7 @@ static int plan_prepare(moin_plan *plan, const int32_t *seq_offsets, const int32
     pv.max_tiles = L.max_tiles;
     pv.max_groups = L.max_groups;
     pv.decode = L.decode;
+    pv.chunk = group_chunk(T);
     return 0;
 }
 

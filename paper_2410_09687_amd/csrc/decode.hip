@@ -3,17 +3,23 @@
 // streaming W_a and W_b of every distinct adapter from HBM once (Section 1:
 // many small adapters served together; Section 3.2: y = W x + W_b (W_a x)).
 //
-// Tokens arrive grouped by expert (plan).  One workgroup handles one
-// (expert, slab of adapter rows): it streams the slab with 16-byte lane loads
-// straight into MFMA operands -- no LDS staging, each adapter byte is used by
-// exactly one wave -- and multiplies it against the (at most a few) tokens of
-// that expert with v_mfma_f32_16x16x32_bf16, whose 16 columns are 16 tokens.
-// Idle MFMA columns cost nothing here: the kernels are HBM-bound, and what
-// decides their speed is how many independent loads are in flight, so every
-// wave issues all loads of a batch before the first MFMA that consumes them
-// and the grid is shaped for several resident workgroups per compute unit.
+// Tokens arrive grouped by expert (plan), in records of at most `chunk` tokens.  An item of work is a slab of one
+// record's adapter rows against its (at most a few) tokens with v_mfma_f32_16x16x32_bf16, whose 16 columns are 16
+// tokens.  Idle MFMA columns cost nothing here: the kernels are HBM-bound, and what decides their speed is
+//  * how the adapter is asked for: 512 consecutive bytes of a row or more per instruction, non-temporal, and into the
+//    MFMA operand's order through LDS of the wave's own.  The operand's map as a load (16 rows x 64 bytes per
+//    instruction) reads 400 adapters of 512 KB at 5.6 TB/s, 3.5 when the Infinity Cache is full of dirty lines (as
+//    after a base product); this one at 6.3 and 6.1, it leaves that cache alone (operand map and non-temporal: 5.4).
+//  * that loads are always in flight: a workgroup (a wave, in the expand) walks through items, the next one's
+//    adapter rows going out before the present one's are waited for (two sets of registers, in turn; a step after the
+//    last, or without an adapter, loads a few bytes that nobody uses, so that the number of loads in flight is the same
+//    on every path and the compiler can wait for the older ones alone);
+//  * that no workgroup is launched for nothing: the number of distinct experts is known on the device only (a batch
+//    of 1024 Zipf-drawn sequences has 340), and a workgroup for a record that is not there costs a slot and a trip to
+//    memory.  The grids are sized for the chip.
+// Records of several token blocks (longer sequences) keep their slab in registers instead (the "held" kernels).
 //
-//   base   : ybase[s] = x[:, range s] W[:, range s]^T   (fp32, linear.hip)
+//   base   : ybase[s] = x[:, range s] W[:, range s]^T   (fp32; tiles of linear_tile.h, or slabs in the smallest batches)
 //   shrink : ug[pos, :] = scale * A_e x_tok             (bf16 high part + remainder)
 //   expand : y[tok, :]  = sum_s ybase[s][tok, :] + B_e ug[pos]
 #include <algorithm>
@@ -37,27 +43,19 @@ __device__ __forceinline__ bf16x8_t ldg_frag(const char *row, int k, int klen)
     return __builtin_bit_cast(bf16x8_t, v);
 }
 
-// Group records and the first token indices of a group come through the scalar
-// cache: a scalar load does not queue behind the compute unit's vector-memory
-// traffic, so a workgroup knows its adapter and its tokens a few hundred
-// nanoseconds after it starts and can then issue ALL of its vector loads at once --
-// one trip to memory per workgroup instead of a chain of three.  (Under load
-// every dependent vector load costs a full queueing delay of several
-// microseconds, which is what kept these kernels at half the streaming rate.)
+// Group records and the token indices of a block come through the scalar cache: a
+// scalar load does not queue behind the compute unit's vector-memory traffic, so a
+// workgroup knows its adapter and its tokens a few hundred nanoseconds after it starts
+// and can then issue ALL of its vector loads at once -- one trip to memory per item
+// instead of a chain of three.  (Under load every dependent vector load costs a full
+// queueing delay of several microseconds.)  Reading through the constant address space
+// at a uniform address is what makes a load a scalar one.
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
-typedef int i32x16_t __attribute__((ext_vector_type(16)));
-__device__ __forceinline__ i32x4_t sload_x4(const void *p)   // p: uniform, 4-byte aligned
-{
-    i32x4_t v;
-    asm volatile("s_load_dwordx4 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(p) : "memory");
-    return v;
-}
-__device__ __forceinline__ i32x16_t sload_x16(const void *p)
-{
-    i32x16_t v;
-    asm volatile("s_load_dwordx16 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(p) : "memory");
-    return v;
-}
+typedef int i32x16_t __attribute__((ext_vector_type(16), aligned(4)));
+#define MOIN_CONST_AS __attribute__((address_space(4)))
+__device__ __forceinline__ int sload_x1(const int *p) { return *(const MOIN_CONST_AS int *)(uintptr_t)p; }
+__device__ __forceinline__ i32x4_t sload_x4(const int4 *p) { return *(const MOIN_CONST_AS i32x4_t *)(uintptr_t)p; }
+__device__ __forceinline__ i32x16_t sload_x16(const int *p) { return *(const MOIN_CONST_AS i32x16_t *)(uintptr_t)p; }
 // Element (lane % 16) of sixteen wave-uniform values.
 __device__ __forceinline__ int pick16(const i32x16_t &t, int lane)
 {
@@ -96,48 +94,66 @@ struct ShrinkDParams {
     int act;
 };
 
-// One (expert group g, 16-row slab of A_e) of the decode shrink; `red` is the
-// workgroup's [SHRINK_WAVES][64][4] floats of LDS.
-// KS_HOLD > 0 (batches beyond the small-batch size, whose group records hold up
-// to GROUP_CHUNK tokens: several blocks of 16): a wave's share of the slab is at
+typedef float Partials[SHRINK_WAVES][64][4] __attribute__((aligned(16)));   // of one 16 x 16 block, a wave's share each
+
+// Added in wave order: runs repeat bit for bit.
+__device__ __forceinline__ f32x4_t sum_partials(const Partials &red, int lane)
+{
+    f32x4_t f = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < SHRINK_WAVES; ++w) f += *reinterpret_cast<const f32x4_t *>(red[w][lane]);
+    return f;
+}
+
+// u for one block of 16 positions and 16 rows of A_e from the waves' partial sums, as a bf16 pair.  One wave calls it.
+__device__ __forceinline__ void store_u(const Partials &red, int lane, int pos0, int ge, int j0, int r, int ldr, int act,
+                                        float scale, char *ug_hi, char *ug_lo)
+{
+    // lane holds u[token = lane % 16][j0 + 4 * (lane / 16) + i]
+    const f32x4_t s = sum_partials(red, lane);
+    uint32_t h[4], l[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float f = adapter_act(s[i], act) * scale;
+        h[i] = f32_to_bf16_bits(f);
+        l[i] = f32_to_bf16_bits(f - bf16_bits_to_f32(h[i]));
+    }
+    const int pos = pos0 + (lane & 15), jj = j0 + 4 * (lane >> 4);
+    if (pos < ge && jj < r) {   // r % 8 == 0, so a group of 4 is all in or all out
+        const int64_t off = ((int64_t)pos * ldr + jj) * 2;
+        *reinterpret_cast<uint2 *>(ug_hi + off) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+        *reinterpret_cast<uint2 *>(ug_lo + off) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+    }
+}
+
+// Barrier for data that goes through LDS: loads from memory stay in flight across it (__syncthreads waits for them).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// One (expert group g, 16-row slab of A_e) of a large batch's shrink; `red` is two buffers, used in turn (`flip`).
+// KS_HOLD > 0 (records of several blocks of 16 tokens): a wave's share of the slab is at
 // most KS_HOLD k-steps and stays in registers for all of the record's token
 // blocks, instead of being fetched again for each.
-template <int UNR, int KS_HOLD = 0>
-__device__ __forceinline__ void decode_shrink_slab(const ShrinkDParams &p, int slab, int g,
-                                                   float (*red)[64][4])
+template <int UNR, int KS_HOLD>
+__device__ __forceinline__ void decode_shrink_slab(const ShrinkDParams &p, int slab, int g, Partials *red, int &flip)
 {
+    static_assert(KS_HOLD > 0 && KS_HOLD % UNR == 0, "whole batches");
     constexpr int NW = SHRINK_WAVES;
     const char *__restrict__ x = p.x;
     const char *__restrict__ A_stack = p.A_stack;
-    char *__restrict__ ug_hi = p.ug_hi;
-    char *__restrict__ ug_lo = p.ug_lo;
     const int *__restrict__ tok_sorted = p.tok_sorted;
-    const int4 *__restrict__ grp_meta = p.grp_meta;
-    const int *__restrict__ n_groups = p.n_groups;
     const int d_in = p.d_in;
-    const float scale = p.scale;
-    (void)n_groups;   // records past the group count are empty
-    const i32x4_t gm = sload_x4(grp_meta + g);
-    const int e = gm.x;
-    if (e < 0) return;
-    const int gs = gm.y, ge = gm.z;
-    if (ge <= gs) return;
+    const i32x4_t gm = sload_x4(p.grp_meta + g);
+    const int e = gm.x, gs = gm.y, ge = gm.z;
     // the expert's own rank (a multiple of 8): slabs beyond it are never read, u is
     // stored [pos, p.r] and only its first r columns are written and later read
     const int r = min(p.r, gm.w);
-    const int ldr = p.r;
-    if (slab * 16 >= r) return;
+    if (e < 0 || ge <= gs || slab * 16 >= r) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    // tokens of the first block of 16 positions (entries past the group's end are read --
-    // the list is followed by more of the plan -- and not used)
-    const i32x16_t toks = sload_x16(tok_sorted + gs);
-    const int tok_first = pick16(toks, lane);
-    const int tok_gs = toks[0];   // lanes past the group's end take its first token (in bounds, result unused)
     const int j0 = slab * 16;
     const int jrow = j0 + (lane & 15);
     const int kq = (lane >> 4) * 8;               // element offset of this lane's k-group
     const int64_t ld = (int64_t)d_in * 2;
-    const char *arow = A_stack + ((int64_t)e * ldr + (jrow < r ? jrow : 0)) * ld;
+    const char *arow = A_stack + ((int64_t)e * p.r + (jrow < r ? jrow : 0)) * ld;
     // each wave owns a contiguous run of k-steps: its 16 rows are read as 16
     // contiguous segments
     const int nks = (d_in + 31) / 32;
@@ -146,70 +162,33 @@ __device__ __forceinline__ void decode_shrink_slab(const ShrinkDParams &p, int s
     const int ks_end = min(nks, ks_beg + per);
     const int klen = min(d_in, ks_end * 32);
 
-    bf16x8_t held[KS_HOLD > 0 ? KS_HOLD : 1];
-    if constexpr (KS_HOLD > 0) {
+    bf16x8_t held[KS_HOLD];
 #pragma unroll
-        for (int u = 0; u < KS_HOLD; ++u) held[u] = ldg_frag(arow, (ks_beg + u) * 32 + kq, klen);   // past the range: zero
-    }
+    for (int u = 0; u < KS_HOLD; ++u) held[u] = ldg_frag(arow, (ks_beg + u) * 32 + kq, klen);   // past the range: zero
     for (int t0 = gs; t0 < ge; t0 += 16) {
-        const int pos = t0 + (lane & 15);
-        const bool tvalid = pos < ge;
+        // (entries past the record's end are read -- the list is followed by more of the plan -- and not used: such
+        // lanes take the block's first token, in bounds, result unused)
+        const i32x16_t toks = sload_x16(tok_sorted + t0);
+        const int tok = t0 + (lane & 15) < ge ? pick16(toks, lane) : toks[0];
         f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-        int tok = tvalid ? tok_first : tok_gs;
-        if (t0 != gs) tok = tok_sorted[tvalid ? pos : gs];
         const char *xrow = x + (int64_t)tok * ld;
-        if constexpr (KS_HOLD > 0) {
 #pragma unroll
-            for (int u0 = 0; u0 < KS_HOLD; u0 += UNR) {
-                if (ks_beg + u0 < ks_end) {   // the same for the whole wave
-                    bf16x8_t b[UNR];
+        for (int u0 = 0; u0 < KS_HOLD; u0 += UNR) {
+            if (ks_beg + u0 < ks_end) {   // the same for the whole wave
+                bf16x8_t b[UNR];
 #pragma unroll
-                    for (int u = 0; u < UNR; ++u) b[u] = ldg_frag(xrow, (ks_beg + u0 + u) * 32 + kq, klen);
+                for (int u = 0; u < UNR; ++u) b[u] = ldg_frag(xrow, (ks_beg + u0 + u) * 32 + kq, klen);
 #pragma unroll
-                    for (int u = 0; u < UNR; ++u)
-                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(held[u0 + u], b[u], acc, 0, 0, 0);
-                }
-            }
-        } else
-        for (int ks0 = ks_beg; ks0 < ks_end; ks0 += UNR) {
-            // every load of the batch is issued before the first one is used
-            uint4 ra[UNR], rb[UNR];
-#pragma unroll
-            for (int u = 0; u < UNR; ++u) ra[u] = ldg_raw(arow, (ks0 + u) * 32 + kq, klen);
-#pragma unroll
-            for (int u = 0; u < UNR; ++u) rb[u] = ldg_raw(xrow, (ks0 + u) * 32 + kq, klen);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                const int k = (ks0 + u) * 32 + kq;   // past the wave's range: zero
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_of(ra[u], k, klen), frag_of(rb[u], k, klen), acc,
-                                                              0, 0, 0);
+                for (int u = 0; u < UNR; ++u)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(held[u0 + u], b[u], acc, 0, 0, 0);
             }
         }
+        Partials &part = red[flip & 1];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) red[wave][lane][i] = acc[i];
-        __syncthreads();
-        if (wave == 0) {
-            // lane holds u[token = lane % 16][j0 + 4 * (lane / 16) + i]; the
-            // partial sums are added in wave order, so runs repeat bit for bit
-            uint32_t h[4], l[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float f = 0.f;
-#pragma unroll
-                for (int w = 0; w < NW; ++w) f += red[w][lane][i];
-                f = adapter_act(f, p.act) * scale;
-                h[i] = f32_to_bf16_bits(f);
-                l[i] = f32_to_bf16_bits(f - bf16_bits_to_f32(h[i]));
-            }
-            const int jj = j0 + 4 * (lane >> 4);
-            if (tvalid && jj < r) {   // r % 8 == 0, so a group of 4 is all in or all out
-                const int64_t off = ((int64_t)pos * ldr + jj) * 2;
-                *reinterpret_cast<uint2 *>(ug_hi + off) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-                *reinterpret_cast<uint2 *>(ug_lo + off) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
-            }
-        }
-        __syncthreads();
+        for (int i = 0; i < 4; ++i) part[wave][lane][i] = acc[i];
+        lds_barrier();   // (one is enough: a buffer is written again only after the next one)
+        if (wave == (flip & (NW - 1))) store_u(part, lane, t0, ge, j0, r, p.r, p.act, p.scale, p.ug_hi, p.ug_lo);
+        ++flip;
     }
 }
 
@@ -227,55 +206,261 @@ struct DecodeMore {
     int d_out[MAX_SHARED_X], n_tiles_n[MAX_SHARED_X];
 };
 
-// grid (ceil(r / 16), max_groups): the slabs of one expert are neighbours in
-// dispatch order, so its rows of A_e stream from HBM as one contiguous run.
-template <int KS_HOLD>
-__global__ __launch_bounds__(SHRINK_WAVES * 64) void decode_shrink_kernel(ShrinkDParams p)
+// Which items a workgroup of a persistent launch takes.  `n_base` long items (base products) go first, workgroup w
+// taking numbers w, w + P, ...; each of them stands for `c` short ones (shrink slabs), which fill the turns that are
+// left, also in the order of the workgroups: static, so that nothing has to be counted in memory, and even.
+struct Turns {
+    int P, n_base, c;
+    __device__ __forceinline__ int short_item(int w, int j) const
+    {
+        const int rem = n_base % P;   // workgroups with one long item more than the others
+        if (w < rem) return c * (P - rem) + j * P + w;
+        if (j < c) return j * (P - rem) + (w - rem);
+        return c * (P - rem) + (j - c) * P + w;
+    }
+};
+
+constexpr int STREAM_KSTEPS = 8;                          // k-steps (of 32) per wave and step
+constexpr int STREAM_COL = STREAM_KSTEPS * 64;            // bytes of a row that a wave takes in a step
+constexpr int STREAM_STAGE = SHRINK_WAVES * 16 * STREAM_COL;   // 16 rows x 4 KB
+constexpr int STREAM_SMEM = STREAM_STAGE + 2 * (int)sizeof(Partials);   // 80 KB: two workgroups per compute unit
+
+// The same value, which the compiler cannot know: what is derived from it is computed where it is used and does not
+// stay in registers across a streaming loop, whose loads in flight need them.
+__device__ __forceinline__ int opaque(int v)
 {
-    __shared__ float red[SHRINK_WAVES][64][4];
-    decode_shrink_slab<SHRINK_BATCH, KS_HOLD>(p, (int)blockIdx.x, (int)blockIdx.y, red);
+    asm volatile("" : "+v"(v));
+    return v;
 }
 
-// Base GEMM tiles and shrink slabs in one launch: the two are independent, the
-// shrink is bound by HBM and the base GEMM by the latency of its short serial
-// loops, so side by side the base GEMM costs little time of its own.  The
-// first `n_base` workgroups take base tiles (dispatched first, they run
-// longest), the others one shrink slab each.
+// 16 bytes of an adapter, read once per call: not to displace what is in the Infinity Cache.
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint4 ldg_nt(const char *p)
+{
+    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p)));
+}
+
+// The arguments of the streaming kernels, read back where they are needed from the kernel's argument block: uniform
+// loads through the scalar cache, so that what a projection picks can be indexed and does not stay in registers.
+struct ShrinkStreamArgs {
+    ShrinkDParams sp;
+    LinearKParams lp;
+    DecodeMore m;
+    Turns turns;
+    int n_w, n_slabs;
+};
+template <class A>
+__device__ __forceinline__ const MOIN_CONST_AS A *kernel_args()
+{
+    return (const MOIN_CONST_AS A *)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+// The shrink as one stream of loads per workgroup, two workgroups per compute unit.  An item is 16 rows of A_e of one
+// (record, projection) -- or, in the smallest batches (decode_base_shape), 16 rows of W (`n_w` of them, first) against the whole
+// batch: the base product is the same kind of work there.  A step is 4 KB of each of the 16 rows and one block of 16
+// tokens: each wave owns 512 bytes of the rows and reads them as such, two rows per instruction; they take the MFMA
+// operand's order in LDS of the wave's own, so there is no barrier but one per item, on LDS alone, where the waves'
+// sums meet; one wave at a time adds them up.  The records' own loads (scalar) are an item ahead.
+__device__ __forceinline__ void shrink_stream(const MOIN_CONST_AS ShrinkStreamArgs *args, char *smem)
+{
+    constexpr int NW = SHRINK_WAVES, KS = STREAM_KSTEPS;
+    Partials *red = reinterpret_cast<Partials *>(smem + STREAM_STAGE);
+    const int lane_id = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6), w = (int)blockIdx.x;
+    char *const mine = smem + wave * (16 * STREAM_COL);
+    const Turns turns{args->turns.P, args->turns.n_base, args->turns.c};
+    const int n_w = args->n_w, n_slabs = args->n_slabs, r_stack = args->sp.r, d_in = args->sp.d_in;
+    const int per_g = n_slabs * args->m.n;
+    const int4 *grp_meta = args->sp.grp_meta;
+    const int *tok_sorted = args->sp.tok_sorted;
+    const char *x = args->sp.x;
+    const int n_items = n_w + sload_x1(args->sp.n_groups) * per_g;
+    const uint32_t ld = (uint32_t)d_in * 2u;
+    const int n_batches = (int)((ld + NW * STREAM_COL - 1) / (NW * STREAM_COL));
+    const uint32_t col = (uint32_t)wave * STREAM_COL;
+
+    struct Item {
+        const char *A;           // first of the 16 rows
+        int rows, t0, ge;        // rows that exist (0: nothing to do), the block's first position, one past the last
+        int proj, j0, r;         // proj < 0: rows of W of projection ~proj; r: rank, or d_out
+        int batch;               // the step's piece of the rows
+        int kept;                // the rows are in LDS already: only the tokens change
+    };
+    int turn = 0;
+    int it_next = turns.short_item(w, 0);
+    if (it_next >= n_items) return;
+    auto meta_of = [&](int it) __attribute__((always_inline)) {
+        return sload_x4(grp_meta + (it >= n_w && it < n_items ? (it - n_w) / per_g : 0));
+    };
+    i32x4_t gm_next = meta_of(it_next);
+    bool more = true;
+    // The workgroup's next item.  Past the expert's rank there is nothing to read, nor without an adapter.
+    auto advance = [&]() __attribute__((always_inline)) {
+        Item o;
+        const int it = it_next;
+        const i32x4_t gm = gm_next;
+        more = it < n_items;
+        it_next = turns.short_item(w, ++turn);
+        gm_next = meta_of(it_next);
+        o.batch = o.kept = 0;
+        if (it < n_w) {
+            int q = 0;
+#pragma unroll
+            for (int i = 1; i < MAX_SHARED_X; ++i) q += i < args->m.n && it >= args->m.base_first[i];
+            o.proj = ~q;
+            o.j0 = (it - args->m.base_first[q]) * 16;
+            o.r = args->m.d_out[q];
+            o.rows = min(16, o.r - o.j0);
+            o.A = args->m.W[q] + (int64_t)o.j0 * ld;
+            o.t0 = 0;
+            o.ge = (int)args->lp.T;
+        } else {
+            const int idx = (it - n_w) % per_g;
+            o.proj = idx / n_slabs;
+            o.j0 = (idx - o.proj * n_slabs) * 16;
+            o.t0 = gm.y;
+            o.ge = gm.z;
+            o.r = min(r_stack, gm.w);
+            o.rows = more && gm.x >= 0 ? max(0, min(16, o.r - o.j0)) : 0;
+            o.A = args->m.A_stack[o.proj] + ((int64_t)(o.rows > 0 ? gm.x : 0) * r_stack + (o.rows > 0 ? o.j0 : 0)) * ld;
+        }
+        return o;
+    };
+    // The wave's 16 x 512 bytes of a step's rows (instruction u: rows 2u and 2u + 1).  Past the rows or the row's end a
+    // valid address is read instead and masked or never used.
+    auto issue_rows = [&](const Item &o, uint4(&ra)[KS]) __attribute__((always_inline)) {
+        const int lane = opaque(lane_id);
+        const uint32_t ka = (uint32_t)o.batch * (NW * STREAM_COL) + col + (uint32_t)(lane & 31) * 16;
+        const int rows = o.kept ? 0 : o.rows;
+        const uint32_t kk = rows > 0 && ka < ld ? ka : 0u;
+#pragma unroll
+        for (int u = 0; u < KS; ++u) {
+            const int row = 2 * u + (lane >> 5);
+            ra[u] = ldg_nt(o.A + ((row < rows ? (uint32_t)row * ld : 0u) + kk));
+        }
+    };
+    auto toks_of = [&](const Item &o) __attribute__((always_inline)) {
+        // (entries past the record's end are read -- the list is followed by more of the plan -- and not used)
+        return sload_x16(tok_sorted + o.t0);
+    };
+    Item cur = advance();
+    i32x16_t toks = toks_of(cur);
+    int flip = 0;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    // One step: its rows are in flight to `ra`; the next one's go to `ra_next`.
+    auto step = [&](uint4(&ra)[KS], uint4(&ra_next)[KS]) __attribute__((always_inline)) {
+        const int lane = opaque(lane_id);
+        const uint32_t k0 = (uint32_t)cur.batch * (NW * STREAM_COL) + col;
+        // (lanes past the record's end take the block's first token)
+        const int tok = cur.t0 + (lane & 15) < cur.ge ? pick16(toks, lane) : toks[0];
+        const char *xrow = x + (int64_t)tok * ld;
+        uint4 rx[KS];
+#pragma unroll
+        for (int u = 0; u < KS; ++u) {
+            const uint32_t k = k0 + (uint32_t)(u * 64 + (lane >> 4) * 16);
+            rx[u] = *reinterpret_cast<const uint4 *>(xrow + (k < ld ? k : 0u));
+        }
+        const bool last = cur.batch + 1 == n_batches;
+        Item nxt = cur;
+        if (!last) ++nxt.batch;
+        else if (cur.t0 + 16 < cur.ge) {   // several blocks
+            nxt.t0 += 16;
+            nxt.kept = n_batches == 1;
+            nxt.batch = 0;
+        }
+        else nxt = advance();
+        toks = toks_of(nxt);
+        __builtin_amdgcn_sched_barrier(0);
+        issue_rows(nxt, ra_next);
+        __builtin_amdgcn_sched_barrier(0);
+        const int ln = opaque(lane_id);
+        // 16-byte chunk c of row j stands at place c ^ j: neither the writes (consecutive chunks) nor the operand's
+        // reads (16 rows at one chunk) meet a bank twice
+        if (!cur.kept) {
+#pragma unroll
+            for (int u = 0; u < KS; ++u) {
+                const int row = 2 * u + (ln >> 5);
+                *reinterpret_cast<uint4 *>(mine + row * STREAM_COL + (((ln & 31) ^ row) * 16)) = ra[u];
+            }
+        }
+        const char *src = mine + (ln & 15) * STREAM_COL;
+#pragma unroll
+        for (int u = 0; u < KS; ++u) {
+            const uint4 fa = *reinterpret_cast<const uint4 *>(src + (((u * 4 + (ln >> 4)) ^ (ln & 15)) * 16));
+            const int k = (int)(k0 >> 1) + u * 32 + (ln >> 4) * 8;
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_of(fa, k, d_in), frag_of(rx[u], k, d_in), acc, 0, 0, 0);
+        }
+        if (last) {
+            Partials &part = red[flip & 1];
+            const int le = opaque(lane_id);
+            *reinterpret_cast<f32x4_t *>(part[wave][le]) = acc;
+            acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            lds_barrier();   // (one is enough: a buffer is written again only after the next one)
+            if (wave == (flip & (NW - 1)) && cur.rows > 0) {
+                if (cur.proj < 0) {
+                    const int pos = cur.t0 + (le & 15), o = cur.j0 + 4 * (le >> 4);
+                    const f32x4_t v = sum_partials(part, le);
+                    if (pos < cur.ge && o < cur.r)   // d_out % 8 == 0
+                        *reinterpret_cast<f32x4_t *>(args->m.ybase[~cur.proj] + (int64_t)pos * cur.r + o) = v;
+                } else {
+                    store_u(part, le, cur.t0, cur.ge, cur.j0, cur.r, r_stack, args->sp.act, args->sp.scale,
+                            args->m.ug_hi[cur.proj], args->m.ug_lo[cur.proj]);
+                }
+            }
+            ++flip;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        cur = nxt;
+    };
+    uint4 ra0[KS], ra1[KS];
+    issue_rows(cur, ra0);
+    for (;;) {
+        step(ra0, ra1);
+        if (!more) return;
+        step(ra1, ra0);
+        if (!more) return;
+    }
+}
+
+// The shrink of a large batch: items of (record, 16 rows of A_e), the slabs of one expert neighbours in dispatch
+// order, so its rows of A_e stream from HBM as one contiguous run.
+template <int KS_HOLD>
+__global__ __launch_bounds__(SHRINK_WAVES * 64) void decode_shrink_kernel(ShrinkDParams p, int n_slabs)
+{
+    __shared__ Partials red[2];
+    const int n_items = sload_x1(p.n_groups) * n_slabs;
+    int flip = 0;
+    for (int it = (int)blockIdx.x; it < n_items; it += (int)gridDim.x)
+        decode_shrink_slab<SHRINK_BATCH, KS_HOLD>(p, it % n_slabs, it / n_slabs, red, flip);
+}
+
+// Base products and shrink slabs in one launch: the two are independent, the
+// shrink is bound by HBM and the base tiles by latency, so side by side the base
+// costs little time of its own.  TILES: base tiles of 128 x 128, each standing for
+// turns.c items; else n_w slabs of 16 rows of W among the items (or none: the shrink alone).  With several projections
+// in the call (`m`) the base work of all of them comes first.
 static_assert(CfgDecodeBase::NT == SHRINK_WAVES * 64, "both roles share one workgroup size");
-// With several projections in the call (`m`): the base tiles of all of them first, then the slabs of
-// all of them, `slabs_per_proj` each.
-__global__ __launch_bounds__(SHRINK_WAVES * 64) void decode_base_shrink_kernel(LinearKParams lp, ShrinkDParams sp,
-                                                                             DecodeMore m, int n_base, int n_slabs,
-                                                                             int slabs_per_proj)
+static_assert(CfgDecodeBase::SMEM_BYTES <= STREAM_SMEM, "the tiles' stages in the stream's LDS");
+template <bool TILES>
+__global__ __launch_bounds__(SHRINK_WAVES * 64, 4) void decode_base_shrink_kernel(ShrinkStreamArgs by_value)
 {
     extern __shared__ __align__(16) char smem[];
-    if ((int)blockIdx.x < n_base) {
-        int first = 0;
-        // (picked by comparison, not by indexing: indexing the parameter arrays would put them in scratch)
+    const MOIN_CONST_AS ShrinkStreamArgs *args = kernel_args<ShrinkStreamArgs>();
+    if constexpr (TILES) {
+        const int n_base = args->turns.n_base, P = args->turns.P;
+        for (int b = (int)blockIdx.x; b < n_base; b += P) {
+            int i = 0;
 #pragma unroll
-        for (int i = 1; i < MAX_SHARED_X; ++i)
-            if (i < m.n && (int)blockIdx.x >= m.base_first[i]) {
-                first = m.base_first[i];
-                lp.W = m.W[i];
-                lp.y = reinterpret_cast<char *>(m.ybase[i]);
-                lp.d_out = m.d_out[i];
-                lp.n_tiles_n = m.n_tiles_n[i];
-            }
-        linear_tile<CfgDecodeBase>(lp, (int)blockIdx.x - first, smem);
-    } else {
-        // (the shrink role keeps its partial sums where the base role keeps its stages)
-        int idx = (int)blockIdx.x - n_base;
-#pragma unroll
-        for (int i = 1; i < MAX_SHARED_X; ++i)
-            if (i < m.n && idx >= slabs_per_proj) {
-                idx -= slabs_per_proj;
-                sp.A_stack = m.A_stack[i];
-                sp.ug_hi = m.ug_hi[i];
-                sp.ug_lo = m.ug_lo[i];
-            }
-        decode_shrink_slab<SHRINK_BATCH>(sp, idx % n_slabs, idx / n_slabs,
-                                         reinterpret_cast<float(*)[64][4]>(smem));
+            for (int j = 1; j < MAX_SHARED_X; ++j) i += j < args->m.n && b >= args->m.base_first[j];
+            LinearKParams q = by_value.lp;
+            q.W = args->m.W[i];
+            q.y = reinterpret_cast<char *>(args->m.ybase[i]);
+            q.d_out = args->m.d_out[i];
+            q.n_tiles_n = args->m.n_tiles_n[i];
+            linear_tile<CfgDecodeBase>(q, b - args->m.base_first[i], smem);
+            __syncthreads();   // (the tile's epilogue has left LDS)
+        }
     }
+    shrink_stream(args, smem);
 }
 
 struct ExpandKParams {
@@ -291,13 +476,13 @@ struct ExpandKParams {
 
 constexpr int EXPAND_WAVES = 4;
 
-__device__ __forceinline__ void store_out(const ExpandKParams &p, int tok, int o, f32x4_t v)
+__device__ __forceinline__ void store_out(char *y, int d_out, int y_f32, int tok, int o, f32x4_t v)
 {
-    const int64_t at = (int64_t)tok * p.d_out + o;
-    if (p.y_f32) {
-        *reinterpret_cast<f32x4_t *>(p.y + at * 4) = v;
+    const int64_t at = (int64_t)tok * d_out + o;
+    if (y_f32) {
+        *reinterpret_cast<f32x4_t *>(y + at * 4) = v;
     } else {
-        *reinterpret_cast<uint2 *>(p.y + at * 2) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+        *reinterpret_cast<uint2 *>(y + at * 2) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
     }
 }
 
@@ -425,37 +610,202 @@ __device__ __forceinline__ void expand_item(const ExpandKParams &p, int slab, in
 #pragma unroll
         for (int c = 0; c < RB; ++c) {
             const int oo = o_base + c * 16 + 4 * (lane >> 4);
-            if (tvalid && oo < d_out) store_out(p, tok, oo, acc[c]);   // d_out % 4 == 0
+            if (tvalid && oo < d_out) store_out(p.y, d_out, p.y_f32, tok, oo, acc[c]);   // d_out % 4 == 0
         }
     }
 }
 
-// grid (ceil(d_out / (EXPAND_WAVES * RB * 16)), max_groups)
-// With several projections in the call (`m`): grid.x holds the row blocks of all of them.
+// Items of (record, EXPAND_WAVES * RB * 16 rows of B_e), the row blocks of one record neighbours; with several
+// projections in the call (`m`) a record's items are the row blocks of all of them (n_xb).
 template <int KS_HOLD, int NSPLIT, bool BY_POS, int RB>
-__global__ __launch_bounds__(EXPAND_WAVES * 64) void decode_expand_kernel(ExpandKParams p, DecodeMore m)
+__global__ __launch_bounds__(EXPAND_WAVES * 64) void decode_expand_kernel(ExpandKParams p, DecodeMore m, int n_xb)
 {
-    const i32x4_t gm = sload_x4(p.grp_meta + blockIdx.y);   // records past the group count are empty
-    const int e = gm.x, gs = gm.y, ge = gm.z;
-    if (ge <= gs) return;
-    const int r = min(p.r, gm.w);
-    int first = 0;
+    const int n_items = sload_x1(p.n_groups) * n_xb;
+    for (int it = (int)blockIdx.x; it < n_items; it += (int)gridDim.x) {
+        const int g = it / n_xb, xb = it - g * n_xb;
+        const i32x4_t gm = sload_x4(p.grp_meta + g);
+        const int e = gm.x, gs = gm.y, ge = gm.z;
+        if (ge <= gs) continue;
+        const int r = min(p.r, gm.w);
+        ExpandKParams q = p;
+        int first = 0;
 #pragma unroll
-    for (int i = 1; i < MAX_SHARED_X; ++i)
-        if (i < m.n && (int)blockIdx.x >= m.xb_first[i]) {
-            first = m.xb_first[i];
-            p.B_stack = m.B_stack[i];
-            p.ug_hi = m.ug_hi[i];
-            p.ug_lo = m.ug_lo[i];
-            p.ybase = m.ybase[i];
-            p.y = m.y[i];
-            p.d_out = m.d_out[i];
+        for (int i = 1; i < MAX_SHARED_X; ++i)
+            if (i < m.n && xb >= m.xb_first[i]) {
+                first = m.xb_first[i];
+                q.B_stack = m.B_stack[i];
+                q.ug_hi = m.ug_hi[i];
+                q.ug_lo = m.ug_lo[i];
+                q.ybase = m.ybase[i];
+                q.y = m.y[i];
+                q.d_out = m.d_out[i];
+            }
+        if (KS_HOLD > 0 && r == KS_HOLD * 32)
+            expand_item<KS_HOLD, NSPLIT, BY_POS, RB, true>(q, xb - first, e, gs, ge, r);
+        else
+            expand_item<KS_HOLD, NSPLIT, BY_POS, RB, false>(q, xb - first, e, gs, ge, r);
+    }
+}
+
+// The expand of batches whose records are mostly one block of 16 tokens: every wave walks through items of its own,
+// 16 * RB rows of B_e of one (record, projection), one block of tokens at a time.  The rows are read as they lie (1 KB
+// of consecutive bytes per instruction where r fills its k-steps) and take the operand's order in the wave's own LDS.
+// KS: k-steps of 32 that the stacks' rank takes (1, 2 or 4).
+// RB: at KS = 4 two, so that the small batches have items enough (8 single tokens, 2048 -> 5632 twice: 8.6 us, with four
+// 10.3), but four beyond DECODE_MAX_T, where every item loads u and few tokens (8192 of them, 1558 experts: 547 us with
+// two, 514); below, where the rows are short, always four.
+constexpr int expand_stream_rb(int ks, bool large) { return ks <= 2 || large ? 4 : 2; }
+// workgroups per compute unit, as the registers allow
+constexpr int expand_stream_wgs(int ks, int parts, int rb)
+{
+    return ks == 1 ? (parts <= 2 ? 4 : 3) : ks == 2 ? (parts <= 2 ? 3 : 2) : rb > 2 ? 2 : parts == 1 ? 4 : 3;
+}
+constexpr int expand_stage(int ks, int rb) { return rb * 16 * ks * 64; }
+struct ExpandStreamArgs {
+    ExpandKParams p;
+    DecodeMore m;
+    int n_xb;
+};
+template <int KS, int NSPLIT, bool BY_POS, int RB>
+__global__ __launch_bounds__(EXPAND_WAVES * 64, expand_stream_wgs(KS, NSPLIT, RB)) void decode_expand_stream_kernel(ExpandStreamArgs)
+{
+    constexpr int CPR = 4 * KS;   // 16-byte chunks per row
+    extern __shared__ __align__(16) char smem[];
+    const MOIN_CONST_AS ExpandStreamArgs *args = kernel_args<ExpandStreamArgs>();
+    const int lane_id = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6);
+    char *const mine = smem + wave * expand_stage(KS, RB);
+    const int n_xb = args->n_xb, r_stack = args->p.r, y_f32 = args->p.y_f32;
+    const int4 *grp_meta = args->p.grp_meta;
+    const int *tok_sorted = args->p.tok_sorted;
+    const int n_items = sload_x1(args->p.n_groups) * n_xb;
+    const int P = (int)gridDim.x * EXPAND_WAVES;
+    const uint32_t ldb = (uint32_t)r_stack * 2u;
+    const int64_t T = args->p.T;
+
+    struct Item {
+        const char *B;   // first of the rows
+        int proj, o0, d_out, r, t0, ge;
+        int kept;        // the rows are in LDS already: only the tokens change
+    };
+    int it_next = (int)blockIdx.x * EXPAND_WAVES + wave;
+    if (it_next >= n_items) return;
+    auto meta_of = [&](int it) __attribute__((always_inline)) { return sload_x4(grp_meta + (it < n_items ? it / n_xb : 0)); };
+    i32x4_t gm_next = meta_of(it_next);
+    bool more = true;
+    auto advance = [&]() __attribute__((always_inline)) {
+        Item o;
+        const int it = it_next;
+        const i32x4_t gm = gm_next;
+        more = it < n_items;
+        it_next = it + P;
+        gm_next = meta_of(it_next);
+        const int xb = more ? it % n_xb : 0;
+        o.proj = 0;
+#pragma unroll
+        for (int i = 1; i < MAX_SHARED_X; ++i) o.proj += i < args->m.n && xb >= args->m.xb_first[i];
+        o.d_out = args->m.d_out[o.proj];
+        o.o0 = (xb - args->m.xb_first[o.proj]) * (RB * 16);
+        o.t0 = gm.y;
+        o.ge = gm.z;
+        o.r = more && gm.x >= 0 ? min(r_stack, gm.w) : 0;
+        o.kept = 0;
+        o.B = args->m.B_stack[o.proj] + ((int64_t)max(gm.x, 0) * o.d_out + o.o0) * ldb;
+        return o;
+    };
+    // Lane i of instruction j takes chunk i % CPR of row j * (64 / CPR) + i / CPR.  Chunks past the expert's rank are
+    // not read (the row's first one is, and masked); without an adapter nothing is but one chunk.
+    auto issue_rows = [&](const Item &o, uint4(&rb)[RB * KS]) __attribute__((always_inline)) {
+        const int lane = opaque(lane_id);
+        const int c = lane % CPR;
+        const uint32_t cc = c * 8 < o.r && !o.kept ? (uint32_t)c * 16u : 0u;
+        const int rows = o.r > 0 && !o.kept ? o.d_out - o.o0 : 0;
+#pragma unroll
+        for (int j = 0; j < RB * KS; ++j) {
+            const int row = j * (64 / CPR) + lane / CPR;
+            rb[j] = ldg_nt(o.B + ((row < rows ? (uint32_t)row * ldb : 0u) + cc));
         }
-    const int slab = (int)blockIdx.x - first;
-    if (KS_HOLD > 0 && r == KS_HOLD * 32)
-        expand_item<KS_HOLD, NSPLIT, BY_POS, RB, true>(p, slab, e, gs, ge, r);
-    else
-        expand_item<KS_HOLD, NSPLIT, BY_POS, RB, false>(p, slab, e, gs, ge, r);
+    };
+    Item cur = advance();
+    i32x16_t toks = sload_x16(tok_sorted + cur.t0);   // (entries past the record's end: read, not used)
+    auto step = [&](uint4(&rb)[RB * KS], uint4(&rb_next)[RB * KS]) __attribute__((always_inline)) {
+        const int lane = opaque(lane_id), kq = (lane >> 4) * 8;
+        const int pos = cur.t0 + (lane & 15);
+        const bool tvalid = pos < cur.ge;
+        const int ps = tvalid ? pos : cur.t0;
+        const int tok = tvalid ? pick16(toks, lane) : toks[0];
+        // lane holds y[token = lane % 16][o0 + b * 16 + 4 * (lane / 16) + i]; rows past d_out read (and never store)
+        // the last valid group of four
+        f32x4_t part[RB][NSPLIT];
+        uint4 h[KS], l[KS];
+        {
+            const int64_t plane = T * (int64_t)cur.d_out;
+            const float *ybase = args->m.ybase[cur.proj] + (int64_t)(BY_POS ? ps : tok) * cur.d_out;
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+                for (int sp = 0; sp < NSPLIT; ++sp)
+                    part[b][sp] = *reinterpret_cast<const f32x4_t *>(
+                        ybase + sp * plane + min(cur.o0 + b * 16 + 4 * (lane >> 4), cur.d_out - 4));
+            const char *uh = args->m.ug_hi[cur.proj] + (int64_t)ps * ldb, *ul = args->m.ug_lo[cur.proj] + (int64_t)ps * ldb;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                h[ks] = ldg_raw(uh, ks * 32 + kq, cur.r);
+                l[ks] = ldg_raw(ul, ks * 32 + kq, cur.r);
+            }
+        }
+        Item nxt = cur;
+        if (cur.t0 + 16 < cur.ge) nxt.t0 += 16, nxt.kept = 1;   // a record of several blocks
+        else nxt = advance();
+        toks = sload_x16(tok_sorted + nxt.t0);
+        __builtin_amdgcn_sched_barrier(0);
+        issue_rows(nxt, rb_next);
+        __builtin_amdgcn_sched_barrier(0);
+        // chunk c of row i stands at place c ^ (i / (rows per 256 bytes)): no bank is met twice
+        if (!cur.kept) {
+#pragma unroll
+            for (int j = 0; j < RB * KS; ++j) {
+                const int row = j * (64 / CPR) + lane / CPR;
+                *reinterpret_cast<uint4 *>(mine + (row * CPR + ((lane % CPR) ^ ((row / (16 / CPR)) & (CPR - 1)))) * 16) =
+                    rb[j];
+            }
+        }
+        f32x4_t acc[RB];
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+            acc[b] = part[b][0];   // parts are added in order: repeatable
+#pragma unroll
+            for (int sp = 1; sp < NSPLIT; ++sp) acc[b] += part[b][sp];
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int k = ks * 32 + kq;   // (past the rank, or without an adapter: zeros)
+            const bf16x8_t fh = frag_of(h[ks], k, cur.r), fl = frag_of(l[ks], k, cur.r);
+#pragma unroll
+            for (int b = 0; b < RB; ++b) {
+                const int row = b * 16 + (lane & 15);
+                const int ch = (ks * 4 + (lane >> 4)) ^ ((row / (16 / CPR)) & (CPR - 1));
+                const bf16x8_t fa = frag_of(*reinterpret_cast<const uint4 *>(mine + (row * CPR + ch) * 16), k, cur.r);
+                acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fh, acc[b], 0, 0, 0);
+                acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fl, acc[b], 0, 0, 0);
+            }
+        }
+        char *y = args->m.y[cur.proj];
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+            const int oo = cur.o0 + b * 16 + 4 * (lane >> 4);
+            if (tvalid && oo < cur.d_out) store_out(y, cur.d_out, y_f32, tok, oo, acc[b]);   // d_out % 4 == 0
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        cur = nxt;
+    };
+    uint4 rb0[RB * KS], rb1[RB * KS];
+    issue_rows(cur, rb0);
+    for (;;) {
+        step(rb0, rb1);
+        if (!more) return;
+        step(rb1, rb0);
+        if (!more) return;
+    }
 }
 
 static ShrinkDParams shrink_params(const PlanView &pv, const DecodeArgs &d)
@@ -469,37 +819,67 @@ static ShrinkDParams shrink_params(const PlanView &pv, const DecodeArgs &d)
     return p;
 }
 
+static DecodeMore decode_more(const DecodeArgs *d, int n);
+
+constexpr int HELD_WGS = 16;            // workgroups per compute unit of the held kernels, at most: a few rounds each
+constexpr int DECODE_TILE_ITEMS = 3;    // shrink items that a base tile of 32 blocks takes the time of
+
+// Workgroups of a persistent launch: what the chip holds at a time, a multiple of 8 (the XCDs), and no more than
+// there can be items.
+static int persistent_grid(int per_cu, int64_t items)
+{
+    const int64_t P = (int64_t)per_cu * compute_units();
+    return (int)((std::min(P, std::max<int64_t>(items, 1)) + 7) & ~7LL);
+}
+
+// Records tend to span several blocks of 16 tokens (4 tokens per possible group on average is where holding a slab
+// in registers for all of a record's blocks began to pay on the 5632-wide projection).
+static bool several_blocks(const PlanView &pv)
+{
+    return pv.chunk > GROUP_CHUNK_MIN && pv.T >= 4 * std::min<int64_t>(pv.S, (int64_t)pv.E + 1);
+}
+
 hipError_t launch_decode_shrink(const PlanView &pv, const DecodeArgs &d, hipStream_t stream)
 {
     const LinearArgs &a = d.lin;
     if (a.r <= 0 || pv.max_groups <= 0) return hipSuccess;
-    dim3 grid((unsigned)((a.r + 15) / 16), (unsigned)pv.max_groups);
+    const int n_slabs = (a.r + 15) / 16;
+    const int64_t items = (int64_t)n_slabs * pv.max_groups;
+    if (items > 0x3fffffffLL) return hipErrorInvalidValue;
     // k-steps of 32 per wave
     const int per = ((a.d_in + 31) / 32 + SHRINK_WAVES - 1) / SHRINK_WAVES;
     const ShrinkDParams p = shrink_params(pv, d);
-    // holding 24 k-steps costs occupancy: worth it only where records tend to span several token
-    // blocks, i.e. not with about one token per group (4 tokens per possible group on average is
-    // where it began to pay on the 5632-wide projection)
-    const bool several_blocks = pv.T >= 4 * std::min<int64_t>(pv.S, (int64_t)pv.E + 1);
-    if (pv.T > DECODE_MAX_T && per <= 8)
-        hipLaunchKernelGGL(decode_shrink_kernel<8>, grid, dim3(SHRINK_WAVES * 64), 0, stream, p);
-    else if (pv.T > DECODE_MAX_T && per <= 24 && several_blocks)
-        hipLaunchKernelGGL(decode_shrink_kernel<24>, grid, dim3(SHRINK_WAVES * 64), 0, stream, p);
-    else
-        hipLaunchKernelGGL(decode_shrink_kernel<0>, grid, dim3(SHRINK_WAVES * 64), 0, stream, p);
+    const dim3 block(SHRINK_WAVES * 64);
+    if (several_blocks(pv) && per <= 8) {
+        hipLaunchKernelGGL(decode_shrink_kernel<8>, dim3(persistent_grid(HELD_WGS, items)), block, 0, stream, p, n_slabs);
+    } else if (several_blocks(pv) && per <= 24) {
+        hipLaunchKernelGGL(decode_shrink_kernel<24>, dim3(persistent_grid(HELD_WGS, items)), block, 0, stream, p, n_slabs);
+    } else {
+        const Turns turns{persistent_grid(2, items), 0, 1};
+        hipLaunchKernelGGL(decode_base_shrink_kernel<false>, dim3(turns.P), block, STREAM_SMEM, stream,
+                           ShrinkStreamArgs{p, LinearKParams{}, decode_more(&d, 1), turns, 0, n_slabs});
+    }
     return hipGetLastError();
 }
 
 bool decode_base_shrink_fits(const PlanView &pv, const DecodeArgs &d)
 {
-    return d.lin.r > 0 && pv.max_groups > 0 && pv.T > 0 &&
-           decode_base_shape(pv.T, d.lin.d_in, d.lin.d_out).dma;
+    if (d.lin.r <= 0 || pv.max_groups <= 0 || pv.T <= 0) return false;
+    const DecodeBaseShape sh = decode_base_shape(pv.T, d.lin.d_in, d.lin.d_out);
+    return sh.dma || sh.slab_blocks > 0;
+}
+
+template <class K>
+static hipError_t allow_lds(K kern, int bytes)
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
 hipError_t prepare_decode_kernels()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&decode_base_shrink_kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, CfgDecodeBase::SMEM_BYTES);
+    hipError_t e = allow_lds(&decode_base_shrink_kernel<true>, STREAM_SMEM);
+    if (e == hipSuccess) e = allow_lds(&decode_base_shrink_kernel<false>, STREAM_SMEM);
+    return e;
 }
 
 // True when the n projections of a call that share x can share its two launches: the same input,
@@ -510,6 +890,8 @@ bool decode_shared_fits(const PlanView &pv, const DecodeArgs *d, int n)
     for (int i = 0; i < n; ++i) {
         if (!decode_base_shrink_fits(pv, d[i])) return false;
         const LinearArgs &a = d[i].lin, &a0 = d[0].lin;
+        if (decode_base_shape(pv.T, a.d_in, a.d_out).slab_blocks != decode_base_shape(pv.T, a0.d_in, a0.d_out).slab_blocks)
+            return false;
         if (a.x != a0.x || a.d_in != a0.d_in || a.r != a0.r || a.scale != a0.scale || a.act != a0.act ||
             a.y_f32 != a0.y_f32 || d[i].k_splits != d[0].k_splits || d[i].ybase_by_pos != d[0].ybase_by_pos)
             return false;
@@ -540,21 +922,38 @@ hipError_t launch_decode_base_shrink_shared(const PlanView &pv, const DecodeArgs
     DecodeMore m = decode_more(d, n);
     int64_t n_base = 0;
     LinearKParams lp{};
+    DecodeBaseShape first{};
     for (int i = 0; i < n; ++i) {
         const DecodeBaseShape sh = decode_base_shape(pv.T, a.d_in, d[i].lin.d_out);
-        if (!sh.dma || sh.k_splits != d[i].k_splits) return hipErrorInvalidValue;
-        if (i == 0) lp = decode_base_params(pv, a, d[0].ybase, 1, sh, pv.tok_sorted);   // rows in by-expert order
+        if (!(sh.dma || sh.slab_blocks) || sh.k_splits != d[i].k_splits) return hipErrorInvalidValue;
+        if (i == 0) {
+            first = sh;
+            lp = decode_base_params(pv, a, d[0].ybase, 1, sh, pv.tok_sorted);   // rows in by-expert order
+        }
         m.base_first[i] = (int)n_base;
         m.n_tiles_n[i] = sh.n_tiles_n;
-        n_base += sh.grid;   // (a multiple of 8: every projection's tiles keep their place in the XCD rotation)
+        n_base += sh.grid;   // (tiles: a multiple of 8, every projection's tiles keep their place in the XCD rotation)
     }
     const int n_slabs = (a.r + 15) / 16;
-    const int64_t per_proj = (int64_t)n_slabs * pv.max_groups;
-    const int64_t grid = n_base + per_proj * n;
-    if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(decode_base_shrink_kernel, dim3((unsigned)grid), dim3(SHRINK_WAVES * 64),
-                       CfgDecodeBase::SMEM_BYTES, stream, lp, shrink_params(pv, d[0]), m, (int)n_base, n_slabs,
-                       (int)per_proj);
+    const int64_t items = (int64_t)n_slabs * pv.max_groups * n;
+    if (n_base + items > 0x3fffffffLL) return hipErrorInvalidValue;
+    const ShrinkDParams sp = shrink_params(pv, d[0]);
+    const dim3 block(SHRINK_WAVES * 64);
+    Turns turns;
+    turns.P = persistent_grid(2, n_base + items);
+    if (first.slab_blocks == 0) {
+        turns.n_base = (int)n_base;
+        // a tile of 32 blocks takes about as long as DECODE_TILE_ITEMS items of one batch of k-steps
+        const int batches = (a.d_in * 2 + SHRINK_WAVES * STREAM_COL - 1) / (SHRINK_WAVES * STREAM_COL);
+        turns.c = std::max(1, (DECODE_TILE_ITEMS * first.kb_per_split + 16 * batches) / (32 * batches));
+        hipLaunchKernelGGL(decode_base_shrink_kernel<true>, dim3(turns.P), block, STREAM_SMEM, stream,
+                           ShrinkStreamArgs{sp, lp, m, turns, 0, n_slabs});
+    } else {
+        turns.n_base = 0;
+        turns.c = 1;
+        hipLaunchKernelGGL(decode_base_shrink_kernel<false>, dim3(turns.P), block, STREAM_SMEM, stream,
+                           ShrinkStreamArgs{sp, lp, m, turns, (int)n_base, n_slabs});
+    }
     return hipGetLastError();
 }
 
@@ -577,19 +976,33 @@ hipError_t launch_decode_expand_shared(const PlanView &pv, const DecodeArgs *d, 
     p.ybase = d[0].ybase; p.y = (char *)a.y;
     p.tok_sorted = pv.tok_sorted; p.grp_meta = pv.grp_meta; p.n_groups = pv.n_groups;
     p.T = pv.T; p.d_out = a.d_out; p.r = a.r; p.k_splits = d[0].k_splits; p.y_f32 = a.y_f32;
-    constexpr int RB = 4;   // 16-row blocks per wave: 64 KB of B_e per workgroup and rank-128 adapter
-    const int rows = EXPAND_WAVES * RB * 16;
+    const int nks = (a.r + 31) / 32;
+    const bool streams = nks <= 4 && !several_blocks(pv);
+    constexpr int RB = 4;   // 16-row blocks per wave of the held form
+    const bool large = pv.T > DECODE_MAX_T && d[0].k_splits == 1 && !d[0].ybase_by_pos;
+    const int ks = nks <= 2 ? nks : 4, stream_rb = expand_stream_rb(ks, large);
+    const int rows = streams ? stream_rb * 16 : EXPAND_WAVES * RB * 16;
     DecodeMore m = decode_more(d, n);
     int64_t xb = 0;
     for (int i = 0; i < n; ++i) {
         m.xb_first[i] = (int)xb;
         xb += (d[i].lin.d_out + rows - 1) / rows;
     }
-    if (xb > 0x7fffffffLL) return hipErrorInvalidValue;
-    dim3 grid((unsigned)xb, (unsigned)pv.max_groups);
-    const int nks = (a.r + 31) / 32;
-#define MOIN_EXPAND_R(KS, NS, BP) \
-    hipLaunchKernelGGL((decode_expand_kernel<KS, NS, BP, RB>), grid, dim3(EXPAND_WAVES * 64), 0, stream, p, m)
+    const int64_t items = xb * pv.max_groups;
+    if (items > 0x3fffffffLL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(streams ? persistent_grid(expand_stream_wgs(ks, d[0].k_splits, stream_rb), (items + EXPAND_WAVES - 1) / EXPAND_WAVES)
+                                       : persistent_grid(HELD_WGS, items)));
+#define MOIN_EXPAND_STREAM(KS, NS, BP, SRB)                                                                          \
+    hipLaunchKernelGGL((decode_expand_stream_kernel<(KS > 0 ? KS : 1), NS, BP, SRB>), grid, dim3(EXPAND_WAVES * 64), \
+                       EXPAND_WAVES * expand_stage(KS, SRB), stream, ExpandStreamArgs{p, m, (int)xb})
+#define MOIN_EXPAND_R(KS, NS, BP)                                                                                      \
+    do {                                                                                                               \
+        if (KS > 0 && streams && NS == 1 && !BP && large) MOIN_EXPAND_STREAM(KS, 1, false, 4);                         \
+        else if (KS > 0 && streams) MOIN_EXPAND_STREAM(KS, NS, BP, (expand_stream_rb(KS, false)));                     \
+        else                                                                                                           \
+            hipLaunchKernelGGL((decode_expand_kernel<KS, NS, BP, RB>), grid, dim3(EXPAND_WAVES * 64), 0, stream, p, m, \
+                               (int)xb);                                                                               \
+    } while (0)
 #define MOIN_EXPAND_S(KS, NS)                                                                                  \
     do {                                                                                                       \
         if (d[0].ybase_by_pos) MOIN_EXPAND_R(KS, NS, true);                                                    \
@@ -610,6 +1023,7 @@ hipError_t launch_decode_expand_shared(const PlanView &pv, const DecodeArgs *d, 
 #undef MOIN_EXPAND
 #undef MOIN_EXPAND_S
 #undef MOIN_EXPAND_R
+#undef MOIN_EXPAND_STREAM
     return hipGetLastError();
 }
 

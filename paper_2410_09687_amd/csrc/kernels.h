@@ -15,7 +15,17 @@ constexpr int TILE_M = 256;        // rows per plan tile (prefill)
 // where a row tile per sequence would be mostly padding.
 constexpr int DECODE_MAX_T = 1024;
 constexpr int GATHER_MAX_AVG_LEN = 128;
-constexpr int GROUP_CHUNK = 128;   // tokens per group record: a hot expert's tokens are spread over several
+// Tokens per group record: a hot expert's tokens are spread over several.  The decode kernels walk a record's
+// tokens in blocks of 16, one trip to memory after the other, so a small batch has records of a single block (4 x 64
+// tokens on a 256-wide projection: 37 us in one record per expert, 11 us in four); large ones, which have records
+// enough, read an expert's adapter fewer times in longer records.
+constexpr int GROUP_CHUNK_MIN = 16, GROUP_CHUNK_MAX = 128;
+constexpr int group_chunk(int64_t T)
+{
+    return T <= DECODE_MAX_T ? GROUP_CHUNK_MIN : T <= 4096 ? 32 : T <= 16384 ? 64 : GROUP_CHUNK_MAX;
+}
+// Records that cutting the groups into pieces adds at most.
+constexpr int64_t group_chunk_records(int64_t T) { return T / group_chunk(T) + 1; }
 
 // sticky error bits (device word)
 constexpr int ERR_BAD_EXPERT = 1;
@@ -35,7 +45,7 @@ struct PlanView {
     // decode grouping (built only for batches that take the decode path)
     int *tok_sorted;   // [T] token index, grouped by expert
     int4 *grp_meta;    // [max_groups] {adapter slot or -1, first, one-past-last position in tok_sorted, rank};
-                       // an expert with more than GROUP_CHUNK tokens has several records
+                       // an expert with more than `chunk` tokens has several records
     int *grp_start;    // [max_groups + 1] scratch while building
     int2 *grp_tmp;     // [max_groups] scratch while building: {slot, rank} of each expert's group
     // plain row tiles over all T tokens, no adapter (built with the decode grouping when
@@ -52,6 +62,7 @@ struct PlanView {
     int64_t T;
     int E;
     int decode;  // grouping arrays valid
+    int chunk;   // tokens per group record at most
 };
 
 // rank_of_expert: [E] or null (every adapter at the stacks' full rank)

@@ -10,6 +10,8 @@
 // tile.  The same linear kernel, in a smaller tile shape and over a regular
 // grid of tiles, is the decode path's base GEMM; there the contraction range
 // may be cut into several parts, each writing its own fp32 partial result.
+#include <algorithm>
+
 #include "gemm_core.h"
 #include "kernels.h"
 #include "linear_tile.h"
@@ -405,6 +407,17 @@ static void shape_for(int64_t T, int d_in, int d_out, bool may_split, DecodeBase
 static DecodeBaseShape base_shape(int64_t T, int d_in, int d_out, bool may_split)
 {
     DecodeBaseShape sh;
+    sh.slab_blocks = 0;
+    const int slabs = (d_out + 15) / 16;
+    if (may_split && (T <= 16 || (T <= 32 && d_in <= BASE_SLAB_PIECE && slabs <= BASE_SLAB_MAX))) {
+        sh.dma = 0;
+        sh.slab_blocks = (int)((T + 15) / 16);
+        sh.m_tiles = 1;
+        sh.n_tiles_n = sh.grid = slabs;
+        sh.k_splits = 1;
+        sh.kb_per_split = (d_in + 31) / 32;
+        return sh;
+    }
     sh.dma = (d_in % 64 == 0);
     if (sh.dma) shape_for<CfgDecodeBase>(T, d_in, d_out, may_split, &sh);
     else shape_for<CfgThin>(T, d_in, d_out, may_split, &sh);
@@ -451,7 +464,7 @@ static hipError_t launch_plain(const PlanView &pv, const LinearArgs &a, void *ou
 hipError_t launch_decode_base(const PlanView &pv, const DecodeArgs &d, hipStream_t stream)
 {
     const DecodeBaseShape sh = decode_base_shape(pv.T, d.lin.d_in, d.lin.d_out);
-    if (sh.k_splits != d.k_splits) return hipErrorInvalidValue;
+    if (sh.k_splits != d.k_splits || sh.slab_blocks) return hipErrorInvalidValue;
     return launch_plain(pv, d.lin, d.ybase, 1, sh, pv.tok_sorted, stream);   // partial sums in by-expert order
 }
 

@@ -173,19 +173,27 @@ __global__ __launch_bounds__(C::NT) void linear_kernel(LinearKParams p)
 }
 
 // Decode base GEMM, contraction length a multiple of 64: 8 waves, wave patch
-// 64 x 32, four 16 KB stages.  64 KB of LDS lets two workgroups share a compute
-// unit, and the workgroup size matches the decode shrink's, so both kinds of
-// workgroup can live in one launch.
+// 64 x 32, four 16 KB stages.  Two workgroups share a compute unit, and the workgroup size matches
+// the decode shrink's, so both kinds of work can live in one launch.
 using CfgDecodeBase = DmaCore<128, 128, 32, 2, 4, 4>;
 using CfgThin = GemmCore<128, 64, 64, 2, 2>;         // decode base GEMM, any contraction length: 4 waves, 64 x 32
+
+// In the smallest batches a tile would be mostly padding and a chain of trips to memory; the base product is slabs of
+// 16 rows of W against the whole batch instead.  Up to one block of 16 tokens always (8 tokens, us of the launch with
+// tiles / slabs: 2048 -> 2560 in three projections 16 / 10, -> 2048 15 / 7.6, 5632 -> 2048 19 / 12, 2048 -> 5632 twice
+// 17.8 / 17.7), with two blocks where each slab is one step and a projection's two blocks of them one round of the
+// chip's workgroups (17 tokens, first two of these: 19 / 13 and 16 / 10, 32 tokens: 20 / 16 and 17 / 14; but 2048 ->
+// 5632 twice 20 / 23 and 20 / 28).
+constexpr int BASE_SLAB_PIECE = 2048, BASE_SLAB_MAX = 256;
 
 // How the decode base GEMM of a shape is cut up.
 struct DecodeBaseShape {
     int dma;            // 1: CfgDecodeBase, 0: CfgThin
-    int k_splits, kb_per_split;
+    int slab_blocks;    // > 0: slabs of 16 rows of W in the shrink's stream (decode.hip; any d_in), blocks of 16 tokens
+    int k_splits, kb_per_split;   // (blocks of the tile's BK; with slabs k-steps of 32)
     int n_tiles_n;
     int64_t m_tiles;
-    int grid;           // workgroups, a multiple of 8
+    int grid;           // workgroups, a multiple of 8 (with slabs: their number)
 };
 DecodeBaseShape decode_base_shape(int64_t T, int d_in, int d_out);
 // gather: null, or the plan's token order (rows of the result then follow that order)

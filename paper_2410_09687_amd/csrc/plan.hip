@@ -219,19 +219,19 @@ __global__ __launch_bounds__(PLAN_THREADS_MAX) void plan_large_kernel(PlanView p
     }
     if (pv.decode) {
         // A group ends where the next one starts.  It is cut into records of at most
-        // GROUP_CHUNK tokens: the decode kernels hand a record to one column of
+        // pv.chunk tokens: the decode kernels hand a record to one column of
         // workgroups, and a hot expert's tokens must not all queue behind one column.
         __syncthreads();   // grp_start / grp_tmp are complete, a1 is free
         for (int gi = tid; gi < n_groups; gi += PLAN_THREADS)
-            a1[gi] = (pv.grp_start[gi + 1] - pv.grp_start[gi] + GROUP_CHUNK - 1) / GROUP_CHUNK;
+            a1[gi] = (pv.grp_start[gi + 1] - pv.grp_start[gi] + pv.chunk - 1) / pv.chunk;
         __syncthreads();
         const int n_rec = min(block_exclusive_scan<PLAN_THREADS>(a1, n_groups, lds), pv.max_groups);
         for (int gi = tid; gi < n_groups; gi += PLAN_THREADS) {
             const int2 er = pv.grp_tmp[gi];
             const int ge = pv.grp_start[gi + 1];
             int rec = a1[gi];
-            for (int t = pv.grp_start[gi]; t < ge && rec < pv.max_groups; t += GROUP_CHUNK, ++rec)
-                pv.grp_meta[rec] = make_int4(er.x, t, min(t + GROUP_CHUNK, ge), er.y);
+            for (int t = pv.grp_start[gi]; t < ge && rec < pv.max_groups; t += pv.chunk, ++rec)
+                pv.grp_meta[rec] = make_int4(er.x, t, min(t + pv.chunk, ge), er.y);
         }
         if (tid == 0) *pv.n_groups = n_rec;
         // unused records read as empty groups, so the decode kernels need not

@@ -101,10 +101,10 @@ __device__ __forceinline__ void plan_base_only(const PlanView &pv, int nt_thread
     if (tid == 0) *pv.n_tiles = nt;
     if (pv.decode) {
         for (int t = tid; t < T; t += nt_threads) pv.tok_sorted[t] = t;
-        const int nc = min((T + GROUP_CHUNK - 1) / GROUP_CHUNK, pv.max_groups);
+        const int nc = min((T + pv.chunk - 1) / pv.chunk, pv.max_groups);
         if (tid == 0) *pv.n_groups = nc;
         for (int gi = tid; gi < pv.max_groups; gi += nt_threads)
-            pv.grp_meta[gi] = gi < nc ? make_int4(-1, gi * GROUP_CHUNK, min(T, (gi + 1) * GROUP_CHUNK), 0)
+            pv.grp_meta[gi] = gi < nc ? make_int4(-1, gi * pv.chunk, min(T, (gi + 1) * pv.chunk), 0)
                                       : make_int4(-1, 0, 0, 0);
     }
 }
@@ -268,7 +268,7 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
             pv.tok_sorted[t] = seq_offsets[order[first]] + (t - L.tokbase[first]);
         }
     }
-    // 4. A group ends where the next one starts.  It is cut into records of at most GROUP_CHUNK tokens: the
+    // 4. A group ends where the next one starts.  It is cut into records of at most pv.chunk tokens: the
     // decode kernels hand a record to one column of workgroups, and a hot expert's tokens must not all queue
     // behind one column.
     const int gper = (n_groups + PT - 1) / PT;
@@ -276,7 +276,7 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
     int n[1] = {0}, n_rec[1];
     for (int g = g0; g < g1; ++g) {
         const int gs = L.tokbase[head_at[g]], ge = g + 1 < n_groups ? L.tokbase[head_at[g + 1]] : n_tok;
-        n[0] += (ge - gs + GROUP_CHUNK - 1) / GROUP_CHUNK;
+        n[0] += (ge - gs + pv.chunk - 1) / pv.chunk;
     }
     plan_scan<PT, 1>(n, n_rec, L.sums);
     for (int g = g0; g < g1; ++g) {
@@ -284,8 +284,8 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
         const int gs = L.tokbase[p], ge = g + 1 < n_groups ? L.tokbase[head_at[g + 1]] : n_tok;
         const int e = (int)L.ekey[order[p]] - 1;
         const int rk = plan_rank_of(e, rank_of_expert, err_word);
-        for (int t = gs; t < ge && n[0] < pv.max_groups; t += GROUP_CHUNK, ++n[0])
-            pv.grp_meta[n[0]] = make_int4(e, t, min(t + GROUP_CHUNK, ge), rk);
+        for (int t = gs; t < ge && n[0] < pv.max_groups; t += pv.chunk, ++n[0])
+            pv.grp_meta[n[0]] = make_int4(e, t, min(t + pv.chunk, ge), rk);
     }
     const int n_out = min(n_rec[0], pv.max_groups);
     if (tid == 0) *pv.n_groups = n_out;
