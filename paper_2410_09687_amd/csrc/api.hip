@@ -373,7 +373,8 @@ int linear_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, con
     a.d_in = d_in; a.d_out = d_out; a.r = adapters ? r : 0; a.scale = scale; a.act = ctx->act;
     a.u_hi = a.u_lo = nullptr;
 
-    const size_t u_bytes = align_up((size_t)pv.T * (size_t)a.r * 2, 256);
+    a.ldu = pv.decode ? a.r : prefill_ldu(a);
+    const size_t u_bytes = align_up((size_t)pv.T * (size_t)a.ldu * 2, 256);
     if (!pv.decode) {
         if (a.r > 0) {
             const int rc = ensure_ws(ctx, 2 * u_bytes, stream);
@@ -465,6 +466,7 @@ int linear_mx_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, 
     a.y = y; a.y_f32 = (y_dt == MOIN_F32);
     a.d_in = d_in; a.d_out = d_out; a.r = adapters ? r : 0; a.scale = scale; a.act = ctx->act;
     a.u_hi = a.u_lo = nullptr;
+    a.ldu = a.r;                          // (a multiple of 64 here)
     const size_t u_bytes = align_up((size_t)pv.T * (size_t)a.r * 2, 256);
     const bool ws_q = xq == nullptr;      // codes and scales live in the workspace
     const bool own_q = !x_given;          // this call quantises x
@@ -1040,7 +1042,13 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
         }
         return MOIN_OK;
     }
-    const size_t u_bytes = align_up((size_t)pv.T * (size_t)r * 2, 256);
+    LinearArgs a;
+    a.x = x; a.W = nullptr; a.A_stack = nullptr; a.B_stack = nullptr;
+    a.u_hi = a.u_lo = nullptr;
+    a.y = nullptr; a.y_f32 = (y_dt == MOIN_F32);
+    a.d_in = d_in; a.d_out = 0; a.r = r; a.scale = scale; a.act = ctx->act;
+    a.ldu = prefill_ldu(a);
+    const size_t u_bytes = align_up((size_t)pv.T * (size_t)a.ldu * 2, 256);
     const int rc = ensure_ws(ctx, (size_t)n * 2 * u_bytes, st);
     if (rc != MOIN_OK) return rc;
     void *u_hi[MAX_SHARED_X], *u_lo[MAX_SHARED_X];
@@ -1048,11 +1056,6 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
         u_hi[i] = static_cast<char *>(ctx->ws) + (size_t)i * 2 * u_bytes;
         u_lo[i] = static_cast<char *>(u_hi[i]) + u_bytes;
     }
-    LinearArgs a;
-    a.x = x; a.W = nullptr; a.A_stack = nullptr; a.B_stack = nullptr;
-    a.u_hi = a.u_lo = nullptr;
-    a.y = nullptr; a.y_f32 = (y_dt == MOIN_F32);
-    a.d_in = d_in; a.d_out = 0; a.r = r; a.scale = scale; a.act = ctx->act;
     if (timed(ctx, MOIN_K_SHRINK, st, [&] {
             return launch_prefill_shrink_shared(pv, a, n, A_stack, u_hi, u_lo, st);
         }) != hipSuccess)

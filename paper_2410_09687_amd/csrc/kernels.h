@@ -71,10 +71,11 @@ hipError_t launch_plan(const PlanView &pv, const int *seq_offsets, const int *ex
 
 struct LinearArgs {
     const void *x, *W, *A_stack, *B_stack;
-    void *u_hi, *u_lo;     // [T, r] bf16 scratch
+    void *u_hi, *u_lo;     // [T, ldu] bf16 scratch
     void *y;
     int y_f32;
     int d_in, d_out, r;
+    int ldu = 0;           // prefill: columns of u_hi / u_lo as stored (prefill_ldu)
     float scale;
     int act = 0;           // activation on W_a x (moin_set_adapter_activation)
 };
@@ -94,6 +95,8 @@ hipError_t launch_prefill_linear(const PlanView &pv, const LinearArgs &a, hipStr
 hipError_t launch_prefill_linear_shared(const PlanView &pv, const LinearArgs *a, int n, hipStream_t stream);
 // shapes the persistent streaming prefill kernel takes (anything else: the tiled kernel)
 bool stream_kernel_fits(const LinearArgs &a);
+// Row length of u on the prefill path: the streaming kernel reads it in blocks of 64 columns.
+int prefill_ldu(const LinearArgs &a);
 // shrink + MXFP8 codes / blocked scales of x in one pass over x (d_in a multiple of 128)
 hipError_t launch_prefill_shrink_quant(const PlanView &pv, const LinearArgs &a, void *xq, void *xs,
                                        hipStream_t stream);

@@ -28,7 +28,7 @@ struct ShrinkKParams {
     const char *A_more[MAX_SHARED_X - 1];
     char *uh_more[MAX_SHARED_X - 1], *ul_more[MAX_SHARED_X - 1];
     const int *tile_row0, *tile_rows, *tile_expert, *tile_rank, *n_tiles;
-    int d_in, r;
+    int d_in, r, ldu;
     int n_tiles_n;
     float scale;
     int act;
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(C::NT) void shrink_kernel(ShrinkKParams p)
     // the expert's own rank: rows of A_e beyond it do not exist; the main kernel
     // reads u in blocks of 64 columns, so the rest of the last block is written as zeros
     const int re = e < 0 ? 0 : min(p.r, uniform(p.tile_rank[t]));
-    const int r_read = min(p.r, (re + 63) & ~63);
+    const int r_read = min(p.ldu, (re + 63) & ~63);
     const bool shrink = n0 < r_read;
     if (!shrink && !quant) return;
     const int ncols = max(1, min(C::BN, re - n0));      // rows of A_e to fetch (at least one, in bounds)
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(C::NT) void shrink_kernel(ShrinkKParams p)
     }
     if (!shrink) return;
 
-    const int64_t ldu = (int64_t)p.r * 2;
+    const int64_t ldu = (int64_t)p.ldu * 2;
     char *uh = u_hi + (int64_t)row0 * ldu;
     char *ul = u_lo + (int64_t)row0 * ldu;
     const float s = p.scale;
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(C::NT) void shrink_kernel(ShrinkKParams p)
 
 // Tile shapes.  The *Dma variants need the contraction length to be a multiple
 // of BK = 64; the register-staged ones take any multiple of 8.  CfgMain is the
-// prefill fallback for shapes the streaming kernel (linear_stream.hip) does not
+// prefill fallback for contraction lengths the streaming kernel (linear_stream.hip) does not
 // take.
 using CfgMain = GemmCore<256, 256, 64, 4, 2>;        // 8 waves, wave patch 64 x 128
 using CfgShrink = GemmCore<64, 64, 64, 2, 2>;        // 4 waves, wave patch 32 x 32
@@ -280,7 +280,7 @@ static hipError_t launch_shrink_as(const PlanView &pv, const LinearArgs &a, hipS
     p.tile_row0 = pv.tile_row0; p.tile_rows = pv.tile_rows; p.tile_expert = pv.tile_expert;
     p.tile_rank = pv.tile_rank;
     p.n_tiles = pv.n_tiles;
-    p.d_in = a.d_in; p.r = a.r; p.scale = a.scale; p.act = a.act;
+    p.d_in = a.d_in; p.r = a.r; p.ldu = a.ldu; p.scale = a.scale; p.act = a.act;
     p.tiles_per_proj = (a.r + C::BN - 1) / C::BN;
     p.n_proj = shared ? shared->n : 1;
     for (int i = 1; i < MAX_SHARED_X; ++i) {
@@ -366,6 +366,7 @@ hipError_t launch_prefill_linear(const PlanView &pv, const LinearArgs &a, hipStr
     p.tile_rank = pv.tile_rank;
     p.n_tiles = pv.n_tiles;
     p.T = pv.T;
+    if (a.r > 0 && a.ldu != a.r) return hipErrorInvalidValue;   // (the tiled kernel's rows of u are r long)
     p.d_in = a.d_in; p.d_out = a.d_out; p.r = a.r;
     p.n_tiles_n = 0;
     p.y_f32 = a.y_f32;

@@ -17,7 +17,9 @@
 //    lane ends up with four consecutive outputs of one token; the epilogue
 //    regroups them through 8 KB of LDS per wave that lie outside the stages,
 //    so it runs while the next tile's first blocks are landing.
-// Contraction lengths (d_in, r) must be multiples of 64 and d_in >= 128.
+// d_in must be a multiple of 64 and >= 128, and u comes in rows of whole blocks of 64 columns, zeros from the rank on.
+// Rows of B_e are r long, any multiple of 8 (RAGGED: not of 64): in a row's last block the lanes past its end fetch the
+// block's first chunk again, which meets the zeros of u.
 #include <type_traits>
 
 #include "gemm_core.h"
@@ -46,7 +48,7 @@ struct Params {
     int tn_start[MAX_SHARED_X];   // first column tile of each projection (tn_start[0] = 0)
     int n_proj;
     const int *tile_row0, *tile_rows, *tile_expert, *tile_rank, *n_tiles;
-    int d_in, r;
+    int d_in, r, ldu;             // (ldu: columns of u as stored)
     int n_tiles_n;                // column tiles of all projections together
     int y_f32;
 };
@@ -89,7 +91,7 @@ __device__ __forceinline__ Tile load_tile(const Params &p, int id, int n_work)
         }
     t.n0 = (tn - tn0) * BT;
     t.p_rows = min(BT, t.d_out - t.n0);
-    const int64_t ldx = (int64_t)p.d_in * 2, ldu = (int64_t)p.r * 2;
+    const int64_t ldx = (int64_t)p.d_in * 2, ldu = (int64_t)p.ldu * 2, ldb = (int64_t)p.r * 2;
     t.q0 = p.x + (int64_t)t.row0 * ldx;
     t.p0 = W + (int64_t)t.n0 * ldx;
     // adapter blocks up to the expert's own rank (the shrink wrote zeros from there to the block end)
@@ -99,7 +101,7 @@ __device__ __forceinline__ Tile load_tile(const Params &p, int id, int n_work)
     t.total = p.d_in / BK + 2 * t.nkb1;
     t.uh = lora ? u_hi + (int64_t)t.row0 * ldu : t.q0;
     t.ul = lora ? u_lo + (int64_t)t.row0 * ldu : t.q0;
-    t.be = lora ? B_stack + ((int64_t)e * t.d_out + t.n0) * ldu : t.p0;
+    t.be = lora ? B_stack + ((int64_t)e * t.d_out + t.n0) * ldb : t.p0;
     return t;
 }
 
@@ -126,7 +128,7 @@ constexpr int SCR_BYTES = 8192;        // per-wave epilogue scratch: 16 tokens x
 constexpr int SMEM_BYTES = SMEM_STAGES + NW * SCR_BYTES;   // 160 KB
 }  // namespace s16
 
-template <bool Y_F32>
+template <bool Y_F32, bool RAGGED>
 __global__ __launch_bounds__(s16::NT) void linear_stream_kernel(stream::Params p)
 {
     using namespace s16;
@@ -144,7 +146,7 @@ __global__ __launch_bounds__(s16::NT) void linear_stream_kernel(stream::Params p
     if (id >= band_end) return;
 
     const int nkb0 = p.d_in / BK;
-    const uint32_t ldx = (uint32_t)p.d_in * 2u, ldu = (uint32_t)p.r * 2u;
+    const uint32_t ldx = (uint32_t)p.d_in * 2u, ldu = (uint32_t)p.ldu * 2u, ldb = (uint32_t)p.r * 2u;
 
     // DMA: instruction j of a wave fills LDS rows (wave*8 + j)*8 .. +8 of an operand tile; the lane
     // fetches logical 16-byte chunk (lane%8) ^ swz(row), swz(row) = (row >> 1) & 7, which for
@@ -165,6 +167,7 @@ __global__ __launch_bounds__(s16::NT) void linear_stream_kernel(stream::Params p
     struct Fetch {
         const char *pp, *pq;   // the operands' rows 0 at the block's first k
         uint32_t ld;
+        uint32_t ldp, ca, cb;   // RAGGED: the output rows' own pitch and chunk offsets
     };
     auto fetch_of = [&](const Tile &t, int b) __attribute__((always_inline)) {
         Fetch f;
@@ -175,12 +178,20 @@ __global__ __launch_bounds__(s16::NT) void linear_stream_kernel(stream::Params p
         f.pq = (base ? t.q0 : (hi ? t.uh : t.ul)) + kb * (BK * 2);
         f.pp = (base ? t.p0 : t.be) + kb * (BK * 2);
         f.ld = base ? ldx : ldu;
+        if constexpr (RAGGED) {
+            f.ldp = base ? ldx : ldb;
+            const uint32_t end = base ? (uint32_t)(BK * 2) : ldb - (uint32_t)kb * (BK * 2);   // >= 16: nkb1 stops at the rank
+            f.ca = c16a < end ? c16a : 0u;
+            f.cb = c16b < end ? c16b : 0u;
+        }
         return f;
     };
     auto issue_one = [&](const Fetch &f, char *stage, int n) __attribute__((always_inline)) {
         const int j = n & 7;
         const bool q = n >= LOADS;
-        const uint32_t off = __umul24(rowc[n], f.ld) + ((j & 1) ? c16b : c16a);
+        uint32_t off = __umul24(rowc[n], f.ld) + ((j & 1) ? c16b : c16a);
+        if constexpr (RAGGED)
+            if (!q) off = __umul24(rowc[n], f.ldp) + ((j & 1) ? f.cb : f.ca);
         __builtin_amdgcn_global_load_lds(MOIN_GPTR((q ? f.pq : f.pp) + off),
                                          MOIN_LPTR(stage + (q ? OP_BYTES : 0) + (wave * LOADS + j) * 1024), 16, 0, 0);
     };
@@ -383,20 +394,28 @@ __global__ __launch_bounds__(s16::NT) void linear_stream_kernel(stream::Params p
     }
 }
 
+template <bool Y_F32, bool RAGGED>
+static hipError_t allow_lds()
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_stream_kernel<Y_F32, RAGGED>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, s16::SMEM_BYTES);
+}
+
 hipError_t prepare_stream_kernel()
 {
-    hipError_t e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_stream_kernel<false>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, s16::SMEM_BYTES)) != hipSuccess)
-        return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_stream_kernel<true>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, s16::SMEM_BYTES);
+    hipError_t e = allow_lds<false, false>();
+    if (e == hipSuccess) e = allow_lds<true, false>();
+    if (e == hipSuccess) e = allow_lds<false, true>();
+    if (e == hipSuccess) e = allow_lds<true, true>();
+    return e;
 }
 
 bool stream_kernel_fits(const LinearArgs &a)
 {
-    return a.d_in % 64 == 0 && a.r % 64 == 0 && a.d_in >= 128;
+    return a.d_in % 64 == 0 && a.d_in >= 128;
 }
+
+int prefill_ldu(const LinearArgs &a) { return stream_kernel_fits(a) ? (a.r + 63) / 64 * 64 : a.r; }
 
 // n projections that share x, d_in, r and the output type (a[i]: W, B_stack, u_hi, u_lo, y, d_out of
 // projection i; a[0] also x, d_in, r, y_f32)
@@ -419,7 +438,7 @@ hipError_t launch_linear_stream_shared(const PlanView &pv, const LinearArgs *a, 
     p.tile_row0 = pv.tile_row0; p.tile_rows = pv.tile_rows; p.tile_expert = pv.tile_expert;
     p.tile_rank = pv.tile_rank;
     p.n_tiles = pv.n_tiles;
-    p.d_in = a[0].d_in; p.r = a[0].r;
+    p.d_in = a[0].d_in; p.r = a[0].r; p.ldu = a[0].ldu;
     p.n_tiles_n = tn;
     p.y_f32 = a[0].y_f32;
     // one workgroup per compute unit (the LDS footprint allows no more), fewer
@@ -429,10 +448,14 @@ hipError_t launch_linear_stream_shared(const PlanView &pv, const LinearArgs *a, 
     int64_t grid = n_cus > 0 ? n_cus : 256;
     if (grid > max_work) grid = max_work;
     grid = (grid + 7) / 8 * 8;
-    if (p.y_f32)
-        hipLaunchKernelGGL(linear_stream_kernel<true>, dim3((unsigned)grid), dim3(s16::NT), s16::SMEM_BYTES, stream_, p);
-    else
-        hipLaunchKernelGGL(linear_stream_kernel<false>, dim3((unsigned)grid), dim3(s16::NT), s16::SMEM_BYTES, stream_, p);
+#define MOIN_STREAM(Y32, RAG) \
+    hipLaunchKernelGGL((linear_stream_kernel<Y32, RAG>), dim3((unsigned)grid), dim3(s16::NT), s16::SMEM_BYTES, stream_, p)
+    const bool ragged = p.r % stream::BK != 0;
+    if (p.y_f32 && ragged) MOIN_STREAM(true, true);
+    else if (p.y_f32) MOIN_STREAM(true, false);
+    else if (ragged) MOIN_STREAM(false, true);
+    else MOIN_STREAM(false, false);
+#undef MOIN_STREAM
     return hipGetLastError();
 }
 
