@@ -282,31 +282,37 @@ __device__ __forceinline__ void pipelined_blocks(char *smem, int total, Issue is
 // that stream from HBM: a load to registers may stay outstanding for several
 // blocks, and the registers of block `it` go to LDS just before they are needed.
 // `on_block(it, g)` sees block `it` in registers (after its copy to LDS, before
-// the registers are reused).
+// the registers are reused).  Whole rounds of PF blocks have no branch around a load (past the last block the last one
+// is fetched again): with one, the compiler no longer knows how many loads are outstanding and waits for all of them,
+// once per round.
 template <class C, int PF, class Issue, class OnBlock>
 __device__ __forceinline__ void pipelined_blocks_deep(char *smem, int total, Issue issue,
                                                       typename C::Acc &acc, OnBlock on_block)
 {
     typename C::Stage g[PF];
 #pragma unroll
-    for (int u = 0; u < PF; ++u)
-        if (u < total) issue(u, g[u]);
-    for (int it0 = 0; it0 < total; it0 += PF) {
+    for (int u = 0; u < PF; ++u) issue(min(u, total - 1), g[u]);
+    auto one = [&](int it, int u) __attribute__((always_inline)) {
+        // stage it & 1 was last read for block it - 2: every wave has left that
+        // block's MFMAs behind when it met the others at the barrier of block it - 1
+        char *st = smem + (it & 1) * C::STAGE_BYTES;
+        C::store_stage(st, g[u]);
+        on_block(it, g[u]);
+        issue(min(it + PF, total - 1), g[u]);
+        // (nor may the next block's registers be touched before this one's MFMAs are out: that would wait for them here)
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        C::compute_stage(st, acc);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int it0 = 0;
+    for (; it0 + PF <= total; it0 += PF) {
 #pragma unroll
-        for (int u = 0; u < PF; ++u) {
-            const int it = it0 + u;
-            if (it < total) {
-                // stage it & 1 was last read for block it - 2: every wave has left that
-                // block's MFMAs behind when it met the others at the barrier of block it - 1
-                char *st = smem + (it & 1) * C::STAGE_BYTES;
-                C::store_stage(st, g[u]);
-                on_block(it, g[u]);
-                if (it + PF < total) issue(it + PF, g[u]);
-                __syncthreads();
-                C::compute_stage(st, acc);
-            }
-        }
+        for (int u = 0; u < PF; ++u) one(it0 + u, u);
     }
+#pragma unroll
+    for (int u = 0; u < PF - 1; ++u)
+        if (it0 + u < total) one(it0 + u, u);
     __syncthreads();
 }
 
