@@ -20,6 +20,8 @@
 //                      their old centre; the objective is summed in a fixed
 //                      order in fp64
 // No floating-point atomics anywhere.
+#include <algorithm>
+
 #include "gemm_core.h"
 #include "kernels.h"
 
@@ -232,6 +234,8 @@ __device__ __forceinline__ void km_unpack(const uint4 &v, float (&f)[VPC])
     }
 }
 
+// Bound by HBM: 262 144 rows of 768 bf16 (403 MB) against 5000 centres in 94 us, 4.3 TB/s.  (145 us with the point's
+// index and then its row fetched four rows at a time behind conditions, 110 with loads that displace the Infinity Cache.)
 // One piece (at most KM_PIECE points of one centre) and one block of up to 256
 // 16-byte column chunks per workgroup.  With cw chunks in the block, 256 / cw
 // rows are in flight per pass ("phases"); every thread owns one chunk of one
@@ -242,6 +246,7 @@ __global__ __launch_bounds__(256) void km_segsum(KmeansArgs a)
 {
     __shared__ float red[256 * VPC];
     __shared__ double dred[4];
+    __shared__ int list[KM_PIECE];
     const int piece = blockIdx.x;
     if (piece >= uniform(*a.n_pieces)) return;
     const int4 rec = a.pieces[piece];
@@ -255,6 +260,9 @@ __global__ __launch_bounds__(256) void km_segsum(KmeansArgs a)
     const bool active = phase < rpp;
     const int64_t row_bytes = (int64_t)a.D * (16 / VPC);
     const char *emb = static_cast<const char *>(a.emb) + (int64_t)ch * 16;
+    const int n = last - first;   // <= KM_PIECE
+    for (int i = tid; i < n; i += 256) list[i] = a.perm[first + i];
+    __syncthreads();
 
     float old[VPC], acc[VPC];
 #pragma unroll
@@ -262,18 +270,20 @@ __global__ __launch_bounds__(256) void km_segsum(KmeansArgs a)
     double dacc = 0.0;
     if (active) {
         km_unpack<VPC>(*reinterpret_cast<const uint4 *>(static_cast<const char *>(a.cent) + k * row_bytes + (int64_t)ch * 16), old);
-        constexpr int UNR = 4;
-        for (int row = first + phase; row < last; row += rpp * UNR) {
-            int idx[UNR];
+        // A step is UNR rows per thread, one trip to memory: their indices are in LDS, and no load is conditional (past
+        // the end the last row is fetched again and left out of the sums).
+        typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+        constexpr int UNR = 8;
+        for (int i = phase; i < n; i += rpp * UNR) {
             uint4 v[UNR];
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) idx[u] = (row + u * rpp < last) ? a.perm[row + u * rpp] : -1;
-#pragma unroll
-            for (int u = 0; u < UNR; ++u)
-                if (idx[u] >= 0) v[u] = *reinterpret_cast<const uint4 *>(emb + idx[u] * row_bytes);
+            for (int u = 0; u < UNR; ++u) {
+                const char *src = emb + list[min(i + u * rpp, n - 1)] * row_bytes;
+                v[u] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src)));
+            }
 #pragma unroll
             for (int u = 0; u < UNR; ++u) {
-                if (idx[u] < 0) continue;
+                if (i + u * rpp >= n) continue;
                 float f[VPC];
                 km_unpack<VPC>(v[u], f);
                 float d2 = 0.f;
@@ -390,7 +400,9 @@ hipError_t prepare_kmeans_kernels()
 
 void kmeans_shape(int64_t N, int K, int D, int is_bf16, int *chunk, int *n_chunks, int *max_pieces, int *ncb)
 {
-    int64_t c = 4096;
+    // a workgroup per chunk in the histogram and the scatter: 256 of them as soon as there are points enough (262 144
+    // points: 8.4 + 18.8 us with chunks of 4096), in exact steps, so that the table never shrinks as N grows
+    int64_t c = std::min<int64_t>(4096, std::max<int64_t>(512, (N + 255) / 256));
     if ((N + c - 1) / c > 1024) c = ((N + 1023) / 1024 + 63) / 64 * 64;
     *chunk = (int)c;
     *n_chunks = (int)((N + c - 1) / c);
