@@ -822,7 +822,10 @@ static ShrinkDParams shrink_params(const PlanView &pv, const DecodeArgs &d)
 static DecodeMore decode_more(const DecodeArgs *d, int n);
 
 constexpr int HELD_WGS = 16;            // workgroups per compute unit of the held kernels, at most: a few rounds each
-constexpr int DECODE_TILE_ITEMS = 3;    // shrink items that a base tile of 32 blocks takes the time of
+// Shrink items that a base tile of 32 blocks stands for (one step each; an item of b steps counts as (b + 1) / 2, its
+// steps overlap).  q, k, v and down of 256 single tokens: 46 and 49 us counting 1, 44 and 49 with 3, 39 and 41 with 6,
+// 40 and 43 with 8.
+constexpr int DECODE_TILE_ITEMS = 6;
 
 // Workgroups of a persistent launch: what the chip holds at a time, a multiple of 8 (the XCDs), and no more than
 // there can be items.
@@ -943,9 +946,8 @@ hipError_t launch_decode_base_shrink_shared(const PlanView &pv, const DecodeArgs
     turns.P = persistent_grid(2, n_base + items);
     if (first.slab_blocks == 0) {
         turns.n_base = (int)n_base;
-        // a tile of 32 blocks takes about as long as DECODE_TILE_ITEMS items of one batch of k-steps
         const int batches = (a.d_in * 2 + SHRINK_WAVES * STREAM_COL - 1) / (SHRINK_WAVES * STREAM_COL);
-        turns.c = std::max(1, (DECODE_TILE_ITEMS * first.kb_per_split + 16 * batches) / (32 * batches));
+        turns.c = std::max(1, DECODE_TILE_ITEMS * first.kb_per_split / (16 * (batches + 1)));
         hipLaunchKernelGGL(decode_base_shrink_kernel<true>, dim3(turns.P), block, STREAM_SMEM, stream,
                            ShrinkStreamArgs{sp, lp, m, turns, 0, n_slabs});
     } else {
