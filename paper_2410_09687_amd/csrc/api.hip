@@ -779,14 +779,15 @@ static int route_impl(moin_ctx *ctx, const void *emb, const void *centroids, int
     const bool need_cid = counts && !centroid_ids && N > 0;
     RouteScratch L = route_scratch(N, K, D, dt, need_cid);
     if (route_one_launch(N, K, D, dt, expert_ids, centroid_ids)) {
-        // (minima and counter first, at offsets that do not move with K: they must stay clean)
+        // (minima and counter first, at offsets that do not move with K: they must stay clean; then the norms, which
+        // another call's reuse may rely on: nothing else has a place that moves with K.  Centroid ids need none, the
+        // finishing workgroup tallies them.)
         const size_t cn_bytes = L.cinit - L.cnorm;
         L.best = 0;
         L.arrivals = (size_t)ROUTE_SMALL_MAX_N * 8;
         L.cnorm = L.arrivals + ARRIVALS_BYTES;
         L.cinit = L.cnorm + cn_bytes;
-        L.cid = L.cinit + cn_bytes;
-        L.total = L.cid + (need_cid ? align_up((size_t)N * 4, 256) : 0);
+        L.cid = L.total = L.cinit + cn_bytes;
         // Request-sized batches: one launch.  Norms, packed minima and the arrival counter live in a
         // block of the context's own (the shared workspace is overwritten by the linear calls in
         // between); the kernel's finishing workgroup leaves minima and counter clean and zeroes the
@@ -821,7 +822,7 @@ static int route_impl(moin_ctx *ctx, const void *emb, const void *centroids, int
         if (cap) ctx->route_pinned = 1;
         if (dt == MOIN_F32)   // distances computed directly: no norms to keep
             return route_launches(ctx, emb, centroids, N, K, D, dt, slot_of_centroid, flags, expert_ids, centroid_ids,
-                                  counts, static_cast<char *>(ctx->route_buf), L, need_cid, true, st, 2, fuse);
+                                  counts, static_cast<char *>(ctx->route_buf), L, false, true, st, 2, fuse);
         const int retained = (flags & MOIN_ROUTE_RETAINED_ONLY) ? 1 : 0;
         const bool same = ctx->route_key.valid && ctx->route_key.cent == centroids &&
                           ctx->route_key.slot == (retained ? slot_of_centroid : nullptr) && ctx->route_key.K == K &&
@@ -832,7 +833,7 @@ static int route_impl(moin_ctx *ctx, const void *emb, const void *centroids, int
         ctx->route_key.K = K; ctx->route_key.D = D; ctx->route_key.dt = (int)dt;
         ctx->route_key.retained = retained; ctx->route_key.valid = 1;
         return route_launches(ctx, emb, centroids, N, K, D, dt, slot_of_centroid, flags, expert_ids,
-                              centroid_ids, counts, static_cast<char *>(ctx->route_buf), L, need_cid, true, st,
+                              centroid_ids, counts, static_cast<char *>(ctx->route_buf), L, false, true, st,
                               reuse ? 2 : 1, fuse);
     }
     if (fuse) return MOIN_EINVAL;   // (the caller asks for it only where it applies)

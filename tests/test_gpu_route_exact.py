@@ -75,3 +75,22 @@ def test_screened_topk_equals_the_exhaustive_one(dtype, D, kind):
             assert torch.equal(a, b)
     if kind != "odd":
         check_topk(emb[:60].contiguous(), cent, 8, what=kind)
+
+
+def test_a_small_fp32_call_leaves_the_norms_kept_for_bf16_alone():
+    # a server that routes bf16 requests against one table and, in between, tallies fp32 queries against another:
+    # the second call's scratch must not reach the norms that MOIN_ROUTE_SAME_CENTROIDS lets the third one reuse
+    ctx = moin.Context(0)
+    try:
+        emb, cent = _inputs(64, 5000, 64, torch.bfloat16, "plain", 3)
+        small, table = _inputs(1000, 500, 16, torch.float32, "plain", 4)
+        print("[gpu] bf16 norms kept across a small fp32 call", flush=True)
+        first = moin.moin_route(ctx, emb, cent, want_counts=True)
+        _, none, counts = moin.moin_route(ctx, small, table, want_centroid_ids=False, want_counts=True)
+        again = moin.moin_route(ctx, emb, cent, want_counts=True, same_centroids=True)
+        ctx.check()
+        assert none is None and int(counts.sum()) == 1000
+        for a, b in zip(first, again):
+            assert torch.equal(a, b)
+    finally:
+        ctx.close()
