@@ -83,7 +83,8 @@ typedef enum {
 /* ---- context ----------------------------------------------------------- */
 
 /* Creates a context bound to HIP device `device`.  Allocates only its own
- * small bookkeeping (the sticky error word); workspace grows on first use. */
+ * small bookkeeping (the sticky error word and the minima that request-sized
+ * routing calls merge); workspace grows on first use. */
 int moin_create(moin_ctx **out, int device);
 
 /* Frees the context and its workspace.  The caller must have synchronised
@@ -218,11 +219,12 @@ int moin_route_plan(moin_ctx *ctx, moin_plan *plan, const void *emb, const void 
                     int32_t *centroid_ids, int32_t *counts, void *stream);
 
 /* ---- HIP graphs and the library's own device memory ----------------------------
- * The context's workspace and a plan's buffer grow on demand (hipMalloc), which a
- * stream under capture must not do.  A call on a capturing stream that would have
- * to grow either returns MOIN_ECAPTURE and records nothing: make the first call
- * with the largest shapes outside the capture, or reserve beforehand.  A workspace
- * or plan buffer that a captured call has used is kept until moin_destroy /
+ * The context's workspace, a plan's buffer and the centroid norms that request-sized
+ * bf16 routing calls keep (one call with as many centroids sizes them; fp32 calls keep
+ * none) grow on demand (hipMalloc), which a stream under capture must not do.  A call
+ * on a capturing stream that would have to grow any of them returns MOIN_ECAPTURE and
+ * records nothing: make the first call with the largest shapes outside the capture, or
+ * reserve beforehand.  What a captured call has used is kept until moin_destroy /
  * moin_plan_destroy even when a later, larger call replaces it, so replays of the
  * graph keep reading valid memory (results of a replay are then only defined if
  * no other call on the context runs concurrently, as for eager calls).

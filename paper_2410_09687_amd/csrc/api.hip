@@ -82,6 +82,12 @@ struct moin_ctx {
 // kernels get is looked up once per device (moin_create, with that device
 // current) and kept in g_scratch_ptr.
 constexpr int ROUTE_SELF_CLEAN_MAX_K = 65536;   // one workgroup zeroes the histogram in these calls
+// What a one-launch routing call keeps clean for the next: packed minima and arrival counters, at the start of
+// moin_ctx::route_buf.  A context has this much from its creation on, which is all that fp32 calls need: they never
+// allocate, so a stream under capture takes them as it always did.
+constexpr size_t ARRIVALS_BYTES = ((size_t)ARRIVAL_WORDS * 4 + 255) / 256 * 256;
+constexpr size_t ROUTE_MINIMA_BYTES = (size_t)ROUTE_SMALL_MAX_N * 8;
+constexpr size_t ROUTE_CLEAN_BYTES = ROUTE_MINIMA_BYTES + ARRIVALS_BYTES;
 constexpr size_t SCRATCH_BYTES = 1u << 20;
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 constexpr int MAX_DEVICES = 64;
@@ -592,6 +598,18 @@ int moin_create(moin_ctx **out, int device)
         delete ctx;
         return MOIN_EHIP;
     }
+    if (hipMalloc(&ctx->route_buf, ROUTE_CLEAN_BYTES) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->route_buf = nullptr;
+        moin_destroy(ctx);
+        return MOIN_ENOMEM;
+    }
+    if (hipMemset(ctx->route_buf, 0xFF, ROUTE_MINIMA_BYTES) != hipSuccess ||
+        hipMemset(static_cast<char *>(ctx->route_buf) + ROUTE_MINIMA_BYTES, 0, ARRIVALS_BYTES) != hipSuccess) {
+        moin_destroy(ctx);
+        return MOIN_EHIP;
+    }
+    ctx->route_bytes = ROUTE_CLEAN_BYTES;
     *out = ctx;
     return MOIN_OK;
 }
@@ -666,7 +684,6 @@ struct RoutePlanFuse {
 };
 
 // Where a routing call keeps its intermediate results inside a block of device memory.
-constexpr size_t ARRIVALS_BYTES = ((size_t)ARRIVAL_WORDS * 4 + 255) / 256 * 256;
 struct RouteScratch {
     size_t cnorm, cinit, best, arrivals, cid, total;
     int group;
@@ -784,10 +801,11 @@ static int route_impl(moin_ctx *ctx, const void *emb, const void *centroids, int
         // finishing workgroup tallies them.)
         const size_t cn_bytes = L.cinit - L.cnorm;
         L.best = 0;
-        L.arrivals = (size_t)ROUTE_SMALL_MAX_N * 8;
-        L.cnorm = L.arrivals + ARRIVALS_BYTES;
+        L.arrivals = ROUTE_MINIMA_BYTES;
+        L.cnorm = ROUTE_CLEAN_BYTES;
         L.cinit = L.cnorm + cn_bytes;
-        L.cid = L.total = L.cinit + cn_bytes;
+        L.cid = L.cinit + cn_bytes;
+        L.total = dt == MOIN_F32 ? ROUTE_CLEAN_BYTES : L.cid;   // (fp32: distances computed directly, no norms)
         // Request-sized batches: one launch.  Norms, packed minima and the arrival counter live in a
         // block of the context's own (the shared workspace is overwritten by the linear calls in
         // between); the kernel's finishing workgroup leaves minima and counter clean and zeroes the
@@ -820,7 +838,7 @@ static int route_impl(moin_ctx *ctx, const void *emb, const void *centroids, int
                 return MOIN_EHIP;
         }
         if (cap) ctx->route_pinned = 1;
-        if (dt == MOIN_F32)   // distances computed directly: no norms to keep
+        if (dt == MOIN_F32)
             return route_launches(ctx, emb, centroids, N, K, D, dt, slot_of_centroid, flags, expert_ids, centroid_ids,
                                   counts, static_cast<char *>(ctx->route_buf), L, false, true, st, 2, fuse);
         const int retained = (flags & MOIN_ROUTE_RETAINED_ONLY) ? 1 : 0;

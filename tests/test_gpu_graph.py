@@ -275,3 +275,82 @@ def test_capture_refuses_to_grow_and_keeps_what_a_graph_recorded():
         plan.close()
     finally:
         ctx.close()
+
+
+def _captured_on_a_fresh_context(what, prepare, call, outs):
+    """call(ctx, state) is recorded on a context that has made no call yet, and replayed on changed inputs."""
+    ctx, eager = moin.Context(0), gc.ctx()
+    try:
+        st, ref = prepare(ctx), prepare(eager)
+        torch.cuda.synchronize()
+        print(f"[gpu] graph {what}: capture on a fresh context", flush=True)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            call(ctx, st)
+        for rep in range(3):
+            print(f"[gpu] graph {what}: replay {rep}", flush=True)
+            g = torch.Generator(device="cuda").manual_seed(20 + rep)
+            st["emb"].copy_(torch.randn(st["emb"].shape, device="cuda", generator=g))
+            ref["emb"].copy_(st["emb"])
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            call(eager, ref)
+            ctx.check()
+            eager.check()
+            for a, b in zip(outs(st), outs(ref)):
+                assert torch.equal(a, b), f"{what}: replay {rep}"
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
+
+
+def _fp32_routing(ctx, N=48, K=300, D=96):
+    r = wl.make_route_inputs(wl.RouteWorkload("graph_f32", N, K, D, "f32", False, 91), "cuda")
+    i32 = lambda n: torch.empty(n, dtype=torch.int32, device="cuda")
+    return dict(emb=r.emb.clone(), cent=r.centroids.clone(), out=(i32(N), i32(N), i32(K)))
+
+
+def test_small_fp32_routing_call_needs_no_call_before_its_capture():
+    _captured_on_a_fresh_context(
+        "f32 route", _fp32_routing, lambda c, s: moin.moin_route(c, s["emb"], s["cent"], out=s["out"]),
+        lambda s: s["out"])
+
+
+def test_small_fp32_route_and_plan_call_needs_the_plan_reserved_only():
+    S, T, E = 48, 96, 300
+    off = torch.arange(0, T + 1, 2, dtype=torch.int32, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(92)
+    W = torch.randn((64, 64), device="cuda", generator=g).to(torch.bfloat16)
+    A = torch.randn((E, 16, 64), device="cuda", generator=g).to(torch.bfloat16)
+    B = torch.randn((E, 64, 16), device="cuda", generator=g).to(torch.bfloat16)
+    x = torch.randn((T, 64), device="cuda", generator=g).to(torch.bfloat16)
+
+    def prepare(ctx):
+        st = _fp32_routing(ctx, N=S, K=E)
+        st["plan"], st["y"] = moin.Plan(ctx), torch.empty((T, 64), dtype=torch.bfloat16, device="cuda")
+        st["plan"].reserve(S, T, E)
+        ctx.reserve_workspace(1 << 20)
+        return st
+
+    def call(ctx, st):
+        moin.moin_route_plan(ctx, st["plan"], st["emb"], st["cent"], off, T, E, out=st["out"])
+        moin.moin_lora_linear_planned(ctx, st["plan"], x, W, A, B, 2.0, out=st["y"])
+
+    _captured_on_a_fresh_context("f32 route + plan", prepare, call, lambda s: (*s["out"], s["y"].view(torch.int16)))
+
+
+def test_kmeans_on_few_fp32_points_needs_the_workspace_reserved_only():
+    N, K, D = 900, 40, 64
+
+    def prepare(ctx):
+        st = _fp32_routing(ctx, N=N, K=K, D=D)
+        st["first"] = st["cent"].clone()
+        ctx.reserve_workspace(1 << 22)
+        return st
+
+    def call(ctx, st):
+        st["cent"].copy_(st["first"])
+        st["got"] = moin.moin_kmeans_fit(ctx, st["emb"], st["cent"], 2)
+
+    _captured_on_a_fresh_context("f32 kmeans", prepare, call, lambda s: (*s["got"], s["cent"]))
