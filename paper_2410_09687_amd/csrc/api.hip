@@ -689,14 +689,15 @@ struct RouteScratch {
     int group;
 };
 
-static RouteScratch route_scratch(int64_t N, int32_t K, int32_t D, moin_dtype dt, bool need_cid)
+// `padded`: for a bf16 call that works on padded copies of its rows (its centroid range is split over workgroups).
+static RouteScratch route_scratch(int64_t N, int32_t K, int32_t D, moin_dtype dt, bool need_cid, bool padded = false)
 {
     RouteScratch L;
     const size_t Kpad = align_up((size_t)K, 256);
     const size_t cn_bytes = align_up(Kpad * 4, 256);
     L.group = route_stream_group(N, K, D, dt == MOIN_BF16);
-    const size_t n_best = L.group > 1 || dt == MOIN_F32 || route_pad_pays(N, D, dt == MOIN_BF16) ? (size_t)std::max<int64_t>(N, ROUTE_SMALL_MAX_N)
-                                                        : (size_t)ROUTE_SMALL_MAX_N;
+    const size_t n_best = L.group > 1 || dt == MOIN_F32 || padded ? (size_t)std::max<int64_t>(N, ROUTE_SMALL_MAX_N)
+                                                                  : (size_t)ROUTE_SMALL_MAX_N;
     L.cnorm = 0;
     L.cinit = cn_bytes;
     L.best = 2 * cn_bytes;
@@ -855,18 +856,27 @@ static int route_impl(moin_ctx *ctx, const void *emb, const void *centroids, int
                               reuse ? 2 : 1, fuse);
     }
     if (fuse) return MOIN_EINVAL;   // (the caller asks for it only where it applies)
-    // larger fp32 batches are screened by a bf16 product, rows that are no whole blocks are padded, except where
-    // a capture finds the workspace too small
-    const size_t extra_at = align_up(L.total, 256);
-    size_t need = L.total;
-    if (dt == MOIN_F32 && route_screen_pays(N, K, D, false)) need = extra_at + route_screen_bytes(N, K, D, 0);
-    else if (route_pad_pays(N, D, dt == MOIN_BF16)) need = extra_at + route_pad_bytes(N, K, D);
-    if (need > L.total && need > ctx->ws_bytes && capturing(st)) need = L.total;
-    const int rc = ensure_ws(ctx, need, st);
+    // Larger fp32 batches are screened by a bf16 product, rows that are no whole blocks are padded; both work on copies.
+    // Where those do not fit -- the device has too little memory left, a capture finds the workspace too small -- the
+    // same answer comes from the rows as they are.
+    size_t extra = 0;
+    if (dt == MOIN_F32 && route_screen_pays(N, K, D, false)) extra = route_screen_bytes(N, K, D, 0);
+    else if (route_pad_pays(N, D, dt == MOIN_BF16)) extra = route_pad_bytes(N, K, D);
+    if (extra) {
+        const RouteScratch LX = route_scratch(N, K, D, dt, need_cid, dt == MOIN_BF16);
+        const size_t at = align_up(LX.total, 256);
+        const int rc = ensure_ws(ctx, at + extra, st);
+        if (rc == MOIN_OK) {
+            char *w = static_cast<char *>(ctx->ws);
+            return route_launches(ctx, emb, centroids, N, K, D, dt, slot_of_centroid, flags, expert_ids, centroid_ids,
+                                  counts, w, LX, need_cid, true, st, 0, nullptr, w + at);
+        }
+        if (rc != MOIN_ENOMEM && rc != MOIN_ECAPTURE) return rc;
+    }
+    const int rc = ensure_ws(ctx, L.total, st);
     if (rc != MOIN_OK) return rc;
-    char *w = static_cast<char *>(ctx->ws);
     return route_launches(ctx, emb, centroids, N, K, D, dt, slot_of_centroid, flags, expert_ids, centroid_ids, counts,
-                          w, L, need_cid, true, st, 0, nullptr, need > L.total ? w + extra_at : nullptr);
+                          static_cast<char *>(ctx->ws), L, need_cid, true, st);
 }
 
 int moin_route(moin_ctx *ctx, const void *emb, const void *centroids, int64_t N, int32_t K,
@@ -1358,13 +1368,10 @@ int moin_route_topk(moin_ctx *ctx, const void *emb, const void *centroids, int64
     a.expert_ids = expert_ids;
     void *ws = nullptr;
     if (route_screen_pays(N, K, D, true)) {
-        const size_t need = route_screen_bytes(N, K, D, a.is_bf16);
-        // (a capture that finds the workspace too small records the search over all centroids)
-        if (need <= ctx->ws_bytes || !capturing(st)) {
-            const int rc = ensure_ws(ctx, need, st);
-            if (rc != MOIN_OK) return rc;
-            ws = ctx->ws;
-        }
+        // (without the memory, or in a capture that finds the workspace too small: the search over all centroids)
+        const int rc = ensure_ws(ctx, route_screen_bytes(N, K, D, a.is_bf16), st);
+        if (rc == MOIN_OK) ws = ctx->ws;
+        else if (rc != MOIN_ENOMEM && rc != MOIN_ECAPTURE) return rc;
     }
     if (timed(ctx, MOIN_K_ROUTE, st, [&] { return launch_route_topk(a, k, dist2, ws, st); }) != hipSuccess)
         return MOIN_EHIP;

@@ -94,3 +94,43 @@ def test_a_small_fp32_call_leaves_the_norms_kept_for_bf16_alone():
             assert torch.equal(a, b)
     finally:
         ctx.close()
+
+
+def test_searches_whose_copies_do_not_fit_answer_without_them():
+    # the screened and the padded search copy the table; with less than that left on the device the search that
+    # needs no copy gives the same answer
+    f32, bf16 = torch.float32, torch.bfloat16
+    shapes = {f32: (600_000, 1024), bf16: (1_200_000, 1032)}     # 2.4 GB, and as much again copied
+    g = torch.Generator(device="cuda").manual_seed(12)
+    tables, picks = {}, {}
+    for dtype, (K, D) in shapes.items():
+        cent = torch.empty((K, D), dtype=dtype, device="cuda").normal_(generator=g)
+        picks[dtype] = torch.arange(8, device="cuda") * (K // 8) + 3
+        emb = cent[picks[dtype]].float() + 0.1 * torch.randn((8, D), device="cuda", generator=g)
+        tables[dtype] = (emb.to(dtype), cent)
+
+    def run(dtype, topk):
+        ctx = moin.Context(0)
+        try:
+            out = moin.moin_route_topk(ctx, *tables[dtype], 2) if topk else moin.moin_route(ctx, *tables[dtype])[:2]
+            ctx.check()
+            return out, ctx.workspace_bytes()
+        finally:
+            ctx.close()
+
+    cases = ((f32, True), (f32, False), (bf16, False))
+    print("[gpu] searches with their copies", flush=True)
+    want = [run(*c) for c in cases]
+    torch.cuda.empty_cache()
+    rest = torch.empty(torch.cuda.mem_get_info()[0] - (1 << 30), dtype=torch.uint8, device="cuda")
+    try:
+        print("[gpu] and without", flush=True)
+        got = [run(*c) for c in cases]
+    finally:
+        del rest
+        torch.cuda.empty_cache()
+    for (dtype, _), (a, ua), (b, ub) in zip(cases, want, got):
+        assert ua > 2 << 30 > 1 << 30 > ub
+        assert torch.equal(a[1].reshape(8, -1)[:, 0].long(), picks[dtype])
+        for x, y in zip(a, b):
+            assert torch.equal(x, y)
