@@ -15,6 +15,8 @@
 //    every group of 16 centroids leaves the workgroup; a wave per query then computes the exact distances of
 //    the groups that can hold one of its k nearest centroids, by a bound on what the screening arithmetic
 //    can be wrong by.  The answer is that of the exhaustive search, bit for bit.
+#include <algorithm>
+
 #include "gemm_core.h"
 #include "kernels.h"
 #include "route_finish.h"
@@ -487,7 +489,9 @@ constexpr int64_t SCREEN_MIN_WORK = 150'000'000;
 // moin_route_topk: with this many centroids even a few queries gain, since eight waves then take more than
 // eight turns of 16 centroids, 3.6 us each (8 queries, 5000 centroids: 144 us / 37 us).
 constexpr int TOPK_SCREEN_MIN_K = 1024;
-constexpr int64_t SCREEN_QUERIES = 32768;    // queries screened at a time: bounds the workspace
+// Queries screened at a time: at most this many, 64 MiB of group minima (which grow with K) and 128 MiB of planes
+// (which grow with D), but 128 at least.  The centroids' planes are a copy of the whole table.
+constexpr int64_t SCREEN_QUERIES = 32768, SCREEN_MINIMA_BYTES = 64 << 20, SCREEN_PLANES_BYTES = 128 << 20;
 
 bool route_direct_small(int64_t N, int K, int D, int is_bf16)
 {
@@ -513,9 +517,9 @@ static ScreenLayout screen_layout(int64_t N, int K, int D, int is_bf16)
     L.Dp = (D + 63) / 64 * 64;
     L.nct = (K + 127) / 128;
     L.planes = is_bf16 ? (L.Dp == D ? 0 : 1) : 2;
-    // parts of about 64 MiB of group minima and at most SCREEN_QUERIES queries
-    int64_t part = ((int64_t)64 << 20) / ((int64_t)L.nct * 32);
-    part = part < 128 ? 128 : (part > SCREEN_QUERIES ? SCREEN_QUERIES : part / 128 * 128);
+    int64_t part = std::min(SCREEN_QUERIES, SCREEN_MINIMA_BYTES / ((int64_t)L.nct * 32));
+    if (L.planes) part = std::min(part, SCREEN_PLANES_BYTES / ((int64_t)L.Dp * 2 * L.planes));
+    part = std::max<int64_t>(128, part / 128 * 128);
     L.part = N < part ? N : part;
     size_t off = 0;
     auto take = [&](size_t bytes) {

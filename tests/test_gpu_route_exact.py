@@ -134,3 +134,19 @@ def test_searches_whose_copies_do_not_fit_answer_without_them():
         assert torch.equal(a[1].reshape(8, -1)[:, 0].long(), picks[dtype])
         for x, y in zip(a, b):
             assert torch.equal(x, y)
+
+
+def test_screened_parts_of_long_rows_stay_small():
+    # the planes of the queries are written for a part of the batch at a time, whatever the rows' length
+    emb, cent = _inputs(20001, 300, 4096, torch.float32, "near", 5)
+    ctx = moin.Context(0)
+    try:
+        print("[gpu] screened fp32 router, long rows", flush=True)
+        got = moin.moin_route(ctx, emb, cent, want_counts=True)
+        ref = moin.moin_route(ctx, emb, cent, want_counts=True, static=True)
+        ctx.check()
+        for a, b in zip(got, ref):
+            assert torch.equal(a, b)
+        assert ctx.workspace_bytes() <= 256 << 20
+    finally:
+        ctx.close()
