@@ -822,6 +822,12 @@ static ShrinkDParams shrink_params(const PlanView &pv, const DecodeArgs &d)
 static DecodeMore decode_more(const DecodeArgs *d, int n);
 
 constexpr int HELD_WGS = 16;            // workgroups per compute unit of the held kernels, at most: a few rounds each
+// From here on the adapters' stream keeps HBM busy for as long as the launch lasts, and tiles that ask for several blocks
+// at a time only hold it up (us of a call with one block in flight / three, 300 experts: q, k, v at rank 128 of 256
+// tokens 52.8 / 55.0, of 512 79.2 / 83.8; gate + up at rank 64 of 256 65.5 / 68.0; o at rank 64 of 1024 47.2 / 49.4).
+// With fewer tokens or shorter adapters the tiles' own chain of trips to memory is what the launch waits for (33
+// tokens, down, rank 16 31.5 / 25.2; 128, q, k, v, rank 64 36.5 / 34.2; 256, down, rank 16 39.1 / 33.8).
+constexpr int PACED_MIN_T = 256, PACED_MIN_R = 64;
 // Shrink items that a base tile of 32 blocks stands for (one step each; an item of b steps counts as (b + 1) / 2, its
 // steps overlap).  q, k, v and down of 256 single tokens: 46 and 49 us counting 1, 44 and 49 with 3, 39 and 41 with 6,
 // 40 and 43 with 8.
@@ -947,6 +953,7 @@ hipError_t launch_decode_base_shrink_shared(const PlanView &pv, const DecodeArgs
     if (first.slab_blocks == 0) {
         turns.n_base = (int)n_base;
         const int batches = (a.d_in * 2 + SHRINK_WAVES * STREAM_COL - 1) / (SHRINK_WAVES * STREAM_COL);
+        lp.paced = pv.T >= PACED_MIN_T && a.r >= PACED_MIN_R;
         turns.c = std::max(1, DECODE_TILE_ITEMS * first.kb_per_split / (16 * (batches + 1)));
         hipLaunchKernelGGL(decode_base_shrink_kernel<true>, dim3(turns.P), block, STREAM_SMEM, stream,
                            ShrinkStreamArgs{sp, lp, m, turns, 0, n_slabs});

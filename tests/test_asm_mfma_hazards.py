@@ -119,3 +119,50 @@ def test_quantised_base_kernel_does_not_spill():
     for sym, lines in bodies:
         assert not any(re.search(r"\bscratch_(load|store)", l) for l in lines), f"{sym} spills to scratch"
         assert sum("v_mfma" in l for l in lines) >= 96, f"{sym}: expected the unrolled MFMA blocks"
+
+
+def _whole_bodies(asm, name):
+    """(symbol, lines) of every kernel whose mangled name contains `name`, to its end (past early returns)"""
+    out, sym = [], None
+    for line in asm.split("\n"):
+        m = re.match(r"^(_Z\w+):", line)
+        if m and name in m.group(1):
+            sym, cur = m.group(1), []
+        elif line.startswith(".Lfunc_end") and sym:
+            out.append((sym, cur))
+            sym = None
+        elif sym:
+            cur.append(line)
+    return out
+
+
+def _dma_loops(lines):
+    """the innermost loops that hold both matrix instructions and direct-to-LDS loads, as lists of lines"""
+    label, loops = {}, []
+    for j, l in enumerate(lines):
+        m = re.match(r"^(\.LBB\w+):", l)
+        if m:
+            label[m.group(1)] = j
+        m = re.search(r"s_c?branch\w* (\.LBB\w+)", l)
+        if m and m.group(1) in label:
+            a = label[m.group(1)]
+            body = "\n".join(lines[a:j])
+            if "load_lds" in body and "v_mfma" in body:
+                loops.append((a, j))
+    inner = [r for r in loops if not any(o != r and r[0] <= o[0] and o[1] <= r[1] for o in loops)]
+    return [lines[a:b] for a, b in inner]
+
+
+@pytest.mark.parametrize("src,kernel", [("decode.hip", "decode_base_shrink_kernelILb1"), ("linear.hip", "13linear_kernel")])
+def test_the_base_tiles_of_small_batches_keep_blocks_in_flight(src, kernel):
+    # A tile's loop waits for the block it is about to use, in an assembly statement that counts the others.  A wait
+    # for everything that the compiler adds (for a value loaded before the loop and first used in it) leaves no block
+    # in flight under another.
+    loops = [(sym, l) for sym, lines in _whole_bodies(_device_asm(src), kernel) for l in _dma_loops(lines)]
+    assert loops
+    for sym, lines in loops:
+        in_asm = False
+        for l in lines:
+            if "#ASMSTART" in l or "#ASMEND" in l:
+                in_asm = "#ASMSTART" in l
+            assert in_asm or not re.search(r"s_waitcnt.*vmcnt\(0\)", l), f"{sym}: `{l.strip()}` drains the loads"
