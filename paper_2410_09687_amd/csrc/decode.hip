@@ -198,8 +198,10 @@ __device__ __forceinline__ void decode_shrink_slab(const ShrinkDParams &p, int s
 // launches' ramp and tail are paid once.  Entry 0 repeats what the plain parameter blocks hold.
 struct DecodeMore {
     int n;                          // projections of the call (1..MAX_SHARED_X)
-    int base_first[MAX_SHARED_X];   // first base-role workgroup of each (multiples of 8)
+    int tile_first[MAX_SHARED_X];   // first base tile of each (multiples of 8; the next one's where it has none)
+    int slab_first[MAX_SHARED_X];   // first slab of W of each (likewise)
     int xb_first[MAX_SHARED_X];     // first expand row block of each
+    int k_splits[MAX_SHARED_X];     // parts of each one's base product
     const char *W[MAX_SHARED_X], *A_stack[MAX_SHARED_X], *B_stack[MAX_SHARED_X];
     char *ug_hi[MAX_SHARED_X], *ug_lo[MAX_SHARED_X], *y[MAX_SHARED_X];
     float *ybase[MAX_SHARED_X];
@@ -305,9 +307,9 @@ __device__ __forceinline__ void shrink_stream(const MOIN_CONST_AS ShrinkStreamAr
         if (it < n_w) {
             int q = 0;
 #pragma unroll
-            for (int i = 1; i < MAX_SHARED_X; ++i) q += i < args->m.n && it >= args->m.base_first[i];
+            for (int i = 1; i < MAX_SHARED_X; ++i) q += i < args->m.n && it >= args->m.slab_first[i];
             o.proj = ~q;
-            o.j0 = (it - args->m.base_first[q]) * 16;
+            o.j0 = (it - args->m.slab_first[q]) * 16;
             o.r = args->m.d_out[q];
             o.rows = min(16, o.r - o.j0);
             o.A = args->m.W[q] + (int64_t)o.j0 * ld;
@@ -450,13 +452,13 @@ __global__ __launch_bounds__(SHRINK_WAVES * 64, 4) void decode_base_shrink_kerne
         for (int b = (int)blockIdx.x; b < n_base; b += P) {
             int i = 0;
 #pragma unroll
-            for (int j = 1; j < MAX_SHARED_X; ++j) i += j < args->m.n && b >= args->m.base_first[j];
+            for (int j = 1; j < MAX_SHARED_X; ++j) i += j < args->m.n && b >= args->m.tile_first[j];
             LinearKParams q = by_value.lp;
             q.W = args->m.W[i];
             q.y = reinterpret_cast<char *>(args->m.ybase[i]);
             q.d_out = args->m.d_out[i];
             q.n_tiles_n = args->m.n_tiles_n[i];
-            linear_tile<CfgDecodeBase>(q, b - args->m.base_first[i], smem);
+            linear_tile<CfgDecodeBase>(q, b - args->m.tile_first[i], smem);
             __syncthreads();   // (the tile's epilogue has left LDS)
         }
     }
@@ -500,7 +502,7 @@ __device__ __forceinline__ void store_out(char *y, int d_out, int y_f32, int tok
 // Phase 1 of a token block issues every load (for the first block also B_e, the HBM
 // traffic); phase 2 consumes them; a scheduling barrier between the two keeps all
 // loads ahead of the first wait.
-template <int KS_HOLD, int NSPLIT, bool BY_POS, int RB, bool FULL>
+template <int KS_HOLD, int NSPLIT, bool BY_POS, int RB, bool MIXED, bool FULL>
 __device__ __forceinline__ void expand_item(const ExpandKParams &p, int slab, int e, int gs, int ge, int r)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -554,7 +556,8 @@ __device__ __forceinline__ void expand_item(const ExpandKParams &p, int slab, in
                 const int oo = min(o_base + c * 16 + 4 * (lane >> 4), d_out - 4);
                 const float *src = p.ybase + (int64_t)brow_idx * d_out + oo;
 #pragma unroll
-                for (int sp = 0; sp < NSPLIT; ++sp) part[c][sp] = *reinterpret_cast<const f32x4_t *>(src + sp * plane);
+                for (int sp = 0; sp < NSPLIT; ++sp)
+                    part[c][sp] = *reinterpret_cast<const f32x4_t *>(src + (!MIXED || sp < p.k_splits ? sp * plane : 0));
             }
         }
         const char *uh = p.ug_hi + (int64_t)ps * ldb + koff;
@@ -576,7 +579,8 @@ __device__ __forceinline__ void expand_item(const ExpandKParams &p, int slab, in
         for (int c = 0; c < RB; ++c) {
             acc[c] = part[c][0];   // parts are added in order: repeatable
 #pragma unroll
-            for (int sp = 1; sp < NSPLIT; ++sp) acc[c] += part[c][sp];
+            for (int sp = 1; sp < NSPLIT; ++sp)
+                if (!MIXED || sp < p.k_splits) acc[c] += part[c][sp];
         }
         if (lora) {
             if constexpr (KS_HOLD > 0) {
@@ -617,7 +621,8 @@ __device__ __forceinline__ void expand_item(const ExpandKParams &p, int slab, in
 
 // Items of (record, EXPAND_WAVES * RB * 16 rows of B_e), the row blocks of one record neighbours; with several
 // projections in the call (`m`) a record's items are the row blocks of all of them (n_xb).
-template <int KS_HOLD, int NSPLIT, bool BY_POS, int RB>
+// MIXED: projections with fewer parts of the base product than NSPLIT among them (slabs of W beside tiles).
+template <int KS_HOLD, int NSPLIT, bool BY_POS, int RB, bool MIXED>
 __global__ __launch_bounds__(EXPAND_WAVES * 64) void decode_expand_kernel(ExpandKParams p, DecodeMore m, int n_xb)
 {
     const int n_items = sload_x1(p.n_groups) * n_xb;
@@ -639,11 +644,12 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64) void decode_expand_kernel(Expand
                 q.ybase = m.ybase[i];
                 q.y = m.y[i];
                 q.d_out = m.d_out[i];
+                q.k_splits = m.k_splits[i];
             }
         if (KS_HOLD > 0 && r == KS_HOLD * 32)
-            expand_item<KS_HOLD, NSPLIT, BY_POS, RB, true>(q, xb - first, e, gs, ge, r);
+            expand_item<KS_HOLD, NSPLIT, BY_POS, RB, MIXED, true>(q, xb - first, e, gs, ge, r);
         else
-            expand_item<KS_HOLD, NSPLIT, BY_POS, RB, false>(q, xb - first, e, gs, ge, r);
+            expand_item<KS_HOLD, NSPLIT, BY_POS, RB, MIXED, false>(q, xb - first, e, gs, ge, r);
     }
 }
 
@@ -666,7 +672,7 @@ struct ExpandStreamArgs {
     DecodeMore m;
     int n_xb;
 };
-template <int KS, int NSPLIT, bool BY_POS, int RB>
+template <int KS, int NSPLIT, bool BY_POS, int RB, bool MIXED>
 __global__ __launch_bounds__(EXPAND_WAVES * 64, expand_stream_wgs(KS, NSPLIT, RB)) void decode_expand_stream_kernel(ExpandStreamArgs)
 {
     constexpr int CPR = 4 * KS;   // 16-byte chunks per row
@@ -736,6 +742,7 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, expand_stream_wgs(KS, NSPLIT, RB
         // lane holds y[token = lane % 16][o0 + b * 16 + 4 * (lane / 16) + i]; rows past d_out read (and never store)
         // the last valid group of four
         f32x4_t part[RB][NSPLIT];
+        const int splits = MIXED ? args->m.k_splits[cur.proj] : NSPLIT;   // the projection's own number of parts
         uint4 h[KS], l[KS];
         {
             const int64_t plane = T * (int64_t)cur.d_out;
@@ -745,7 +752,7 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, expand_stream_wgs(KS, NSPLIT, RB
 #pragma unroll
                 for (int sp = 0; sp < NSPLIT; ++sp)
                     part[b][sp] = *reinterpret_cast<const f32x4_t *>(
-                        ybase + sp * plane + min(cur.o0 + b * 16 + 4 * (lane >> 4), cur.d_out - 4));
+                        ybase + (sp < splits ? sp * plane : 0) + min(cur.o0 + b * 16 + 4 * (lane >> 4), cur.d_out - 4));
             const char *uh = args->m.ug_hi[cur.proj] + (int64_t)ps * ldb, *ul = args->m.ug_lo[cur.proj] + (int64_t)ps * ldb;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
@@ -774,7 +781,8 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, expand_stream_wgs(KS, NSPLIT, RB
         for (int b = 0; b < RB; ++b) {
             acc[b] = part[b][0];   // parts are added in order: repeatable
 #pragma unroll
-            for (int sp = 1; sp < NSPLIT; ++sp) acc[b] += part[b][sp];
+            for (int sp = 1; sp < NSPLIT; ++sp)
+                if (sp < splits) acc[b] += part[b][sp];
         }
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -891,18 +899,21 @@ hipError_t prepare_decode_kernels()
     return e;
 }
 
-// True when the n projections of a call that share x can share its two launches: the same input,
-// contraction length, rank, scale, activation, output type and number of base parts.
+// True when the n projections of a call that share x can share its two launches: the same input, contraction length,
+// rank, scale, activation, output type and -- those whose base product is cut into tiles -- number of its parts.
 bool decode_shared_fits(const PlanView &pv, const DecodeArgs *d, int n)
 {
     if (n < 1 || n > MAX_SHARED_X) return false;
+    int tile_splits = 0;
     for (int i = 0; i < n; ++i) {
         if (!decode_base_shrink_fits(pv, d[i])) return false;
         const LinearArgs &a = d[i].lin, &a0 = d[0].lin;
-        if (decode_base_shape(pv.T, a.d_in, a.d_out).slab_blocks != decode_base_shape(pv.T, a0.d_in, a0.d_out).slab_blocks)
-            return false;
+        if (decode_base_shape(pv.T, a.d_in, a.d_out).slab_blocks == 0) {
+            if (tile_splits != 0 && d[i].k_splits != tile_splits) return false;
+            tile_splits = d[i].k_splits;
+        }
         if (a.x != a0.x || a.d_in != a0.d_in || a.r != a0.r || a.scale != a0.scale || a.act != a0.act ||
-            a.y_f32 != a0.y_f32 || d[i].k_splits != d[0].k_splits || d[i].ybase_by_pos != d[0].ybase_by_pos)
+            a.y_f32 != a0.y_f32 || d[i].ybase_by_pos != d[0].ybase_by_pos)
             return false;
     }
     return true;
@@ -914,7 +925,8 @@ static DecodeMore decode_more(const DecodeArgs *d, int n)
     m.n = n;
     for (int i = 0; i < MAX_SHARED_X; ++i) {
         const DecodeArgs &q = d[i < n ? i : 0];
-        m.base_first[i] = m.xb_first[i] = 0;
+        m.tile_first[i] = m.slab_first[i] = m.xb_first[i] = 0;
+        m.k_splits[i] = q.k_splits;
         m.W[i] = (const char *)q.lin.W; m.A_stack[i] = (const char *)q.lin.A_stack;
         m.B_stack[i] = (const char *)q.lin.B_stack;
         m.ug_hi[i] = (char *)q.ug_hi; m.ug_lo[i] = (char *)q.ug_lo; m.y[i] = (char *)q.lin.y;
@@ -929,39 +941,39 @@ hipError_t launch_decode_base_shrink_shared(const PlanView &pv, const DecodeArgs
     if (!decode_shared_fits(pv, d, n)) return hipErrorInvalidValue;
     const LinearArgs &a = d[0].lin;
     DecodeMore m = decode_more(d, n);
-    int64_t n_base = 0;
+    int64_t n_tiles = 0, n_w = 0;
     LinearKParams lp{};
-    DecodeBaseShape first{};
+    int tile_blocks = 0;   // of a tile's part of the contraction
     for (int i = 0; i < n; ++i) {
         const DecodeBaseShape sh = decode_base_shape(pv.T, a.d_in, d[i].lin.d_out);
         if (!(sh.dma || sh.slab_blocks) || sh.k_splits != d[i].k_splits) return hipErrorInvalidValue;
-        if (i == 0) {
-            first = sh;
-            lp = decode_base_params(pv, a, d[0].ybase, 1, sh, pv.tok_sorted);   // rows in by-expert order
-        }
-        m.base_first[i] = (int)n_base;
+        m.tile_first[i] = (int)n_tiles;
+        m.slab_first[i] = (int)n_w;
         m.n_tiles_n[i] = sh.n_tiles_n;
-        n_base += sh.grid;   // (tiles: a multiple of 8, every projection's tiles keep their place in the XCD rotation)
+        if (sh.slab_blocks > 0) {
+            n_w += sh.grid;
+        } else {
+            n_tiles += sh.grid;   // (a multiple of 8, every projection's tiles keep their place in the XCD rotation)
+            tile_blocks = sh.kb_per_split;
+        }
+        if (i == 0 || sh.slab_blocks == 0)   // (what the slabs need of it is the batch's size)
+            lp = decode_base_params(pv, a, d[i].ybase, 1, sh, pv.tok_sorted);   // rows in by-expert order
     }
     const int n_slabs = (a.r + 15) / 16;
-    const int64_t items = (int64_t)n_slabs * pv.max_groups * n;
-    if (n_base + items > 0x3fffffffLL) return hipErrorInvalidValue;
+    const int64_t items = n_w + (int64_t)n_slabs * pv.max_groups * n;
+    if (n_tiles + items > 0x3fffffffLL) return hipErrorInvalidValue;
     const ShrinkDParams sp = shrink_params(pv, d[0]);
     const dim3 block(SHRINK_WAVES * 64);
-    Turns turns;
-    turns.P = persistent_grid(2, n_base + items);
-    if (first.slab_blocks == 0) {
-        turns.n_base = (int)n_base;
+    Turns turns{persistent_grid(2, n_tiles + items), (int)n_tiles, 1};
+    if (n_tiles > 0) {
         const int batches = (a.d_in * 2 + SHRINK_WAVES * STREAM_COL - 1) / (SHRINK_WAVES * STREAM_COL);
         lp.paced = pv.T >= PACED_MIN_T && a.r >= PACED_MIN_R;
-        turns.c = std::max(1, DECODE_TILE_ITEMS * first.kb_per_split / (16 * (batches + 1)));
+        turns.c = std::max(1, DECODE_TILE_ITEMS * tile_blocks / (16 * (batches + 1)));
         hipLaunchKernelGGL(decode_base_shrink_kernel<true>, dim3(turns.P), block, STREAM_SMEM, stream,
-                           ShrinkStreamArgs{sp, lp, m, turns, 0, n_slabs});
+                           ShrinkStreamArgs{sp, lp, m, turns, (int)n_w, n_slabs});
     } else {
-        turns.n_base = 0;
-        turns.c = 1;
         hipLaunchKernelGGL(decode_base_shrink_kernel<false>, dim3(turns.P), block, STREAM_SMEM, stream,
-                           ShrinkStreamArgs{sp, lp, m, turns, (int)n_base, n_slabs});
+                           ShrinkStreamArgs{sp, lp, m, turns, (int)n_w, n_slabs});
     }
     return hipGetLastError();
 }
@@ -976,10 +988,12 @@ hipError_t launch_decode_expand_shared(const PlanView &pv, const DecodeArgs *d, 
     if (n < 1 || n > MAX_SHARED_X) return hipErrorInvalidValue;
     if (pv.max_groups <= 0) return hipSuccess;
     const LinearArgs &a = d[0].lin;
-    for (int i = 1; i < n; ++i)
-        if (d[i].lin.r != a.r || d[i].k_splits != d[0].k_splits || d[i].lin.y_f32 != a.y_f32 ||
-            d[i].ybase_by_pos != d[0].ybase_by_pos)
+    int k_splits = d[0].k_splits;   // of the kernel; a projection with fewer parts (slabs beside tiles) adds its own
+    for (int i = 1; i < n; ++i) {
+        if (d[i].lin.r != a.r || d[i].lin.y_f32 != a.y_f32 || d[i].ybase_by_pos != d[0].ybase_by_pos)
             return hipErrorInvalidValue;
+        k_splits = std::max(k_splits, d[i].k_splits);
+    }
     ExpandKParams p;
     p.B_stack = (const char *)a.B_stack; p.ug_hi = (const char *)d[0].ug_hi; p.ug_lo = (const char *)d[0].ug_lo;
     p.ybase = d[0].ybase; p.y = (char *)a.y;
@@ -988,7 +1002,7 @@ hipError_t launch_decode_expand_shared(const PlanView &pv, const DecodeArgs *d, 
     const int nks = (a.r + 31) / 32;
     const bool streams = nks <= 4 && !several_blocks(pv);
     constexpr int RB = 4;   // 16-row blocks per wave of the held form
-    const bool large = pv.T > DECODE_MAX_T && d[0].k_splits == 1 && !d[0].ybase_by_pos;
+    const bool large = pv.T > DECODE_MAX_T && k_splits == 1 && !d[0].ybase_by_pos;
     const int ks = nks <= 2 ? nks : 4, stream_rb = expand_stream_rb(ks, large);
     const int rows = streams ? stream_rb * 16 : EXPAND_WAVES * RB * 16;
     DecodeMore m = decode_more(d, n);
@@ -999,18 +1013,25 @@ hipError_t launch_decode_expand_shared(const PlanView &pv, const DecodeArgs *d, 
     }
     const int64_t items = xb * pv.max_groups;
     if (items > 0x3fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(streams ? persistent_grid(expand_stream_wgs(ks, d[0].k_splits, stream_rb), (items + EXPAND_WAVES - 1) / EXPAND_WAVES)
+    const dim3 grid((unsigned)(streams ? persistent_grid(expand_stream_wgs(ks, k_splits, stream_rb), (items + EXPAND_WAVES - 1) / EXPAND_WAVES)
                                        : persistent_grid(HELD_WGS, items)));
-#define MOIN_EXPAND_STREAM(KS, NS, BP, SRB)                                                                          \
-    hipLaunchKernelGGL((decode_expand_stream_kernel<(KS > 0 ? KS : 1), NS, BP, SRB>), grid, dim3(EXPAND_WAVES * 64), \
+    // parts that differ come from slabs (one) beside tiles of up to 64 blocks (two): decode_base_shape
+    bool mixed = false;
+    for (int i = 1; i < n; ++i) mixed = mixed || d[i].k_splits != d[0].k_splits;
+    if (mixed && !(k_splits == 2 && d[0].ybase_by_pos)) return hipErrorInvalidValue;
+#define MOIN_EXPAND_STREAM(KS, NS, BP, SRB, MIX)                                                                          \
+    hipLaunchKernelGGL((decode_expand_stream_kernel<(KS > 0 ? KS : 1), NS, BP, SRB, MIX>), grid, dim3(EXPAND_WAVES * 64), \
                        EXPAND_WAVES * expand_stage(KS, SRB), stream, ExpandStreamArgs{p, m, (int)xb})
+#define MOIN_EXPAND_HELD(KS, NS, BP, MIX)                                                                               \
+    hipLaunchKernelGGL((decode_expand_kernel<KS, NS, BP, RB, MIX>), grid, dim3(EXPAND_WAVES * 64), 0, stream, p, m, (int)xb)
 #define MOIN_EXPAND_R(KS, NS, BP)                                                                                      \
     do {                                                                                                               \
-        if (KS > 0 && streams && NS == 1 && !BP && large) MOIN_EXPAND_STREAM(KS, 1, false, 4);                         \
-        else if (KS > 0 && streams) MOIN_EXPAND_STREAM(KS, NS, BP, (expand_stream_rb(KS, false)));                     \
-        else                                                                                                           \
-            hipLaunchKernelGGL((decode_expand_kernel<KS, NS, BP, RB>), grid, dim3(EXPAND_WAVES * 64), 0, stream, p, m, \
-                               (int)xb);                                                                               \
+        constexpr bool may_mix = NS == 2 && BP;                                                                        \
+        if (KS > 0 && streams && NS == 1 && !BP && large) MOIN_EXPAND_STREAM(KS, 1, false, 4, false);                  \
+        else if (KS > 0 && streams && mixed) MOIN_EXPAND_STREAM(KS, NS, BP, (expand_stream_rb(KS, false)), may_mix);   \
+        else if (KS > 0 && streams) MOIN_EXPAND_STREAM(KS, NS, BP, (expand_stream_rb(KS, false)), false);              \
+        else if (mixed) MOIN_EXPAND_HELD(KS, NS, BP, (KS == 0 && may_mix)); /* (a small batch streams) */             \
+        else MOIN_EXPAND_HELD(KS, NS, BP, false);                                                                      \
     } while (0)
 #define MOIN_EXPAND_S(KS, NS)                                                                                  \
     do {                                                                                                       \
@@ -1018,7 +1039,7 @@ hipError_t launch_decode_expand_shared(const PlanView &pv, const DecodeArgs *d, 
         else MOIN_EXPAND_R(KS, NS, false);                                                                     \
     } while (0)
 #define MOIN_EXPAND(KS)                                  \
-    switch (d[0].k_splits) {                             \
+    switch (k_splits) {                                  \
     case 1: MOIN_EXPAND_S(KS, 1); break;                 \
     case 2: MOIN_EXPAND_S(KS, 2); break;                 \
     case 3: MOIN_EXPAND_S(KS, 3); break;                 \
@@ -1032,6 +1053,7 @@ hipError_t launch_decode_expand_shared(const PlanView &pv, const DecodeArgs *d, 
 #undef MOIN_EXPAND
 #undef MOIN_EXPAND_S
 #undef MOIN_EXPAND_R
+#undef MOIN_EXPAND_HELD
 #undef MOIN_EXPAND_STREAM
     return hipGetLastError();
 }

@@ -185,11 +185,11 @@ using CfgDecodeBase = DmaCore<128, 128, 32, 2, 4, 4>;
 using CfgThin = GemmCore<128, 64, 64, 2, 2>;         // decode base GEMM, any contraction length: 4 waves, 64 x 32
 
 // In the smallest batches a tile would be mostly padding and a chain of trips to memory; the base product is slabs of
-// 16 rows of W against the whole batch instead.  Up to one block of 16 tokens always (8 tokens, us of the launch with
-// tiles / slabs: 2048 -> 2560 in three projections 16 / 10, -> 2048 15 / 7.6, 5632 -> 2048 19 / 12, 2048 -> 5632 twice
-// 17.8 / 17.7), with two blocks where each slab is one step and a projection's two blocks of them one round of the
-// chip's workgroups (17 tokens, first two of these: 19 / 13 and 16 / 10, 32 tokens: 20 / 16 and 17 / 14; but 2048 ->
-// 5632 twice 20 / 23 and 20 / 28).
+// 16 rows of W against the whole batch instead.  Up to one block of 16 tokens always, with two blocks where each slab is
+// one step and a projection's two blocks of them one round of the chip's workgroups.  Us of a call at rank 16, tiles /
+// slabs: 8 tokens 2048 -> 2048 20.1 / 12.8, -> 5632 twice 22.6 / 21.1, 5632 -> 2048 25.0 / 16.5; 16 tokens 20.0 / 12.8,
+// 23.1 / 22.6, 25.2 / 18.1; 17 tokens 2048 -> 2048 19.5 / 14.6, -> 4096 20.2 / 17.5, but -> 5632 twice 22.4 / 27.1, 4096
+// -> 4096 21.5 / 27.0; 32 tokens 19.4 / 15.3, 20.7 / 18.9, 23.6 / 30.7, 22.1 / 29.4, 5632 -> 2048 25.1 / 27.6.
 constexpr int BASE_SLAB_PIECE = 2048, BASE_SLAB_MAX = 256;
 
 // How the decode base GEMM of a shape is cut up.

@@ -88,3 +88,36 @@ def test_shared_call_of_widths_on_both_sides_of_the_slab_rule(T):
     gc.ctx().check()
     for y, i in zip(ys, ins):
         _check(y, _reference(i, ids, lens, None, r), d_in, r)
+
+
+@pytest.mark.parametrize("d_in,r", [(256, 32), (2048, 64), (2048, 136)])
+def test_a_shared_call_with_slabs_and_tiles_takes_two_launches(d_in, r):
+    # 17 tokens: 4096 outputs and fewer come from slabs of W, more from tiles (at 2048 inputs in two parts)
+    T, E = 17, 6
+    lens = [1] * T
+    ids, _ = _batch(lens, E, T)
+    ins = [wl.make_linear_inputs(wl.LinearWorkload("stream", d_in, d, r, E, lens, "uniform", scale=2.0, seed=60 + d),
+                                 "cuda", expert_ids=ids) for d in (264, 4112, 48, 4104)]
+    for i in ins[1:]:
+        i.x.copy_(ins[0].x)
+    ctx = moin.Context(0)
+    try:
+        plan = moin.Plan(ctx)
+        plan.build(ins[0].seq_offsets, ins[0].expert_ids, T, E)
+        print(f"[gpu] decode stream, slabs and tiles in one call, d_in={d_in} r={r}", flush=True)
+        for pick in (ins, ins[1:3], ins[:2]):
+            ctx.timing_enable(True)
+            ctx.timing_reset()
+            ys = moin.moin_lora_linear_planned_shared(ctx, plan, pick[0].x, [i.W for i in pick], [i.A_stack for i in pick],
+                                                      [i.B_stack for i in pick], 2.0)
+            ctx.check()
+            n = [ctx.timing_read(k)[1] for k in (moin.K_DECODE_SHRINK, moin.K_DECODE_EXPAND)]
+            ctx.timing_enable(False)
+            for y, i in zip(ys, pick):
+                one = moin.moin_lora_linear_planned(ctx, plan, pick[0].x, i.W, i.A_stack, i.B_stack, 2.0)
+                assert torch.equal(y.view(torch.int16), one.view(torch.int16))
+            ctx.check()
+            assert n == [1, 1], n
+        plan.close()
+    finally:
+        ctx.close()
