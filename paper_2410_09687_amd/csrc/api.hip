@@ -246,7 +246,7 @@ PlanLayout plan_layout(int32_t S, int64_t T, int32_t E, bool upper_bound = false
     L.grp_meta = take((size_t)(L.max_groups + 1) * 16);
     L.grp_start = take((size_t)(L.max_groups + 2) * 4);
     L.grp_tmp = take((size_t)(L.max_groups + 1) * 8);
-    L.n_groups = take(4);
+    L.n_groups = take(8);
     L.tmp = take((size_t)4 * ((size_t)S + 1) * 4);
     L.max_plain = (L.decode && (T > DECODE_MAX_T || upper_bound)) ? (int)((T + TILE_M - 1) / TILE_M) : 0;
     L.plain = take(((size_t)4 * L.max_plain + 1) * 4);

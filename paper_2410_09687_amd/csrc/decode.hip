@@ -275,7 +275,8 @@ __device__ __forceinline__ void shrink_stream(const MOIN_CONST_AS ShrinkStreamAr
     const int4 *grp_meta = args->sp.grp_meta;
     const int *tok_sorted = args->sp.tok_sorted;
     const char *x = args->sp.x;
-    const int n_items = n_w + sload_x1(args->sp.n_groups) * per_g;
+    const int g_first = sload_x1(args->sp.n_groups + 1);   // base-only records come first: nothing to do for them
+    const int n_items = n_w + (sload_x1(args->sp.n_groups) - g_first) * per_g;
     const uint32_t ld = (uint32_t)d_in * 2u;
     const int n_batches = (int)((ld + NW * STREAM_COL - 1) / (NW * STREAM_COL));
     const uint32_t col = (uint32_t)wave * STREAM_COL;
@@ -291,7 +292,7 @@ __device__ __forceinline__ void shrink_stream(const MOIN_CONST_AS ShrinkStreamAr
     int it_next = turns.short_item(w, 0);
     if (it_next >= n_items) return;
     auto meta_of = [&](int it) __attribute__((always_inline)) {
-        return sload_x4(grp_meta + (it >= n_w && it < n_items ? (it - n_w) / per_g : 0));
+        return sload_x4(grp_meta + (it >= n_w && it < n_items ? g_first + (it - n_w) / per_g : 0));
     };
     i32x4_t gm_next = meta_of(it_next);
     bool more = true;
@@ -431,7 +432,7 @@ __global__ __launch_bounds__(SHRINK_WAVES * 64) void decode_shrink_kernel(Shrink
     __shared__ Partials red[2];
     const int n_items = sload_x1(p.n_groups) * n_slabs;
     int flip = 0;
-    for (int it = (int)blockIdx.x; it < n_items; it += (int)gridDim.x)
+    for (int it = sload_x1(p.n_groups + 1) * n_slabs + (int)blockIdx.x; it < n_items; it += (int)gridDim.x)
         decode_shrink_slab<SHRINK_BATCH, KS_HOLD>(p, it % n_slabs, it / n_slabs, red, flip);
 }
 
@@ -672,6 +673,64 @@ struct ExpandStreamArgs {
     DecodeMore m;
     int n_xb;
 };
+
+// The base-only records (the first `n_rec`): y is the sum of the base product's parts.  Bound by memory; a wave takes 512
+// consecutive columns of one token, two such pieces at a time.  (1024 base-only tokens through 2048 -> 5632, two parts:
+// 10.2 us, 5.7 TB/s; as items like the others, 16 tokens by 32 rows of an adapter that is not there, 24.9.)
+template <int NSPLIT, bool BY_POS, bool MIXED>
+__device__ __forceinline__ void write_base_only(const MOIN_CONST_AS ExpandStreamArgs *args, int n_rec, int wave_id, int n_waves)
+{
+    constexpr int COLS = 512, UNR = NSPLIT <= 2 ? 2 : 1;
+    const int lane = threadIdx.x & 63, y_f32 = args->p.y_f32, n = args->m.n;
+    const int n_pos = sload_x4(args->p.grp_meta + n_rec - 1).z;
+    int per_pos = 0;   // column blocks of all projections
+    for (int i = 0; i < n; ++i) per_pos += (args->m.d_out[i] + COLS - 1) / COLS;
+    const uint32_t total = (uint32_t)n_pos * (uint32_t)per_pos;
+    for (uint32_t u0 = wave_id; u0 < total; u0 += UNR * n_waves) {
+        f32x4_t part[UNR][NSPLIT][2];
+        char *dst[UNR];
+        int splits[UNR];
+#pragma unroll
+        for (int k = 0; k < UNR; ++k) {
+            const uint32_t u = min(u0 + k * n_waves, total - 1);
+            const int pos = (int)(u / (uint32_t)per_pos);
+            int c = (int)u - pos * per_pos, i = 0;
+            for (; i + 1 < n && c >= (args->m.d_out[i] + COLS - 1) / COLS; ++i) c -= (args->m.d_out[i] + COLS - 1) / COLS;
+            const int d_out = args->m.d_out[i], tok = sload_x1(args->p.tok_sorted + pos);
+            const int col = c * COLS + lane * 8;
+            const bool ok = col < d_out && u0 + k * n_waves < total;   // d_out % 8 == 0
+            const float *src = args->m.ybase[i] + (int64_t)(BY_POS ? pos : tok) * d_out + min(col, d_out - 8);
+            const int64_t plane = args->p.T * (int64_t)d_out;
+            splits[k] = MIXED ? args->m.k_splits[i] : NSPLIT;
+            dst[k] = ok ? args->m.y[i] + ((int64_t)tok * d_out + col) * (y_f32 ? 4 : 2) : nullptr;
+#pragma unroll
+            for (int sp = 0; sp < NSPLIT; ++sp)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    part[k][sp][h] = *reinterpret_cast<const f32x4_t *>(src + (sp < splits[k] ? sp * plane : 0) + h * 4);
+        }
+#pragma unroll
+        for (int k = 0; k < UNR; ++k) {
+            f32x4_t v[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                v[h] = part[k][0][h];   // parts are added in order: repeatable
+#pragma unroll
+                for (int sp = 1; sp < NSPLIT; ++sp)
+                    if (sp < splits[k]) v[h] += part[k][sp][h];
+            }
+            if (!dst[k]) continue;
+            if (y_f32) {
+                *reinterpret_cast<f32x4_t *>(dst[k]) = v[0];
+                *reinterpret_cast<f32x4_t *>(dst[k] + 16) = v[1];
+            } else {
+                *reinterpret_cast<uint4 *>(dst[k]) = make_uint4(pack_bf16x2(v[0][0], v[0][1]), pack_bf16x2(v[0][2], v[0][3]),
+                                                                pack_bf16x2(v[1][0], v[1][1]), pack_bf16x2(v[1][2], v[1][3]));
+            }
+        }
+    }
+}
+
 template <int KS, int NSPLIT, bool BY_POS, int RB, bool MIXED>
 __global__ __launch_bounds__(EXPAND_WAVES * 64, expand_stream_wgs(KS, NSPLIT, RB)) void decode_expand_stream_kernel(ExpandStreamArgs)
 {
@@ -683,10 +742,12 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, expand_stream_wgs(KS, NSPLIT, RB
     const int n_xb = args->n_xb, r_stack = args->p.r, y_f32 = args->p.y_f32;
     const int4 *grp_meta = args->p.grp_meta;
     const int *tok_sorted = args->p.tok_sorted;
-    const int n_items = sload_x1(args->p.n_groups) * n_xb;
+    const int g_first = sload_x1(args->p.n_groups + 1);
+    const int n_items = (sload_x1(args->p.n_groups) - g_first) * n_xb;
     const int P = (int)gridDim.x * EXPAND_WAVES;
     const uint32_t ldb = (uint32_t)r_stack * 2u;
     const int64_t T = args->p.T;
+    if (g_first > 0) write_base_only<NSPLIT, BY_POS, MIXED>(args, g_first, (int)blockIdx.x * EXPAND_WAVES + wave, P);
 
     struct Item {
         const char *B;   // first of the rows
@@ -695,7 +756,7 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, expand_stream_wgs(KS, NSPLIT, RB
     };
     int it_next = (int)blockIdx.x * EXPAND_WAVES + wave;
     if (it_next >= n_items) return;
-    auto meta_of = [&](int it) __attribute__((always_inline)) { return sload_x4(grp_meta + (it < n_items ? it / n_xb : 0)); };
+    auto meta_of = [&](int it) __attribute__((always_inline)) { return sload_x4(grp_meta + (it < n_items ? g_first + it / n_xb : 0)); };
     i32x4_t gm_next = meta_of(it_next);
     bool more = true;
     auto advance = [&]() __attribute__((always_inline)) {

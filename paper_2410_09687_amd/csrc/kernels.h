@@ -44,7 +44,7 @@ struct PlanView {
     int *n_tiles;      // [1]
     // decode grouping (built only for batches that take the decode path)
     int *tok_sorted;   // [T] token index, grouped by expert
-    int4 *grp_meta;    // [max_groups] {adapter slot or -1, first, one-past-last position in tok_sorted, rank};
+    int4 *grp_meta;    // [max_groups] {adapter slot or -1 (none, or of rank 0), first, one-past-last position in tok_sorted, rank};
                        // an expert with more than `chunk` tokens has several records
     int *grp_start;    // [max_groups + 1] scratch while building
     int2 *grp_tmp;     // [max_groups] scratch while building: {slot, rank} of each expert's group
@@ -52,7 +52,7 @@ struct PlanView {
     // T > DECODE_MAX_T): the base product of such a batch runs on them
     int *plain_row0, *plain_rows, *plain_expert, *plain_rank, *plain_n;   // [max_plain] x 4, [1]
     int max_plain;
-    int *n_groups;     // [1]
+    int *n_groups;     // [2] records, and how many of them are base-only: those come first
     // scratch used while building
     unsigned long long *keys; // [pow2 >= S]
     int *tmp;                 // [4 * (S + 1)]

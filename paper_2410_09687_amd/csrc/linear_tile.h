@@ -117,10 +117,11 @@ __device__ __forceinline__ void linear_tile(const LinearKParams &p, int bid, cha
             if (s < total) MOIN_ISSUE_BLOCK(s, smem + s * C::STAGE_BYTES);
         int st = 0;
         for (int it = 0; it < total; ++it) {
-            if (!p.paced && it + C::NS - 2 < total) wait_vm_then_barrier<(C::NS - 2) * C::LPB>();
+            if (it + C::NS - 2 < total) wait_vm_then_barrier<(C::NS - 2) * C::LPB>();
             else wait_vm_then_barrier<0>();
             const int nb = it + C::NS - 1;
             const int ns = (st == 0) ? C::NS - 1 : st - 1;
+            if (p.paced) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (nb < total) MOIN_ISSUE_BLOCK(nb, smem + ns * C::STAGE_BYTES);
             C::compute_stage(smem + st * C::STAGE_BYTES, acc);
             st = (st + 1 == C::NS) ? 0 : st + 1;

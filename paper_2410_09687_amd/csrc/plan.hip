@@ -94,6 +94,7 @@ __global__ __launch_bounds__(PLAN_THREADS_MAX) void plan_large_kernel(PlanView p
                 err |= ERR_BAD_EXPERT;
                 e = -1;
             }
+            if (plan_rank_of(e, rank_of_expert, err_word) == 0) e = -1;   // rank 0: base model only
             lens[s] = hi - lo;
             key = ((unsigned long long)(unsigned)(e + 1) << 32) | (unsigned)s;
         }
@@ -233,7 +234,11 @@ __global__ __launch_bounds__(PLAN_THREADS_MAX) void plan_large_kernel(PlanView p
             for (int t = pv.grp_start[gi]; t < ge && rec < pv.max_groups; t += pv.chunk, ++rec)
                 pv.grp_meta[rec] = make_int4(er.x, t, min(t + pv.chunk, ge), er.y);
         }
-        if (tid == 0) *pv.n_groups = n_rec;
+        if (tid == 0) {
+            pv.n_groups[0] = n_rec;
+            // (base-only sequences sort first; a1 holds the records before each group)
+            pv.n_groups[1] = pv.grp_tmp[0].x >= 0 ? 0 : n_groups > 1 ? min(a1[1], pv.max_groups) : n_rec;
+        }
         // unused records read as empty groups, so the decode kernels need not
         // fetch the group count before their own record
         for (int gi = n_rec + tid; gi < pv.max_groups; gi += PLAN_THREADS) pv.grp_meta[gi] = make_int4(-1, 0, 0, 0);

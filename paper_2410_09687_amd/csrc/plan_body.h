@@ -102,7 +102,7 @@ __device__ __forceinline__ void plan_base_only(const PlanView &pv, int nt_thread
     if (pv.decode) {
         for (int t = tid; t < T; t += nt_threads) pv.tok_sorted[t] = t;
         const int nc = min((T + pv.chunk - 1) / pv.chunk, pv.max_groups);
-        if (tid == 0) *pv.n_groups = nc;
+        if (tid == 0) pv.n_groups[0] = pv.n_groups[1] = nc;
         for (int gi = tid; gi < pv.max_groups; gi += nt_threads)
             pv.grp_meta[gi] = gi < nc ? make_int4(-1, gi * pv.chunk, min(T, (gi + 1) * pv.chunk), 0)
                                       : make_int4(-1, 0, 0, 0);
@@ -138,6 +138,7 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
             err |= ERR_BAD_EXPERT;
             e = -1;
         }
+        if (plan_rank_of(e, rank_of_expert, err_word) == 0) e = -1;   // rank 0: base model only
         L.ekey[s] = (unsigned)(e + 1);
         L.idx[0][s] = (uint16_t)s;
     }
@@ -283,6 +284,7 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
         n[0] += (ge - gs + pv.chunk - 1) / pv.chunk;
     }
     plan_scan<PT, 1>(n, n_rec, L.sums);
+    int base_only = 0;
     for (int g = g0; g < g1; ++g) {
         const int p = head_at[g];
         const int gs = L.tokbase[p], ge = g + 1 < n_groups ? L.tokbase[head_at[g + 1]] : n_tok;
@@ -290,9 +292,13 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
         const int rk = plan_rank_of(e, rank_of_expert, err_word);
         for (int t = gs; t < ge && n[0] < pv.max_groups; t += pv.chunk, ++n[0])
             pv.grp_meta[n[0]] = make_int4(e, t, min(t + pv.chunk, ge), rk);
+        if (e < 0) base_only = n[0];   // (the first group, if any)
     }
     const int n_out = min(n_rec[0], pv.max_groups);
-    if (tid == 0) *pv.n_groups = n_out;
+    if (tid == 0) {
+        pv.n_groups[0] = n_out;
+        pv.n_groups[1] = base_only;
+    }
     // unused records read as empty groups, so the decode kernels need not
     // fetch the group count before their own record
     for (int gi = n_out + tid; gi < pv.max_groups; gi += PT) pv.grp_meta[gi] = make_int4(-1, 0, 0, 0);

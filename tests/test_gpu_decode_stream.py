@@ -121,3 +121,53 @@ def test_a_shared_call_with_slabs_and_tiles_takes_two_launches(d_in, r):
         plan.close()
     finally:
         ctx.close()
+
+
+# base-only tokens (no adapter, or one of rank 0) have a pass of their own: none, some and nothing but them, rows of one
+# and several pieces of 512 columns, ragged; parts of the base product from one to four, and rows by token (T > 1024)
+@pytest.mark.parametrize("share", [1.0, 0.5, 0.02])
+@pytest.mark.parametrize("T,E,d_in,d_out,r", [(5, 9, 256, 520, 64), (40, 9, 2048, 1032, 16), (70, 200, 5632, 488, 128),
+                                              (300, 9, 4096, 8, 40), (1300, 700, 2048, 1544, 128)])
+def test_base_only_tokens(T, E, d_in, d_out, r, share):
+    rng = np.random.default_rng(T + d_out)
+    lens = [1] * T
+    ids = rng.integers(0, E, size=T).astype(np.int32)
+    at = rng.random(T)
+    ids[at < share / 2] = -1
+    ranks = 8 * rng.integers(1, r // 8 + 1, size=E).astype(np.int32)
+    ranks[np.unique(ids[(at < share) & (ids >= 0)])] = 0
+    w = wl.LinearWorkload("base_only", d_in, d_out, r, E, lens, "uniform", scale=2.0, seed=T)
+    inp = wl.make_linear_inputs(w, "cuda", expert_ids=ids)
+    rk = torch.from_numpy(ranks).cuda()
+    ref = _reference(inp, ids, lens, rk, r)
+    print(f"[gpu] base-only tokens T={T} {d_in}->{d_out} share={share}", flush=True)
+    for dt in (torch.float32, torch.bfloat16):
+        y = torch.full((T, d_out), float("nan"), dtype=dt, device="cuda")
+        moin.moin_lora_linear(gc.ctx(), inp.x, inp.seq_offsets, inp.expert_ids, inp.W, inp.A_stack, inp.B_stack, 2.0,
+                              rank_of_expert=rk, out=y, y_dtype=dt)
+        gc.ctx().check()
+        if dt == torch.float32:
+            _check(y, ref, d_in, r)
+        else:   # rounded to nearest: half an ulp (2^-9) of each value, beside the fp32 result's own bound
+            slack = 4 * (d_in ** 0.5 + 128) * 2.0 ** -24 * float(ref.abs().max())
+            assert bool(((y.double() - ref).abs() <= ref.abs() * 2.0 ** -8 + slack).all())
+
+
+def test_base_only_tokens_of_several_projections():
+    T, E, d_in, r = 90, 9, 512, 32
+    lens = [1] * T
+    ids, ranks = _batch(lens, E, T)
+    ids[::2] = -1
+    ins = [wl.make_linear_inputs(wl.LinearWorkload("base_only", d_in, d, r, E, lens, "uniform", scale=2.0, seed=70 + d),
+                                 "cuda", expert_ids=ids) for d in (1032, 8, 520)]
+    for i in ins[1:]:
+        i.x.copy_(ins[0].x)
+    rk = ranks(r)
+    plan = moin.Plan(gc.ctx())
+    plan.build(ins[0].seq_offsets, ins[0].expert_ids, T, E, rank_of_expert=rk)
+    print("[gpu] base-only tokens, three projections", flush=True)
+    ys = moin.moin_lora_linear_planned_shared(gc.ctx(), plan, ins[0].x, [i.W for i in ins], [i.A_stack for i in ins],
+                                              [i.B_stack for i in ins], 2.0, y_dtype=torch.float32)
+    gc.ctx().check()
+    for y, i in zip(ys, ins):
+        _check(y, _reference(i, ids, lens, rk, r), d_in, r)
