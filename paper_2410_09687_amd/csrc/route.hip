@@ -764,7 +764,7 @@ int route_stream_group(int64_t N, int K, int D, int is_bf16)
     if (!use_stream_route(a)) return 1;
     const int64_t nct = (K + r4::BT - 1) / r4::BT;
     const int64_t per_xcd = ((N + r4::BT - 1) / r4::BT + 7) / 8;
-    const int pref[] = {4, 8, 2, 5, 3, 6, 7, 1, 10, 9, 16, 12, 14, 20, 32};
+    const int pref[] = {4, 8, 2, 5, 3, 6, 7, 1, 10, 9, 16, 14, 32};   // (others never have the shortest: more than 16 query tiles)
     int best_g = 1;
     int64_t best = INT64_MAX;
     for (int g : pref) {

@@ -42,7 +42,7 @@ def test_bf16_router_streaming_kernel_edges(N, K, D):
 @pytest.mark.parametrize("N,K,D", [(40000, 520, 64), (70000, 200, 64), (66000, 1100, 128)])
 def test_bf16_router_streaming_kernel_several_items_per_workgroup(N, K, D):
     # more query tiles than the persistent launch has workgroups: a workgroup streams through several
-    # (query tile, group member) items, the last of them ragged; groups of 3, 1 and 5 workgroups per tile
+    # (query tile, group member) items, the last of them ragged; groups of 3, 1 and 5 workgroups per tile (_group)
     rin = _route_case(N, K, D, "bf16", True, seed=N + K + D)
     print(f"[gpu] route bf16 stream, several items N={N} K={K} D={D}", flush=True)
     eids, cids, counts = moin.moin_route(gc.ctx(), rin.emb, rin.centroids, want_counts=True)
@@ -55,12 +55,33 @@ def test_bf16_router_streaming_kernel_several_items_per_workgroup(N, K, D):
                                    (4097, 5000, 64), (33333, 2049, 128)])
 def test_bf16_router_streaming_kernel_shape_sweep(N, K, D):
     # one block per centroid tile (D = 64) with several items per workgroup, a last centroid tile of one row,
-    # fewer centroids than a tile holds, group sizes 1 to 5, ragged last query tiles
+    # fewer centroids than a tile holds, groups of 2, 2, 6, 1, 10 and 5, ragged last query tiles
     rin = _route_case(N, K, D, "bf16", True, seed=3 * N + K + D)
     print(f"[gpu] route bf16 stream sweep N={N} K={K} D={D}", flush=True)
     eids, cids, counts = moin.moin_route(gc.ctx(), rin.emb, rin.centroids, want_counts=True)
     gc.ctx().check()
     gc.check_route(rin.emb, rin.centroids, cids)
+    assert torch.equal(counts.long(), torch.bincount(cids.long(), minlength=K))
+
+
+def _group(N, K):
+    """Workgroups that share a query tile: the shortest sweep of an XCD's 32 compute units (route_stream_group)."""
+    per_xcd, nct = -(-(-(-N // 256)) // 8), -(-K // 256)
+    sizes = [g for g in (4, 8, 2, 5, 3, 6, 7, 1, 10, 9, 16, 14, 32) if g <= nct]
+    return min(sizes, key=lambda g: -(-per_xcd // (32 // g)) * -(-nct // g))     # (the first among equals)
+
+
+@pytest.mark.parametrize("N,K,D,group", [(5003, 1700, 64, 7), (8192, 5000, 64, 8), (5003, 2000, 192, 8),
+                                         (5003, 2233, 64, 9), (5003, 2500, 128, 10), (42999, 3499, 64, 14),
+                                         (12001, 4001, 64, 16), (5003, 8001, 64, 32), (12300, 8190, 128, 32)])
+def test_bf16_router_streaming_kernel_large_groups(N, K, D, group):
+    # few query tiles: many workgroups share one, the last member's last centroid tile ragged
+    assert _group(N, K) == group
+    rin = _route_case(N, K, D, "bf16", True, seed=N + 5 * K + D)
+    print(f"[gpu] route bf16 stream, groups of {group}: N={N} K={K} D={D}", flush=True)
+    eids, cids, counts = moin.moin_route(gc.ctx(), rin.emb, rin.centroids, want_counts=True)
+    gc.ctx().check()
+    gc.check_route(rin.emb, rin.centroids, cids, sample=np.arange(0, N, 5))
     assert torch.equal(counts.long(), torch.bincount(cids.long(), minlength=K))
 
 
