@@ -377,6 +377,8 @@ __global__ __launch_bounds__(W == 1 ? 256 : 64 * W) void route_pick_kernel(PickK
     // have a screened score of at most M, hence a computed distance of at most (M + eps + ||q||^2) (1 + delta);
     // whatever is among the k nearest has one no larger, hence a screened score of at most
     // (M + eps + ||q||^2) (1 + delta) / (1 - delta) - ||q||^2 + eps.
+    // (eps is that of the longest centroid: one of a thousand times the others' length, or one that is no number, and
+    // every group stays a candidate.  1000 x 5000 x 384 in fp32 then takes 643 us instead of 37.)
     float thr = __builtin_inff();
     if (mins) {
         float m = __builtin_inff();
@@ -486,8 +488,14 @@ __global__ __launch_bounds__(W == 1 ? 256 : 64 * W) void route_pick_kernel(PickK
 // call, direct / screened: 300 x 500 x 384 (58 M) 14 / 29, 306 x 1421 x 256 (111 M) 20 / 30, 1000 x 500 x 384
 // (192 M) 27 / 27; 1000 x 5000 x 384 (1.9 G) 150 / 35.
 constexpr int64_t SCREEN_MIN_WORK = 150'000'000;
-// moin_route_topk: with this many centroids even a few queries gain, since eight waves then take more than
-// eight turns of 16 centroids, 3.6 us each (8 queries, 5000 centroids: 144 us / 37 us).
+// With fewer centroids the screen's tiles of 128 are half padding and three launches have little to save (moin_route, us
+// direct / screened: 262144 queries x 16 x 384 163 / 759, x 64 549 / 788, 2000 x 200 x 768 35 / 46); large batches would
+// gain from about 128 on (262144 x 128 x 384 1018 / 802, x 200 1495 / 831), small ones lose up to here (2000 x 255 x 768
+// 38 / 46).
+constexpr int SCREEN_MIN_K = 256;
+// moin_route_topk: with this many centroids even one query gains, since its eight waves then take more than eight
+// turns of 16 centroids, 3.6 us each (1 query, every distance / screened: 1030 x 384 28 / 23 in bf16, 29 / 31 in
+// fp32; 1500 x 768 48 / 30 and 56 / 48; 5000 x 768 144 / 34 and 163 / 55; 100000 x 384 1747 / 92 and 2055 / 144).
 constexpr int TOPK_SCREEN_MIN_K = 1024;
 // Queries screened at a time: at most this many, 64 MiB of group minima (which grow with K) and 128 MiB of planes
 // (which grow with D), but 128 at least.  The centroids' planes are a copy of the whole table.
@@ -502,7 +510,7 @@ bool route_screen_pays(int64_t N, int K, int D, bool topk)
 {
     if (N <= 0) return false;
     if (topk && K > TOPK_SCREEN_MIN_K) return true;
-    return K >= 256 && (double)N * K * D > (double)SCREEN_MIN_WORK;
+    return K >= SCREEN_MIN_K && (double)N * K * D > (double)SCREEN_MIN_WORK;
 }
 
 struct ScreenLayout {
