@@ -50,10 +50,12 @@ __device__ __forceinline__ bf16x8_t ldg_frag(const char *row, int k, int klen)
 // instead of a chain of three.  (Under load every dependent vector load costs a full
 // queueing delay of several microseconds.)  Reading through the constant address space
 // at a uniform address is what makes a load a scalar one.
+typedef int i32x2_t __attribute__((ext_vector_type(2)));
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 typedef int i32x16_t __attribute__((ext_vector_type(16), aligned(4)));
 #define MOIN_CONST_AS __attribute__((address_space(4)))
 __device__ __forceinline__ int sload_x1(const int *p) { return *(const MOIN_CONST_AS int *)(uintptr_t)p; }
+__device__ __forceinline__ i32x2_t sload_x2(const int *p) { return *(const MOIN_CONST_AS i32x2_t *)(uintptr_t)p; }
 __device__ __forceinline__ i32x4_t sload_x4(const int4 *p) { return *(const MOIN_CONST_AS i32x4_t *)(uintptr_t)p; }
 __device__ __forceinline__ i32x16_t sload_x16(const int *p) { return *(const MOIN_CONST_AS i32x16_t *)(uintptr_t)p; }
 // Element (lane % 16) of sixteen wave-uniform values.
@@ -275,8 +277,9 @@ __device__ __forceinline__ void shrink_stream(const MOIN_CONST_AS ShrinkStreamAr
     const int4 *grp_meta = args->sp.grp_meta;
     const int *tok_sorted = args->sp.tok_sorted;
     const char *x = args->sp.x;
-    const int g_first = sload_x1(args->sp.n_groups + 1);   // base-only records come first: nothing to do for them
-    const int n_items = n_w + (sload_x1(args->sp.n_groups) - g_first) * per_g;
+    const i32x2_t recs = sload_x2(args->sp.n_groups);
+    const int g_first = recs.y;   // base-only records come first: nothing to do for them
+    const int n_items = n_w + (recs.x - g_first) * per_g;
     const uint32_t ld = (uint32_t)d_in * 2u;
     const int n_batches = (int)((ld + NW * STREAM_COL - 1) / (NW * STREAM_COL));
     const uint32_t col = (uint32_t)wave * STREAM_COL;
@@ -430,9 +433,10 @@ template <int KS_HOLD>
 __global__ __launch_bounds__(SHRINK_WAVES * 64) void decode_shrink_kernel(ShrinkDParams p, int n_slabs)
 {
     __shared__ Partials red[2];
-    const int n_items = sload_x1(p.n_groups) * n_slabs;
+    const i32x2_t recs = sload_x2(p.n_groups);
+    const int n_items = recs.x * n_slabs;
     int flip = 0;
-    for (int it = sload_x1(p.n_groups + 1) * n_slabs + (int)blockIdx.x; it < n_items; it += (int)gridDim.x)
+    for (int it = recs.y * n_slabs + (int)blockIdx.x; it < n_items; it += (int)gridDim.x)
         decode_shrink_slab<SHRINK_BATCH, KS_HOLD>(p, it % n_slabs, it / n_slabs, red, flip);
 }
 
@@ -443,7 +447,7 @@ __global__ __launch_bounds__(SHRINK_WAVES * 64) void decode_shrink_kernel(Shrink
 // in the call (`m`) the base work of all of them comes first.
 static_assert(CfgDecodeBase::NT == SHRINK_WAVES * 64, "both roles share one workgroup size");
 static_assert(CfgDecodeBase::SMEM_BYTES <= STREAM_SMEM, "the tiles' stages in the stream's LDS");
-template <bool TILES>
+template <bool TILES, bool PACED>
 __global__ __launch_bounds__(SHRINK_WAVES * 64, 4) void decode_base_shrink_kernel(ShrinkStreamArgs by_value)
 {
     extern __shared__ __align__(16) char smem[];
@@ -459,7 +463,7 @@ __global__ __launch_bounds__(SHRINK_WAVES * 64, 4) void decode_base_shrink_kerne
             q.y = reinterpret_cast<char *>(args->m.ybase[i]);
             q.d_out = args->m.d_out[i];
             q.n_tiles_n = args->m.n_tiles_n[i];
-            linear_tile<CfgDecodeBase>(q, b - args->m.tile_first[i], smem);
+            linear_tile<CfgDecodeBase, PACED>(q, b - args->m.tile_first[i], smem);
             __syncthreads();   // (the tile's epilogue has left LDS)
         }
     }
@@ -675,79 +679,71 @@ struct ExpandStreamArgs {
 };
 
 // The base-only records (the first `n_rec`): y is the sum of the base product's parts.  Bound by memory; a wave takes 512
-// consecutive columns of one token, two such pieces at a time.  (1024 base-only tokens through 2048 -> 5632, two parts:
-// 10.2 us, 5.7 TB/s; as items like the others, 16 tokens by 32 rows of an adapter that is not there, 24.9.)
+// consecutive columns of one token, whole lines per instruction.  (1024 base-only tokens through 2048 -> 5632, two parts:
+// 10.5 us; as items like the others, 16 tokens by 32 rows of an adapter that is not there, 24.9.)
+constexpr int BASE_ONLY_COLS = 512;
 template <int NSPLIT, bool BY_POS, bool MIXED>
 __device__ __forceinline__ void write_base_only(const MOIN_CONST_AS ExpandStreamArgs *args, int n_rec, int wave_id, int n_waves)
 {
-    constexpr int COLS = 512, UNR = NSPLIT <= 2 ? 2 : 1;
+    constexpr int COLS = BASE_ONLY_COLS;
+    struct Proj {
+        const float *ybase;
+        char *y;
+        int d_out, splits;
+    };
     const int lane = threadIdx.x & 63, y_f32 = args->p.y_f32, n = args->m.n;
+    const int64_t T = args->p.T;
+    const int *tok_sorted = args->p.tok_sorted;
     const int n_pos = sload_x4(args->p.grp_meta + n_rec - 1).z;
-    int per_pos = 0;   // column blocks of all projections
-    for (int i = 0; i < n; ++i) per_pos += (args->m.d_out[i] + COLS - 1) / COLS;
+    const Proj only{args->p.ybase, args->p.y, args->p.d_out, NSPLIT};   // (most calls' one: its loads come all at once)
+    auto blocks = [](int d_out) __attribute__((always_inline)) { return (d_out + COLS - 1) / COLS; };
+    int per_pos = blocks(only.d_out);   // column blocks of all projections
+    for (int i = 1; i < n; ++i) per_pos += blocks(args->m.d_out[i]);
     const uint32_t total = (uint32_t)n_pos * (uint32_t)per_pos;
-    for (uint32_t u0 = wave_id; u0 < total; u0 += UNR * n_waves) {
-        f32x4_t part[UNR][NSPLIT][2];
-        char *dst[UNR];
-        int splits[UNR];
-#pragma unroll
-        for (int k = 0; k < UNR; ++k) {
-            const uint32_t u = min(u0 + k * n_waves, total - 1);
-            const int pos = (int)(u / (uint32_t)per_pos);
-            int c = (int)u - pos * per_pos, i = 0;
-            for (; i + 1 < n && c >= (args->m.d_out[i] + COLS - 1) / COLS; ++i) c -= (args->m.d_out[i] + COLS - 1) / COLS;
-            const int d_out = args->m.d_out[i], tok = sload_x1(args->p.tok_sorted + pos);
-            const int col = c * COLS + lane * 8;
-            const bool ok = col < d_out && u0 + k * n_waves < total;   // d_out % 8 == 0
-            const float *src = args->m.ybase[i] + (int64_t)(BY_POS ? pos : tok) * d_out + min(col, d_out - 8);
-            const int64_t plane = args->p.T * (int64_t)d_out;
-            splits[k] = MIXED ? args->m.k_splits[i] : NSPLIT;
-            dst[k] = ok ? args->m.y[i] + ((int64_t)tok * d_out + col) * (y_f32 ? 4 : 2) : nullptr;
-#pragma unroll
-            for (int sp = 0; sp < NSPLIT; ++sp)
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    part[k][sp][h] = *reinterpret_cast<const f32x4_t *>(src + (sp < splits[k] ? sp * plane : 0) + h * 4);
+    for (uint32_t u = wave_id; u < total; u += n_waves) {
+        const int pos = (int)(u / (uint32_t)per_pos);
+        const int tok = sload_x1(tok_sorted + pos);
+        int c = (int)u - pos * per_pos;
+        Proj q = only;
+        if (n > 1) {
+            int i = 0;
+            for (; i + 1 < n && c >= blocks(args->m.d_out[i]); ++i) c -= blocks(args->m.d_out[i]);
+            q = Proj{args->m.ybase[i], args->m.y[i], args->m.d_out[i], MIXED ? args->m.k_splits[i] : NSPLIT};
         }
+        const float *src = q.ybase + (int64_t)(BY_POS ? pos : tok) * q.d_out;
+        const int64_t plane = T * (int64_t)q.d_out;
+        f32x4_t part[NSPLIT][2];
 #pragma unroll
-        for (int k = 0; k < UNR; ++k) {
-            f32x4_t v[2];
+        for (int sp = 0; sp < NSPLIT; ++sp)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                v[h] = part[k][0][h];   // parts are added in order: repeatable
+            for (int h = 0; h < 2; ++h)
+                part[sp][h] = *reinterpret_cast<const f32x4_t *>(src + (sp < q.splits ? sp * plane : 0) +
+                                                                 min(c * COLS + h * (COLS / 2) + lane * 4, q.d_out - 4));
 #pragma unroll
-                for (int sp = 1; sp < NSPLIT; ++sp)
-                    if (sp < splits[k]) v[h] += part[k][sp][h];
-            }
-            if (!dst[k]) continue;
-            if (y_f32) {
-                *reinterpret_cast<f32x4_t *>(dst[k]) = v[0];
-                *reinterpret_cast<f32x4_t *>(dst[k] + 16) = v[1];
-            } else {
-                *reinterpret_cast<uint4 *>(dst[k]) = make_uint4(pack_bf16x2(v[0][0], v[0][1]), pack_bf16x2(v[0][2], v[0][3]),
-                                                                pack_bf16x2(v[1][0], v[1][1]), pack_bf16x2(v[1][2], v[1][3]));
-            }
+        for (int h = 0; h < 2; ++h) {
+            f32x4_t v = part[0][h];   // parts are added in order: repeatable
+#pragma unroll
+            for (int sp = 1; sp < NSPLIT; ++sp)
+                if (sp < q.splits) v += part[sp][h];
+            const int o = c * COLS + h * (COLS / 2) + lane * 4;
+            if (o < q.d_out) store_out(q.y, q.d_out, y_f32, tok, o, v);   // d_out % 4 == 0
         }
     }
 }
 
 template <int KS, int NSPLIT, bool BY_POS, int RB, bool MIXED>
-__global__ __launch_bounds__(EXPAND_WAVES * 64, expand_stream_wgs(KS, NSPLIT, RB)) void decode_expand_stream_kernel(ExpandStreamArgs)
+__device__ __forceinline__ void expand_stream(const MOIN_CONST_AS ExpandStreamArgs *args, char *smem, i32x2_t recs)
 {
     constexpr int CPR = 4 * KS;   // 16-byte chunks per row
-    extern __shared__ __align__(16) char smem[];
-    const MOIN_CONST_AS ExpandStreamArgs *args = kernel_args<ExpandStreamArgs>();
     const int lane_id = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6);
     char *const mine = smem + wave * expand_stage(KS, RB);
     const int n_xb = args->n_xb, r_stack = args->p.r, y_f32 = args->p.y_f32;
     const int4 *grp_meta = args->p.grp_meta;
     const int *tok_sorted = args->p.tok_sorted;
-    const int g_first = sload_x1(args->p.n_groups + 1);
-    const int n_items = (sload_x1(args->p.n_groups) - g_first) * n_xb;
+    const int g_first = recs.y, n_items = (recs.x - g_first) * n_xb;
     const int P = (int)gridDim.x * EXPAND_WAVES;
     const uint32_t ldb = (uint32_t)r_stack * 2u;
     const int64_t T = args->p.T;
-    if (g_first > 0) write_base_only<NSPLIT, BY_POS, MIXED>(args, g_first, (int)blockIdx.x * EXPAND_WAVES + wave, P);
 
     struct Item {
         const char *B;   // first of the rows
@@ -877,6 +873,21 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, expand_stream_wgs(KS, NSPLIT, RB
     }
 }
 
+template <int KS, int NSPLIT, bool BY_POS, int RB, bool MIXED>
+__global__ __launch_bounds__(EXPAND_WAVES * 64, expand_stream_wgs(KS, NSPLIT, RB)) void decode_expand_stream_kernel(ExpandStreamArgs)
+{
+    extern __shared__ __align__(16) char smem[];
+    const MOIN_CONST_AS ExpandStreamArgs *args = kernel_args<ExpandStreamArgs>();
+    const i32x2_t recs = sload_x2(args->p.n_groups);
+    if (recs.y > 0) {
+        // (the waves that find no item among the others' first)
+        const int P = (int)gridDim.x * EXPAND_WAVES, w = (int)blockIdx.x * EXPAND_WAVES + uniform((int)threadIdx.x >> 6);
+        const int busy = (recs.x - recs.y) * args->n_xb % P;
+        write_base_only<NSPLIT, BY_POS, MIXED>(args, recs.y, w >= busy ? w - busy : w - busy + P, P);
+    }
+    expand_stream<KS, NSPLIT, BY_POS, RB, MIXED>(args, smem, recs);
+}
+
 static ShrinkDParams shrink_params(const PlanView &pv, const DecodeArgs &d)
 {
     const LinearArgs &a = d.lin;
@@ -891,12 +902,15 @@ static ShrinkDParams shrink_params(const PlanView &pv, const DecodeArgs &d)
 static DecodeMore decode_more(const DecodeArgs *d, int n);
 
 constexpr int HELD_WGS = 16;            // workgroups per compute unit of the held kernels, at most: a few rounds each
-// From here on the adapters' stream keeps HBM busy for as long as the launch lasts, and tiles that ask for several blocks
-// at a time only hold it up (us of a call with one block in flight / three, 300 experts: q, k, v at rank 128 of 256
-// tokens 52.8 / 55.0, of 512 79.2 / 83.8; gate + up at rank 64 of 256 65.5 / 68.0; o at rank 64 of 1024 47.2 / 49.4).
-// With fewer tokens or shorter adapters the tiles' own chain of trips to memory is what the launch waits for (33
-// tokens, down, rank 16 31.5 / 25.2; 128, q, k, v, rank 64 36.5 / 34.2; 256, down, rank 16 39.1 / 33.8).
-constexpr int PACED_MIN_T = 256, PACED_MIN_R = 64;
+// Tiles keep one block in flight instead of three where the adapters' stream outlasts them (bytes of A_e, if every
+// sequence has its own expert): tiles that ask for more only hold it up.  Us of a call, one / three, 300 experts: 256
+// tokens, q, k, v at rank 128 (402 MB) 52.8 / 55.0, gate + up at rank 64 (134 MB) 65.5 / 68.0; 512 tokens, q, k, v at rank
+// 32 (118 MB) 38.6 / 40.2, rank 128 79.2 / 83.8.  With shorter adapters or fewer of them the launch waits for the tiles'
+// own chain of trips to memory (256 tokens, gate + up, rank 32, 67 MB, 60.0 / 56.2; down, rank 16, 46 MB, 39.1 / 33.8),
+// and so it does with fewer tokens, whose experts repeat less than the bound says (200 tokens, down, rank 64, 144 MB
+// 45.1 / 42.0; 33 tokens, rank 16 31.5 / 25.2).
+constexpr int PACED_MIN_T = 256;
+constexpr int64_t PACED_MIN_BYTES = 96 << 20;
 // Shrink items that a base tile of 32 blocks stands for (one step each; an item of b steps counts as (b + 1) / 2, its
 // steps overlap).  q, k, v and down of 256 single tokens: 46 and 49 us counting 1, 44 and 49 with 3, 39 and 41 with 6,
 // 40 and 43 with 8.
@@ -934,7 +948,7 @@ hipError_t launch_decode_shrink(const PlanView &pv, const DecodeArgs &d, hipStre
         hipLaunchKernelGGL(decode_shrink_kernel<24>, dim3(persistent_grid(HELD_WGS, items)), block, 0, stream, p, n_slabs);
     } else {
         const Turns turns{persistent_grid(2, items), 0, 1};
-        hipLaunchKernelGGL(decode_base_shrink_kernel<false>, dim3(turns.P), block, STREAM_SMEM, stream,
+        hipLaunchKernelGGL((decode_base_shrink_kernel<false, false>), dim3(turns.P), block, STREAM_SMEM, stream,
                            ShrinkStreamArgs{p, LinearKParams{}, decode_more(&d, 1), turns, 0, n_slabs});
     }
     return hipGetLastError();
@@ -955,8 +969,9 @@ static hipError_t allow_lds(K kern, int bytes)
 
 hipError_t prepare_decode_kernels()
 {
-    hipError_t e = allow_lds(&decode_base_shrink_kernel<true>, STREAM_SMEM);
-    if (e == hipSuccess) e = allow_lds(&decode_base_shrink_kernel<false>, STREAM_SMEM);
+    hipError_t e = allow_lds(&decode_base_shrink_kernel<true, false>, STREAM_SMEM);
+    if (e == hipSuccess) e = allow_lds(&decode_base_shrink_kernel<true, true>, STREAM_SMEM);
+    if (e == hipSuccess) e = allow_lds(&decode_base_shrink_kernel<false, false>, STREAM_SMEM);
     return e;
 }
 
@@ -1028,12 +1043,16 @@ hipError_t launch_decode_base_shrink_shared(const PlanView &pv, const DecodeArgs
     Turns turns{persistent_grid(2, n_tiles + items), (int)n_tiles, 1};
     if (n_tiles > 0) {
         const int batches = (a.d_in * 2 + SHRINK_WAVES * STREAM_COL - 1) / (SHRINK_WAVES * STREAM_COL);
-        lp.paced = pv.T >= PACED_MIN_T && a.r >= PACED_MIN_R;
+        const int64_t bytes = (int64_t)std::min(pv.S, pv.E) * a.r * n * a.d_in * 2;
         turns.c = std::max(1, DECODE_TILE_ITEMS * tile_blocks / (16 * (batches + 1)));
-        hipLaunchKernelGGL(decode_base_shrink_kernel<true>, dim3(turns.P), block, STREAM_SMEM, stream,
-                           ShrinkStreamArgs{sp, lp, m, turns, (int)n_w, n_slabs});
+        if (pv.T >= PACED_MIN_T && bytes > PACED_MIN_BYTES)
+            hipLaunchKernelGGL((decode_base_shrink_kernel<true, true>), dim3(turns.P), block, STREAM_SMEM, stream,
+                               ShrinkStreamArgs{sp, lp, m, turns, (int)n_w, n_slabs});
+        else
+            hipLaunchKernelGGL((decode_base_shrink_kernel<true, false>), dim3(turns.P), block, STREAM_SMEM, stream,
+                               ShrinkStreamArgs{sp, lp, m, turns, (int)n_w, n_slabs});
     } else {
-        hipLaunchKernelGGL(decode_base_shrink_kernel<false>, dim3(turns.P), block, STREAM_SMEM, stream,
+        hipLaunchKernelGGL((decode_base_shrink_kernel<false, false>), dim3(turns.P), block, STREAM_SMEM, stream,
                            ShrinkStreamArgs{sp, lp, m, turns, (int)n_w, n_slabs});
     }
     return hipGetLastError();
@@ -1067,14 +1086,17 @@ hipError_t launch_decode_expand_shared(const PlanView &pv, const DecodeArgs *d, 
     const int ks = nks <= 2 ? nks : 4, stream_rb = expand_stream_rb(ks, large);
     const int rows = streams ? stream_rb * 16 : EXPAND_WAVES * RB * 16;
     DecodeMore m = decode_more(d, n);
-    int64_t xb = 0;
+    int64_t xb = 0, base_only = 0;
     for (int i = 0; i < n; ++i) {
         m.xb_first[i] = (int)xb;
         xb += (d[i].lin.d_out + rows - 1) / rows;
+        base_only += pv.T * ((d[i].lin.d_out + BASE_ONLY_COLS - 1) / BASE_ONLY_COLS);
     }
     const int64_t items = xb * pv.max_groups;
     if (items > 0x3fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(streams ? persistent_grid(expand_stream_wgs(ks, k_splits, stream_rb), (items + EXPAND_WAVES - 1) / EXPAND_WAVES)
+    // (a wave per item, or per piece of a base-only token, as far as the chip holds them)
+    const int64_t stream_wgs = (std::max(items, base_only) + EXPAND_WAVES - 1) / EXPAND_WAVES;
+    const dim3 grid((unsigned)(streams ? persistent_grid(expand_stream_wgs(ks, k_splits, stream_rb), stream_wgs)
                                        : persistent_grid(HELD_WGS, items)));
     // parts that differ come from slabs (one) beside tiles of up to 64 blocks (two): decode_base_shape
     bool mixed = false;

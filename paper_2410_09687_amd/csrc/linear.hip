@@ -382,7 +382,6 @@ hipError_t launch_prefill_linear(const PlanView &pv, const LinearArgs &a, hipStr
     p.plain_tiles = 0;
     p.gather = nullptr;
     p.k_splits = 1; p.kb_per_split = 0;
-    p.paced = 0;
     return launch_linear_as<CfgMain>(p, pv.max_tiles, stream);
 }
 
@@ -455,7 +454,6 @@ LinearKParams decode_base_params(const PlanView &pv, const LinearArgs &a, void *
     p.plain_tiles = 1;
     p.gather = gather;
     p.k_splits = sh.k_splits; p.kb_per_split = sh.kb_per_split;
-    p.paced = 0;
     return p;
 }
 

@@ -20,12 +20,12 @@ struct LinearKParams {
                              // decode path's tokens in their by-expert order)
     int k_splits;            // plain tiles only: parts of the contraction range, one output plane each
     int kb_per_split;        // BK blocks per part
-    int paced;               // one block in flight: the tiles share the launch with a stream that memory bounds
 };
 
 // One output tile: `bid` is the workgroup's index in a grid of (tiles rounded
-// up to a multiple of 8) workgroups, `smem` its C::SMEM_BYTES of LDS.
-template <class C>
+// up to a multiple of 8) workgroups, `smem` its C::SMEM_BYTES of LDS.  PACED: one block in flight, for tiles that share
+// the launch with a stream that memory bounds.
+template <class C, bool PACED = false>
 __device__ __forceinline__ void linear_tile(const LinearKParams &p, int bid, char *smem)
 {
     int ntm, row0, rows, e;
@@ -121,7 +121,7 @@ __device__ __forceinline__ void linear_tile(const LinearKParams &p, int bid, cha
             else wait_vm_then_barrier<0>();
             const int nb = it + C::NS - 1;
             const int ns = (st == 0) ? C::NS - 1 : st - 1;
-            if (p.paced) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if constexpr (PACED) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (nb < total) MOIN_ISSUE_BLOCK(nb, smem + ns * C::STAGE_BYTES);
             C::compute_stage(smem + st * C::STAGE_BYTES, acc);
             st = (st + 1 == C::NS) ? 0 : st + 1;
