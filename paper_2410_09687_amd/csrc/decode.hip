@@ -251,12 +251,34 @@ struct ShrinkStreamArgs {
     LinearKParams lp;
     DecodeMore m;
     Turns turns;
-    int n_w, n_slabs;
+    int n_w, n_slabs, max_groups;
 };
 template <class A>
 __device__ __forceinline__ const MOIN_CONST_AS A *kernel_args()
 {
-    return (const MOIN_CONST_AS A *)__builtin_amdgcn_kernarg_segment_ptr();
+    const MOIN_CONST_AS int *words = (const MOIN_CONST_AS int *)__builtin_amdgcn_kernarg_segment_ptr();
+    // A word of each of its 64-byte lines, together: one trip to memory, and later reads of the block find their line in
+    // the scalar cache.
+    constexpr int LINES = (sizeof(A) + 63) / 64;
+    int v[LINES];
+#pragma unroll
+    for (int i = 0; i < LINES; ++i) v[i] = words[i * 16];
+#pragma unroll
+    for (int i = 0; i < LINES; ++i) asm volatile("" ::"s"(v[i]));
+    return (const MOIN_CONST_AS A *)words;
+}
+
+// Number of records, how many of them are base-only, and the first record that a workgroup (a wave, in the expand) will
+// want if none of them is: one trip to memory for both.
+struct FirstRecord {
+    i32x2_t recs;
+    i32x4_t meta;
+};
+__device__ __forceinline__ FirstRecord first_record(const int *n_groups, const int4 *grp_meta, int g)
+{
+    FirstRecord f{sload_x2(n_groups), sload_x4(grp_meta + g)};
+    asm volatile("" : "+s"(f.recs), "+s"(f.meta));
+    return f;
 }
 
 // The shrink as one stream of loads per workgroup, two workgroups per compute unit.  An item is 16 rows of A_e of one
@@ -277,9 +299,12 @@ __device__ __forceinline__ void shrink_stream(const MOIN_CONST_AS ShrinkStreamAr
     const int4 *grp_meta = args->sp.grp_meta;
     const int *tok_sorted = args->sp.tok_sorted;
     const char *x = args->sp.x;
-    const i32x2_t recs = sload_x2(args->sp.n_groups);
-    const int g_first = recs.y;   // base-only records come first: nothing to do for them
-    const int n_items = n_w + (recs.x - g_first) * per_g;
+    int turn = 0;
+    int it_next = turns.short_item(w, 0);
+    const FirstRecord fr =
+        first_record(args->sp.n_groups, grp_meta, min(max(it_next - n_w, 0) / per_g, args->max_groups - 1));
+    const int g_first = fr.recs.y;   // base-only records come first: nothing to do for them
+    const int n_items = n_w + (fr.recs.x - g_first) * per_g;
     const uint32_t ld = (uint32_t)d_in * 2u;
     const int n_batches = (int)((ld + NW * STREAM_COL - 1) / (NW * STREAM_COL));
     const uint32_t col = (uint32_t)wave * STREAM_COL;
@@ -291,13 +316,11 @@ __device__ __forceinline__ void shrink_stream(const MOIN_CONST_AS ShrinkStreamAr
         int batch;               // the step's piece of the rows
         int kept;                // the rows are in LDS already: only the tokens change
     };
-    int turn = 0;
-    int it_next = turns.short_item(w, 0);
     if (it_next >= n_items) return;
     auto meta_of = [&](int it) __attribute__((always_inline)) {
         return sload_x4(grp_meta + (it >= n_w && it < n_items ? g_first + (it - n_w) / per_g : 0));
     };
-    i32x4_t gm_next = meta_of(it_next);
+    i32x4_t gm_next = g_first == 0 ? fr.meta : meta_of(it_next);
     bool more = true;
     // The workgroup's next item.  Past the expert's rank there is nothing to read, nor without an adapter.
     auto advance = [&]() __attribute__((always_inline)) {
@@ -675,7 +698,7 @@ constexpr int expand_stage(int ks, int rb) { return rb * 16 * ks * 64; }
 struct ExpandStreamArgs {
     ExpandKParams p;
     DecodeMore m;
-    int n_xb;
+    int n_xb, max_groups;
 };
 
 // The base-only records (the first `n_rec`): y is the sum of the base product's parts.  Bound by memory; a wave takes 512
@@ -732,7 +755,7 @@ __device__ __forceinline__ void write_base_only(const MOIN_CONST_AS ExpandStream
 }
 
 template <int KS, int NSPLIT, bool BY_POS, int RB, bool MIXED>
-__device__ __forceinline__ void expand_stream(const MOIN_CONST_AS ExpandStreamArgs *args, char *smem, i32x2_t recs)
+__device__ __forceinline__ void expand_stream(const MOIN_CONST_AS ExpandStreamArgs *args, char *smem, const FirstRecord &fr)
 {
     constexpr int CPR = 4 * KS;   // 16-byte chunks per row
     const int lane_id = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6);
@@ -740,7 +763,7 @@ __device__ __forceinline__ void expand_stream(const MOIN_CONST_AS ExpandStreamAr
     const int n_xb = args->n_xb, r_stack = args->p.r, y_f32 = args->p.y_f32;
     const int4 *grp_meta = args->p.grp_meta;
     const int *tok_sorted = args->p.tok_sorted;
-    const int g_first = recs.y, n_items = (recs.x - g_first) * n_xb;
+    const int g_first = fr.recs.y, n_items = (fr.recs.x - g_first) * n_xb;
     const int P = (int)gridDim.x * EXPAND_WAVES;
     const uint32_t ldb = (uint32_t)r_stack * 2u;
     const int64_t T = args->p.T;
@@ -753,7 +776,7 @@ __device__ __forceinline__ void expand_stream(const MOIN_CONST_AS ExpandStreamAr
     int it_next = (int)blockIdx.x * EXPAND_WAVES + wave;
     if (it_next >= n_items) return;
     auto meta_of = [&](int it) __attribute__((always_inline)) { return sload_x4(grp_meta + (it < n_items ? g_first + it / n_xb : 0)); };
-    i32x4_t gm_next = meta_of(it_next);
+    i32x4_t gm_next = g_first == 0 ? fr.meta : meta_of(it_next);
     bool more = true;
     auto advance = [&]() __attribute__((always_inline)) {
         Item o;
@@ -878,14 +901,14 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, expand_stream_wgs(KS, NSPLIT, RB
 {
     extern __shared__ __align__(16) char smem[];
     const MOIN_CONST_AS ExpandStreamArgs *args = kernel_args<ExpandStreamArgs>();
-    const i32x2_t recs = sload_x2(args->p.n_groups);
-    if (recs.y > 0) {
+    const int P = (int)gridDim.x * EXPAND_WAVES, w = (int)blockIdx.x * EXPAND_WAVES + uniform((int)threadIdx.x >> 6);
+    const FirstRecord fr = first_record(args->p.n_groups, args->p.grp_meta, min(w / args->n_xb, args->max_groups - 1));
+    if (fr.recs.y > 0) {
         // (the waves that find no item among the others' first)
-        const int P = (int)gridDim.x * EXPAND_WAVES, w = (int)blockIdx.x * EXPAND_WAVES + uniform((int)threadIdx.x >> 6);
-        const int busy = (recs.x - recs.y) * args->n_xb % P;
-        write_base_only<NSPLIT, BY_POS, MIXED>(args, recs.y, w >= busy ? w - busy : w - busy + P, P);
+        const int busy = (fr.recs.x - fr.recs.y) * args->n_xb % P;
+        write_base_only<NSPLIT, BY_POS, MIXED>(args, fr.recs.y, w >= busy ? w - busy : w - busy + P, P);
     }
-    expand_stream<KS, NSPLIT, BY_POS, RB, MIXED>(args, smem, recs);
+    expand_stream<KS, NSPLIT, BY_POS, RB, MIXED>(args, smem, fr);
 }
 
 static ShrinkDParams shrink_params(const PlanView &pv, const DecodeArgs &d)
@@ -949,7 +972,7 @@ hipError_t launch_decode_shrink(const PlanView &pv, const DecodeArgs &d, hipStre
     } else {
         const Turns turns{persistent_grid(2, items), 0, 1};
         hipLaunchKernelGGL((decode_base_shrink_kernel<false, false>), dim3(turns.P), block, STREAM_SMEM, stream,
-                           ShrinkStreamArgs{p, LinearKParams{}, decode_more(&d, 1), turns, 0, n_slabs});
+                           ShrinkStreamArgs{p, LinearKParams{}, decode_more(&d, 1), turns, 0, n_slabs, pv.max_groups});
     }
     return hipGetLastError();
 }
@@ -1047,13 +1070,13 @@ hipError_t launch_decode_base_shrink_shared(const PlanView &pv, const DecodeArgs
         turns.c = std::max(1, DECODE_TILE_ITEMS * tile_blocks / (16 * (batches + 1)));
         if (pv.T >= PACED_MIN_T && bytes > PACED_MIN_BYTES)
             hipLaunchKernelGGL((decode_base_shrink_kernel<true, true>), dim3(turns.P), block, STREAM_SMEM, stream,
-                               ShrinkStreamArgs{sp, lp, m, turns, (int)n_w, n_slabs});
+                               ShrinkStreamArgs{sp, lp, m, turns, (int)n_w, n_slabs, pv.max_groups});
         else
             hipLaunchKernelGGL((decode_base_shrink_kernel<true, false>), dim3(turns.P), block, STREAM_SMEM, stream,
-                               ShrinkStreamArgs{sp, lp, m, turns, (int)n_w, n_slabs});
+                               ShrinkStreamArgs{sp, lp, m, turns, (int)n_w, n_slabs, pv.max_groups});
     } else {
         hipLaunchKernelGGL((decode_base_shrink_kernel<false, false>), dim3(turns.P), block, STREAM_SMEM, stream,
-                           ShrinkStreamArgs{sp, lp, m, turns, (int)n_w, n_slabs});
+                           ShrinkStreamArgs{sp, lp, m, turns, (int)n_w, n_slabs, pv.max_groups});
     }
     return hipGetLastError();
 }
@@ -1104,7 +1127,7 @@ hipError_t launch_decode_expand_shared(const PlanView &pv, const DecodeArgs *d, 
     if (mixed && !(k_splits == 2 && d[0].ybase_by_pos)) return hipErrorInvalidValue;
 #define MOIN_EXPAND_STREAM(KS, NS, BP, SRB, MIX)                                                                          \
     hipLaunchKernelGGL((decode_expand_stream_kernel<(KS > 0 ? KS : 1), NS, BP, SRB, MIX>), grid, dim3(EXPAND_WAVES * 64), \
-                       EXPAND_WAVES * expand_stage(KS, SRB), stream, ExpandStreamArgs{p, m, (int)xb})
+                       EXPAND_WAVES * expand_stage(KS, SRB), stream, ExpandStreamArgs{p, m, (int)xb, pv.max_groups})
 #define MOIN_EXPAND_HELD(KS, NS, BP, MIX)                                                                               \
     hipLaunchKernelGGL((decode_expand_kernel<KS, NS, BP, RB, MIX>), grid, dim3(EXPAND_WAVES * 64), 0, stream, p, m, (int)xb)
 #define MOIN_EXPAND_R(KS, NS, BP)                                                                                      \
