@@ -113,8 +113,9 @@ int moin_check(moin_ctx *ctx, void *stream);
  *   slot_of_centroid [K] int32 or NULL: adapter slot of each centroid, -1 = none
  *   flags            0, MOIN_ROUTE_RETAINED_ONLY (needs slot_of_centroid) and / or
  *                    MOIN_ROUTE_SAME_CENTROIDS (a serving loop routes every batch against
- *                    the same topic table; request-sized batches -- bf16, D a multiple of
- *                    64, N <= 4096 -- then take a single kernel launch)
+ *                    the same topic table; request-sized bf16 batches -- D a multiple of
+ *                    64, N <= 4096 -- then take a single kernel launch; fp32 ones -- N <=
+ *                    4096, up to 150 M products N K D -- always do)
  *   expert_ids       [N] int32 out or NULL: slot_of_centroid[centroid] (or the
  *                    centroid index itself when slot_of_centroid is NULL)
  *   centroid_ids     [N] int32 out or NULL: argmin centroid index
@@ -187,13 +188,14 @@ int moin_lora_linear_planned(moin_ctx *ctx, const moin_plan *plan, const void *x
  * each projection's main product runs as in moin_lora_linear_planned (in one launch
  * where all of them fit the streaming kernel); on the decode path the projections'
  * work shares the call's two launches (base products and first adapter products,
- * then second adapter products) where those whose base product is cut into tiles agree
- * in the number of its parts, else they run one after the other.  The results are, bit for bit, those of
- * n single calls.  W, A_stack, B_stack, y: host arrays
+ * then second adapter products) where those whose base product is cut into tiles
+ * agree in the number of its parts, else they run one after the other.  The results
+ * are, bit for bit, those of n single calls.  W, A_stack, B_stack, y: host arrays
  * of n device pointers (stacks [E, r, d_in] / [E, d_out[i], r]; A_stack and B_stack
  * may be NULL when there are no adapters), d_out: host array of n widths; r and
- * scale are common.  Needs 2 n T r bf16 of workspace.  Errors as
- * moin_lora_linear_planned; n outside 1..4: MOIN_EINVAL. */
+ * scale are common.  The prefill path needs 2 n T r bf16 of workspace, r rounded up
+ * to a multiple of 64 where d_in is one.  Errors as moin_lora_linear_planned; n
+ * outside 1..4: MOIN_EINVAL. */
 int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const void *x, int32_t n,
                                     const void *const *W, const void *const *A_stack,
                                     const void *const *B_stack, int32_t d_in, const int32_t *d_out,
@@ -203,8 +205,8 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
 /* moin_route followed by moin_plan_build_ranked on the ids it produced, for a batch
  * whose N queries ARE its S = N sequences (Section 1: each query goes to one expert;
  * Section 3.2: the expert's adapter then serves every linear layer of that query).
- * A request-sized batch (bf16, D a multiple of 64, N <= 512, K <= 65536) takes ONE
- * launch: the workgroup that finishes the routing groups the batch by the ids it has
+ * A request-sized batch (N <= 512, K <= 65536; bf16 with D a multiple of 64, or fp32
+ * with N K D up to 150 M) takes ONE launch: the workgroup that finishes the routing groups the batch by the ids it has
  * just written; any other batch takes the launches of the two calls.  Results are
  * those of the two calls.  Arguments as in moin_route and moin_plan_build_ranked;
  * expert_ids [N] is required (it is the plan's input and stays the caller's), the
@@ -479,8 +481,10 @@ int moin_set_adapter_activation(moin_ctx *ctx, int32_t activation);
  * NULL: centroid_ids, expert_ids (slot_of_centroid applied; -1 also where fewer
  * than k centroids took part), dist2 (fp32 squared distances, +inf where
  * unfilled).  Column 0 is moin_route's answer up to fp32 rounding of the
- * distances.  A request-time call (one wave per query, distances as plain sums of
- * squared differences), not the bulk router.  k outside 1..8: MOIN_EINVAL. */
+ * distances.  Distances are plain fp32 sums of squared differences; larger searches
+ * are screened by a bf16 product first, on copies in the workspace (without the
+ * memory for them: every distance is computed), with the same bits.  k outside 1..8:
+ * MOIN_EINVAL. */
 int moin_route_topk(moin_ctx *ctx, const void *emb, const void *centroids, int64_t N,
                     int32_t K, int32_t D, moin_dtype dt, const int32_t *slot_of_centroid,
                     uint32_t flags, int32_t k, int32_t *expert_ids, int32_t *centroid_ids,

@@ -234,9 +234,9 @@ __device__ __forceinline__ void km_unpack(const uint4 &v, float (&f)[VPC])
     }
 }
 
-// Bound by HBM: 262 144 rows of 768 bf16 (403 MB) against 5000 centres in 94 us, 4.3 TB/s, four times as
-// many in 279, 5.8.  (145 us with the point's
-// index and then its row fetched four rows at a time behind conditions, 110 with loads that displace the Infinity Cache.)
+// Bound by HBM: 262 144 rows of 768 bf16 (403 MB) against 5000 centres in 94 us, 4.3 TB/s, four times as many in 279, 5.8.
+// (145 us with the point's index and then its row fetched four rows at a time behind conditions, 110 with loads that
+// displace the Infinity Cache.)
 // One piece (at most KM_PIECE points of one centre) and one block of up to 256
 // 16-byte column chunks per workgroup.  With cw chunks in the block, 256 / cw
 // rows are in flight per pass ("phases"); every thread owns one chunk of one

@@ -11,6 +11,7 @@ error.  This test compiles the kernels to assembly (no GPU) and checks, in every
 The scan follows the listing top to bottom; it does not follow branches, so a copy at a loop's head is checked
 against the MFMAs listed above it, not against those at the loop's end.
 """
+import functools
 import os
 import re
 import subprocess
@@ -25,6 +26,7 @@ MIN_GAP_AFTER_WRITE = 3
 KERNELS = {"linear_stream.hip": "linear_stream_kernel", "route.hip": "route_stream4_kernel"}
 
 
+@functools.lru_cache(None)
 def _device_asm(src):
     with tempfile.TemporaryDirectory() as d:
         out = os.path.join(d, "k.s")
@@ -166,3 +168,13 @@ def test_the_base_tiles_of_small_batches_keep_blocks_in_flight(src, kernel):
             if "#ASMSTART" in l or "#ASMEND" in l:
                 in_asm = "#ASMSTART" in l
             assert in_asm or not re.search(r"s_waitcnt.*vmcnt\(0\)", l), f"{sym}: `{l.strip()}` drains the loads"
+
+
+def test_streaming_decode_kernels_do_not_spill():
+    # two register sets of loads in flight under a bound on the registers (workgroups per compute unit): a spill's
+    # reload would wait for all of them
+    bodies = _whole_bodies(_device_asm("decode.hip"), "decode_base_shrink_kernel") + \
+        _whole_bodies(_device_asm("decode.hip"), "decode_expand_stream_kernel")
+    assert len(bodies) >= 20
+    for sym, lines in bodies:
+        assert not any(re.search(r"\bscratch_(load|store)", l) for l in lines), f"{sym} spills to scratch"
