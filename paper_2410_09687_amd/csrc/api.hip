@@ -398,10 +398,10 @@ int linear_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, con
     }
 
     // Beyond the small-batch size the base product runs on plain row tiles in the
-    // prefill kernel (full 256-row tiles, no adapter), where its shapes allow.
+    // prefill kernels (256-row tiles, no adapter).
     LinearArgs ab = a;
     ab.r = 0;
-    const bool big = pv.max_plain > 0 && stream_kernel_fits(ab);
+    const bool big = pv.max_plain > 0;
     PlanView pp = pv;
     pp.tile_row0 = pv.plain_row0; pp.tile_rows = pv.plain_rows; pp.tile_expert = pv.plain_expert;
     pp.tile_rank = pv.plain_rank; pp.n_tiles = pv.plain_n; pp.max_tiles = pv.max_plain;

@@ -93,6 +93,10 @@ hipError_t launch_prefill_linear(const PlanView &pv, const LinearArgs &a, hipStr
 // streaming kernel (a[i]: W, B_stack, u_hi, u_lo, y, d_out of projection i); every a[i] must satisfy
 // stream_kernel_fits.  Results are those of n single launches, bit for bit.
 hipError_t launch_prefill_linear_shared(const PlanView &pv, const LinearArgs *a, int n, hipStream_t stream);
+// The 128 x 128 tiles of linear_mid.hip: whether they beat the larger ones for this call, and the call (a[0].ldu: columns
+// of u as stored, r or more).
+bool mid_kernel_pays(const PlanView &pv, const LinearArgs *a, int n, int n_cus);
+hipError_t launch_linear_mid(const PlanView &pv, const LinearArgs *a, int n, int n_cus, hipStream_t stream);
 // shapes the persistent streaming prefill kernel takes (anything else: the tiled kernel)
 bool stream_kernel_fits(const LinearArgs &a);
 // Row length of u on the prefill path: the streaming kernel reads it in blocks of 64 columns.

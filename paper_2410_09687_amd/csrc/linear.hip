@@ -367,6 +367,7 @@ hipError_t launch_prefill_linear(const PlanView &pv, const LinearArgs &a, hipStr
 {
     if (pv.max_tiles <= 0) return hipSuccess;
     if (stream_kernel_fits(a)) return launch_linear_stream(pv, a, compute_units(), stream);
+    if (mid_kernel_pays(pv, &a, 1, compute_units())) return launch_linear_mid(pv, &a, 1, compute_units(), stream);
     LinearKParams p;
     p.x = (const char *)a.x; p.W = (const char *)a.W; p.B_stack = (const char *)a.B_stack;
     p.u_hi = (const char *)a.u_hi; p.u_lo = (const char *)a.u_lo;

@@ -1,0 +1,313 @@
+// Prefill main kernel for calls of few tiles, and for contraction lengths that are not whole blocks (Section 3.2:
+// y = W x + W_b (W_a x), one adapter per sequence).
+//
+// The products of linear_stream.hip, k-step for k-step in the same order, so that its results are the same bits, on
+// 128 x 128 tiles: one per workgroup, four waves of 64 x 64 each, the hardware dealing the tiles out.
+//  * What bounds it: LDS.  A block of 64 contraction steps takes 512 cycles of the matrix cores, 768 of LDS at its peak
+//    (64 KB read by the waves, 32 KB written by the loads) and 600 of the path from L2 (55 bytes a cycle when an
+//    instruction takes 128 bytes of each row); measured 1000-1100.  A 256 x 256 tile moves half of that per product, so
+//    this kernel is for where too few of those tiles exist to fill the chip.
+//  * Up to a tile per compute unit: four stages, three blocks in flight; beyond, two workgroups share a unit, two stages
+//    each, and hide each other's waits, starts and epilogues.
+//  * Rows may end anywhere (d_in and r any multiple of 8): in a row's last block the lanes past its end fetch zeros.
+// Us of a call (its shrink of 14-29 us included), 256 x 256 tiles / these: 1890 tokens 2048 -> 2048 59 / 37, 5632 -> 2048
+// 132 / 81; 4096 tokens 2048 -> 2048 58 / 49; 16 384 tokens 2048 -> 256 57 / 37; 256 -> 256 20 / 15.
+#include <algorithm>
+#include <type_traits>
+
+#include "gemm_core.h"
+#include "kernels.h"
+#include "stream_epilogue.h"
+#include "stream_tile.h"
+
+namespace moin {
+
+namespace mid {
+
+using stream::BK;
+using stream::ROWB;
+constexpr int NW = 4, NT = NW * 64;
+
+constexpr int FP = 4, FQ = 4;          // 16 x 16 accumulators per wave: 64 outputs x 64 tokens
+constexpr int BT = 128;                // tile edge, both ways
+constexpr int SUB = TILE_M / BT;       // tiles per plan tile
+constexpr int P_BYTES = BT * ROWB, STAGE_BYTES = 2 * P_BYTES;
+constexpr int LOADS = FP + FQ;         // requests of a wave per block, 8 rows each
+constexpr int SCR_BYTES = 16 * FP * 16 * 4;   // epilogue scratch of a wave: 16 tokens x its outputs, fp32
+static_assert(NW * SCR_BYTES <= 2 * STAGE_BYTES, "the scratch takes the stages' place");
+
+// what the lanes past an operand row's end fetch
+__device__ __align__(16) const unsigned int zero16[4] = {0, 0, 0, 0};
+
+}  // namespace mid
+
+template <int NS, bool Y_F32, bool RAGGED>
+__global__ __launch_bounds__(mid::NT, NS == 2 ? 2 : 1) void linear_mid_kernel(stream::Params p)
+{
+    using namespace mid;
+    extern __shared__ __align__(16) char smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = uniform(threadIdx.x >> 6);
+    const int wp = wave >> 1, wq = wave & 1;
+
+    const int ntm = uniform(*p.n_tiles) * SUB;
+    const int id = xcd_band_id(blockIdx.x, ntm * p.n_tiles_n);
+    if (id < 0) return;
+    const int tm = p.by_columns ? id % ntm : id / p.n_tiles_n;
+    const int tn = p.by_columns ? id / ntm : id % p.n_tiles_n;
+    const stream::Tile t = stream::load_tile<BT, BT>(p, tm, tn);
+    if (t.q_rows <= 0) return;
+
+    const int nkb0 = (p.d_in + BK - 1) / BK;
+    const uint32_t ldx = (uint32_t)p.d_in * 2u, ldu = (uint32_t)p.ldu * 2u, ldb = (uint32_t)p.r * 2u;
+    // Requests: number n of a wave fills 8 rows of an operand tile (the outputs' first); the lane fetches logical chunk
+    // (lane % 8) ^ swz(row), swz(row) = (row >> 1) & 7.
+    const uint32_t c16a = (((uint32_t)lane & 7) ^ ((uint32_t)lane >> 4)) * 16, c16b = c16a ^ 64u;   // even, odd
+    uint32_t rowc[LOADS];
+#pragma unroll
+    for (int n = 0; n < LOADS; ++n) {
+        const bool q = n >= FP;
+        const uint32_t row = (uint32_t)((wave * FP + (n & (FP - 1))) * 8) + ((uint32_t)lane >> 3);
+        rowc[n] = min(row, (uint32_t)((q ? t.q_rows : t.p_rows) - 1));
+    }
+    struct Fetch {
+        const char *pp, *pq;
+        uint32_t ldp, ldq, endp, endq;   // pitches; bytes of a row that are left at the block's start
+    };
+    auto fetch_of = [&](int b) __attribute__((always_inline)) {
+        Fetch f;
+        const bool base = b < nkb0;
+        const int jb = b - nkb0;
+        const bool hi = jb < t.nkb1;
+        const int kb = base ? b : (hi ? jb : jb - t.nkb1);
+        f.pq = (base ? t.q0 : (hi ? t.uh : t.ul)) + kb * ROWB;
+        f.pp = (base ? t.p0 : t.be) + kb * ROWB;
+        f.ldq = base ? ldx : ldu;
+        f.ldp = base ? ldx : ldb;
+        f.endq = f.ldq - (uint32_t)kb * ROWB;
+        f.endp = f.ldp - (uint32_t)kb * ROWB;
+        return f;
+    };
+    auto issue_one = [&](const Fetch &f, char *stage, int n) __attribute__((always_inline)) {
+        const bool q = n >= FP;
+        const int j = n & (FP - 1);
+        const uint32_t c = (j & 1) ? c16b : c16a;
+        const char *src = (q ? f.pq : f.pp) + (__umul24(rowc[n], q ? f.ldq : f.ldp) + c);
+        if constexpr (RAGGED) src = c < (q ? f.endq : f.endp) ? src : reinterpret_cast<const char *>(zero16);
+        __builtin_amdgcn_global_load_lds(MOIN_GPTR(src), MOIN_LPTR(stage + (q ? P_BYTES : 0) + (wave * FP + j) * 1024), 16, 0, 0);
+    };
+
+    // Fragments and MFMAs as in linear_stream.hip: row lane%16 of a 16-row block, k-step 1 at k-step 0's address ^ 64.
+    const int lo0 = ((lane & 15) * ROWB) | ((((lane >> 4) ^ ((lane & 15) >> 1)) & 7) * 16);
+    const int lo1 = lo0 ^ 64;
+    const int baseP = wp * (FP * 16) * ROWB, baseQ = P_BYTES + wq * (FQ * 16) * ROWB;
+    bf16x8_t fr[2][FP + FQ];
+    auto read_one = [&](const char *stage, int lo_, int set, int n) __attribute__((always_inline)) {
+        const int base_ = n < FP ? baseP + n * 16 * ROWB : baseQ + (n - FP) * 16 * ROWB;
+        fr[set][n] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(stage + base_ + lo_));
+    };
+    auto frag_at = [](int k) { return k == 0 ? 0 : (k <= FQ ? FP + k - 1 : k - FQ); };
+    f32x4_t acc[FP][FQ];
+    auto mfma = [&](int set, int i, int j) __attribute__((always_inline)) {
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(fr[set][i]), "v"(fr[set][FP + j]));
+    };
+    auto mfma_first = [&](int i, int j) __attribute__((always_inline)) {
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc[i][j]) : "v"(fr[0][i]), "v"(fr[0][FP + j]));
+    };
+
+    const int total = t.total;
+    constexpr int M = FP * FQ, R = FP + FQ;
+    static_assert(M >= 2 * R, "a gap for every read and every request");
+    // One block: k-step 0 with the reads of k-step 1, the barrier, k-step 1 with the reads of the next block's k-step 0
+    // and (MORE) the requests of the block NS ahead into the stage that is now free.
+    auto body = [&](int b, char *st_cur, const char *st_nxt, auto first_tag, auto more_tag) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first_tag)::value, MORE = decltype(more_tag)::value;
+        Fetch f;
+        if constexpr (MORE) f = fetch_of(b + NS);
+#pragma unroll
+        for (int n = 0; n < M; ++n) {
+            if constexpr (FIRST) mfma_first(n / FQ, n % FQ);
+            else mfma(0, n / FQ, n % FQ);
+            if (n < R) {
+                read_one(st_cur, lo1, 1, frag_at(n));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (MORE) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 2) * LOADS) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+        for (int n = 0; n < M; ++n) {
+            mfma(1, n / FQ, n % FQ);
+            if (n % 2 == 0 && n / 2 < R) {
+                read_one(st_nxt, lo0, 0, frag_at(n / 2));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (MORE)
+                if (n % 2 == 1 && n / 2 < R) {
+                    issue_one(f, st_cur, n / 2);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const Fetch f = fetch_of(min(s, total - 1));
+#pragma unroll
+        for (int n = 0; n < LOADS; ++n) issue_one(f, smem + s * STAGE_BYTES, n);
+    }
+    wait_vm_then_barrier<(NS - 1) * LOADS>();
+#pragma unroll
+    for (int n = 0; n < R; ++n) read_one(smem, lo0, 0, n);
+    int st = 0;   // stage of block b
+    auto next_of = [](int s) { return s + 1 == NS ? 0 : s + 1; };
+    auto one = [&](int b, auto first_tag) __attribute__((always_inline)) {
+        const int nx = next_of(st);
+        char *cur = smem + st * STAGE_BYTES;
+        const char *nxt = smem + nx * STAGE_BYTES;
+        if (b + NS < total) body(b, cur, nxt, first_tag, std::true_type{});
+        else body(b, cur, nxt, first_tag, std::false_type{});   // (the last block reads stale bytes that nothing uses)
+        st = nx;
+    };
+    one(0, std::true_type{});
+    int b = 1;
+    for (; b + NS < total; ++b) {
+        const int nx = next_of(st);
+        body(b, smem + st * STAGE_BYTES, smem + nx * STAGE_BYTES, std::false_type{}, std::true_type{});
+        st = nx;
+    }
+    for (; b < total; ++b) {
+        const int nx = next_of(st);
+        body(b, smem + st * STAGE_BYTES, smem + nx * STAGE_BYTES, std::false_type{}, std::false_type{});
+        st = nx;
+    }
+    // Every wave has passed the last block's barrier with its fragments in registers and no request in flight, but the
+    // stale reads of the last half block may still be under way where another wave's scratch will lie.
+    asm volatile("s_nop 15\n\ts_nop 15\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+    // Epilogue: a lane holds, per accumulator (i, j), token 16 j + lane%16 and outputs 16 i + 4 (lane/16) + 0..3; blocks of
+    // 16 tokens are regrouped through the wave's scratch into whole lines of a token's row.
+    {
+        char *scr = smem + wave * SCR_BYTES;
+        const int t16 = lane & 15, kg = lane >> 4;
+        constexpr int EB = Y_F32 ? 4 : 2;
+        constexpr int SLOT = 4 * EB;                // four outputs
+        constexpr int ROW = FP * 16 * EB;           // a token's outputs
+        constexpr int SLOTS = FP * 4;
+        constexpr int CPR = ROW / 16;
+        constexpr int SPC = 16 / SLOT;
+        constexpr int NPS = 16 * CPR / 64;
+        constexpr int TPP = 64 / CPR;
+        const int tl = lane / CPR, ch = lane % CPR;
+        const int n = wp * (FP * 16) + ch * (16 / EB);
+        const bool n_ok = n < t.p_rows;             // d_out % 8 == 0: a chunk is all in or all out
+        const uint32_t ldy = (uint32_t)t.d_out * EB;
+        char *ybase = t.y + (int64_t)(t.row0 + wq * (FQ * 16)) * ldy + (int64_t)t.n0 * EB;
+        const uint32_t voff = (uint32_t)tl * ldy + (uint32_t)n * EB;
+        const int m_lane = wq * (FQ * 16) + tl;
+#pragma unroll
+        for (int j = 0; j < FQ; ++j) {
+#pragma unroll
+            for (int i = 0; i < FP; ++i) {
+                const int slot_ = (i * 4 + kg) ^ ((2 * t16) & (SLOTS - 1));
+                f32x4_t a;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(a[e]) : "a"(acc[i][j][e]));
+                if constexpr (Y_F32)
+                    *reinterpret_cast<f32x4_t *>(scr + t16 * ROW + slot_ * SLOT) = a;
+                else
+                    *reinterpret_cast<uint2 *>(scr + t16 * ROW + slot_ * SLOT) =
+                        make_uint2(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]));
+            }
+            lds_order();
+            auto rd = [&](int ps) {
+                const int tt = ps * TPP + tl;
+                return *reinterpret_cast<const uint4 *>(scr + tt * ROW + ((ch * SPC) ^ ((2 * tt) & (SLOTS - 1))) * SLOT);
+            };
+            auto st_ = [&](int ps, const uint4 &v) {
+                const int m = m_lane + j * 16 + ps * TPP;
+                if (n_ok && m < t.q_rows)
+                    *reinterpret_cast<uint4 *>(ybase + (uint32_t)(j * 16 + ps * TPP) * ldy + voff) = v;
+            };
+#pragma unroll
+            for (int ps = 0; ps < NPS; ps += 2) {
+                const uint4 v0 = rd(ps), v1 = rd(ps + 1);
+                st_(ps, v0), st_(ps + 1, v1);
+            }
+            lds_order();
+        }
+    }
+}
+
+template <int NS, bool Y_F32, bool RAGGED>
+static hipError_t allow_lds()
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_mid_kernel<NS, Y_F32, RAGGED>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, NS * mid::STAGE_BYTES);
+}
+template <int NS>
+static hipError_t allow_lds_all()
+{
+    hipError_t e = allow_lds<NS, false, false>();
+    if (e == hipSuccess) e = allow_lds<NS, true, false>();
+    if (e == hipSuccess) e = allow_lds<NS, false, true>();
+    if (e == hipSuccess) e = allow_lds<NS, true, true>();
+    return e;
+}
+
+hipError_t prepare_mid_kernels()
+{
+    const hipError_t e = allow_lds_all<2>();
+    return e == hipSuccess ? allow_lds_all<4>() : e;
+}
+
+// Tiles of a call, as far as the host knows: sequences of equal length.
+static int64_t mid_tiles(const PlanView &pv, const LinearArgs *a, int n)
+{
+    int64_t tn = 0;
+    for (int i = 0; i < n; ++i) tn += (a[i].d_out + mid::BT - 1) / mid::BT;
+    const int64_t S = std::max<int64_t>(1, std::min<int64_t>(pv.S, pv.max_tiles)), len = (pv.T + S - 1) / S;
+    return S * ((len + mid::BT - 1) / mid::BT) * tn;
+}
+
+// Up to the tiles that the chip holds at a time.  Us of a call, 256 x 256 tiles / these, 2048 -> 2048: 448 tiles 58 / 46,
+// 512 58 / 49, 576 59 / 68, 768 63 / 71 (one round of the larger tiles until 1024); beyond those' first round 1088 tiles
+// 103 / 97, 1280 106 / 100, but 1280 with 5632 outputs 106 / 113.  1000 -> 2048 against tiles that go through registers:
+// 256 tiles 50 / 30, 1024 59 / 62, 1416 -> 5632 at 11264 654 / 776.
+bool mid_kernel_pays(const PlanView &pv, const LinearArgs *a, int n, int n_cus)
+{
+    return mid_tiles(pv, a, n) <= 2 * (int64_t)n_cus;
+}
+
+template <int NS>
+static hipError_t launch_mid(const stream::Params &p, unsigned grid, hipStream_t stream_)
+{
+#define MOIN_MID(Y32, RAG) \
+    hipLaunchKernelGGL((linear_mid_kernel<NS, Y32, RAG>), dim3(grid), dim3(mid::NT), NS * mid::STAGE_BYTES, stream_, p)
+    const bool ragged = p.r % mid::BK != 0 || p.d_in % mid::BK != 0;
+    if (p.y_f32 && ragged) MOIN_MID(true, true);
+    else if (p.y_f32) MOIN_MID(true, false);
+    else if (ragged) MOIN_MID(false, true);
+    else MOIN_MID(false, false);
+#undef MOIN_MID
+    return hipGetLastError();
+}
+
+hipError_t launch_linear_mid(const PlanView &pv, const LinearArgs *a, int n, int n_cus, hipStream_t stream_)
+{
+    if (n < 1 || n > MAX_SHARED_X) return hipErrorInvalidValue;
+    stream::Params p;
+    const int tn = stream::fill_params(&p, pv, a, n, mid::BT);
+    // the larger operand's rows are dealt out over the XCDs, the smaller one is read by all of them
+    p.by_columns = (int64_t)tn * mid::BT > pv.T;
+    const int64_t work = (int64_t)pv.max_tiles * mid::SUB * tn;
+    if (work > 0x7ffffff0LL) return hipErrorInvalidValue;
+    const unsigned grid = (unsigned)((work + 7) / 8 * 8);
+    // (2000 tokens 2048 -> 2048, 256 tiles: 53 us with two stages, 48 with four; 384 tiles 44 and 50)
+    if (mid_tiles(pv, a, n) <= n_cus) return launch_mid<4>(p, grid, stream_);
+    return launch_mid<2>(p, grid, stream_);
+}
+
+}  // namespace moin

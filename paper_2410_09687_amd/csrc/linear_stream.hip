@@ -25,83 +25,25 @@
 #include "gemm_core.h"
 #include "kernels.h"
 #include "stream_epilogue.h"
+#include "stream_tile.h"
 
 namespace moin {
 
 namespace stream {
 
 constexpr int BT = 256;              // tile edge, both ways
-constexpr int BK = 64;
-constexpr int ROWB = BK * 2;         // LDS row pitch
 constexpr int OP_BYTES = BT * ROWB;  // one operand tile: 32 KB
 constexpr int STAGE_BYTES = 2 * OP_BYTES;
 constexpr int SMEM_STAGES = 2 * STAGE_BYTES;
 
-// Up to MAX_SHARED_X projections that read the same x (q, k, v; gate, up) in one launch: the column
-// tiles of projection i follow those of projection i - 1, so a narrow projection's tiles (k, v: one
-// column of tiles) ride in the wide one's stream and share its x panels in L2.
-struct Params {
-    const char *x;
-    const char *W[MAX_SHARED_X], *B_stack[MAX_SHARED_X], *u_hi[MAX_SHARED_X], *u_lo[MAX_SHARED_X];
-    char *y[MAX_SHARED_X];
-    int d_out[MAX_SHARED_X];
-    int tn_start[MAX_SHARED_X];   // first column tile of each projection (tn_start[0] = 0)
-    int n_proj;
-    const int *tile_row0, *tile_rows, *tile_expert, *tile_rank, *n_tiles;
-    int d_in, r, ldu;             // (ldu: columns of u as stored)
-    int n_tiles_n;                // column tiles of all projections together
-    int y_f32;
-};
-
-// Everything a tile needs, all wave-uniform.
-struct Tile {
-    const char *q0, *p0;       // x rows / W rows of the tile at k = 0
-    const char *uh, *ul, *be;  // adapter operands (aliases of q0 / p0 without adapter)
-    int q_rows, p_rows;        // valid tokens / outputs (1..256)
-    int nkb1;                  // adapter blocks per half (0: no adapter)
-    int total;                 // blocks of the tile: nkb0 + 2 * nkb1
-    int row0, n0;
-    char *y;                   // the projection's output and its width
-    int d_out;
-    int valid;
-};
-
-__device__ __forceinline__ Tile load_tile(const Params &p, int id, int n_work)
+// Tile number id of a workgroup's list; past its end the first one, marked invalid.
+__device__ __forceinline__ Tile nth_tile(const Params &p, int id, int n_work)
 {
-    Tile t;
-    t.valid = id < n_work;
-    const int cid = t.valid ? id : 0;
-    const int tm = cid / p.n_tiles_n, tn = cid - tm * p.n_tiles_n;
-    const int e = uniform(p.tile_expert[tm]);
-    t.row0 = uniform(p.tile_row0[tm]);
-    t.q_rows = uniform(p.tile_rows[tm]);
-    // the projection of this column tile (picked by comparison, not by indexing: indexing the
-    // parameter arrays would put them in scratch)
-    const char *W = p.W[0], *B_stack = p.B_stack[0], *u_hi = p.u_hi[0], *u_lo = p.u_lo[0];
-    int tn0 = 0;
-    t.y = p.y[0];
-    t.d_out = p.d_out[0];
-#pragma unroll
-    for (int i = 1; i < MAX_SHARED_X; ++i)
-        if (i < p.n_proj && tn >= p.tn_start[i]) {
-            W = p.W[i]; B_stack = p.B_stack[i]; u_hi = p.u_hi[i]; u_lo = p.u_lo[i];
-            t.y = p.y[i];
-            t.d_out = p.d_out[i];
-            tn0 = p.tn_start[i];
-        }
-    t.n0 = (tn - tn0) * BT;
-    t.p_rows = min(BT, t.d_out - t.n0);
-    const int64_t ldx = (int64_t)p.d_in * 2, ldu = (int64_t)p.ldu * 2, ldb = (int64_t)p.r * 2;
-    t.q0 = p.x + (int64_t)t.row0 * ldx;
-    t.p0 = W + (int64_t)t.n0 * ldx;
-    // adapter blocks up to the expert's own rank (the shrink wrote zeros from there to the block end)
-    const int re = min(p.r, uniform(p.tile_rank[tm]));
-    const bool lora = e >= 0 && re > 0;
-    t.nkb1 = lora ? (re + BK - 1) / BK : 0;
-    t.total = p.d_in / BK + 2 * t.nkb1;
-    t.uh = lora ? u_hi + (int64_t)t.row0 * ldu : t.q0;
-    t.ul = lora ? u_lo + (int64_t)t.row0 * ldu : t.q0;
-    t.be = lora ? B_stack + ((int64_t)e * t.d_out + t.n0) * ldb : t.p0;
+    const bool valid = id < n_work;
+    const int cid = valid ? id : 0;
+    const int tm = cid / p.n_tiles_n;
+    Tile t = load_tile<BT, BT>(p, tm, cid - tm * p.n_tiles_n);
+    t.valid = valid;
     return t;
 }
 
@@ -232,9 +174,9 @@ __global__ __launch_bounds__(s16::NT) void linear_stream_kernel(stream::Params p
         asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc[i][j]) : "v"(fr[0][i]), "v"(fr[0][FP + j]));
     };
 
-    Tile cur = stream::load_tile(p, id, band_end);
+    Tile cur = stream::nth_tile(p, id, band_end);
     id += nslot;
-    Tile nxt = stream::load_tile(p, id, band_end);
+    Tile nxt = stream::nth_tile(p, id, band_end);
     Tile pft = cur;
     int pfb = 2;
     rows_of(cur);
@@ -390,7 +332,7 @@ __global__ __launch_bounds__(s16::NT) void linear_stream_kernel(stream::Params p
         if (!nxt.valid) break;
         cur = nxt;
         id += nslot;
-        nxt = stream::load_tile(p, id, band_end);
+        nxt = stream::nth_tile(p, id, band_end);
     }
 }
 
@@ -401,8 +343,11 @@ static hipError_t allow_lds()
                                hipFuncAttributeMaxDynamicSharedMemorySize, s16::SMEM_BYTES);
 }
 
+hipError_t prepare_mid_kernels();
+
 hipError_t prepare_stream_kernel()
 {
+    if (hipError_t m = prepare_mid_kernels()) return m;
     hipError_t e = allow_lds<false, false>();
     if (e == hipSuccess) e = allow_lds<true, false>();
     if (e == hipSuccess) e = allow_lds<false, true>();
@@ -417,30 +362,15 @@ bool stream_kernel_fits(const LinearArgs &a)
 
 int prefill_ldu(const LinearArgs &a) { return stream_kernel_fits(a) ? (a.r + 63) / 64 * 64 : a.r; }
 
+
 // n projections that share x, d_in, r and the output type (a[i]: W, B_stack, u_hi, u_lo, y, d_out of
 // projection i; a[0] also x, d_in, r, y_f32)
 hipError_t launch_linear_stream_shared(const PlanView &pv, const LinearArgs *a, int n, int n_cus, hipStream_t stream_)
 {
     if (n < 1 || n > MAX_SHARED_X) return hipErrorInvalidValue;
+    if (mid_kernel_pays(pv, a, n, n_cus)) return launch_linear_mid(pv, a, n, n_cus, stream_);
     stream::Params p;
-    p.x = (const char *)a[0].x;
-    p.n_proj = n;
-    int tn = 0;
-    for (int i = 0; i < MAX_SHARED_X; ++i) {
-        const LinearArgs &ai = a[i < n ? i : 0];
-        p.W[i] = (const char *)ai.W; p.B_stack[i] = (const char *)ai.B_stack;
-        p.u_hi[i] = (const char *)ai.u_hi; p.u_lo[i] = (const char *)ai.u_lo;
-        p.y[i] = (char *)ai.y;
-        p.d_out[i] = ai.d_out;
-        p.tn_start[i] = tn;
-        if (i < n) tn += (ai.d_out + stream::BT - 1) / stream::BT;
-    }
-    p.tile_row0 = pv.tile_row0; p.tile_rows = pv.tile_rows; p.tile_expert = pv.tile_expert;
-    p.tile_rank = pv.tile_rank;
-    p.n_tiles = pv.n_tiles;
-    p.d_in = a[0].d_in; p.r = a[0].r; p.ldu = a[0].ldu;
-    p.n_tiles_n = tn;
-    p.y_f32 = a[0].y_f32;
+    stream::fill_params(&p, pv, a, n, stream::BT);
     // one workgroup per compute unit (the LDS footprint allows no more), fewer
     // when the batch has fewer tiles than that; always a multiple of 8
     const int64_t max_work = (int64_t)pv.max_tiles * p.n_tiles_n;

@@ -23,7 +23,7 @@ from paper_2410_09687_amd import build as B
 
 MIN_GAP = 6          # instructions (4 cycles each at the least) between an MFMA of 4 passes and a read of its result
 MIN_GAP_AFTER_WRITE = 3
-KERNELS = {"linear_stream.hip": "linear_stream_kernel", "route.hip": "route_stream4_kernel"}
+KERNELS = {"linear_stream.hip": "linear_stream_kernel", "linear_mid.hip": "linear_mid_kernel", "route.hip": "route_stream4_kernel"}
 
 
 @functools.lru_cache(None)
