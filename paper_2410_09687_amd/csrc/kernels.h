@@ -81,6 +81,8 @@ struct LinearArgs {
 };
 
 hipError_t launch_prefill_shrink(const PlanView &pv, const LinearArgs &a, hipStream_t stream);
+// the same for a call on a quantised base, in the order of launch_prefill_shrink_quant's sums
+hipError_t launch_prefill_shrink_mx(const PlanView &pv, const LinearArgs &a, hipStream_t stream);
 // The shrinks of up to MAX_SHARED_X projections that read the same x (q, k, v; gate, up)
 // in one launch: the column tiles of projection i take A_stack[i] and write u_hi[i] /
 // u_lo[i] ([T, r] each), and x streams from HBM once for all of them.  a: x, d_in, r,

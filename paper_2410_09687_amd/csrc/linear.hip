@@ -76,6 +76,20 @@ __device__ __forceinline__ uint2 mx_quantize8(const uint4 &v, int &scale_byte)
     return make_uint2((uint32_t)lo, (uint32_t)hi);
 }
 
+// u for 8 consecutive columns, the first `left` of which exist (the others are zeros), as a bf16 pair.
+__device__ __forceinline__ void u_pair(const f32x4_t (&v)[2], int left, int act, float s, uint4 &hi, uint4 &lo)
+{
+    uint32_t h[8], l[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const float f = q < left ? adapter_act(v[q >> 2][q & 3], act) * s : 0.f;
+        h[q] = f32_to_bf16_bits(f);
+        l[q] = f32_to_bf16_bits(f - bf16_bits_to_f32(h[q]));
+    }
+    hi = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+    lo = make_uint4(l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16));
+}
+
 // QUANT (register-staged tile shapes with BK = 64, d_in a multiple of 128): the
 // pass over x also writes x in MXFP8 for the quantised-base layer, so that x
 // comes from HBM once for both.  The workgroups of the first column tile do it,
@@ -193,22 +207,164 @@ __global__ __launch_bounds__(C::NT) void shrink_kernel(ShrinkKParams p)
     const int act = p.act;
     C::epilogue(smem, acc, [&](int row, int col, float(&v)[8]) {
         if (row >= rows || col >= ncols_out) return;
-        uint32_t h[8], l[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const float f = (n0 + col + q < re) ? adapter_act(v[q], act) * s : 0.f;
-            h[q] = f32_to_bf16_bits(f);
-            l[q] = f32_to_bf16_bits(f - bf16_bits_to_f32(h[q]));
-        }
         uint4 oh, ol;
-        oh.x = h[0] | (h[1] << 16); oh.y = h[2] | (h[3] << 16);
-        oh.z = h[4] | (h[5] << 16); oh.w = h[6] | (h[7] << 16);
-        ol.x = l[0] | (l[1] << 16); ol.y = l[2] | (l[3] << 16);
-        ol.z = l[4] | (l[5] << 16); ol.w = l[6] | (l[7] << 16);
+        const f32x4_t v2[2] = {{v[0], v[1], v[2], v[3]}, {v[4], v[5], v[6], v[7]}};
+        u_pair(v2, re - n0 - col, act, s, oh, ol);
         const int64_t off = (int64_t)row * ldu + (int64_t)(n0 + col) * 2;
         *reinterpret_cast<uint4 *>(uh + off) = oh;
         *reinterpret_cast<uint4 *>(ul + off) = ol;
     });
+}
+
+// The shrink of a batch with few row tiles.  Bound by the chain of a tile's blocks, which a 64 x 64 tile of the kernel
+// above works off one by one, behind a barrier each, at 0.4 us (32 x 32 accumulators that wait for their own reads and
+// for themselves), on as many compute units as there are tiles.  Here a tile is 32 tokens by the whole rank (BN columns),
+// and its four waves take every fourth block each, through stages of their own, so that there is no barrier until
+// their sums meet in LDS.  (The waves' blocks lie side by side: 512 bytes of a row at a time.)
+// Us of the kernel, above / this: 1890 tokens by 2048 at rank 64 15.4 / 8.6, at rank 128 25 / 15, by 5632 at rank 64 31 / 14, at
+// rank 128 64 / 27; with codes as well, 1890 by 2048 at rank 64 32 / 17, 8192 by 5632 80 / 41.
+template <int BN_>
+struct SplitCfg {
+    static constexpr int NW = 4, NT = NW * 64, BM = 32, BN = BN_, BK = 64, ROWB = BK * 2;
+    static constexpr int A_I = BM / 8, B_I = BN / 8, LPB = A_I + B_I;       // requests per block, 8 rows each
+    static constexpr int A_BYTES = BM * ROWB, STAGE_BYTES = (BM + BN) * ROWB;
+    static constexpr int WAVE_BYTES = 160 * 1024 / NW, NS = WAVE_BYTES / STAGE_BYTES;   // 5, 3 or 2 stages
+    static constexpr int PITCH = BN + 4;                                    // of the waves' sums, in floats
+    static constexpr int SMEM_BYTES = NW * WAVE_BYTES;
+    static_assert(BM * PITCH * 4 <= WAVE_BYTES && (NS - 1) * LPB < 64, "");
+};
+
+// QUANT: as above, x in MXFP8 as well, from the blocks in LDS; also of tiles without an adapter.
+template <int BN, bool QUANT>
+__global__ __launch_bounds__(256) void shrink_split_kernel(ShrinkKParams p)
+{
+    using C = SplitCfg<BN>;
+    extern __shared__ __align__(16) char smem[];
+    constexpr int SUB = TILE_M / C::BM;
+    const int ntm = uniform(*p.n_tiles) * SUB;
+    const int id = xcd_band_id(blockIdx.x, ntm * p.n_tiles_n);
+    if (id < 0) return;
+    const int tm = uniform(id / p.n_tiles_n), proj = uniform(id % p.n_tiles_n);
+    const int t = tm / SUB, sub = tm % SUB;
+    const int e = uniform(p.tile_expert[t]);
+    const int rows = min(uniform(p.tile_rows[t]) - sub * C::BM, C::BM);
+    const int re = min(p.r, uniform(p.tile_rank[t]));
+    const bool shrink = e >= 0 && re > 0;
+    if (rows <= 0 || (!QUANT && !shrink)) return;
+    const int row0 = uniform(p.tile_row0[t]) + sub * C::BM;
+    const char *A_stack = p.A_stack;
+    char *u_hi = p.u_hi, *u_lo = p.u_lo;
+#pragma unroll
+    for (int i = 1; i < MAX_SHARED_X; ++i)
+        if (proj == i) {
+            A_stack = p.A_more[i - 1];
+            u_hi = p.uh_more[i - 1];
+            u_lo = p.ul_more[i - 1];
+        }
+    const int r_out = min(p.ldu, (re + 63) & ~63);   // columns of u to write, zeros from the rank on
+    const uint32_t ldx = (uint32_t)p.d_in * 2u;
+    const char *xa = p.x + (int64_t)row0 * ldx;
+    // (a walk for the quantiser alone puts x in A_e's place: valid addresses, unused products)
+    const char *ae = shrink ? A_stack + (int64_t)e * p.r * ldx : xa;
+    const int a_rows = shrink ? re : rows;
+    const int nkb = p.d_in / C::BK;
+    const int k_first = (int)(((uint32_t)(row0 - sub * C::BM) / (uint32_t)TILE_M * 5u) % (uint32_t)nkb);
+
+    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
+    char *const mine = smem + wave * C::WAVE_BYTES;
+    // as in DmaCore: 8 rows of 128 bytes a request, 16-byte chunks XORed with swz(row) = (row >> 1) & 7
+    const uint32_t c16a = (((uint32_t)lane & 7) ^ ((uint32_t)lane >> 4)) * 16, c16b = c16a ^ 64u;   // even, odd requests
+    uint32_t off[C::LPB];
+#pragma unroll
+    for (int j = 0; j < C::LPB; ++j) {
+        const bool a = j < C::A_I;
+        const int row = (a ? j : j - C::A_I) * 8 + (lane >> 3);
+        off[j] = (uint32_t)min(row, (a ? rows : a_rows) - 1) * ldx + ((j & 1) ? c16b : c16a);
+    }
+    const int nb = (nkb - wave + C::NW - 1) / C::NW;   // the wave's blocks
+    auto block_of = [&](int i) __attribute__((always_inline)) {
+        const int kb = k_first + wave + i * C::NW;
+        return kb >= nkb ? kb - nkb : kb;
+    };
+    auto issue = [&](int i) __attribute__((always_inline)) {
+        const int kb = block_of(i);
+        char *st = mine + (i % C::NS) * C::STAGE_BYTES;
+#pragma unroll
+        for (int j = 0; j < C::LPB; ++j)
+            __builtin_amdgcn_global_load_lds(MOIN_GPTR((j < C::A_I ? xa : ae) + (off[j] + (uint32_t)kb * C::ROWB)),
+                                             MOIN_LPTR(st + j * 1024), 16, 0, 0);
+    };
+    constexpr int FN = BN / 32;
+    f32x16_t acc[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[j][q] = 0.f;
+    const int r32 = lane & 31, h = lane >> 5, f = (r32 >> 1) & 7;
+#pragma unroll
+    for (int s = 0; s < C::NS; ++s)
+        if (s < nb) issue(s);
+    for (int i = 0; i < nb; ++i) {
+        if (i + C::NS <= nb) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((C::NS - 1) * C::LPB) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const char *st = mine + (i % C::NS) * C::STAGE_BYTES;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const int o = ((ks * 2 + h) ^ f) * 16;
+            const bf16x8_t a = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(st + r32 * C::ROWB + o));
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                const bf16x8_t b = __builtin_bit_cast(
+                    bf16x8_t, *reinterpret_cast<const uint4 *>(st + C::A_BYTES + (j * 32 + r32) * C::ROWB + o));
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[j], 0, 0, 0);
+            }
+        }
+        if constexpr (QUANT) {
+            const int k0 = block_of(i) * C::BK, c = lane & 7;
+#pragma unroll
+            for (int j = 0; j < C::A_I; ++j) {
+                const int row = j * 8 + (lane >> 3);
+                int E;
+                const uint2 codes = mx_quantize8(
+                    *reinterpret_cast<const uint4 *>(st + row * C::ROWB + ((c ^ ((row >> 1) & 7)) * 16)), E);
+                const uint32_t pair = (uint32_t)E | ((uint32_t)dpp_move<DPP_FROM_PLUS4>(E) << 8);
+                if (row < rows) {
+                    *reinterpret_cast<uint2 *>(p.xq + (int64_t)(row0 + row) * p.d_in + k0 + c * 8) = codes;
+                    if (c == 0)
+                        *reinterpret_cast<uint16_t *>(p.xs + ((int64_t)(k0 >> 7) * p.T + row0 + row) * 4 + ((k0 >> 5) & 3)) =
+                            (uint16_t)pair;
+                }
+            }
+        }
+        // (the stage's reads have returned: the products above took them)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (i + C::NS < nb) issue(i + C::NS);
+    }
+    if (!shrink) return;   // (the whole workgroup)
+    float *sum = reinterpret_cast<float *>(mine);
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) sum[mfma32_acc_row(q, lane) * C::PITCH + j * 32 + r32] = acc[j][q];
+    __syncthreads();
+    const int64_t ldu = (int64_t)p.ldu * 2;
+    constexpr int COLS = BN < 64 ? 64 : BN;   // (u goes to the end of a block of 64)
+    for (int i = threadIdx.x; i < C::BM * (COLS / 8); i += C::NT) {
+        const int row = i / (COLS / 8), col = i % (COLS / 8) * 8;
+        if (row >= rows || col >= r_out) continue;
+        f32x4_t v[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        if (col < BN)
+#pragma unroll
+            for (int w = 0; w < C::NW; ++w)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    v[q] += *reinterpret_cast<const f32x4_t *>(smem + w * C::WAVE_BYTES + (row * C::PITCH + col + q * 4) * 4);
+        uint4 hi, lo;
+        u_pair(v, re - col, p.act, p.scale, hi, lo);
+        const int64_t at = (int64_t)(row0 + row) * ldu + (int64_t)col * 2;
+        *reinterpret_cast<uint4 *>(u_hi + at) = hi;
+        *reinterpret_cast<uint4 *>(u_lo + at) = lo;
+    }
 }
 
 // Tile shapes.  The *Dma variants need the contraction length to be a multiple
@@ -245,6 +401,11 @@ hipError_t prepare_linear_kernels()
 {
     hipError_t e;
     if ((e = prepare_stream_kernel()) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_split_kernel<64, true>, SplitCfg<64>::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_split_kernel<128, true>, SplitCfg<128>::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_split_kernel<32, false>, SplitCfg<32>::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_split_kernel<64, false>, SplitCfg<64>::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_split_kernel<128, false>, SplitCfg<128>::SMEM_BYTES)) != hipSuccess) return e;
     if ((e = allow_lds(&linear_kernel<CfgMain>, CfgMain::SMEM_BYTES)) != hipSuccess) return e;
     if ((e = allow_lds(&linear_kernel<CfgThin>, CfgThin::SMEM_BYTES)) != hipSuccess) return e;
     if ((e = allow_lds(&linear_kernel<CfgDecodeBase>, CfgDecodeBase::SMEM_BYTES)) != hipSuccess) return e;
@@ -278,11 +439,10 @@ struct SharedX {
     void *const *u_hi, *const *u_lo;
 };
 
-template <class C, bool QUANT = false>
-static hipError_t launch_shrink_as(const PlanView &pv, const LinearArgs &a, hipStream_t stream, void *xq = nullptr,
-                                   void *xs = nullptr, const SharedX *shared = nullptr)
+// Column tiles of bn; returns the number of workgroups with row tiles of bm (negative: too many).
+static int64_t shrink_params(ShrinkKParams &p, const PlanView &pv, const LinearArgs &a, const SharedX *shared, void *xq,
+                             void *xs, int bm, int bn)
 {
-    ShrinkKParams p;
     p.xq = (char *)xq; p.xs = (char *)xs; p.T = pv.T;
     p.x = (const char *)a.x; p.A_stack = (const char *)a.A_stack;
     p.u_hi = (char *)a.u_hi; p.u_lo = (char *)a.u_lo;
@@ -290,7 +450,7 @@ static hipError_t launch_shrink_as(const PlanView &pv, const LinearArgs &a, hipS
     p.tile_rank = pv.tile_rank;
     p.n_tiles = pv.n_tiles;
     p.d_in = a.d_in; p.r = a.r; p.ldu = a.ldu; p.scale = a.scale; p.act = a.act;
-    p.tiles_per_proj = (a.r + C::BN - 1) / C::BN;
+    p.tiles_per_proj = (a.r + bn - 1) / bn;
     p.n_proj = shared ? shared->n : 1;
     for (int i = 1; i < MAX_SHARED_X; ++i) {
         const bool on = shared && i < shared->n;
@@ -304,11 +464,43 @@ static hipError_t launch_shrink_as(const PlanView &pv, const LinearArgs &a, hipS
         p.u_lo = (char *)shared->u_lo[0];
     }
     p.n_tiles_n = p.tiles_per_proj * p.n_proj;
-    const int64_t grid = (int64_t)pv.max_tiles * (TILE_M / C::BM) * p.n_tiles_n;
-    if (grid > 0x7ffffff0LL) return hipErrorInvalidValue;
+    const int64_t grid = (int64_t)pv.max_tiles * (TILE_M / bm) * p.n_tiles_n;
+    return grid > 0x7ffffff0LL ? -1 : grid;
+}
+
+template <class C, bool QUANT = false>
+static hipError_t launch_shrink_as(const PlanView &pv, const LinearArgs &a, hipStream_t stream, void *xq = nullptr,
+                                   void *xs = nullptr, const SharedX *shared = nullptr)
+{
+    ShrinkKParams p;
+    const int64_t grid = shrink_params(p, pv, a, shared, xq, xs, C::BM, C::BN);
+    if (grid < 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL((shrink_kernel<C, QUANT>), dim3((unsigned)round_up8((int)grid)), dim3(C::NT),
                        C::SMEM_BYTES, stream, p);
     return hipGetLastError();
+}
+
+template <int BN, bool QUANT = false>
+static hipError_t launch_shrink_split(const PlanView &pv, const LinearArgs &a, const SharedX *shared, hipStream_t stream,
+                                      void *xq = nullptr, void *xs = nullptr)
+{
+    using C = SplitCfg<BN>;
+    ShrinkKParams p;
+    const int64_t grid = shrink_params(p, pv, a, shared, xq, xs, C::BM, BN);
+    if (grid < 0 || p.tiles_per_proj != 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((shrink_split_kernel<BN, QUANT>), dim3((unsigned)round_up8((int)grid)), dim3(C::NT), C::SMEM_BYTES, stream, p);
+    return hipGetLastError();
+}
+
+// Whether the whole rank in tiles of 32 tokens, `tiles` of them at most (of sequences of equal length, as far as the host
+// knows), is the faster form.  The order in which u is summed differs between the forms, so the rule looks at the batch alone and not at
+// how many projections the call has: a shared call gives the bits of the single ones, and on a quantised base codes
+// made on the way give those of codes that were there.
+static bool shrink_split_pays(const PlanView &pv, const LinearArgs &a, int tiles)
+{
+    if (a.d_in % 64 || a.r > 128) return false;
+    const int64_t S = std::max<int64_t>(1, std::min<int64_t>(pv.S, pv.max_tiles)), len = (pv.T + S - 1) / S;
+    return S * ((len + 31) / 32) <= tiles;
 }
 
 // The prefill shrink and the MXFP8 quantisation of x in one pass over x (r >= 1,
@@ -318,23 +510,34 @@ hipError_t launch_prefill_shrink_quant(const PlanView &pv, const LinearArgs &a, 
 {
     if (pv.max_tiles <= 0) return hipSuccess;
     if (a.r <= 0 || a.d_in % 128) return hipErrorInvalidValue;
+    if (shrink_split_pays(pv, a, compute_units()))
+        return a.r <= 64 ? launch_shrink_split<64, true>(pv, a, nullptr, stream, xq, xs)
+                         : launch_shrink_split<128, true>(pv, a, nullptr, stream, xq, xs);
     if (a.r > 64 && a.r <= 128) return launch_shrink_as<CfgShrinkDeep, true>(pv, a, stream, xq, xs);
     return launch_shrink_as<CfgShrinkDeep64, true>(pv, a, stream, xq, xs);
 }
 
-static hipError_t launch_prefill_shrink_any(const PlanView &pv, const LinearArgs &a, const SharedX *shared,
+static hipError_t launch_prefill_shrink_any(const PlanView &pv, const LinearArgs &a, const SharedX *shared, int split_tiles,
                                             hipStream_t stream)
 {
     if (a.r <= 0 || pv.max_tiles <= 0) return hipSuccess;
+    if (shrink_split_pays(pv, a, split_tiles)) {
+        if (a.r <= 32) return launch_shrink_split<32>(pv, a, shared, stream);
+        if (a.r <= 64) return launch_shrink_split<64>(pv, a, shared, stream);
+        return launch_shrink_split<128>(pv, a, shared, stream);
+    }
     if (a.d_in % 64 == 0 && a.r > 64 && a.r <= 128)
         return launch_shrink_as<CfgShrinkR128>(pv, a, stream, nullptr, nullptr, shared);
     if (a.d_in % 64 == 0) return launch_shrink_as<CfgShrinkDma>(pv, a, stream, nullptr, nullptr, shared);
     return launch_shrink_as<CfgShrink>(pv, a, stream, nullptr, nullptr, shared);
 }
 
+// The split form where a call of any number of projections gains or loses nothing by it.  Us, tiles above / split, rank 64
+// and 128, by 2048: 4096 tokens, one projection 15.4 / 9.1 and 23 / 15, three 16 / 16.5 and 28 / 26; 5120 tokens, three
+// 16.5 / 17 and 29 / 27.5; 6144, three 18 / 23 and 29 / 37.
 hipError_t launch_prefill_shrink(const PlanView &pv, const LinearArgs &a, hipStream_t stream)
 {
-    return launch_prefill_shrink_any(pv, a, nullptr, stream);
+    return launch_prefill_shrink_any(pv, a, nullptr, compute_units() * 5 / 8, stream);
 }
 
 hipError_t launch_prefill_shrink_shared(const PlanView &pv, const LinearArgs &a, int n, const void *const *A_stack,
@@ -342,7 +545,14 @@ hipError_t launch_prefill_shrink_shared(const PlanView &pv, const LinearArgs &a,
 {
     if (n < 1 || n > MAX_SHARED_X) return hipErrorInvalidValue;
     const SharedX sh{n, A_stack, u_hi, u_lo};
-    return launch_prefill_shrink_any(pv, a, &sh, stream);
+    return launch_prefill_shrink_any(pv, a, &sh, compute_units() * 5 / 8, stream);
+}
+
+// On a quantised base every call is of one projection: a tile per compute unit.  (Us of a call, tiles above / split, 8192
+// tokens by 2048 at rank 64 42 / 37, with codes 58 / 45; 12 288 tokens 43 / 44 and 59 / 57.)
+hipError_t launch_prefill_shrink_mx(const PlanView &pv, const LinearArgs &a, hipStream_t stream)
+{
+    return launch_prefill_shrink_any(pv, a, nullptr, compute_units(), stream);
 }
 
 template <class C>
