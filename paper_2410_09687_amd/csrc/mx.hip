@@ -19,6 +19,7 @@
 // lanes with h = 0, of the second from those with h = 1.  Read as bf16 the same
 // two 16-byte pieces are the operands of two v_mfma_f32_32x32x16_bf16, so both
 // block kinds share one LDS read pattern.
+#include <algorithm>
 #include <type_traits>
 
 #include "gemm_core.h"
@@ -161,10 +162,12 @@ struct Tile {
     int valid;
 };
 
-template <bool MX>
+// E: the tile's edge; a plan tile is TILE_M / E of them along the tokens (the last may be empty: q_rows <= 0).
+template <bool MX, int E = BT>
 __device__ __forceinline__ Tile load_tile(const Params &p, int id, int n_work)
 {
     constexpr int EB = MX ? 1 : 2;   // bytes per base operand element
+    constexpr int SUB = TILE_M / E;
     Tile t;
     t.valid = id < n_work;
     const int cid = t.valid ? id : 0;
@@ -173,10 +176,10 @@ __device__ __forceinline__ Tile load_tile(const Params &p, int id, int n_work)
         const int per_part = p.tiles_m * p.n_tiles_n;
         const int part = cid / per_part, rem = cid - part * per_part;
         const int tm = rem / p.n_tiles_n, tn = rem - tm * p.n_tiles_n;
-        t.row0 = tm * BT;
-        t.q_rows = (int)min((int64_t)BT, p.T - t.row0);
-        t.n0 = tn * BT;
-        t.p_rows = min(BT, p.d_out - t.n0);
+        t.row0 = tm * E;
+        t.q_rows = (int)min((int64_t)E, p.T - t.row0);
+        t.n0 = tn * E;
+        t.p_rows = min(E, p.d_out - t.n0);
         t.kb0 = part * p.kb_per_split;
         t.y_off = (int64_t)part * p.plane_bytes;
         t.q0 = p.xq + (int64_t)t.row0 * ldq + (int64_t)t.kb0 * ROWB;
@@ -188,16 +191,17 @@ __device__ __forceinline__ Tile load_tile(const Params &p, int id, int n_work)
         return t;
     }
     const int tm = cid / p.n_tiles_n, tn = cid - tm * p.n_tiles_n;
-    const int e = uniform(p.tile_expert[tm]);
-    t.row0 = uniform(p.tile_row0[tm]);
-    t.q_rows = uniform(p.tile_rows[tm]);
-    t.n0 = tn * BT;
-    t.p_rows = min(BT, p.d_out - t.n0);
+    const int pt = tm / SUB, sub = tm % SUB;
+    const int e = uniform(p.tile_expert[pt]);
+    t.row0 = uniform(p.tile_row0[pt]) + sub * E;
+    t.q_rows = min(E, uniform(p.tile_rows[pt]) - sub * E);
+    t.n0 = tn * E;
+    t.p_rows = min(E, p.d_out - t.n0);
     t.kb0 = 0;
     t.y_off = 0;
     t.q0 = p.xq + (int64_t)t.row0 * ldq;
     t.p0 = p.Wq + (int64_t)t.n0 * ldq;
-    const int re = min(p.r, uniform(p.tile_rank[tm]));
+    const int re = min(p.r, uniform(p.tile_rank[pt]));
     const bool lora = e >= 0 && re > 0;
     t.nkb1 = lora ? (re + KB16 - 1) / KB16 : 0;
     t.total = p.d_in * EB / ROWB + 2 * t.nkb1;
@@ -497,16 +501,221 @@ __global__ __launch_bounds__(mxs::NT) void linear_stream4_kernel(mxs::Params p)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+// The same products, k-step for k-step in the same order, on 128 x 128 tiles, one per workgroup of four waves (2 x 2 accumulators
+// each), for calls whose 256 x 256 tiles do not fill the chip: the small batches and narrow projections of decode
+// and prefill.  LDS bounds it (see linear_mid.hip); two workgroups share a compute unit, two stages each (four stages and
+// the unit to itself: the same time where there is a tile per unit).
+// Us of a layer, seven projections, 256 x 256 tiles / these: decode of 1 token 167 / 144, 32 196 / 164, 130 245 / 203, 488 359 /
+// 315, 1000 463 / 424; prefill of 1890 tokens 349 / 298, of 4000 441 / 403.
+namespace mxm {
+using mxs::Frag;
+using mxs::NT;
+using mxs::NW;
+using mxs::Params;
+using mxs::ROWB;
+using mxs::SCR_BYTES;
+using mxs::Tile;
+constexpr int BT = 128, FP = 2, FQ = 2;
+constexpr int OP_BYTES = BT * ROWB;
+constexpr int LOADS = 4;                  // requests of a wave per operand per block, 8 rows each, and one of scale words
+constexpr int REQ = 2 * LOADS + 1;
+constexpr int SC_BYTES = 2 * BT * 4;      // scale words of a block: 128 output rows, then 128 tokens
+constexpr int NS = 2, STAGE_BYTES = 2 * OP_BYTES + SC_BYTES;   // 33 KB a stage
+}  // namespace mxm
+
+template <bool Y_F32>
+__global__ __launch_bounds__(mxm::NT, 2) void linear_mx_mid_kernel(mxs::Params p)
+{
+    using namespace mxm;
+    using mxs::i32x4_t;
+    extern __shared__ __align__(16) char smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = uniform(threadIdx.x >> 6);
+    const int wp = wave >> 1, wq = wave & 1;
+
+    const int n_work = p.plain ? p.tiles_m * p.n_tiles_n * p.k_splits : uniform(*p.n_tiles) * (TILE_M / BT) * p.n_tiles_n;
+    const int id = xcd_band_id(blockIdx.x, n_work);
+    if (id < 0) return;
+    const Tile t = mxs::load_tile<true, BT>(p, id, n_work);
+    const int q_rows = t.q_rows, p_rows = t.p_rows, row0 = t.row0, n0 = t.n0, kb0 = t.kb0, nkb1 = t.nkb1, total = t.total;
+    const char *const q0 = t.q0, *const p0 = t.p0, *const uh = t.uh, *const ul = t.ul, *const be = t.be;
+    char *const y = p.y + t.y_off;
+    if (q_rows <= 0) return;
+    const int nb = min(p.d_in / ROWB, total);   // blocks; of the base
+
+    const uint32_t ldq = (uint32_t)p.d_in, ldu = (uint32_t)p.r * 2u;
+    const uint32_t c16a = (((uint32_t)lane & 7) ^ ((uint32_t)lane >> 4)) * 16, c16b = c16a ^ 64u;   // even, odd requests
+    uint32_t rowc[2 * LOADS];
+#pragma unroll
+    for (int n = 0; n < 2 * LOADS; ++n)
+        rowc[n] = min((uint32_t)((wave * LOADS + (n & (LOADS - 1))) * 8) + ((uint32_t)lane >> 3),
+                      (uint32_t)((n >= LOADS ? q_rows : p_rows) - 1));
+    // scale words: waves 0 and 1 those of the outputs, 2 and 3 of the tokens
+    const bool sq = wave >= 2;
+    const uint32_t srow = min((uint32_t)((wave & 1) * 64 + lane), (uint32_t)((sq ? q_rows : p_rows) - 1)) * 4u;
+    const char *const xs = p.xs, *const Ws = p.Ws;
+    const int64_t sc_pitch = (sq ? p.T : (int64_t)p.d_out) * 4;
+    const char *const sc0 = (sq ? xs : Ws) + (sq ? row0 : n0) * 4 + kb0 * sc_pitch;
+    struct Fetch {
+        const char *pp, *pq, *ps;
+        uint32_t ld;
+    };
+    auto fetch_of = [=](int b) __attribute__((always_inline)) {
+        Fetch f;
+        const bool base = b < nb;
+        const int jb = b - nb;
+        const bool hi = jb < nkb1;
+        const int kb = base ? b : (hi ? jb : jb - nkb1);
+        f.pq = (base ? q0 : (hi ? uh : ul)) + kb * ROWB;
+        f.pp = (base ? p0 : be) + kb * ROWB;
+        f.ps = sc0 + (base ? b : 0) * sc_pitch;   // (an adapter block repeats the first one's: no branch)
+        f.ld = base ? ldq : ldu;
+        return f;
+    };
+    auto issue = [&](const Fetch &f, int st, int n) __attribute__((always_inline)) {
+        char *stage = smem + st * STAGE_BYTES;
+        if (n < 2 * LOADS) {
+            const bool q = n >= LOADS;
+            const uint32_t off = __umul24(rowc[n], f.ld) + ((n & 1) ? c16b : c16a);
+            __builtin_amdgcn_global_load_lds(MOIN_GPTR((q ? f.pq : f.pp) + off),
+                                             MOIN_LPTR(stage + (q ? OP_BYTES : 0) + (wave * LOADS + (n & (LOADS - 1))) * 1024), 16, 0, 0);
+        } else {
+            __builtin_amdgcn_global_load_lds(MOIN_GPTR(f.ps + srow), MOIN_LPTR(stage + 2 * OP_BYTES + wave * 256), 4, 0, 0);
+        }
+    };
+
+    // fragments and scales as in linear_stream4_kernel
+    const int lo_ = ((lane & 31) * ROWB) | ((((lane >> 5) ^ (lane >> 1)) & 7) * 16);
+    const int baseP = wp * (FP * 32) * ROWB, baseQ = OP_BYTES + wq * (FQ * 32) * ROWB;
+    Frag fr[2][FP + FQ];
+    auto read_frag = [&](int st, int ks, int n) __attribute__((always_inline)) {
+        const char *stage = smem + st * STAGE_BYTES;
+        const int row = (n < FP ? baseP + n * 32 * ROWB : baseQ + (n - FP) * 32 * ROWB) + lo_;
+        const i32x4_t lo = *reinterpret_cast<const i32x4_t *>(stage + (row ^ (ks * 64)));
+        const i32x4_t hi = *reinterpret_cast<const i32x4_t *>(stage + (row ^ (ks * 64 + 32)));
+        fr[ks][n] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+    uint32_t sc_raw[FP + FQ], sc[2];
+    auto read_scale = [&](int st, int n) __attribute__((always_inline)) {
+        const char *area = smem + st * STAGE_BYTES + 2 * OP_BYTES;
+        const int row = (n < FP ? wp * (FP * 32) + n * 32 : BT + wq * (FQ * 32) + (n - FP) * 32) + (lane & 31);
+        sc_raw[n] = *reinterpret_cast<const uint32_t *>(area + row * 4);
+    };
+    auto regroup = [&]() __attribute__((always_inline)) {
+        const uint32_t pick = 0x06040200u + (uint32_t)(lane >> 5) * 0x01010101u;
+#pragma unroll
+        for (int n = 0; n < 2; ++n) sc[n] = __builtin_amdgcn_perm(sc_raw[2 * n + 1], sc_raw[2 * n], pick);
+    };
+    f32x16_t acc[FP][FQ];
+#pragma unroll
+    for (int i = 0; i < FP; ++i)
+#pragma unroll
+        for (int j = 0; j < FQ; ++j)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+    auto lo16 = [](const Frag &g) __attribute__((always_inline)) {
+        return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(g, g, 0, 1, 2, 3));
+    };
+    auto hi16 = [](const Frag &g) __attribute__((always_inline)) {
+        return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(g, g, 4, 5, 6, 7));
+    };
+    auto products = [&](auto base_tag, auto ks_tag) __attribute__((always_inline)) {
+        constexpr int KS = decltype(ks_tag)::value;
+        if constexpr (decltype(base_tag)::value) {
+#define MOIN_MXM(I, J)                                                                                                \
+    acc[I][J] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fr[KS][I], fr[KS][FP + J], acc[I][J], 0, 0,             \
+                                                                I * 2 + KS, (int)sc[0], J * 2 + KS, (int)sc[1])
+            MOIN_MXM(0, 0); MOIN_MXM(0, 1); MOIN_MXM(1, 0); MOIN_MXM(1, 1);
+#undef MOIN_MXM
+        } else {
+#pragma unroll
+            for (int i = 0; i < FP; ++i)
+#pragma unroll
+                for (int j = 0; j < FQ; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo16(fr[KS][i]), lo16(fr[KS][FP + j]), acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < FP; ++i)
+#pragma unroll
+                for (int j = 0; j < FQ; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi16(fr[KS][i]), hi16(fr[KS][FP + j]), acc[i][j], 0, 0, 0);
+        }
+    };
+    using K0 = std::integral_constant<int, 0>;
+    using K1 = std::integral_constant<int, 1>;
+    int st = 0;   // stage of the present block
+    // One block: k-step 0 with the reads of k-step 1; the barrier, behind which the block's stage is free and the next one's
+    // full; k-step 1 with the requests of the block NS ahead and the reads of the next one's k-step 0 and scales.
+    auto body = [&](int b, auto base_tag) __attribute__((always_inline)) {
+        const int cur = st, nxt = st + 1 == NS ? 0 : st + 1;
+        st = nxt;
+#pragma unroll
+        for (int n = 0; n < FP + FQ; ++n) read_frag(cur, 1, n);
+        __builtin_amdgcn_sched_barrier(0);
+        products(base_tag, K0{});
+        const bool more = b + NS < total;
+        if (more) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 2) * REQ) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (more) {
+            const Fetch f = fetch_of(b + NS);
+#pragma unroll
+            for (int n = 0; n < REQ; ++n) issue(f, cur, n);
+        }
+        // (after the last block: stale bytes that nothing uses)
+#pragma unroll
+        for (int n = 0; n < FP + FQ; ++n) read_frag(nxt, 0, n);
+#pragma unroll
+        for (int n = 0; n < FP + FQ; ++n) read_scale(nxt, n);
+        __builtin_amdgcn_sched_barrier(0);
+        products(base_tag, K1{});
+        __builtin_amdgcn_sched_barrier(0);
+        regroup();
+    };
+
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const Fetch f = fetch_of(min(s, total - 1));
+#pragma unroll
+        for (int n = 0; n < REQ; ++n) issue(f, s, n);
+    }
+    wait_vm_then_barrier<(NS - 1) * REQ>();
+#pragma unroll
+    for (int n = 0; n < FP + FQ; ++n) read_frag(0, 0, n);
+#pragma unroll
+    for (int n = 0; n < FP + FQ; ++n) read_scale(0, n);
+    regroup();
+    int b = 0;
+    for (; b < nb; ++b) body(b, std::true_type{});
+    for (; b < total; ++b) body(b, std::false_type{});
+    // the stages become the waves' scratch: no request (waited for in the last blocks) and no stale read is under way
+    asm volatile("s_nop 15\n\ts_nop 15\n\ts_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    stream_epilogue_as<FP, FQ, Y_F32>(smem + wave * SCR_BYTES, acc, y, p.d_out, row0, n0, q_rows, p_rows, wp,
+                                      wq, lane);
+}
+
+template <bool Y_F32>
+static hipError_t allow_mid_lds()
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_mx_mid_kernel<Y_F32>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, mxm::NS * mxm::STAGE_BYTES);
+}
+
 hipError_t prepare_mx_kernels()
 {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_stream4_kernel<true, false>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, mxs::SMEM_BYTES);
     if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_stream4_kernel<true, true>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, mxs::SMEM_BYTES);
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_stream4_kernel<true, true>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, mxs::SMEM_BYTES);
+    if (e == hipSuccess) e = allow_mid_lds<false>();
+    if (e == hipSuccess) e = allow_mid_lds<true>();
+    return e;
 }
 
 bool mx_stream_kernel_fits(int d_in, int r) { return d_in % 128 == 0 && d_in >= 256 && r % 64 == 0; }
+
+// 128 x 128 tiles as long as the chip holds all of them at a time, as in linear_mid.hip.  (Beyond: a layer of 18 700 tokens,
+// q, k, v, o, gate, up, down 1200 us, with 128 x 128 tiles throughout 1397.)
+static bool mx_mid_pays(int64_t tiles, int n_cus) { return tiles <= 2 * (int64_t)n_cus; }
 
 // Parts of the contraction range for the plain (decode) base product: enough
 // workgroups to keep many loads in flight, at least two blocks per part, at most
@@ -516,6 +725,9 @@ void mx_plain_shape(int64_t T, int d_in, int d_out, int *k_splits, int *kb_per_s
     const int nkb = d_in / 128;
     const int64_t tiles = ((T + mxs::BT - 1) / mxs::BT) * ((d_out + mxs::BT - 1) / mxs::BT);
     int want = (int)((128 + tiles - 1) / (tiles > 0 ? tiles : 1));
+    // (128 x 128 tiles need a workgroup per compute unit: 512 instead of 256 lost up to 3 %)
+    const int64_t small = ((T + mxm::BT - 1) / mxm::BT) * ((d_out + mxm::BT - 1) / mxm::BT);
+    if (mx_mid_pays(small, compute_units())) want = (int)(compute_units() / std::max<int64_t>(small, 1));
     if (want > 4) want = 4;
     if (want < 1) want = 1;
     for (;; --want) {
@@ -549,6 +761,21 @@ hipError_t launch_linear_mx_stream(const PlanView &pv, const MxLinearArgs &a, in
     p.k_splits = a.plain_splits > 0 ? a.plain_splits : 1;
     p.kb_per_split = a.plain_kb_per_split;
     p.plane_bytes = (int64_t)pv.T * a.lin.d_out * (a.lin.y_f32 ? 4 : 2);
+    const int64_t cols = (a.lin.d_out + mxm::BT - 1) / mxm::BT;
+    const int64_t S = std::max<int64_t>(1, std::min<int64_t>(pv.S, pv.max_tiles)), len = p.plain ? pv.T : (pv.T + S - 1) / S;
+    const int64_t rows = (p.plain ? 1 : S) * ((len + mxm::BT - 1) / mxm::BT);   // (sequences of equal length, as far as the host knows)
+    if (mx_mid_pays(rows * cols, n_cus)) {
+        p.n_tiles_n = (int)cols;
+        p.tiles_m = (int)rows;
+        const int64_t work = (p.plain ? rows * p.k_splits : (int64_t)pv.max_tiles * (TILE_M / mxm::BT)) * cols;
+        if (work > 0x7ffffff0LL) return hipErrorInvalidValue;
+        const dim3 grid((unsigned)((work + 7) / 8 * 8));
+        if (p.y_f32)
+            hipLaunchKernelGGL((linear_mx_mid_kernel<true>), grid, dim3(mxm::NT), mxm::NS * mxm::STAGE_BYTES, stream_, p);
+        else
+            hipLaunchKernelGGL((linear_mx_mid_kernel<false>), grid, dim3(mxm::NT), mxm::NS * mxm::STAGE_BYTES, stream_, p);
+        return hipGetLastError();
+    }
     // one workgroup per compute unit (the LDS footprint allows no more), fewer
     // when the batch has fewer tiles than that; always a multiple of 8
     const int64_t max_work = p.plain ? (int64_t)p.tiles_m * p.n_tiles_n * p.k_splits
