@@ -97,3 +97,22 @@ def test_slot_map_retained_only_and_argument_errors():
         moin.moin_route_topk(gc.ctx(), emb, cent, 2, retained_only=True)
     e, c, d = moin.moin_route_topk(gc.ctx(), emb[:0], cent, 2)
     assert e.shape == (0, 2)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("k", [2, 8])
+def test_waves_per_query(dtype, k):
+    # a screened batch's queries have four waves each, two or one, by its size: the answers are the same bits
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    g = torch.Generator(device="cuda").manual_seed(k)
+    emb = torch.randn((8 * cu + 1, 256), device="cuda", generator=g).to(dtype)
+    cent = torch.randn((1500, 256), device="cuda", generator=g).to(dtype)
+    cent[700:740] = cent[100]   # ties
+    call = lambda n: moin.moin_route_topk(gc.ctx(), emb[:n].contiguous(), cent, k)
+    print(f"[gpu] route_topk waves per query k={k} {dtype}", flush=True)
+    want = call(8 * cu + 1)
+    for n in (8 * cu, 4 * cu + 1, 4 * cu, 100):
+        for a, b in zip(call(n), want):
+            assert torch.equal(a, b[:n])
+    gc.ctx().check()
+    _check(emb[:60].contiguous(), cent, k, what="four waves")
