@@ -534,10 +534,18 @@ static hipError_t launch_prefill_shrink_any(const PlanView &pv, const LinearArgs
 
 // The split form where a call of any number of projections gains or loses nothing by it.  Us, tiles above / split, rank 64
 // and 128, by 2048: 4096 tokens, one projection 15.4 / 9.1 and 23 / 15, three 16 / 16.5 and 28 / 26; 5120 tokens, three
-// 16.5 / 17 and 29 / 27.5; 6144, three 18 / 23 and 29 / 37.
+// 16.5 / 17 and 29 / 27.5; 6144, three 18 / 23 and 29 / 37.  Long rows, whose chains of blocks cost the tiles above the more,
+// a tile per compute unit (a call, by 5632, 8192 tokens: one projection 67 / 54 and 99 / 65, two 69 / 67 and 100 / 86; three, which
+// models have on their shorter rows, 73 / 81 and 101 / 107).
+constexpr int SPLIT_LONG_ROWS = 4096;
+static int split_tiles_of(int d_in)
+{
+    return d_in >= SPLIT_LONG_ROWS ? compute_units() : compute_units() * 5 / 8;
+}
+
 hipError_t launch_prefill_shrink(const PlanView &pv, const LinearArgs &a, hipStream_t stream)
 {
-    return launch_prefill_shrink_any(pv, a, nullptr, compute_units() * 5 / 8, stream);
+    return launch_prefill_shrink_any(pv, a, nullptr, split_tiles_of(a.d_in), stream);
 }
 
 hipError_t launch_prefill_shrink_shared(const PlanView &pv, const LinearArgs &a, int n, const void *const *A_stack,
@@ -545,7 +553,7 @@ hipError_t launch_prefill_shrink_shared(const PlanView &pv, const LinearArgs &a,
 {
     if (n < 1 || n > MAX_SHARED_X) return hipErrorInvalidValue;
     const SharedX sh{n, A_stack, u_hi, u_lo};
-    return launch_prefill_shrink_any(pv, a, &sh, compute_units() * 5 / 8, stream);
+    return launch_prefill_shrink_any(pv, a, &sh, split_tiles_of(a.d_in), stream);
 }
 
 // On a quantised base every call is of one projection: a tile per compute unit.  (Us of a call, tiles above / split, 8192
