@@ -99,7 +99,7 @@ hipError_t launch_prefill_linear_shared(const PlanView &pv, const LinearArgs *a,
 // of u as stored, r or more).
 bool mid_kernel_pays(const PlanView &pv, const LinearArgs *a, int n, int n_cus);
 hipError_t launch_linear_mid(const PlanView &pv, const LinearArgs *a, int n, int n_cus, hipStream_t stream);
-// shapes the persistent streaming prefill kernel takes (anything else: the tiled kernel)
+// shapes the persistent streaming prefill kernel takes (anything else: linear_mid.hip or the tiled kernel)
 bool stream_kernel_fits(const LinearArgs &a);
 // Row length of u on the prefill path: the streaming kernel reads it in blocks of 64 columns.
 int prefill_ldu(const LinearArgs &a);

@@ -368,9 +368,9 @@ __global__ __launch_bounds__(256) void shrink_split_kernel(ShrinkKParams p)
 }
 
 // Tile shapes.  The *Dma variants need the contraction length to be a multiple
-// of BK = 64; the register-staged ones take any multiple of 8.  CfgMain is the
-// prefill fallback for contraction lengths the streaming kernel (linear_stream.hip) does not
-// take.
+// of BK = 64; the register-staged ones take any multiple of 8.  CfgMain is for
+// contraction lengths the streaming kernel (linear_stream.hip) does not take, in calls of more tiles
+// than linear_mid.hip takes.
 using CfgMain = GemmCore<256, 256, 64, 4, 2>;        // 8 waves, wave patch 64 x 128
 using CfgShrink = GemmCore<64, 64, 64, 2, 2>;        // 4 waves, wave patch 32 x 32
 using CfgShrinkDma = DmaCore<64, 64, 64, 2, 2, 4>;
