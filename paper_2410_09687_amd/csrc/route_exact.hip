@@ -16,6 +16,7 @@
 //    the groups that can hold one of its k nearest centroids, by a bound on what the screening arithmetic
 //    can be wrong by.  The answer is that of the exhaustive search, bit for bit.
 #include <algorithm>
+#include <type_traits>
 
 #include "gemm_core.h"
 #include "kernels.h"
@@ -190,7 +191,7 @@ __global__ __launch_bounds__(256) void route_direct_kernel(RouteKParams p, int n
 
 struct ScreenKParams {
     const char *cent, *emb;    // rows as they came
-    char *cent_p, *emb_p;      // bf16 planes (fp32: high parts, then the remainders, of Dp values each;
+    char *cent_p, *emb_p;      // bf16 planes of Dp values (fp32: of every 32 values the high parts, then the remainders;
                                // bf16 with D % 64: the values padded with zeros), or the rows themselves
     float *cnorm, *qnorm;      // ||.||^2; cnorm [nct * 128], +inf for what takes no part in the search
     float *cmax;               // [nct] largest finite cnorm of a tile
@@ -252,8 +253,9 @@ __global__ __launch_bounds__(256) void route_prep_kernel(ScreenKParams p)
                 h[t] = pack_bf16x2(f[2 * t], f[2 * t + 1]);
                 l[t] = pack_bf16x2(f[2 * t] - bits_f32(h[t] << 16), f[2 * t + 1] - bits_f32(h[t] & 0xFFFF0000u));
             }
-            *reinterpret_cast<uint4 *>(dst + ch * 16) = make_uint4(h[0], h[1], h[2], h[3]);
-            *reinterpret_cast<uint4 *>(dst + (int64_t)p.Dp * 2 + ch * 16) = make_uint4(l[0], l[1], l[2], l[3]);
+            char *at = dst + (ch >> 2) * 128 + (ch & 3) * 16;
+            *reinterpret_cast<uint4 *>(at) = make_uint4(h[0], h[1], h[2], h[3]);
+            *reinterpret_cast<uint4 *>(at + 64) = make_uint4(l[0], l[1], l[2], l[3]);
         }
     }
 #pragma unroll
@@ -267,37 +269,70 @@ __global__ __launch_bounds__(256) void route_prep_kernel(ScreenKParams p)
 
 // Matrix product bound by its short contraction (6 to 12 blocks of 64 per tile) and, in the fp32 case, by three
 // times its flops; what leaves is 1/16 of the scores.  1000 x 5000 x 384, fp32: 8100 us for the exhaustive
-// search with one wave per query; 5 + 20 + 11 us for preparation, screening and exact distances.  The same with
-// 768 dimensions in bf16 and the four nearest: 1400 us against 5 + 16 + 26 us.
-// 128 centroids x 128 queries per workgroup, four waves of 64 x 64, two workgroups per compute unit.  fp32
-// planes: three passes over the contraction, high x high, high x remainder, remainder x high.
+// search with one wave per query; 6 + 18 + 11 us for preparation, screening and exact distances.  The same with
+// 768 dimensions in bf16 and the four nearest: 1400 us against 4 + 15 + 22 us.
+// 128 centroids x 128 queries per workgroup, four waves of 64 x 64, two workgroups per compute unit.
 using CfgScreen = DmaCore<128, 128, 64, 2, 2, 2>;
+
+// fp32: a block is the high parts of 32 values, then their remainders, and gives all three products (high x high, high x
+// remainder, remainder x high) from one load into LDS: two thirds of the blocks, barriers, bytes and LDS reads of three
+// passes.  Us of a call, three passes / this: 1000 x 5000 x 384 33.0 / 32.4, 16 000 queries 255 / 231, by 768 500 / 442,
+// 100 x 5000 x 768 43.7 / 36.8, 70 000 x 1000 x 96 207 / 199.
+struct CfgScreenPairs : CfgScreen {
+    __device__ static __forceinline__ void compute_stage(const char *stage, Acc &acc)
+    {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        const int wm = wave / WN, wn = wave % WN;
+        const int r = lane & 31, h = lane >> 5, f = swz(r);
+        __builtin_amdgcn_iglp_opt(1);   // (16 000 x 5000 x 384: without it 234 us instead of 228)
+        const char *pa = stage + (wm * WTM + r) * ROWB;
+        const char *pb = stage + A_BYTES + (wn * WTN + r) * ROWB;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            bf16x8_t a[2][FM], b[2][FN];   // high parts, remainders
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int o = ((q * 4 + ks * 2 + h) ^ f) * 16;
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+                    a[q][i] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(pa + i * 32 * ROWB + o));
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+                    b[q][j] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(pb + j * 32 * ROWB + o));
+            }
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+                        acc.v[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[q == 2][i], b[q == 1][j], acc.v[i][j], 0, 0, 0);
+        }
+    }
+};
 
 // by_cent: the tiles of one centroid tile are neighbours, so that an XCD reads an eighth of the centroids and every query,
 // where those are the fewer: 1000 x 5000 x 384 in fp32 a call 35 -> 32.5 us (16 000 queries that way: 254 -> 276).
+template <bool PAIRS>
 __global__ __launch_bounds__(CfgScreen::NT) void route_screen_kernel(ScreenKParams p, int nqt, int by_cent)
 {
-    using C = CfgScreen;
+    using C = std::conditional_t<PAIRS, CfgScreenPairs, CfgScreen>;
     extern __shared__ __align__(16) char smem[];
     const int id = xcd_band_id(blockIdx.x, nqt * p.nct);
     if (id < 0) return;
     const int qt = uniform(by_cent ? id % nqt : id / p.nct), ct = uniform(by_cent ? id / nqt : id % p.nct);
     const int64_t q0 = (int64_t)qt * C::BN;
     const int nq = (int)min((int64_t)C::BN, p.n - q0), nc = min(C::BM, p.K - ct * C::BM);
-    const int planes = p.planes == 2 ? 2 : 1;
-    const uint32_t half = (uint32_t)p.Dp * 2u, ld = half * planes;
+    const uint32_t ld = (uint32_t)p.Dp * (PAIRS ? 4u : 2u);
     const char *cb = p.cent_p + (int64_t)ct * C::BM * ld, *qb = p.emb_p + q0 * (int64_t)ld;
     const auto lc = C::template make_lanes<C::A_I>(nc);
     const auto lq = C::template make_lanes<C::B_I>(nq);
-    const int nkb = p.Dp / C::BK;
     typename C::Acc acc;
     C::zero(acc);
     auto issue = [=](int b, char *stage) __attribute__((always_inline)) {
-        const int pass = b >= 2 * nkb ? 2 : (b >= nkb ? 1 : 0);
-        const uint32_t kb = (uint32_t)(b - pass * nkb) * (C::BK * 2);
-        C::issue(stage, cb + (pass == 2 ? half : 0), ld, lc, qb + (pass == 1 ? half : 0), ld, lq, kb);
+        C::issue(stage, cb, ld, lc, qb, ld, lq, (uint32_t)b * C::ROWB);
     };
-    dma_pipelined_blocks<C>(smem, planes == 2 ? 3 * nkb : nkb, issue, acc, [](int) {});
+    dma_pipelined_blocks<C>(smem, (int)(ld / C::ROWB), issue, acc, [](int) {});
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave / C::WN, wn = wave % C::WN;
@@ -617,8 +652,13 @@ hipError_t launch_route_screened(const RouteArgs &a, int k, float *d2, int none_
         const int nqt = (int)((s.n + 127) / 128);
         const int64_t grid = ((int64_t)nqt * L.nct + 7) / 8 * 8;
         if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(route_screen_kernel, dim3((unsigned)grid), dim3(CfgScreen::NT), CfgScreen::SMEM_BYTES, stream,
-                           s, nqt, s.n < s.K ? 1 : 0);
+        const int by_cent = s.n < s.K ? 1 : 0;
+        if (L.planes == 2)
+            hipLaunchKernelGGL(route_screen_kernel<true>, dim3((unsigned)grid), dim3(CfgScreen::NT), CfgScreen::SMEM_BYTES, stream,
+                               s, nqt, by_cent);
+        else
+            hipLaunchKernelGGL(route_screen_kernel<false>, dim3((unsigned)grid), dim3(CfgScreen::NT), CfgScreen::SMEM_BYTES, stream,
+                               s, nqt, by_cent);
         if (a.is_bf16) launch_pick<true>(p, pick_waves(p.n, p.k), stream);
         else launch_pick<false>(p, pick_waves(p.n, p.k), stream);
         const hipError_t e = hipGetLastError();
@@ -663,7 +703,10 @@ hipError_t launch_route_topk(const RouteArgs &a, int k, float *d2, void *ws, hip
 
 hipError_t prepare_route_exact_kernels()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&route_screen_kernel),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&route_screen_kernel<false>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, CfgScreen::SMEM_BYTES);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(&route_screen_kernel<true>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, CfgScreen::SMEM_BYTES);
 }
 

@@ -59,6 +59,18 @@ def test_screened_fp32_router_equals_the_exhaustive_one(N, K, D, kind):
         gc.check_route(emb, cent, moin.moin_route(gc.ctx(), emb, cent)[1], sample=np.arange(0, N, 11))
 
 
+# the screen's blocks of 32 values and their remainders: one row's end on both sides of a block and of a padded pair
+@pytest.mark.parametrize("N,K,D", [(2100, 2201, 36), (1500, 1601, 64), (2600, 1001, 68), (2000, 801, 96), (2000, 801, 100)])
+def test_screened_blocks_of_high_parts_and_remainders(N, K, D):
+    emb, cent = _inputs(N, K, D, torch.float32, "near", N + K + D)
+    print(f"[gpu] screened fp32 router N={N} K={K} D={D}", flush=True)
+    got = moin.moin_route(gc.ctx(), emb, cent, want_counts=True)
+    ref = moin.moin_route(gc.ctx(), emb, cent, want_counts=True, static=True)   # every pair
+    gc.ctx().check()
+    for a, b in zip(got, ref):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("kind", ["plain", "offset", "near", "odd"])
 @pytest.mark.parametrize("dtype,D", [(torch.float32, 260), (torch.bfloat16, 264), (torch.bfloat16, 256)])
 def test_screened_topk_equals_the_exhaustive_one(dtype, D, kind):
