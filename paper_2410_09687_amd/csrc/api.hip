@@ -530,7 +530,7 @@ int linear_mx_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, 
     if (a.r > 0 && !pv.decode && timed(ctx, MOIN_K_SHRINK, stream, [&] {
             return fused_q ? launch_prefill_shrink_quant(pv, a, const_cast<void *>(m.xq),
                                                          const_cast<void *>(m.xs), stream)
-                           : launch_prefill_shrink_mx(pv, a, stream);
+                           : launch_prefill_shrink(pv, a, stream);
         }) != hipSuccess)
         return MOIN_EHIP;
     if (timed(ctx, MOIN_K_MX_LINEAR, stream, [&] {

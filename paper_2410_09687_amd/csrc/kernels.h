@@ -2,6 +2,7 @@
 // kernels.  Every function only enqueues work on `stream`; shapes have been
 // validated by the caller.
 #pragma once
+#include <algorithm>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -69,6 +70,13 @@ struct PlanView {
 hipError_t launch_plan(const PlanView &pv, const int *seq_offsets, const int *expert_ids,
                        const int *rank_of_expert, int *err_word, hipStream_t stream);
 
+// Tiles of `rows` tokens that a call's sequences make, as far as the host knows: taken to be of equal length.
+inline int64_t host_tiles(const PlanView &pv, int rows)
+{
+    const int64_t S = std::max<int64_t>(1, std::min<int64_t>(pv.S, pv.max_tiles)), len = (pv.T + S - 1) / S;
+    return S * ((len + rows - 1) / rows);
+}
+
 struct LinearArgs {
     const void *x, *W, *A_stack, *B_stack;
     void *u_hi, *u_lo;     // [T, ldu] bf16 scratch
@@ -81,8 +89,6 @@ struct LinearArgs {
 };
 
 hipError_t launch_prefill_shrink(const PlanView &pv, const LinearArgs &a, hipStream_t stream);
-// the same for a call on a quantised base, in the order of launch_prefill_shrink_quant's sums
-hipError_t launch_prefill_shrink_mx(const PlanView &pv, const LinearArgs &a, hipStream_t stream);
 // The shrinks of up to MAX_SHARED_X projections that read the same x (q, k, v; gate, up)
 // in one launch: the column tiles of projection i take A_stack[i] and write u_hi[i] /
 // u_lo[i] ([T, r] each), and x streams from HBM once for all of them.  a: x, d_in, r,

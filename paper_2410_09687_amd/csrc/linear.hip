@@ -12,6 +12,7 @@
 // may be cut into several parts, each writing its own fp32 partial result.
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "gemm_core.h"
 #include "kernels.h"
@@ -76,18 +77,18 @@ __device__ __forceinline__ uint2 mx_quantize8(const uint4 &v, int &scale_byte)
     return make_uint2((uint32_t)lo, (uint32_t)hi);
 }
 
-// u for 8 consecutive columns, the first `left` of which exist (the others are zeros), as a bf16 pair.
-__device__ __forceinline__ void u_pair(const f32x4_t (&v)[2], int left, int act, float s, uint4 &hi, uint4 &lo)
+// u for 4 consecutive columns, the first `left` of which exist (the others are zeros), as a bf16 pair.
+__device__ __forceinline__ void u_pair(const f32x4_t &v, int left, int act, float s, uint2 &hi, uint2 &lo)
 {
-    uint32_t h[8], l[8];
+    uint32_t h[4], l[4];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const float f = q < left ? adapter_act(v[q >> 2][q & 3], act) * s : 0.f;
+    for (int q = 0; q < 4; ++q) {
+        const float f = q < left ? adapter_act(v[q], act) * s : 0.f;
         h[q] = f32_to_bf16_bits(f);
         l[q] = f32_to_bf16_bits(f - bf16_bits_to_f32(h[q]));
     }
-    hi = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
-    lo = make_uint4(l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16));
+    hi = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+    lo = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
 }
 
 // QUANT (register-staged tile shapes with BK = 64, d_in a multiple of 128): the
@@ -144,8 +145,8 @@ __global__ __launch_bounds__(C::NT) void shrink_kernel(ShrinkKParams p)
     // (the sub-tiles of a tile, and the projections that share x, keep one phase so that they meet
     // in L2): 88 -> 70 us for a 65536 x 2048 pass at rank 128.  The phase comes from the tile's
     // position in the batch, not from its place in the by-expert order, and is the same in every
-    // variant of this kernel, so that a row's sum depends neither on how the experts are numbered
-    // nor on which variant ran.
+    // variant of this kernel and in shrink_wave_kernel, so that a row's sum depends neither on how the
+    // experts are numbered nor on which of them ran.
     const int k_first = (int)(((uint32_t)(row0 - sub * C::BM) / (uint32_t)TILE_M * 5u) % (uint32_t)nkb);
     auto block_of = [=](int it) __attribute__((always_inline)) {
         const int kb = it + k_first;
@@ -207,51 +208,120 @@ __global__ __launch_bounds__(C::NT) void shrink_kernel(ShrinkKParams p)
     const int act = p.act;
     C::epilogue(smem, acc, [&](int row, int col, float(&v)[8]) {
         if (row >= rows || col >= ncols_out) return;
-        uint4 oh, ol;
-        const f32x4_t v2[2] = {{v[0], v[1], v[2], v[3]}, {v[4], v[5], v[6], v[7]}};
-        u_pair(v2, re - n0 - col, act, s, oh, ol);
+        uint2 h0, l0, h1, l1;
+        u_pair(f32x4_t{v[0], v[1], v[2], v[3]}, re - n0 - col, act, s, h0, l0);
+        u_pair(f32x4_t{v[4], v[5], v[6], v[7]}, re - n0 - col - 4, act, s, h1, l1);
         const int64_t off = (int64_t)row * ldu + (int64_t)(n0 + col) * 2;
-        *reinterpret_cast<uint4 *>(uh + off) = oh;
-        *reinterpret_cast<uint4 *>(ul + off) = ol;
+        *reinterpret_cast<uint4 *>(uh + off) = make_uint4(h0.x, h0.y, h1.x, h1.y);
+        *reinterpret_cast<uint4 *>(ul + off) = make_uint4(l0.x, l0.y, l1.x, l1.y);
     });
 }
 
-// The shrink of a batch with few row tiles.  Bound by the chain of a tile's blocks, which a 64 x 64 tile of the kernel
-// above works off one by one, behind a barrier each, at 0.4 us (32 x 32 accumulators that wait for their own reads and
-// for themselves), on as many compute units as there are tiles.  Here a tile is 32 tokens by the whole rank (BN columns),
-// and its four waves take every fourth block each, through stages of their own, so that there is no barrier until
-// their sums meet in LDS.  (The waves' blocks lie side by side: 512 bytes of a row at a time.)
-// Us of the kernel, above / this: 1890 tokens by 2048 at rank 64 15.4 / 8.6, at rank 128 25 / 15, by 5632 at rank 64 31 / 14, at
-// rank 128 64 / 27; with codes as well, 1890 by 2048 at rank 64 32 / 17, 8192 by 5632 80 / 41.
-template <int BN_>
-struct SplitCfg {
-    static constexpr int NW = 4, NT = NW * 64, BM = 32, BN = BN_, BK = 64, ROWB = BK * 2;
-    static constexpr int A_I = BM / 8, B_I = BN / 8, LPB = A_I + B_I;       // requests per block, 8 rows each
-    static constexpr int A_BYTES = BM * ROWB, STAGE_BYTES = (BM + BN) * ROWB;
-    static constexpr int WAVE_BYTES = 160 * 1024 / NW, NS = WAVE_BYTES / STAGE_BYTES;   // 5, 3 or 2 stages
-    static constexpr int PITCH = BN + 4;                                    // of the waves' sums, in floats
-    static constexpr int SMEM_BYTES = NW * WAVE_BYTES;
-    static_assert(BM * PITCH * 4 <= WAVE_BYTES && (NS - 1) * LPB < 64, "");
+template <int... K, class F>
+__device__ __forceinline__ void unrolled(std::integer_sequence<int, K...>, F f)
+{
+    (f(std::integral_constant<int, K>{}), ...);
+}
+
+// x in MXFP8: blocks first, first + step, ... of `rows` (1 to 32) rows, counted from block k_first on, by one wave.  Two
+// blocks' loads are under way while one is worked on; 8 lanes hold a row's 64 values.
+__device__ __forceinline__ void quantise_rows(const ShrinkKParams &p, int row0, int rows, int k_first, int first, int step)
+{
+    constexpr int RG = 4, PF = 3;   // row groups of 8; blocks in registers
+    const int lane = threadIdx.x & 63, c = lane & 7, nkb = p.d_in / 64;
+    const int n = (nkb - first + step - 1) / step;
+    if (n <= 0) return;
+    auto block_of = [=](int i) __attribute__((always_inline)) {
+        const int kb = first + i * step + k_first;
+        return kb >= nkb ? kb - nkb : kb;
+    };
+    const char *xa = p.x + (int64_t)row0 * p.d_in * 2;
+    uint32_t off[RG];
+#pragma unroll
+    for (int j = 0; j < RG; ++j) off[j] = (uint32_t)min(j * 8 + (lane >> 3), rows - 1) * ((uint32_t)p.d_in * 2u) + (uint32_t)c * 16u;
+    uint4 v[PF][RG];
+    auto load = [&](int i, uint4(&g)[RG]) __attribute__((always_inline)) {
+        const uint32_t at = (uint32_t)block_of(min(i, n - 1)) * 128u;   // (past the end the last block once more: no branch)
+#pragma unroll
+        for (int j = 0; j < RG; ++j) g[j] = *reinterpret_cast<const uint4 *>(xa + (off[j] + at));
+    };
+    auto work = [&](int i, const uint4(&g)[RG]) __attribute__((always_inline)) {
+        const int k0 = block_of(i) * 64;
+#pragma unroll
+        for (int j = 0; j < RG; ++j) {
+            const int row = j * 8 + (lane >> 3);
+            int E;
+            const uint2 codes = mx_quantize8(g[j], E);
+            // the two scale bytes of a row's 64 values, into the row's first lane
+            const uint32_t pair = (uint32_t)E | ((uint32_t)dpp_move<DPP_FROM_PLUS4>(E) << 8);
+            if (row < rows) {
+                *reinterpret_cast<uint2 *>(p.xq + (int64_t)(row0 + row) * p.d_in + k0 + c * 8) = codes;
+                if (c == 0)
+                    *reinterpret_cast<uint16_t *>(p.xs + ((int64_t)(k0 >> 7) * p.T + row0 + row) * 4 + ((k0 >> 5) & 3)) = (uint16_t)pair;
+            }
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < PF; ++u) load(u, v[u]);
+    for (int i = 0; i < n; i += PF) {
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+            if (i + u < n) work(i + u, v[u]);
+            load(i + u + PF, v[u]);
+        }
+    }
+}
+
+// The shrink of a batch with few row tiles: the sums of the kernel above, product for product in the same order, so that
+// a sequence's u is the same bits in a batch of any size.  Bound by the chain of a tile's blocks of 64 steps, which the tiles
+// above work off at 0.35 us each, behind a barrier, on as many compute units as there are tiles.  Here a wave has
+// 32 tokens x 16 or 32 columns to itself, blocks that nobody else waits for, and the next block's fragments come to registers under
+// the products of the present one: 0.12 and 0.16 us a block, a wave's own stream of requests, reads and products.  (Six
+// stages of 6 KB or four of 8 KB: 32 columns with eight stages no faster and half as many to a unit.)
+// With codes as well (QW): waves of their own take x straight to registers, since a block's 32 x 64 values cost a wave 0.5 us.
+// Us of the kernel, tiles above / this: 1890 tokens by 2048 at rank 16 14.9 / 8.0, 64 15.0 / 7.8, 128 21 / 8.5, by 5632 at rank 64
+// 32 / 14.5, 128 60 / 17; three projections by 2048 at rank 64 15.9 / 11.6; with codes by 2048 at rank 64 30 / 9.3, by
+// 5632 at rank 128 95 / 22.
+template <int FN_>
+struct WaveCfg {
+    static constexpr int FM = 2, FN = FN_, BM = FM * 16, BN = FN * 16, BK = 64, ROWB = BK * 2;
+    static constexpr int A_I = BM / 8, B_I = BN / 8, LPB = A_I + B_I;   // requests per block, 8 rows each
+    static constexpr int STAGE_BYTES = (BM + BN) * ROWB;
+    static constexpr int NS = FN == 1 ? 6 : 4, SMEM_BYTES = NS * STAGE_BYTES;
+    static_assert((NS - 1) * LPB < 64 && NS % 2 == 0, "vmcnt field; registers by parity");
 };
 
-// QUANT: as above, x in MXFP8 as well, from the blocks in LDS; also of tiles without an adapter.
-template <int BN, bool QUANT>
-__global__ __launch_bounds__(256) void shrink_split_kernel(ShrinkKParams p)
+// QW: further waves of each workgroup, which write x in MXFP8, each its share of the row tile's blocks, also where there is no
+// adapter.
+template <int FN, int QW>
+__global__ __launch_bounds__(64 * (1 + QW)) void shrink_wave_kernel(ShrinkKParams p)
 {
-    using C = SplitCfg<BN>;
+    using C = WaveCfg<FN>;
     extern __shared__ __align__(16) char smem[];
     constexpr int SUB = TILE_M / C::BM;
     const int ntm = uniform(*p.n_tiles) * SUB;
     const int id = xcd_band_id(blockIdx.x, ntm * p.n_tiles_n);
     if (id < 0) return;
-    const int tm = uniform(id / p.n_tiles_n), proj = uniform(id % p.n_tiles_n);
+    const int tm = uniform(id / p.n_tiles_n), tn = uniform(id % p.n_tiles_n);
     const int t = tm / SUB, sub = tm % SUB;
-    const int e = uniform(p.tile_expert[t]);
     const int rows = min(uniform(p.tile_rows[t]) - sub * C::BM, C::BM);
-    const int re = min(p.r, uniform(p.tile_rank[t]));
-    const bool shrink = e >= 0 && re > 0;
-    if (rows <= 0 || (!QUANT && !shrink)) return;
+    if (rows <= 0) return;
     const int row0 = uniform(p.tile_row0[t]) + sub * C::BM;
+    const int nkb = p.d_in / C::BK;
+    const int k_first = (int)(((uint32_t)(row0 - sub * C::BM) / (uint32_t)TILE_M * 5u) % (uint32_t)nkb);
+    const int wave = uniform(threadIdx.x >> 6);
+    if (QW > 0 && wave > 0) {
+        quantise_rows(p, row0, rows, k_first, tn * QW + wave - 1, p.n_tiles_n * QW);
+        return;
+    }
+    const int e = uniform(p.tile_expert[t]);
+    const int re = e < 0 ? 0 : min(p.r, uniform(p.tile_rank[t]));
+    const int r_read = min(p.ldu, (re + 63) & ~63);   // columns of u that are read: zeros from the rank on
+    const int proj = tn / p.tiles_per_proj, tc = tn - proj * p.tiles_per_proj;
+    const int n0 = tc * C::BN;
+    // the columns to write: the wave's own, behind the last tile also what is left of a block of 64
+    const int n_end = tc + 1 == p.tiles_per_proj ? r_read : min(r_read, n0 + C::BN);
+    if (n0 >= n_end) return;
     const char *A_stack = p.A_stack;
     char *u_hi = p.u_hi, *u_lo = p.u_lo;
 #pragma unroll
@@ -261,109 +331,134 @@ __global__ __launch_bounds__(256) void shrink_split_kernel(ShrinkKParams p)
             u_hi = p.uh_more[i - 1];
             u_lo = p.ul_more[i - 1];
         }
-    const int r_out = min(p.ldu, (re + 63) & ~63);   // columns of u to write, zeros from the rank on
-    const uint32_t ldx = (uint32_t)p.d_in * 2u;
-    const char *xa = p.x + (int64_t)row0 * ldx;
-    // (a walk for the quantiser alone puts x in A_e's place: valid addresses, unused products)
-    const char *ae = shrink ? A_stack + (int64_t)e * p.r * ldx : xa;
-    const int a_rows = shrink ? re : rows;
-    const int nkb = p.d_in / C::BK;
-    const int k_first = (int)(((uint32_t)(row0 - sub * C::BM) / (uint32_t)TILE_M * 5u) % (uint32_t)nkb);
 
-    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
-    char *const mine = smem + wave * C::WAVE_BYTES;
-    // as in DmaCore: 8 rows of 128 bytes a request, 16-byte chunks XORed with swz(row) = (row >> 1) & 7
-    const uint32_t c16a = (((uint32_t)lane & 7) ^ ((uint32_t)lane >> 4)) * 16, c16b = c16a ^ 64u;   // even, odd requests
-    uint32_t off[C::LPB];
+    const int lane = threadIdx.x;
+    f32x4_t acc[C::FM][FN];
 #pragma unroll
-    for (int j = 0; j < C::LPB; ++j) {
-        const bool a = j < C::A_I;
-        const int row = (a ? j : j - C::A_I) * 8 + (lane >> 3);
-        off[j] = (uint32_t)min(row, (a ? rows : a_rows) - 1) * ldx + ((j & 1) ? c16b : c16a);
-    }
-    const int nb = (nkb - wave + C::NW - 1) / C::NW;   // the wave's blocks
-    auto block_of = [&](int i) __attribute__((always_inline)) {
-        const int kb = k_first + wave + i * C::NW;
-        return kb >= nkb ? kb - nkb : kb;
-    };
-    auto issue = [&](int i) __attribute__((always_inline)) {
-        const int kb = block_of(i);
-        char *st = mine + (i % C::NS) * C::STAGE_BYTES;
+    for (int i = 0; i < C::FM; ++i)
 #pragma unroll
-        for (int j = 0; j < C::LPB; ++j)
-            __builtin_amdgcn_global_load_lds(MOIN_GPTR((j < C::A_I ? xa : ae) + (off[j] + (uint32_t)kb * C::ROWB)),
-                                             MOIN_LPTR(st + j * 1024), 16, 0, 0);
-    };
-    constexpr int FN = BN / 32;
-    f32x16_t acc[FN];
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if (n0 < re) {   // (else: zeros alone)
+        const uint32_t ldx = (uint32_t)p.d_in * 2u;
+        const char *xa = p.x + (int64_t)row0 * ldx;
+        const char *ae = A_stack + ((int64_t)e * p.r + n0) * ldx;
+        const int a_rows = min(C::BN, re - n0);
+        // as in DmaCore: 8 rows of 128 bytes a request, 16-byte chunks XORed with swz(row) = (row >> 1) & 7
+        const uint32_t c16a = (((uint32_t)lane & 7) ^ ((uint32_t)lane >> 4)) * 16, c16b = c16a ^ 64u;   // even, odd requests
+        uint32_t off[C::LPB];
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
+        for (int j = 0; j < C::LPB; ++j) {
+            const bool a = j < C::A_I;
+            const int row = (a ? j : j - C::A_I) * 8 + (lane >> 3);
+            off[j] = (uint32_t)min(row, (a ? rows : a_rows) - 1) * ldx + ((j & 1) ? c16b : c16a);
+        }
+        auto kbyte_of = [&](int it) __attribute__((always_inline)) {
+            const int kb = it + k_first;
+            uint32_t k = (uint32_t)(kb >= nkb ? kb - nkb : kb) * C::ROWB;
+            asm volatile("" : "+s"(k));   // (one addition per request; taken apart it becomes three)
+            return k;
+        };
+        auto issue_one = [&](uint32_t kbyte, char *st, int j) __attribute__((always_inline)) {
+            __builtin_amdgcn_global_load_lds(MOIN_GPTR((j < C::A_I ? xa : ae) + (off[j] + kbyte)), MOIN_LPTR(st + j * 1024), 16, 0, 0);
+        };
+        auto stage = [&](int it) __attribute__((always_inline)) { return smem + (it % C::NS) * C::STAGE_BYTES; };
+        // fragments: row lane % 16 of 16, the second half of a block at the first one's address ^ 64; of the tokens, then the columns
+        const int lo = (lane & 15) * C::ROWB | ((((lane >> 4) ^ ((lane & 15) >> 1)) & 7) * 16);
+        constexpr int F = C::FM + FN, R = 2 * F, M = 2 * C::FM * FN;   // fragments of a half; reads and products of a block
+        bf16x8_t fr[2][R];
+        auto read_one = [&](const char *st, int set, int n) __attribute__((always_inline)) {
+            fr[set][n] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(st + (n % F) * 16 * C::ROWB + (lo ^ (n / F * 64))));
+        };
+        auto product = [&](int set, int n) __attribute__((always_inline)) {
+            const int ks = n / (M / 2), i = n % (M / 2) / FN, j = n % FN;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[set][ks * F + C::FM + j], fr[set][ks * F + i], acc[i][j], 0, 0, 0);
+        };
+        // Block it, whose fragments are in registers behind the wait.  LEFT blocks beyond the next one may still be under way;
+        // its stage, read out, takes block it + NS (MORE), the next block's fragments come to the other registers (NEXT).
+        auto turn = [&](int it, auto set_tag, auto left_tag, auto more_tag, auto next_tag) __attribute__((always_inline)) {
+            constexpr int SET = decltype(set_tag)::value, LEFT = decltype(left_tag)::value;
+            constexpr bool MORE = decltype(more_tag)::value, NEXT = decltype(next_tag)::value;
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LEFT * C::LPB) : "memory");
+            const uint32_t kbyte = MORE ? kbyte_of(it + C::NS) : 0;
+            char *cur = stage(it);
+            const char *nxt = stage(it + 1);
 #pragma unroll
-        for (int q = 0; q < 16; ++q) acc[j][q] = 0.f;
-    const int r32 = lane & 31, h = lane >> 5, f = (r32 >> 1) & 7;
+            for (int n = 0; n < (M > R ? M : R); ++n) {
+                if (n < M) product(SET, n);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (NEXT)
+                    if (n < R) read_one(nxt, 1 - SET, n);
+                if constexpr (MORE)
+                    if (n < C::LPB) issue_one(kbyte, cur, n);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        using T_ = std::true_type;
+        using F_ = std::false_type;
+        using S0 = std::integral_constant<int, 0>;
+        using S1 = std::integral_constant<int, 1>;
+        using Full = std::integral_constant<int, C::NS - 2>;
+        auto fetch = [&](int it) __attribute__((always_inline)) {
+            const uint32_t kbyte = kbyte_of(it);
 #pragma unroll
-    for (int s = 0; s < C::NS; ++s)
-        if (s < nb) issue(s);
-    for (int i = 0; i < nb; ++i) {
-        if (i + C::NS <= nb) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((C::NS - 1) * C::LPB) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        const char *st = mine + (i % C::NS) * C::STAGE_BYTES;
+            for (int j = 0; j < C::LPB; ++j) issue_one(kbyte, stage(it), j);
+        };
+        auto read_block = [&](int it, int set) __attribute__((always_inline)) {
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const int o = ((ks * 2 + h) ^ f) * 16;
-            const bf16x8_t a = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(st + r32 * C::ROWB + o));
+            for (int n = 0; n < R; ++n) read_one(stage(it), set, n);
+        };
+        if (nkb >= C::NS) {
 #pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                const bf16x8_t b = __builtin_bit_cast(
-                    bf16x8_t, *reinterpret_cast<const uint4 *>(st + C::A_BYTES + (j * 32 + r32) * C::ROWB + o));
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[j], 0, 0, 0);
+            for (int s = 0; s < C::NS; ++s) fetch(s);
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((C::NS - 1) * C::LPB) : "memory");
+            const int more = nkb - C::NS;   // turns that fetch; the first of an odd number by itself, so that the last NS begin with set 0
+            int it = 0;
+            if (more & 1) {
+                read_block(0, 1);
+                turn(0, S1{}, Full{}, T_{}, T_{});
+                it = 1;
+            } else {
+                read_block(0, 0);
+            }
+            for (; it < more; it += 2) {
+                turn(it, S0{}, Full{}, T_{}, T_{});
+                turn(it + 1, S1{}, Full{}, T_{}, T_{});
+            }
+            unrolled(std::make_integer_sequence<int, C::NS>{}, [&](auto k) __attribute__((always_inline)) {
+                constexpr int K = decltype(k)::value;
+                turn(it + K, std::integral_constant<int, (K & 1)>{}, std::integral_constant<int, (K + 2 < C::NS ? C::NS - 2 - K : 0)>{},
+                     F_{}, std::integral_constant<bool, (K + 1 < C::NS)>{});
+            });
+        } else {
+            for (int s = 0; s < nkb; ++s) fetch(s);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            for (int it = 0; it < nkb; ++it) {
+                read_block(it, 0);
+                turn(it, S0{}, S0{}, F_{}, F_{});
             }
         }
-        if constexpr (QUANT) {
-            const int k0 = block_of(i) * C::BK, c = lane & 7;
-#pragma unroll
-            for (int j = 0; j < C::A_I; ++j) {
-                const int row = j * 8 + (lane >> 3);
-                int E;
-                const uint2 codes = mx_quantize8(
-                    *reinterpret_cast<const uint4 *>(st + row * C::ROWB + ((c ^ ((row >> 1) & 7)) * 16)), E);
-                const uint32_t pair = (uint32_t)E | ((uint32_t)dpp_move<DPP_FROM_PLUS4>(E) << 8);
-                if (row < rows) {
-                    *reinterpret_cast<uint2 *>(p.xq + (int64_t)(row0 + row) * p.d_in + k0 + c * 8) = codes;
-                    if (c == 0)
-                        *reinterpret_cast<uint16_t *>(p.xs + ((int64_t)(k0 >> 7) * p.T + row0 + row) * 4 + ((k0 >> 5) & 3)) =
-                            (uint16_t)pair;
-                }
-            }
-        }
-        // (the stage's reads have returned: the products above took them)
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (i + C::NS < nb) issue(i + C::NS);
     }
-    if (!shrink) return;   // (the whole workgroup)
-    float *sum = reinterpret_cast<float *>(mine);
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) sum[mfma32_acc_row(q, lane) * C::PITCH + j * 32 + r32] = acc[j][q];
-    __syncthreads();
+
+    // a lane holds, per accumulator (i, j), token 16 i + lane % 16 and columns 16 j + 4 (lane / 16) + 0..3
     const int64_t ldu = (int64_t)p.ldu * 2;
-    constexpr int COLS = BN < 64 ? 64 : BN;   // (u goes to the end of a block of 64)
-    for (int i = threadIdx.x; i < C::BM * (COLS / 8); i += C::NT) {
-        const int row = i / (COLS / 8), col = i % (COLS / 8) * 8;
-        if (row >= rows || col >= r_out) continue;
-        f32x4_t v[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        if (col < BN)
 #pragma unroll
-            for (int w = 0; w < C::NW; ++w)
+    for (int i = 0; i < C::FM; ++i) {
+        const int row = i * 16 + (lane & 15);
+        if (row >= rows) continue;
+        const int64_t at = (int64_t)(row0 + row) * ldu;
 #pragma unroll
-                for (int q = 0; q < 2; ++q)
-                    v[q] += *reinterpret_cast<const f32x4_t *>(smem + w * C::WAVE_BYTES + (row * C::PITCH + col + q * 4) * 4);
-        uint4 hi, lo;
-        u_pair(v, re - col, p.act, p.scale, hi, lo);
-        const int64_t at = (int64_t)(row0 + row) * ldu + (int64_t)col * 2;
-        *reinterpret_cast<uint4 *>(u_hi + at) = hi;
-        *reinterpret_cast<uint4 *>(u_lo + at) = lo;
+        for (int j = 0; j < FN; ++j) {
+            const int col = n0 + j * 16 + 4 * (lane >> 4);
+            if (col >= n_end) continue;
+            uint2 hi, lo;
+            u_pair(acc[i][j], re - col, p.act, p.scale, hi, lo);
+            *reinterpret_cast<uint2 *>(u_hi + at + col * 2) = hi;
+            *reinterpret_cast<uint2 *>(u_lo + at + col * 2) = lo;
+        }
+        for (int col = n0 + C::BN + 4 * (lane >> 4); col < n_end; col += 16) {
+            *reinterpret_cast<uint2 *>(u_hi + at + col * 2) = make_uint2(0, 0);
+            *reinterpret_cast<uint2 *>(u_lo + at + col * 2) = make_uint2(0, 0);
+        }
     }
 }
 
@@ -401,11 +496,10 @@ hipError_t prepare_linear_kernels()
 {
     hipError_t e;
     if ((e = prepare_stream_kernel()) != hipSuccess) return e;
-    if ((e = allow_lds(&shrink_split_kernel<64, true>, SplitCfg<64>::SMEM_BYTES)) != hipSuccess) return e;
-    if ((e = allow_lds(&shrink_split_kernel<128, true>, SplitCfg<128>::SMEM_BYTES)) != hipSuccess) return e;
-    if ((e = allow_lds(&shrink_split_kernel<32, false>, SplitCfg<32>::SMEM_BYTES)) != hipSuccess) return e;
-    if ((e = allow_lds(&shrink_split_kernel<64, false>, SplitCfg<64>::SMEM_BYTES)) != hipSuccess) return e;
-    if ((e = allow_lds(&shrink_split_kernel<128, false>, SplitCfg<128>::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_wave_kernel<1, 0>, WaveCfg<1>::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_wave_kernel<2, 0>, WaveCfg<2>::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_wave_kernel<1, 1>, WaveCfg<1>::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_wave_kernel<2, 2>, WaveCfg<2>::SMEM_BYTES)) != hipSuccess) return e;
     if ((e = allow_lds(&linear_kernel<CfgMain>, CfgMain::SMEM_BYTES)) != hipSuccess) return e;
     if ((e = allow_lds(&linear_kernel<CfgThin>, CfgThin::SMEM_BYTES)) != hipSuccess) return e;
     if ((e = allow_lds(&linear_kernel<CfgDecodeBase>, CfgDecodeBase::SMEM_BYTES)) != hipSuccess) return e;
@@ -480,27 +574,35 @@ static hipError_t launch_shrink_as(const PlanView &pv, const LinearArgs &a, hipS
     return hipGetLastError();
 }
 
-template <int BN, bool QUANT = false>
-static hipError_t launch_shrink_split(const PlanView &pv, const LinearArgs &a, const SharedX *shared, hipStream_t stream,
-                                      void *xq = nullptr, void *xs = nullptr)
+template <int FN, int QW = 0>
+static hipError_t launch_shrink_wave(const PlanView &pv, const LinearArgs &a, const SharedX *shared, hipStream_t stream,
+                                     void *xq = nullptr, void *xs = nullptr)
 {
-    using C = SplitCfg<BN>;
+    using C = WaveCfg<FN>;
     ShrinkKParams p;
-    const int64_t grid = shrink_params(p, pv, a, shared, xq, xs, C::BM, BN);
-    if (grid < 0 || p.tiles_per_proj != 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((shrink_split_kernel<BN, QUANT>), dim3((unsigned)round_up8((int)grid)), dim3(C::NT), C::SMEM_BYTES, stream, p);
+    const int64_t grid = shrink_params(p, pv, a, shared, xq, xs, C::BM, C::BN);
+    if (grid < 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((shrink_wave_kernel<FN, QW>), dim3((unsigned)round_up8((int)grid)), dim3(64 * (1 + QW)), C::SMEM_BYTES, stream, p);
     return hipGetLastError();
 }
 
-// Whether the whole rank in tiles of 32 tokens, `tiles` of them at most (of sequences of equal length, as far as the host
-// knows), is the faster form.  The order in which u is summed differs between the forms, so the rule looks at the batch alone and not at
-// how many projections the call has: a shared call gives the bits of the single ones, and on a quantised base codes
-// made on the way give those of codes that were there.
-static bool shrink_split_pays(const PlanView &pv, const LinearArgs &a, int tiles)
+// Columns per wave (16 or 32) of the form with a wave per patch, 0 where the larger tiles are the faster form.  Us of the
+// kernel, by 2048 / 5632:
+//  * 16 or 32 columns: 1890 tokens at rank 64 7.8, 14.5 and 9.2, 16.4; 512 waves of 16 columns (4096 tokens, rank 64) 8.2, 15.9
+//    and 9.3, 17.3; 768 (4096 tokens, three at rank 64; 8192, two at rank 32) 20.3, 30.5 and 14.4, 21.6.
+//  * 32 columns or the larger tiles.  Rank 64, 768 waves of 32 columns (12 288 tokens) 13.9, 28.8 and 16.0, 32.0; 1024 (8192,
+//    two projections) 18.8, 38.8 and 16.9, 33.6.  Those of rank 128 are four times as large: 1536 waves (12 288 tokens) 26.6, 65.8 and
+//    28.0, 66.4; 2048 (8192, two) 27.4, 67.2 and 26.6, 65.1.  Up to rank 32 half of a larger tile is padding: 584 row
+//    tiles (18 700 tokens) 16.4, 38.2 and 17.8, 42.8, three 29.1 and 30.9; 1024 (32 768) 24.4, 72.2 and 23.4, 65.0.
+//  * With codes the same lines: 768 waves at rank 64 22.8, 67.7 and 32.8, 74.5; 1168 (18 700 tokens) 32.9, 123 and 34.1, 97.
+static int shrink_wave_columns(const PlanView &pv, const LinearArgs &a, int n_proj)
 {
-    if (a.d_in % 64 || a.r > 128) return false;
-    const int64_t S = std::max<int64_t>(1, std::min<int64_t>(pv.S, pv.max_tiles)), len = (pv.T + S - 1) / S;
-    return S * ((len + 31) / 32) <= tiles;
+    if (a.d_in % 64 || a.r > 128) return 0;
+    const int64_t tiles = host_tiles(pv, 32), cus = compute_units();
+    if (tiles * ((a.r + 15) / 16) * n_proj <= 2 * cus) return 16;
+    const int64_t waves = tiles * ((a.r + 31) / 32) * n_proj;
+    if ((a.r <= 32 ? tiles : a.r <= 64 ? waves : waves / 2) > 3 * cus) return 0;
+    return a.r <= 16 ? 16 : 32;
 }
 
 // The prefill shrink and the MXFP8 quantisation of x in one pass over x (r >= 1,
@@ -510,21 +612,20 @@ hipError_t launch_prefill_shrink_quant(const PlanView &pv, const LinearArgs &a, 
 {
     if (pv.max_tiles <= 0) return hipSuccess;
     if (a.r <= 0 || a.d_in % 128) return hipErrorInvalidValue;
-    if (shrink_split_pays(pv, a, compute_units()))
-        return a.r <= 64 ? launch_shrink_split<64, true>(pv, a, nullptr, stream, xq, xs)
-                         : launch_shrink_split<128, true>(pv, a, nullptr, stream, xq, xs);
+    switch (shrink_wave_columns(pv, a, 1)) {
+    case 16: return launch_shrink_wave<1, 1>(pv, a, nullptr, stream, xq, xs);
+    case 32: return launch_shrink_wave<2, 2>(pv, a, nullptr, stream, xq, xs);
+    }
     if (a.r > 64 && a.r <= 128) return launch_shrink_as<CfgShrinkDeep, true>(pv, a, stream, xq, xs);
     return launch_shrink_as<CfgShrinkDeep64, true>(pv, a, stream, xq, xs);
 }
 
-static hipError_t launch_prefill_shrink_any(const PlanView &pv, const LinearArgs &a, const SharedX *shared, int split_tiles,
-                                            hipStream_t stream)
+static hipError_t launch_prefill_shrink_any(const PlanView &pv, const LinearArgs &a, const SharedX *shared, hipStream_t stream)
 {
     if (a.r <= 0 || pv.max_tiles <= 0) return hipSuccess;
-    if (shrink_split_pays(pv, a, split_tiles)) {
-        if (a.r <= 32) return launch_shrink_split<32>(pv, a, shared, stream);
-        if (a.r <= 64) return launch_shrink_split<64>(pv, a, shared, stream);
-        return launch_shrink_split<128>(pv, a, shared, stream);
+    switch (shrink_wave_columns(pv, a, shared ? shared->n : 1)) {
+    case 16: return launch_shrink_wave<1>(pv, a, shared, stream);
+    case 32: return launch_shrink_wave<2>(pv, a, shared, stream);
     }
     if (a.d_in % 64 == 0 && a.r > 64 && a.r <= 128)
         return launch_shrink_as<CfgShrinkR128>(pv, a, stream, nullptr, nullptr, shared);
@@ -532,20 +633,9 @@ static hipError_t launch_prefill_shrink_any(const PlanView &pv, const LinearArgs
     return launch_shrink_as<CfgShrink>(pv, a, stream, nullptr, nullptr, shared);
 }
 
-// The split form where a call of any number of projections gains or loses nothing by it.  Us, tiles above / split, rank 64
-// and 128, by 2048: 4096 tokens, one projection 15.4 / 9.1 and 23 / 15, three 16 / 16.5 and 28 / 26; 5120 tokens, three
-// 16.5 / 17 and 29 / 27.5; 6144, three 18 / 23 and 29 / 37.  Long rows, whose chains of blocks cost the tiles above the more,
-// a tile per compute unit (a call, by 5632, 8192 tokens: one projection 67 / 54 and 99 / 65, two 69 / 67 and 100 / 86; three, which
-// models have on their shorter rows, 73 / 81 and 101 / 107).
-constexpr int SPLIT_LONG_ROWS = 4096;
-static int split_tiles_of(int d_in)
-{
-    return d_in >= SPLIT_LONG_ROWS ? compute_units() : compute_units() * 5 / 8;
-}
-
 hipError_t launch_prefill_shrink(const PlanView &pv, const LinearArgs &a, hipStream_t stream)
 {
-    return launch_prefill_shrink_any(pv, a, nullptr, split_tiles_of(a.d_in), stream);
+    return launch_prefill_shrink_any(pv, a, nullptr, stream);
 }
 
 hipError_t launch_prefill_shrink_shared(const PlanView &pv, const LinearArgs &a, int n, const void *const *A_stack,
@@ -553,14 +643,7 @@ hipError_t launch_prefill_shrink_shared(const PlanView &pv, const LinearArgs &a,
 {
     if (n < 1 || n > MAX_SHARED_X) return hipErrorInvalidValue;
     const SharedX sh{n, A_stack, u_hi, u_lo};
-    return launch_prefill_shrink_any(pv, a, &sh, split_tiles_of(a.d_in), stream);
-}
-
-// On a quantised base every call is of one projection: a tile per compute unit.  (Us of a call, tiles above / split, 8192
-// tokens by 2048 at rank 64 42 / 37, with codes 58 / 45; 12 288 tokens 43 / 44 and 59 / 57.)
-hipError_t launch_prefill_shrink_mx(const PlanView &pv, const LinearArgs &a, hipStream_t stream)
-{
-    return launch_prefill_shrink_any(pv, a, nullptr, compute_units(), stream);
+    return launch_prefill_shrink_any(pv, a, &sh, stream);
 }
 
 template <class C>

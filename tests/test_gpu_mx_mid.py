@@ -33,7 +33,6 @@ def test_decode_edges(T, d_in, d_out):
 @pytest.mark.parametrize("r", [64, 128])
 def test_same_bits_as_the_larger_tiles(r):
     inp = _case("mx_mid_bits", 256, 4096, r, 4, [400] * 32, [0, 1, 2, 3] * 8, seed=r)   # 4096 tiles
-    inp.A_stack[:, :, 1:] = 0   # (the shrink's order of summing goes by the batch's size: one term, one order)
     Wq, Ws = moin.moin_mx_quantize(gc.ctx(), inp.W, blocked=True)
     call = lambda x, off, e: moin.moin_lora_linear_mx(gc.ctx(), x, off, e, Wq, Ws, inp.A_stack, inp.B_stack, 2.0,
                                                       y_dtype=torch.float32)

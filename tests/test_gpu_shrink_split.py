@@ -1,6 +1,6 @@
-"""The shrink in tiles of 32 tokens whose waves split the contraction: row counts around a tile, one to many blocks of 64
-per wave, every width, ranks that end inside one, on a bf16 and (codes made on the way, and given) an MXFP8 base;
-against torch in fp64, and codes against the quantiser's."""
+"""The shrink of few row tiles, a wave per 32 tokens and 16 or (in the batches of 40 sequences) 32 columns: row counts around a
+tile, fewer blocks of 64 than stages to many more, every width, ranks that end inside one, on a bf16 and (codes made on the
+way, and given) an MXFP8 base; against torch in fp64, and codes against the quantiser's."""
 import numpy as np
 import pytest
 import torch
@@ -17,9 +17,9 @@ IDS = np.array([2, 0, -1, 2, 3, 1, 1, -1, 3, 2], dtype=np.int32)
 E = 5
 
 
-def _inputs(d_in, d_out, r):
-    w = wl.LinearWorkload("split", d_in, d_out, r, E, LENS, "uniform", scale=2.0, seed=d_in + r)
-    inp = wl.make_linear_inputs(w, "cuda", expert_ids=IDS)
+def _inputs(d_in, d_out, r, times=1):
+    w = wl.LinearWorkload("split", d_in, d_out, r, E, LENS * times, "uniform", scale=2.0, seed=d_in + r)
+    inp = wl.make_linear_inputs(w, "cuda", expert_ids=np.tile(IDS, times))
     inp.A_stack[4] = float("nan")   # (no sequence uses it)
     inp.B_stack[4] = float("nan")
     return inp
@@ -37,9 +37,21 @@ def test_against_fp64(d_in, r, ranked):
     _check(y, _reference(inp, IDS, LENS, rk, r), d_in, r)
 
 
-@pytest.mark.parametrize("d_in,r", [(256, 64), (384, 128), (2048, 64), (5632, 128)])
-def test_quantised_base(d_in, r):
-    inp, ctx, T = _inputs(d_in, 72, r), gc.ctx(), sum(LENS)
+@pytest.mark.parametrize("d_in,r,ranked", [(64, 24, False), (192, 32, True), (256, 40, False), (320, 64, True), (704, 72, False),
+                                           (2048, 64, False), (1344, 128, True)])
+def test_wider_patches_against_fp64(d_in, r, ranked):
+    inp, ids, lens = _inputs(d_in, 72, r, 4), np.tile(IDS, 4), LENS * 4
+    rk = torch.tensor([r, 8, max(8, r - 8), 0, 8], dtype=torch.int32, device="cuda") if ranked else None
+    print(f"[gpu] shrink, 32 columns a wave, d_in={d_in} r={r} ranked={ranked}", flush=True)
+    y = moin.moin_lora_linear(gc.ctx(), inp.x, inp.seq_offsets, inp.expert_ids, inp.W, inp.A_stack, inp.B_stack, 2.0,
+                              y_dtype=torch.float32, rank_of_expert=rk)
+    gc.ctx().check()
+    _check(y, _reference(inp, ids, lens, rk, r), d_in, r)
+
+
+@pytest.mark.parametrize("d_in,r,times", [(256, 64, 1), (384, 128, 1), (2048, 64, 1), (5632, 128, 1), (256, 64, 4), (896, 128, 4)])
+def test_quantised_base(d_in, r, times):
+    inp, ctx, T = _inputs(d_in, 72, r, times), gc.ctx(), sum(LENS) * times
     Wq, Ws = moin.moin_mx_quantize(ctx, inp.W, blocked=True)
     want_q, want_s = moin.moin_mx_quantize(ctx, inp.x, blocked=True)
     plan = moin.Plan(ctx).build(inp.seq_offsets, inp.expert_ids, T, E)
@@ -47,7 +59,7 @@ def test_quantised_base(d_in, r):
     xs = torch.zeros((d_in // 128, T, 4), dtype=torch.uint8, device="cuda")
     call = lambda **kw: moin.moin_lora_linear_mx_planned(ctx, plan, inp.x, Wq, Ws, inp.A_stack, inp.B_stack, 2.0,
                                                          y_dtype=torch.float32, **kw)
-    print(f"[gpu] split shrink with codes d_in={d_in} r={r}", flush=True)
+    print(f"[gpu] split shrink with codes d_in={d_in} r={r} times={times}", flush=True)
     y0, y1 = call(xq=xq, xs=xs, emit=True), call(xq=xq, xs=xs)
     ctx.check()
     assert torch.equal(xq, want_q.view(torch.uint8)) and torch.equal(xs, want_s) and torch.equal(y0, y1)
@@ -58,7 +70,7 @@ def test_quantised_base(d_in, r):
     ctx.check()
     zero_w = wl.LinearInputs(inp.wl, inp.x, torch.zeros_like(inp.W), inp.A_stack, inp.B_stack, inp.seq_offsets,
                              inp.expert_ids)
-    term = _reference(zero_w, IDS, LENS, None, r)
+    term = _reference(zero_w, np.tile(IDS, times), LENS * times, None, r)
     ref = base.double() + term
     # u as a bf16 pair (2^-17) and fp32 sums of d_in + r products, against the largest output, taken four times
     bound = 4 * (d_in ** 0.5 + 128) * 2.0 ** -24
