@@ -263,13 +263,11 @@ hipError_t prepare_mid_kernels()
     return e == hipSuccess ? allow_lds_all<4>() : e;
 }
 
-// Tiles of a call, as far as the host knows: sequences of equal length.
 static int64_t mid_tiles(const PlanView &pv, const LinearArgs *a, int n)
 {
     int64_t tn = 0;
     for (int i = 0; i < n; ++i) tn += (a[i].d_out + mid::BT - 1) / mid::BT;
-    const int64_t S = std::max<int64_t>(1, std::min<int64_t>(pv.S, pv.max_tiles)), len = (pv.T + S - 1) / S;
-    return S * ((len + mid::BT - 1) / mid::BT) * tn;
+    return host_tiles(pv, mid::BT) * tn;
 }
 
 // Up to the tiles that the chip holds at a time.  Us of a call, 256 x 256 tiles / these, 2048 -> 2048: 448 tiles 58 / 46,

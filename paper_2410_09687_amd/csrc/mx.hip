@@ -762,8 +762,7 @@ hipError_t launch_linear_mx_stream(const PlanView &pv, const MxLinearArgs &a, in
     p.kb_per_split = a.plain_kb_per_split;
     p.plane_bytes = (int64_t)pv.T * a.lin.d_out * (a.lin.y_f32 ? 4 : 2);
     const int64_t cols = (a.lin.d_out + mxm::BT - 1) / mxm::BT;
-    const int64_t S = std::max<int64_t>(1, std::min<int64_t>(pv.S, pv.max_tiles)), len = p.plain ? pv.T : (pv.T + S - 1) / S;
-    const int64_t rows = (p.plain ? 1 : S) * ((len + mxm::BT - 1) / mxm::BT);   // (sequences of equal length, as far as the host knows)
+    const int64_t rows = p.plain ? (pv.T + mxm::BT - 1) / mxm::BT : host_tiles(pv, mxm::BT);
     if (mx_mid_pays(rows * cols, n_cus)) {
         p.n_tiles_n = (int)cols;
         p.tiles_m = (int)rows;
