@@ -31,6 +31,7 @@ constexpr int NW = 4, NT = NW * 64;
 constexpr int FP = 4, FQ = 4;          // 16 x 16 accumulators per wave: 64 outputs x 64 tokens
 constexpr int BT = 128;                // tile edge, both ways
 constexpr int SUB = TILE_M / BT;       // tiles per plan tile
+static_assert(SUB == 2, "HalfTiles");
 constexpr int P_BYTES = BT * ROWB, STAGE_BYTES = 2 * P_BYTES;
 constexpr int LOADS = FP + FQ;         // requests of a wave per block, 8 rows each
 constexpr int SCR_BYTES = 16 * FP * 16 * 4;   // epilogue scratch of a wave: 16 tokens x its outputs, fp32
@@ -50,12 +51,13 @@ __global__ __launch_bounds__(mid::NT, NS == 2 ? 2 : 1) void linear_mid_kernel(st
     const int wave = uniform(threadIdx.x >> 6);
     const int wp = wave >> 1, wq = wave & 1;
 
-    const int ntm = uniform(*p.n_tiles) * SUB;
+    const HalfTiles halves(p.tile_rows, p.n_tiles, p.max_tiles);
+    const int ntm = halves.count;
     const int id = xcd_band_id(blockIdx.x, ntm * p.n_tiles_n);
     if (id < 0) return;
     const int tm = p.by_columns ? id % ntm : id / p.n_tiles_n;
     const int tn = p.by_columns ? id / ntm : id % p.n_tiles_n;
-    const stream::Tile t = stream::load_tile<BT, BT>(p, tm, tn);
+    const stream::Tile t = stream::load_tile<BT, BT>(p, halves.find(tm), tn);
     if (t.q_rows <= 0) return;
 
     const int nkb0 = (p.d_in + BK - 1) / BK;
@@ -270,10 +272,13 @@ static int64_t mid_tiles(const PlanView &pv, const LinearArgs *a, int n)
     return host_tiles(pv, mid::BT) * tn;
 }
 
-// Up to the tiles that the chip holds at a time.  Us of a call, 256 x 256 tiles / these, 2048 -> 2048: 448 tiles 58 / 46,
-// 512 58 / 49, 576 59 / 68, 768 63 / 71 (one round of the larger tiles until 1024); beyond those' first round 1088 tiles
-// 103 / 97, 1280 106 / 100, but 1280 with 5632 outputs 106 / 113.  1000 -> 2048 against tiles that go through registers:
-// 256 tiles 50 / 30, 1024 59 / 62, 1416 -> 5632 at 11264 654 / 776.
+// Up to the tiles that the chip holds at a time.  Us of the kernel, 256 x 256 tiles / these: 2048 -> 2048 448 tiles 42 / 31, 512 45 /
+// 34, 544 45 / 52, 768 47 / 56, 1024 55 / 64 (one round of the larger tiles until then); beyond their first round 1152 89 / 84,
+// 1280 90 / 87, but 1280 with 5632 outputs a call 106 / 113, so the line stays here; 5632 -> 2048 512 tiles 100 / 81,
+// 544 101 / 132; 2048 -> 2048, 256, 256 480 tiles 46 / 33, 560 48 / 52; 528 tiles 2048 -> 5632 47 / 52.  Uneven sequences can
+// make more tiles than the host takes them to: 16 of 60 to 430 tokens 560 instead of 512, 46 / 53 (were the line lower, as
+// many even ones would lose 11).  1000 -> 2048 against tiles that go through registers, us of a call: 256 tiles 50 / 30,
+// 1024 59 / 62, 1416 -> 5632 at 11264 654 / 776.
 bool mid_kernel_pays(const PlanView &pv, const LinearArgs *a, int n, int n_cus)
 {
     return mid_tiles(pv, a, n) <= 2 * (int64_t)n_cus;
@@ -303,7 +308,7 @@ hipError_t launch_linear_mid(const PlanView &pv, const LinearArgs *a, int n, int
     const int64_t work = (int64_t)pv.max_tiles * mid::SUB * tn;
     if (work > 0x7ffffff0LL) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)((work + 7) / 8 * 8);
-    // (2000 tokens 2048 -> 2048, 256 tiles: 53 us with two stages, 48 with four; 384 tiles 44 and 50)
+    // (Us of the kernel, four stages / two: 240 tiles 20 / 25, 256 22 / 26, 268 37 / 29, 320 36 / 30.)
     if (mid_tiles(pv, a, n) <= n_cus) return launch_mid<4>(p, grid, stream_);
     return launch_mid<2>(p, grid, stream_);
 }

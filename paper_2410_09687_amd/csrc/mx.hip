@@ -25,6 +25,7 @@
 #include "gemm_core.h"
 #include "kernels.h"
 #include "stream_epilogue.h"
+#include "stream_tile.h"
 
 namespace moin {
 
@@ -139,6 +140,7 @@ struct Params {
     const char *B_stack, *u_hi, *u_lo;
     char *y;
     const int *tile_row0, *tile_rows, *tile_expert, *tile_rank, *n_tiles;
+    int max_tiles;                   // entries of those arrays
     int d_in, d_out, r;
     int n_tiles_n;
     int y_f32;
@@ -533,10 +535,19 @@ __global__ __launch_bounds__(mxm::NT, 2) void linear_mx_mid_kernel(mxs::Params p
     const int wave = uniform(threadIdx.x >> 6);
     const int wp = wave >> 1, wq = wave & 1;
 
-    const int n_work = p.plain ? p.tiles_m * p.n_tiles_n * p.k_splits : uniform(*p.n_tiles) * (TILE_M / BT) * p.n_tiles_n;
-    const int id = xcd_band_id(blockIdx.x, n_work);
-    if (id < 0) return;
-    const Tile t = mxs::load_tile<true, BT>(p, id, n_work);
+    static_assert(TILE_M == 2 * BT, "HalfTiles");
+    int id;
+    if (p.plain) {
+        id = xcd_band_id(blockIdx.x, p.tiles_m * p.n_tiles_n * p.k_splits);
+        if (id < 0) return;
+    } else {
+        const HalfTiles halves(p.tile_rows, p.n_tiles, p.max_tiles);
+        id = xcd_band_id(blockIdx.x, halves.count * p.n_tiles_n);
+        if (id < 0) return;
+        const int j = id / p.n_tiles_n;
+        id += (halves.find(j) - j) * p.n_tiles_n;
+    }
+    const Tile t = mxs::load_tile<true, BT>(p, id, id + 1);
     const int q_rows = t.q_rows, p_rows = t.p_rows, row0 = t.row0, n0 = t.n0, kb0 = t.kb0, nkb1 = t.nkb1, total = t.total;
     const char *const q0 = t.q0, *const p0 = t.p0, *const uh = t.uh, *const ul = t.ul, *const be = t.be;
     char *const y = p.y + t.y_off;
@@ -713,8 +724,9 @@ hipError_t prepare_mx_kernels()
 
 bool mx_stream_kernel_fits(int d_in, int r) { return d_in % 128 == 0 && d_in >= 256 && r % 64 == 0; }
 
-// 128 x 128 tiles as long as the chip holds all of them at a time, as in linear_mid.hip.  (Beyond: a layer of 18 700 tokens,
-// q, k, v, o, gate, up, down 1200 us, with 128 x 128 tiles throughout 1397.)
+// 128 x 128 tiles as long as the chip holds all of them at a time, as in linear_mid.hip.  Us of the kernel, 256 x 256 tiles / these:
+// 2048 -> 2048 512 tiles 29.6 / 24.5, 544 29.8 / 33.6, 768 31.2 / 35.7; 5632 -> 2048 512 61 / 52, 544 61 / 76; 2048 -> 5632 528
+// 31.3 / 35.1.  (Beyond the larger tiles' first round about equal: 1152 56 / 52, 5632 outputs 1232 57 / 60.)
 static bool mx_mid_pays(int64_t tiles, int n_cus) { return tiles <= 2 * (int64_t)n_cus; }
 
 // Parts of the contraction range for the plain (decode) base product: enough
@@ -753,6 +765,7 @@ hipError_t launch_linear_mx_stream(const PlanView &pv, const MxLinearArgs &a, in
     p.tile_row0 = pv.tile_row0; p.tile_rows = pv.tile_rows; p.tile_expert = pv.tile_expert;
     p.tile_rank = pv.tile_rank;
     p.n_tiles = pv.n_tiles;
+    p.max_tiles = pv.max_tiles;
     p.d_in = a.lin.d_in; p.d_out = a.lin.d_out; p.r = a.lin.r;
     p.n_tiles_n = (a.lin.d_out + mxs::BT - 1) / mxs::BT;
     p.y_f32 = a.lin.y_f32;

@@ -5,6 +5,50 @@
 
 namespace moin {
 
+// The halves of a call's plan tiles (TILE_M / 2 tokens each) that hold any tokens, numbered without the others: a workgroup that
+// has nothing to do still takes its turn, and the ones behind it may have to wait for a compute unit that is busy although another
+// is free.  (1700 tokens in eight sequences of 75 to 310, three times 2048 -> 1024, 360 halves of 528: eight
+// workgroups started 25 us late, 44 us instead of 30.)
+struct HalfTiles {
+    static constexpr int CHUNKS = 4;           // beyond 64 * CHUNKS plan tiles the empty halves are numbered too
+    unsigned long long second[CHUNKS];         // which plan tiles have tokens in their second half
+    int n_tiles, count;
+
+    __device__ __forceinline__ HalfTiles(const int *tile_rows, const int *n_tiles_, int max_tiles)
+    {
+        const int lane = threadIdx.x & 63;
+        int rows[CHUNKS];
+#pragma unroll
+        for (int i = 0; i < CHUNKS; ++i) rows[i] = i * 64 + lane < max_tiles ? tile_rows[i * 64 + lane] : 0;
+        n_tiles = uniform(*n_tiles_);
+        count = n_tiles;
+#pragma unroll
+        for (int i = 0; i < CHUNKS; ++i) {
+            second[i] = __ballot(i * 64 + lane < n_tiles && rows[i] > TILE_M / 2);
+            count += __popcll(second[i]);
+        }
+        if (n_tiles > 64 * CHUNKS) count = 2 * n_tiles;
+    }
+    // Half number j (< count): its plan tile times two, plus one for a second half.
+    __device__ __forceinline__ int find(int j) const
+    {
+        if (n_tiles > 64 * CHUNKS) return j;
+        const int lane = threadIdx.x & 63;
+        int at = 0;
+#pragma unroll
+        for (int i = 0; i < CHUNKS; ++i) {
+            const int n = min(max(n_tiles - i * 64, 0), 64), halves = n + __popcll(second[i]);
+            if (j >= 0 && j < halves) {
+                auto before = [&](int t) { return t + __popcll(second[i] & ((1ull << t) - 1)); };   // halves of the chunk's first t tiles
+                const int t = __popcll(__ballot(lane < n && before(lane) <= j)) - 1;
+                at = (i * 64 + t) * 2 + j - before(t);
+            }
+            j -= halves;
+        }
+        return uniform(at);
+    }
+};
+
 namespace stream {
 
 constexpr int BK = 64;          // contraction steps of a block
@@ -23,6 +67,7 @@ struct Params {
     const int *tile_row0, *tile_rows, *tile_expert, *tile_rank, *n_tiles;
     int d_in, r, ldu;             // (ldu: columns of u as stored)
     int n_tiles_n;                // column tiles of all projections together
+    int max_tiles;                // entries of the plan's tile arrays
     int y_f32;
     int by_columns;               // linear_mid.hip: tiles of one column are neighbours (else: of one row)
 };
@@ -100,6 +145,7 @@ inline int fill_params(Params *p, const PlanView &pv, const LinearArgs *a, int n
     p->tile_row0 = pv.tile_row0; p->tile_rows = pv.tile_rows; p->tile_expert = pv.tile_expert;
     p->tile_rank = pv.tile_rank;
     p->n_tiles = pv.n_tiles;
+    p->max_tiles = pv.max_tiles;
     p->d_in = a[0].d_in; p->r = a[0].r; p->ldu = a[0].ldu;
     p->n_tiles_n = tn;
     p->y_f32 = a[0].y_f32;

@@ -22,6 +22,12 @@ def test_prefill_edges(d_in, d_out, r, ranks):
     _mx_check(inp, f"mx_mid {d_in}->{d_out} r={r}", rank_of_expert=ranks)
 
 
+@pytest.mark.parametrize("lens,d_out", [([129, 200, 20, 256, 300] * 15, 72), ([20, 400] * 125, 8)])
+def test_many_plan_tiles(lens, d_out):   # 90, and more than the 256 whose empty halves are left out
+    inp = _case("mx_mid_many", 256, d_out, 64, 4, lens, (np.arange(len(lens)) % 5 - 1).tolist(), seed=d_out)
+    _mx_check(inp, f"mx_mid, {len(lens)} sequences, 256->{d_out}")
+
+
 @pytest.mark.parametrize("T,d_in,d_out", [(1, 256, 136), (17, 768, 8), (127, 1024, 264), (128, 2048, 128), (129, 5632, 72),
                                           (1000, 1280, 520)])
 def test_decode_edges(T, d_in, d_out):

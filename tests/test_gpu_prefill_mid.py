@@ -42,6 +42,13 @@ def test_edges(d_in, d_out, r, ranked, f32):
         assert bool(((y.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4).all())
 
 
+@pytest.mark.parametrize("lens,d_out", [([129, 200, 20, 256, 300] * 15, 200), ([140, 128, 250] * 60, 72), ([20, 400] * 125, 8)])
+def test_many_plan_tiles(lens, d_out):   # 90, 180, and more than the 256 whose empty halves are left out
+    ids = (np.arange(len(lens)) % E - 1).astype(np.int32)
+    y, ref = _run(lens, ids, 72, d_out, 24, True, True)
+    _check(y, ref, 72, 24)
+
+
 @pytest.mark.parametrize("S,d_in,d_out", [(1025, 1000, 136), (1300, 2048, 264), (3000, 72, 1000)])
 def test_plain_tiles(S, d_in, d_out):
     ids = (np.arange(S) % E - 1).astype(np.int32)   # -1 .. 3
