@@ -397,11 +397,16 @@ int linear_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, con
         return MOIN_OK;
     }
 
-    // Beyond the small-batch size the base product runs on plain row tiles in the
-    // prefill kernels (256-row tiles, no adapter).
+    // Beyond the small-batch size the base product runs on plain row tiles in the prefill kernels (no adapter), except with
+    // rows that are not whole blocks of 64 where 128 x 128 tiles would leave half of the chip idle and the decode tiles cut
+    // the contraction into parts.  Us of a call at rank 32, decode tiles / plain ones: 1300 tokens 1000 -> 2048 35 / 31, 8192 139 /
+    // 90, 5000 1000 -> 5632 195 / 144, 40 000 1000 -> 136 103 / 96; in parts 1300 5640 -> 256 (22 tiles) 52 / 76, 4000
+    // 2056 -> 256 (64) 41 / 43, 2000 5640 -> 1000 (128) 71 / 76, but 1300 5640 -> 2048 (176) 113 / 79.
     LinearArgs ab = a;
     ab.r = 0;
-    const bool big = pv.max_plain > 0;
+    const bool parts = a.r > 0 && !stream_kernel_fits(ab) && decode_base_splits(pv.T, d_in, d_out) > 1 &&
+                       (pv.T + 127) / 128 * ((d_out + 127) / 128) <= compute_units() / 2;
+    const bool big = pv.max_plain > 0 && !parts;
     PlanView pp = pv;
     pp.tile_row0 = pv.plain_row0; pp.tile_rows = pv.plain_rows; pp.tile_expert = pv.plain_expert;
     pp.tile_rank = pv.plain_rank; pp.n_tiles = pv.plain_n; pp.max_tiles = pv.max_plain;

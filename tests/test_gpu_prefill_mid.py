@@ -56,6 +56,27 @@ def test_plain_tiles(S, d_in, d_out):
     _check(y, ref, d_in, 16)
 
 
+@pytest.mark.parametrize("S,d_in,d_out,r,kernel", [
+    (1300, 5640, 256, 32, moin.K_DECODE_BASE),   # long ragged rows, few tiles: the contraction in parts
+    (1300, 5640, 256, 0, moin.K_LINEAR), (1300, 5640, 2048, 32, moin.K_LINEAR), (1300, 1000, 256, 32, moin.K_LINEAR), (1300, 5632, 256, 32, moin.K_LINEAR)])
+def test_base_product_of_gathered_batches(S, d_in, d_out, r, kernel):
+    ids, ctx = (np.arange(S) % E - 1 if r else np.full(S, -1)).astype(np.int32), gc.ctx()
+    w = wl.LinearWorkload("mid", d_in, d_out, max(r, 8), E, [1] * S, "uniform", scale=2.0, seed=d_in + r)
+    inp = wl.make_linear_inputs(w, "cuda", expert_ids=ids)
+    A, B = (inp.A_stack, inp.B_stack) if r else (None, None)
+    print(f"[gpu] base product of {S} tokens {d_in}->{d_out} r={r}", flush=True)
+    ctx.timing_reset()
+    ctx.timing_enable(True)
+    try:
+        y = moin.moin_lora_linear(ctx, inp.x, inp.seq_offsets, inp.expert_ids, inp.W, A, B, 2.0, y_dtype=torch.float32)
+        ctx.check()
+        launches = {k: ctx.timing_read(k)[1] for k in (moin.K_DECODE_BASE, moin.K_LINEAR)}
+    finally:
+        ctx.timing_enable(False)
+    assert launches == {moin.K_DECODE_BASE: int(kernel == moin.K_DECODE_BASE), moin.K_LINEAR: int(kernel == moin.K_LINEAR)}
+    _check(y, _reference(inp, ids, [1] * S, None, r), d_in, max(r, 8))
+
+
 @pytest.mark.parametrize("r", [64, 24])
 def test_same_bits_as_the_larger_tiles(r):
     d_in, d_out = 192, 4096
