@@ -189,7 +189,8 @@ __global__ __launch_bounds__(mid::NT, NS == 2 ? 2 : 1) void linear_mid_kernel(st
     // stale reads of the last half block may still be under way where another wave's scratch will lie.
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
-    // Epilogue: a lane holds, per accumulator (i, j), token 16 j + lane%16 and outputs 16 i + 4 (lane/16) + 0..3; blocks of
+    // Epilogue, as in linear_stream.hip with half the outputs a wave (one function for both cost that kernel 0.5 %: its registers
+    // are dealt out anew): a lane holds, per accumulator (i, j), token 16 j + lane%16 and outputs 16 i + 4 (lane/16) + 0..3; blocks of
     // 16 tokens are regrouped through the wave's scratch into whole lines of a token's row.
     {
         char *scr = smem + wave * SCR_BYTES;

@@ -362,7 +362,6 @@ bool stream_kernel_fits(const LinearArgs &a)
 
 int prefill_ldu(const LinearArgs &a) { return stream_kernel_fits(a) ? (a.r + 63) / 64 * 64 : a.r; }
 
-
 // n projections that share x, d_in, r and the output type (a[i]: W, B_stack, u_hi, u_lo, y, d_out of
 // projection i; a[0] also x, d_in, r, y_f32)
 hipError_t launch_linear_stream_shared(const PlanView &pv, const LinearArgs *a, int n, int n_cus, hipStream_t stream_)

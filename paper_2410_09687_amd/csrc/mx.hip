@@ -145,8 +145,9 @@ struct Params {
     int n_tiles_n;
     int y_f32;
     // plain mode (decode-sized batches: the base product alone, for all tokens, no
-    // plan): tiles_m row tiles of 256 tokens, the contraction range cut into k_splits
-    // parts of kb_per_split blocks, part s written to y + s * plane_bytes
+    // plan): tiles_m row tiles, the contraction range cut into k_splits parts of
+    // kb_per_split blocks (more than one on 128 x 128 tiles only), part s written to
+    // y + s * plane_bytes
     int plain, tiles_m, k_splits, kb_per_split;
     int64_t plane_bytes;
 };
@@ -729,17 +730,14 @@ bool mx_stream_kernel_fits(int d_in, int r) { return d_in % 128 == 0 && d_in >= 
 // 31.3 / 35.1.  (Beyond the larger tiles' first round about equal: 1152 56 / 52, 5632 outputs 1232 57 / 60.)
 static bool mx_mid_pays(int64_t tiles, int n_cus) { return tiles <= 2 * (int64_t)n_cus; }
 
-// Parts of the contraction range for the plain (decode) base product: enough
-// workgroups to keep many loads in flight, at least two blocks per part, at most
-// four parts (the decode expand kernel sums up to four partial planes).
+// Parts of the contraction range for the plain (decode) base product: a workgroup of the 128 x 128 tiles per compute unit
+// (two per unit lost up to 3 %), at least two blocks per part, at most four parts (the decode expand kernel sums up to
+// four partial planes).  Where the larger tiles run there are more of these than units, hence one part.
 void mx_plain_shape(int64_t T, int d_in, int d_out, int *k_splits, int *kb_per_split)
 {
     const int nkb = d_in / 128;
-    const int64_t tiles = ((T + mxs::BT - 1) / mxs::BT) * ((d_out + mxs::BT - 1) / mxs::BT);
-    int want = (int)((128 + tiles - 1) / (tiles > 0 ? tiles : 1));
-    // (128 x 128 tiles need a workgroup per compute unit: 512 instead of 256 lost up to 3 %)
-    const int64_t small = ((T + mxm::BT - 1) / mxm::BT) * ((d_out + mxm::BT - 1) / mxm::BT);
-    if (mx_mid_pays(small, compute_units())) want = (int)(compute_units() / std::max<int64_t>(small, 1));
+    const int64_t tiles = ((T + mxm::BT - 1) / mxm::BT) * ((d_out + mxm::BT - 1) / mxm::BT);
+    int want = (int)(compute_units() / std::max<int64_t>(tiles, 1));
     if (want > 4) want = 4;
     if (want < 1) want = 1;
     for (;; --want) {
@@ -790,8 +788,8 @@ hipError_t launch_linear_mx_stream(const PlanView &pv, const MxLinearArgs &a, in
     }
     // one workgroup per compute unit (the LDS footprint allows no more), fewer
     // when the batch has fewer tiles than that; always a multiple of 8
-    const int64_t max_work = p.plain ? (int64_t)p.tiles_m * p.n_tiles_n * p.k_splits
-                                     : (int64_t)pv.max_tiles * p.n_tiles_n;
+    if (p.k_splits != 1) return hipErrorInvalidValue;   // (mx_plain_shape)
+    const int64_t max_work = (int64_t)(p.plain ? p.tiles_m : pv.max_tiles) * p.n_tiles_n;
     int64_t grid = n_cus > 0 ? n_cus : 256;
     if (grid > max_work) grid = max_work;
     grid = (grid + 7) / 8 * 8;

@@ -77,8 +77,7 @@ struct Tile {
     const char *q0, *p0;       // x rows / W rows of the tile at k = 0
     const char *uh, *ul, *be;  // adapter operands (aliases of q0 / p0 without adapter)
     int q_rows, p_rows;        // valid tokens (of a plan tile's part: <= 0 where it has none) / outputs
-    int rank;                  // columns of u that count (0: no adapter)
-    int nkb1;                  // adapter blocks per half
+    int nkb1;                  // adapter blocks per half (0: no adapter)
     int total;                 // blocks of the tile: those of the base, 2 * nkb1
     int row0, n0;
     char *y;                   // the projection's output and its width
@@ -118,8 +117,7 @@ __device__ __forceinline__ Tile load_tile(const Params &p, int tm, int tn)
     // adapter blocks up to the expert's own rank (the shrink wrote zeros from there to the block end)
     const int re = min(p.r, uniform(p.tile_rank[pt]));
     const bool lora = e >= 0 && re > 0;
-    t.rank = lora ? re : 0;
-    t.nkb1 = (t.rank + BK - 1) / BK;
+    t.nkb1 = ((lora ? re : 0) + BK - 1) / BK;
     t.total = (p.d_in + BK - 1) / BK + 2 * t.nkb1;
     t.uh = lora ? u_hi + (int64_t)t.row0 * ldu : t.q0;
     t.ul = lora ? u_lo + (int64_t)t.row0 * ldu : t.q0;
