@@ -151,14 +151,19 @@ int moin_histogram(moin_ctx *ctx, const int32_t *ids, int64_t N, int32_t K,
  *                              from the fp32 accumulator) or MOIN_F32
  * Accumulation is fp32; u = s * W_a x is carried as a sum of two bf16 values
  * (high part + remainder) into the expand product.
- * d_in and r must be multiples of 8; d_out a multiple of 8 (bf16 y) or 4.
+ * d_in, d_out and r must be multiples of 8.
+ * A call repeated gives the same bits.  On the prefill path a sequence's bits
+ * depend on its tokens, its adapter and its first row's place in x, not on what
+ * follows it in the batch; on the decode path the order of the fp32 sums also
+ * goes by the number of tokens, and between the two paths results agree to the
+ * rounding of such sums.
  * Small batches (T <= 1024) take the decode path: tokens are grouped by
  * expert so each distinct adapter is read from HBM once.  So do larger batches
  * of short sequences (T <= 128 S, i.e. 128 tokens per sequence on average or
  * fewer, down to one expert per token: "Future Works", per token adapters),
  * where a row tile per sequence would be mostly padding: their base product
- * runs over plain tiles of 256 tokens and the adapter term over the tokens
- * gathered by expert.
+ * runs over plain row tiles and the adapter term over the tokens gathered by
+ * expert.
  */
 int moin_lora_linear(moin_ctx *ctx, const void *x, const int32_t *seq_offsets,
                      const int32_t *expert_ids, int32_t S, int64_t T,

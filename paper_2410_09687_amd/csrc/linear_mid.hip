@@ -10,8 +10,8 @@
 //  * Up to a tile per compute unit: four stages, three blocks in flight; beyond, two workgroups share a unit, two stages
 //    each, and hide each other's waits, starts and epilogues.
 //  * Rows may end anywhere (d_in and r any multiple of 8): in a row's last block the lanes past its end fetch zeros.
-// Us of a call (its shrink of 14-29 us included), 256 x 256 tiles / these: 1890 tokens 2048 -> 2048 59 / 37, 5632 -> 2048
-// 132 / 81; 4096 tokens 2048 -> 2048 58 / 49; 16 384 tokens 2048 -> 256 57 / 37; 256 -> 256 20 / 15.
+// Us of the kernel, 256 x 256 tiles / these: 1536 tokens 2048 -> 2048 43 / 20, 5632 -> 2048 96 / 41; 2560 tokens 43 / 29 and 97 /
+// 66; 4096 tokens 45 / 34; 16 384 tokens 2048 -> 256 41 / 29; 8192 2048 -> 256 40 / 18.
 #include <algorithm>
 #include <type_traits>
 

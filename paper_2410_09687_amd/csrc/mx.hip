@@ -508,8 +508,8 @@ __global__ __launch_bounds__(mxs::NT) void linear_stream4_kernel(mxs::Params p)
 // each), for calls whose 256 x 256 tiles do not fill the chip: the small batches and narrow projections of decode
 // and prefill.  LDS bounds it (see linear_mid.hip); two workgroups share a compute unit, two stages each (four stages and
 // the unit to itself: the same time where there is a tile per unit).
-// Us of a layer, seven projections, 256 x 256 tiles / these: decode of 1 token 167 / 144, 32 196 / 164, 130 245 / 203, 488 359 /
-// 315, 1000 463 / 424; prefill of 1890 tokens 349 / 298, of 4000 441 / 403.
+// Us of a layer, seven projections, 256 x 256 tiles / these: decode of 1 token 167 / 133, 69 225 / 188, 338 327 / 285, 1000 463 /
+// 424.  Of the kernel: 2048 -> 2048 1890 tokens 28 / 20, 4096 30 / 25; 5632 -> 2048 1890 tokens 57 / 42, 4096 61 / 52.
 namespace mxm {
 using mxs::Frag;
 using mxs::NT;

@@ -312,7 +312,9 @@ struct CfgScreenPairs : CfgScreen {
 };
 
 // by_cent: the tiles of one centroid tile are neighbours, so that an XCD reads an eighth of the centroids and every query,
-// where those are the fewer: 1000 x 5000 x 384 in fp32 a call 35 -> 32.5 us (16 000 queries that way: 254 -> 276).
+// where those are the fewer.  Us of a call, by query tile / by centroid tile: fp32 1000 x 5000 x 384 35 / 32.5, 2500 51.8 / 51.2, 4500
+// 76.6 both, 5500 88.4 both, 10 000 148.5 / 149.5, 16 000 254 / 276, 750 x 1500 24.3 / 24.0, 2250 27.1 / 27.6; bf16 with the
+// four nearest 2500 x 5000 x 768 65.4 / 63.6, 4500 95.0 / 94.7, 5500 109.8 / 111.7, 10 000 180 / 195.
 template <bool PAIRS>
 __global__ __launch_bounds__(CfgScreen::NT) void route_screen_kernel(ScreenKParams p, int nqt, int by_cent)
 {

@@ -56,6 +56,7 @@ def test_prefill_ragged_tiles_and_tails():
 
 
 def test_prefill_streaming_kernel_ragged_tiles_mixed_adapters():
+    # (batches of this size run on 128 x 128 tiles; the persistent kernel at such edges: test_gpu_large_batches.py)
     # shapes the persistent streaming kernel takes (d_in, r multiples of 64): ragged
     # token tiles, an output tail of 8 columns, base-only sequences between adapter
     # ones, rank spanning two k blocks

@@ -119,6 +119,7 @@ def _mx_check(inp, what, rows=None, rank_of_expert=None):
 
 
 def test_mx_linear_ragged_tiles_mixed_adapters():
+    # (batches of these sizes run on 128 x 128 tiles; the larger ones at such edges: test_gpu_large_batches.py)
     lens = [300, 1, 0, 257, 255, 512, 77, 256, 3, 640]
     ids = [3, 0, 5, -1, 3, 6, 2, 2, -1, 1]
     inp = _case("mx_ragged", 384, 520, 128, 7, lens, ids, seed=31)

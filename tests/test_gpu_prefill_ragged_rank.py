@@ -1,4 +1,4 @@
-"""Stacks whose rank is not a multiple of 64 through the streaming prefill kernel: one block and several, the first and
+"""Stacks whose rank is not a multiple of 64 on 128 x 128 tiles (on the larger ones: test_gpu_large_batches.py): one block and several, the first and
 the last rank of a block, experts of smaller rank (other experts and rows past the own rank filled with NaN where they
 are never read), ragged tiles, several projections in one call; against torch in fp64."""
 import numpy as np

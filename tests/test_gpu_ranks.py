@@ -52,6 +52,7 @@ def _case(name, d_in, d_out, r, E, lens, ids, seed):
 
 
 def test_prefill_streaming_kernel_with_ranks():
+    # (on 128 x 128 tiles, as the one below; the persistent and the register-staged kernel: test_gpu_large_batches.py)
     lens = [300, 1, 0, 257, 255, 512, 77, 256, 3, 640]
     ids = [3, 0, 5, -1, 3, 6, 2, 2, -1, 1]
     inp = _case("ranked_stream", 192, 520, 128, 7, lens, ids, 31)
@@ -59,7 +60,7 @@ def test_prefill_streaming_kernel_with_ranks():
 
 
 def test_prefill_tiled_kernel_with_ranks():
-    # d_in and r leave tails: the tiled kernels, rank tiles of the 64 x 64 shrink
+    # d_in and r leave tails; rank tiles of the 64 x 64 shrink
     lens = [700, 400, 33]
     inp = _case("ranked_tiled", 328, 264, 136, 4, lens, [2, 0, 1], 32)
     _check(inp, [136, 16, 96, 0], "tiled")
