@@ -145,7 +145,7 @@ __global__ __launch_bounds__(C::NT) void shrink_kernel(ShrinkKParams p)
     // (the sub-tiles of a tile, and the projections that share x, keep one phase so that they meet
     // in L2): 88 -> 70 us for a 65536 x 2048 pass at rank 128.  The phase comes from the tile's
     // position in the batch, not from its place in the by-expert order, and is the same in every
-    // variant of this kernel and in shrink_wave_kernel, so that a row's sum depends neither on how the
+    // variant of this kernel and in shrink_patch_kernel, so that a row's sum depends neither on how the
     // experts are numbered nor on which of them ran.
     const int k_first = (int)(((uint32_t)(row0 - sub * C::BM) / (uint32_t)TILE_M * 5u) % (uint32_t)nkb);
     auto block_of = [=](int it) __attribute__((always_inline)) {
@@ -223,11 +223,27 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, K...>, F f)
     (f(std::integral_constant<int, K>{}), ...);
 }
 
-// x in MXFP8: blocks first, first + step, ... of `rows` (1 to 32) rows, counted from block k_first on, by one wave.  Two
+// x in MXFP8: a lane's 8 values of row `row` (of `rows`, from row0 on) and of the block of 64 from k0 on, lanes 0..7 holding the
+// first of a wave's eight rows.
+__device__ __forceinline__ void quantise_group(const ShrinkKParams &p, const uint4 &v, int row0, int row, int rows, int k0)
+{
+    const int c = threadIdx.x & 7;
+    int E;
+    const uint2 codes = mx_quantize8(v, E);
+    // the two scale bytes of a row's 64 values, into the row's first lane
+    const uint32_t pair = (uint32_t)E | ((uint32_t)dpp_move<DPP_FROM_PLUS4>(E) << 8);
+    if (row < rows) {
+        *reinterpret_cast<uint2 *>(p.xq + (int64_t)(row0 + row) * p.d_in + k0 + c * 8) = codes;
+        if (c == 0)
+            *reinterpret_cast<uint16_t *>(p.xs + ((int64_t)(k0 >> 7) * p.T + row0 + row) * 4 + ((k0 >> 5) & 3)) = (uint16_t)pair;
+    }
+}
+
+// x in MXFP8: blocks first, first + step, ... of `rows` (1 to 8 RG) rows, counted from block k_first on, by one wave.  PF - 1
 // blocks' loads are under way while one is worked on; 8 lanes hold a row's 64 values.
+template <int RG, int PF>
 __device__ __forceinline__ void quantise_rows(const ShrinkKParams &p, int row0, int rows, int k_first, int first, int step)
 {
-    constexpr int RG = 4, PF = 3;   // row groups of 8; blocks in registers
     const int lane = threadIdx.x & 63, c = lane & 7, nkb = p.d_in / 64;
     const int n = (nkb - first + step - 1) / step;
     if (n <= 0) return;
@@ -246,20 +262,8 @@ __device__ __forceinline__ void quantise_rows(const ShrinkKParams &p, int row0, 
         for (int j = 0; j < RG; ++j) g[j] = *reinterpret_cast<const uint4 *>(xa + (off[j] + at));
     };
     auto work = [&](int i, const uint4(&g)[RG]) __attribute__((always_inline)) {
-        const int k0 = block_of(i) * 64;
 #pragma unroll
-        for (int j = 0; j < RG; ++j) {
-            const int row = j * 8 + (lane >> 3);
-            int E;
-            const uint2 codes = mx_quantize8(g[j], E);
-            // the two scale bytes of a row's 64 values, into the row's first lane
-            const uint32_t pair = (uint32_t)E | ((uint32_t)dpp_move<DPP_FROM_PLUS4>(E) << 8);
-            if (row < rows) {
-                *reinterpret_cast<uint2 *>(p.xq + (int64_t)(row0 + row) * p.d_in + k0 + c * 8) = codes;
-                if (c == 0)
-                    *reinterpret_cast<uint16_t *>(p.xs + ((int64_t)(k0 >> 7) * p.T + row0 + row) * 4 + ((k0 >> 5) & 3)) = (uint16_t)pair;
-            }
-        }
+        for (int j = 0; j < RG; ++j) quantise_group(p, g[j], row0, j * 8 + (lane >> 3), rows, block_of(i) * 64);
     };
 #pragma unroll
     for (int u = 0; u < PF; ++u) load(u, v[u]);
@@ -272,33 +276,37 @@ __device__ __forceinline__ void quantise_rows(const ShrinkKParams &p, int row0, 
     }
 }
 
-// The shrink of a batch with few row tiles: the sums of the kernel above, product for product in the same order, so that
-// a sequence's u is the same bits in a batch of any size.  Bound by the chain of a tile's blocks of 64 steps, which the tiles
-// above work off at 0.35 us each, behind a barrier, on as many compute units as there are tiles.  Here a wave has
-// 32 tokens x 16 or 32 columns to itself, blocks that nobody else waits for, and the next block's fragments come to registers under
-// the products of the present one: 0.12 and 0.16 us a block, a wave's own stream of requests, reads and products.  (Six
-// stages of 6 KB or four of 8 KB: 32 columns with eight stages no faster and half as many to a unit.)
-// With codes as well (QW): waves of their own take x straight to registers, since a block's 32 x 64 values cost a wave 0.5 us.
-// Us of the kernel, tiles above / this: 1890 tokens by 2048 at rank 16 14.9 / 8.0, 64 15.0 / 7.8, 128 21 / 8.5, by 5632 at rank 64
-// 32 / 14.5, 128 60 / 17; three projections by 2048 at rank 64 15.9 / 11.6; with codes by 2048 at rank 64 30 / 9.3, by
-// 5632 at rank 128 95 / 22.
-template <int FN_>
-struct WaveCfg {
-    static constexpr int FM = 2, FN = FN_, BM = FM * 16, BN = FN * 16, BK = 64, ROWB = BK * 2;
-    static constexpr int A_I = BM / 8, B_I = BN / 8, LPB = A_I + B_I;   // requests per block, 8 rows each
+// The shrink of batches whose larger tiles do not fill the chip: the sums of the kernel above, product for product in the same
+// order, so that a sequence's u is the same bits in a batch of any size.  Bound by the chain of a tile's blocks of 64 steps,
+// which the tiles above work off at 0.35 us each, on as many compute units as there are tiles; and beyond some 5000 tokens by
+// what the tiles fetch, x once for every tile of columns.  Here a wave holds 32 tokens x 16 or 32 columns, and the next
+// block's fragments come to registers under the products of the present one: 0.12 and 0.16 us a block, the wave's own stream of
+// requests, reads and products.  In the smallest batches a wave is a workgroup, with stages that nobody else waits for; in larger ones
+// two or four share a tile of 64 tokens, and a barrier a block.  (16 columns, us by 5632 of 1890 tokens with cold adapters: four stages 20, six
+// 18.2, eight 15.9, ten 17.1; the others are no faster with six or eight than with four.)
+// With codes as well (QW): waves of their own make them, since a block's 32 x 64 values cost a wave 0.5 us.
+// The rule below gives times.
+template <int FN_, int WM_, int WN_, int NS_>
+struct PatchCfg {
+    static constexpr int FM = 2, FN = FN_, WM = WM_, WN = WN_, NW = WM * WN;
+    static constexpr int BM = WM * FM * 16, BN = WN * FN * 16, BK = 64, ROWB = BK * 2;
+    static constexpr int A_I = BM / 8, B_I = BN / 8, LPB = (A_I + B_I) / NW;   // requests per block, 8 rows each; of a wave
     static constexpr int STAGE_BYTES = (BM + BN) * ROWB;
-    static constexpr int NS = FN == 1 ? 6 : 4, SMEM_BYTES = NS * STAGE_BYTES;
-    static_assert((NS - 1) * LPB < 64 && NS % 2 == 0, "vmcnt field; registers by parity");
+    static constexpr int NS = NS_, SMEM_BYTES = NS * STAGE_BYTES;
+    static_assert((A_I + B_I) % NW == 0 && (NS - 1) * LPB < 64 && NS % 2 == 0, "requests; vmcnt field; registers by parity");
 };
+using CfgPatch16 = PatchCfg<1, 1, 1, 8>;
+using CfgPatch32 = PatchCfg<2, 2, 1, 4>;
+using CfgPatch64 = PatchCfg<2, 2, 2, 4>;
+using CfgPatchWide = PatchCfg<2, 1, 2, 4>;   // with codes at rank 64: x once, and twice as many tiles
 
-// QW: further waves of each workgroup, which write x in MXFP8, each its share of the row tile's blocks, also where there is no
-// adapter.
-template <int FN, int QW>
-__global__ __launch_bounds__(64 * (1 + QW)) void shrink_wave_kernel(ShrinkKParams p)
+// QW: further waves of each workgroup, which write x in MXFP8, also where there is no adapter: beside a single patch each its
+// share of the row tile's blocks, from memory; beside several its share of every block's rows, from LDS.
+template <class C, int QW>
+__global__ __launch_bounds__(64 * (C::NW + QW)) void shrink_patch_kernel(ShrinkKParams p)
 {
-    using C = WaveCfg<FN>;
     extern __shared__ __align__(16) char smem[];
-    constexpr int SUB = TILE_M / C::BM;
+    constexpr int SUB = TILE_M / C::BM, FN = C::FN;
     const int ntm = uniform(*p.n_tiles) * SUB;
     const int id = xcd_band_id(blockIdx.x, ntm * p.n_tiles_n);
     if (id < 0) return;
@@ -310,8 +318,8 @@ __global__ __launch_bounds__(64 * (1 + QW)) void shrink_wave_kernel(ShrinkKParam
     const int nkb = p.d_in / C::BK;
     const int k_first = (int)(((uint32_t)(row0 - sub * C::BM) / (uint32_t)TILE_M * 5u) % (uint32_t)nkb);
     const int wave = uniform(threadIdx.x >> 6);
-    if (QW > 0 && wave > 0) {
-        quantise_rows(p, row0, rows, k_first, tn * QW + wave - 1, p.n_tiles_n * QW);
+    if (QW > 0 && C::NW == 1 && wave > 0) {
+        quantise_rows<4, 3>(p, row0, rows, k_first, tn * QW + wave - 1, p.n_tiles_n * QW);
         return;
     }
     const int e = uniform(p.tile_expert[t]);
@@ -319,8 +327,31 @@ __global__ __launch_bounds__(64 * (1 + QW)) void shrink_wave_kernel(ShrinkKParam
     const int r_read = min(p.ldu, (re + 63) & ~63);   // columns of u that are read: zeros from the rank on
     const int proj = tn / p.tiles_per_proj, tc = tn - proj * p.tiles_per_proj;
     const int n0 = tc * C::BN;
-    // the columns to write: the wave's own, behind the last tile also what is left of a block of 64
+    // the columns to write: the tile's own, behind the last tile also what is left of a block of 64
     const int n_end = tc + 1 == p.tiles_per_proj ? r_read : min(r_read, n0 + C::BN);
+    if constexpr (QW > 0 && C::NW > 1) {
+        if (wave >= C::NW) {
+            const int g0 = wave - C::NW + tc * QW, g_step = QW * p.tiles_per_proj;   // the wave's groups of eight rows
+            if (n0 >= re) {   // (no products, nothing in LDS)
+                for (int g = g0; g * 8 < rows; g += g_step) quantise_rows<1, 6>(p, row0 + g * 8, min(rows - g * 8, 8), k_first, 0, 1);
+                return;
+            }
+            // Block it lies in its stage from the barrier of the turn before on (the first from the one ahead of the
+            // turns) until that of its own turn: as many barriers as the product waves meet.
+            const int l = threadIdx.x & 63;
+            wait_vm_then_barrier<63>();
+            for (int it = 0; it < nkb; ++it) {
+                const char *st = smem + (it % C::NS) * C::STAGE_BYTES;
+                const int kb = it + k_first, k0 = (kb >= nkb ? kb - nkb : kb) * C::BK;
+                for (int g = g0; g < C::BM / 8; g += g_step) {
+                    const int row = g * 8 + (l >> 3);
+                    quantise_group(p, *reinterpret_cast<const uint4 *>(st + row * C::ROWB + (((l & 7) ^ ((row >> 1) & 7)) * 16)), row0, row, rows, k0);
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            }
+            return;
+        }
+    }
     if (n0 >= n_end) return;
     const char *A_stack = p.A_stack;
     char *u_hi = p.u_hi, *u_lo = p.u_lo;
@@ -332,7 +363,8 @@ __global__ __launch_bounds__(64 * (1 + QW)) void shrink_wave_kernel(ShrinkKParam
             u_lo = p.ul_more[i - 1];
         }
 
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wm = wave / C::WN, wn = wave % C::WN;
     f32x4_t acc[C::FM][FN];
 #pragma unroll
     for (int i = 0; i < C::FM; ++i)
@@ -343,14 +375,15 @@ __global__ __launch_bounds__(64 * (1 + QW)) void shrink_wave_kernel(ShrinkKParam
         const char *xa = p.x + (int64_t)row0 * ldx;
         const char *ae = A_stack + ((int64_t)e * p.r + n0) * ldx;
         const int a_rows = min(C::BN, re - n0);
-        // as in DmaCore: 8 rows of 128 bytes a request, 16-byte chunks XORed with swz(row) = (row >> 1) & 7
-        const uint32_t c16a = (((uint32_t)lane & 7) ^ ((uint32_t)lane >> 4)) * 16, c16b = c16a ^ 64u;   // even, odd requests
+        // as in DmaCore: 8 rows of 128 bytes a request, 16-byte chunks XORed with swz(row) = (row >> 1) & 7; x's rows, then A's
         uint32_t off[C::LPB];
 #pragma unroll
         for (int j = 0; j < C::LPB; ++j) {
-            const bool a = j < C::A_I;
-            const int row = (a ? j : j - C::A_I) * 8 + (lane >> 3);
-            off[j] = (uint32_t)min(row, (a ? rows : a_rows) - 1) * ldx + ((j & 1) ? c16b : c16a);
+            const int g = wave * C::LPB + j;
+            const bool a = g < C::A_I;
+            const int row = (a ? g : g - C::A_I) * 8 + (lane >> 3);
+            const uint32_t c16 = (((uint32_t)lane & 7) ^ ((uint32_t)lane >> 4) ^ ((uint32_t)(g & 1) * 4u)) * 16;
+            off[j] = (uint32_t)min(row, (a ? rows : a_rows) - 1) * ldx + c16;
         }
         auto kbyte_of = [&](int it) __attribute__((always_inline)) {
             const int kb = it + k_first;
@@ -359,26 +392,31 @@ __global__ __launch_bounds__(64 * (1 + QW)) void shrink_wave_kernel(ShrinkKParam
             return k;
         };
         auto issue_one = [&](uint32_t kbyte, char *st, int j) __attribute__((always_inline)) {
-            __builtin_amdgcn_global_load_lds(MOIN_GPTR((j < C::A_I ? xa : ae) + (off[j] + kbyte)), MOIN_LPTR(st + j * 1024), 16, 0, 0);
+            const int g = wave * C::LPB + j;
+            __builtin_amdgcn_global_load_lds(MOIN_GPTR((g < C::A_I ? xa : ae) + (off[j] + kbyte)), MOIN_LPTR(st + g * 1024), 16, 0, 0);
         };
         auto stage = [&](int it) __attribute__((always_inline)) { return smem + (it % C::NS) * C::STAGE_BYTES; };
         // fragments: row lane % 16 of 16, the second half of a block at the first one's address ^ 64; of the tokens, then the columns
         const int lo = (lane & 15) * C::ROWB | ((((lane >> 4) ^ ((lane & 15) >> 1)) & 7) * 16);
+        const int base_x = wm * (C::FM * 16) * C::ROWB, base_a = (C::BM + wn * (FN * 16)) * C::ROWB;
         constexpr int F = C::FM + FN, R = 2 * F, M = 2 * C::FM * FN;   // fragments of a half; reads and products of a block
         bf16x8_t fr[2][R];
         auto read_one = [&](const char *st, int set, int n) __attribute__((always_inline)) {
-            fr[set][n] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(st + (n % F) * 16 * C::ROWB + (lo ^ (n / F * 64))));
+            const int f = n % F, at = f < C::FM ? base_x + f * 16 * C::ROWB : base_a + (f - C::FM) * 16 * C::ROWB;
+            fr[set][n] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(st + at + (lo ^ (n / F * 64))));
         };
         auto product = [&](int set, int n) __attribute__((always_inline)) {
             const int ks = n / (M / 2), i = n % (M / 2) / FN, j = n % FN;
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[set][ks * F + C::FM + j], fr[set][ks * F + i], acc[i][j], 0, 0, 0);
         };
         // Block it, whose fragments are in registers behind the wait.  LEFT blocks beyond the next one may still be under way;
-        // its stage, read out, takes block it + NS (MORE), the next block's fragments come to the other registers (NEXT).
+        // its stage, read out (by all waves, behind the barrier), takes block it + NS (MORE), the next block's fragments come to
+        // the other registers (NEXT).
         auto turn = [&](int it, auto set_tag, auto left_tag, auto more_tag, auto next_tag) __attribute__((always_inline)) {
             constexpr int SET = decltype(set_tag)::value, LEFT = decltype(left_tag)::value;
             constexpr bool MORE = decltype(more_tag)::value, NEXT = decltype(next_tag)::value;
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LEFT * C::LPB) : "memory");
+            if constexpr (C::NW == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LEFT * C::LPB) : "memory");
+            else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT * C::LPB) : "memory");
             const uint32_t kbyte = MORE ? kbyte_of(it + C::NS) : 0;
             char *cur = stage(it);
             const char *nxt = stage(it + 1);
@@ -403,6 +441,10 @@ __global__ __launch_bounds__(64 * (1 + QW)) void shrink_wave_kernel(ShrinkKParam
 #pragma unroll
             for (int j = 0; j < C::LPB; ++j) issue_one(kbyte, stage(it), j);
         };
+        auto landed = [](auto left_tag) __attribute__((always_inline)) {
+            if constexpr (C::NW == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(decltype(left_tag)::value * C::LPB) : "memory");
+            else wait_vm_then_barrier<decltype(left_tag)::value * C::LPB>();
+        };
         auto read_block = [&](int it, int set) __attribute__((always_inline)) {
 #pragma unroll
             for (int n = 0; n < R; ++n) read_one(stage(it), set, n);
@@ -410,7 +452,7 @@ __global__ __launch_bounds__(64 * (1 + QW)) void shrink_wave_kernel(ShrinkKParam
         if (nkb >= C::NS) {
 #pragma unroll
             for (int s = 0; s < C::NS; ++s) fetch(s);
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((C::NS - 1) * C::LPB) : "memory");
+            landed(std::integral_constant<int, C::NS - 1>{});
             const int more = nkb - C::NS;   // turns that fetch; the first of an odd number by itself, so that the last NS begin with set 0
             int it = 0;
             if (more & 1) {
@@ -431,7 +473,7 @@ __global__ __launch_bounds__(64 * (1 + QW)) void shrink_wave_kernel(ShrinkKParam
             });
         } else {
             for (int s = 0; s < nkb; ++s) fetch(s);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            landed(S0{});
             for (int it = 0; it < nkb; ++it) {
                 read_block(it, 0);
                 turn(it, S0{}, S0{}, F_{}, F_{});
@@ -441,24 +483,26 @@ __global__ __launch_bounds__(64 * (1 + QW)) void shrink_wave_kernel(ShrinkKParam
 
     // a lane holds, per accumulator (i, j), token 16 i + lane % 16 and columns 16 j + 4 (lane / 16) + 0..3
     const int64_t ldu = (int64_t)p.ldu * 2;
+    const int n0w = n0 + wn * (FN * 16);
 #pragma unroll
     for (int i = 0; i < C::FM; ++i) {
-        const int row = i * 16 + (lane & 15);
+        const int row = wm * (C::FM * 16) + i * 16 + (lane & 15);
         if (row >= rows) continue;
         const int64_t at = (int64_t)(row0 + row) * ldu;
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-            const int col = n0 + j * 16 + 4 * (lane >> 4);
+            const int col = n0w + j * 16 + 4 * (lane >> 4);
             if (col >= n_end) continue;
             uint2 hi, lo;
             u_pair(acc[i][j], re - col, p.act, p.scale, hi, lo);
             *reinterpret_cast<uint2 *>(u_hi + at + col * 2) = hi;
             *reinterpret_cast<uint2 *>(u_lo + at + col * 2) = lo;
         }
-        for (int col = n0 + C::BN + 4 * (lane >> 4); col < n_end; col += 16) {
-            *reinterpret_cast<uint2 *>(u_hi + at + col * 2) = make_uint2(0, 0);
-            *reinterpret_cast<uint2 *>(u_lo + at + col * 2) = make_uint2(0, 0);
-        }
+        if (wn + 1 == C::WN)
+            for (int col = n0 + C::BN + 4 * (lane >> 4); col < n_end; col += 16) {
+                *reinterpret_cast<uint2 *>(u_hi + at + col * 2) = make_uint2(0, 0);
+                *reinterpret_cast<uint2 *>(u_lo + at + col * 2) = make_uint2(0, 0);
+            }
     }
 }
 
@@ -496,10 +540,12 @@ hipError_t prepare_linear_kernels()
 {
     hipError_t e;
     if ((e = prepare_stream_kernel()) != hipSuccess) return e;
-    if ((e = allow_lds(&shrink_wave_kernel<1, 0>, WaveCfg<1>::SMEM_BYTES)) != hipSuccess) return e;
-    if ((e = allow_lds(&shrink_wave_kernel<2, 0>, WaveCfg<2>::SMEM_BYTES)) != hipSuccess) return e;
-    if ((e = allow_lds(&shrink_wave_kernel<1, 1>, WaveCfg<1>::SMEM_BYTES)) != hipSuccess) return e;
-    if ((e = allow_lds(&shrink_wave_kernel<2, 2>, WaveCfg<2>::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_patch_kernel<CfgPatch16, 0>, CfgPatch16::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_patch_kernel<CfgPatch32, 0>, CfgPatch32::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_patch_kernel<CfgPatch64, 0>, CfgPatch64::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_patch_kernel<CfgPatch16, 1>, CfgPatch16::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_patch_kernel<CfgPatchWide, 4>, CfgPatchWide::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&shrink_patch_kernel<CfgPatch64, 4>, CfgPatch64::SMEM_BYTES)) != hipSuccess) return e;
     if ((e = allow_lds(&linear_kernel<CfgMain>, CfgMain::SMEM_BYTES)) != hipSuccess) return e;
     if ((e = allow_lds(&linear_kernel<CfgThin>, CfgThin::SMEM_BYTES)) != hipSuccess) return e;
     if ((e = allow_lds(&linear_kernel<CfgDecodeBase>, CfgDecodeBase::SMEM_BYTES)) != hipSuccess) return e;
@@ -574,35 +620,40 @@ static hipError_t launch_shrink_as(const PlanView &pv, const LinearArgs &a, hipS
     return hipGetLastError();
 }
 
-template <int FN, int QW = 0>
-static hipError_t launch_shrink_wave(const PlanView &pv, const LinearArgs &a, const SharedX *shared, hipStream_t stream,
-                                     void *xq = nullptr, void *xs = nullptr)
+template <class C, int QW = 0>
+static hipError_t launch_shrink_patch(const PlanView &pv, const LinearArgs &a, const SharedX *shared, hipStream_t stream,
+                                      void *xq = nullptr, void *xs = nullptr)
 {
-    using C = WaveCfg<FN>;
     ShrinkKParams p;
     const int64_t grid = shrink_params(p, pv, a, shared, xq, xs, C::BM, C::BN);
     if (grid < 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((shrink_wave_kernel<FN, QW>), dim3((unsigned)round_up8((int)grid)), dim3(64 * (1 + QW)), C::SMEM_BYTES, stream, p);
+    hipLaunchKernelGGL((shrink_patch_kernel<C, QW>), dim3((unsigned)round_up8((int)grid)), dim3(64 * (C::NW + QW)), C::SMEM_BYTES, stream, p);
     return hipGetLastError();
 }
 
-// Columns per wave (16 or 32) of the form with a wave per patch, 0 where the larger tiles are the faster form.  Us of the
-// kernel, by 2048 / 5632:
-//  * 16 or 32 columns: 1890 tokens at rank 64 7.8, 14.5 and 9.2, 16.4; 512 waves of 16 columns (4096 tokens, rank 64) 8.2, 15.9
-//    and 9.3, 17.3; 768 (4096 tokens, three at rank 64; 8192, two at rank 32) 20.3, 30.5 and 14.4, 21.6.
-//  * 32 columns or the larger tiles.  Rank 64, 768 waves of 32 columns (12 288 tokens) 13.9, 28.8 and 16.0, 32.0; 1024 (8192,
-//    two projections) 18.8, 38.8 and 16.9, 33.6.  Those of rank 128 are four times as large: 1536 waves (12 288 tokens) 26.6, 65.8 and
-//    28.0, 66.4; 2048 (8192, two) 27.4, 67.2 and 26.6, 65.1.  Up to rank 32 half of a larger tile is padding: 584 row
-//    tiles (18 700 tokens) 16.4, 38.2 and 17.8, 42.8, three 29.1 and 30.9; 1024 (32 768) 24.4, 72.2 and 23.4, 65.0.
-//  * With codes the same lines: 768 waves at rank 64 22.8, 67.7 and 32.8, 74.5; 1168 (18 700 tokens) 32.9, 123 and 34.1, 97.
-static int shrink_wave_columns(const PlanView &pv, const LinearArgs &a, int n_proj)
+// Which form of shrink_patch_kernel: 16 (a wave by itself), 32, 64 (columns of the tiles below), or 0 where the larger tiles are
+// as fast.  Us of the kernel, by 2048 / 5632, x in the Infinity Cache and adapters from HBM ("cold") or all of it at hand ("hot"):
+//  * 16 up to two of its waves per compute unit.  Rank 64, against 32: 1890 tokens hot 8.6, 15.9 / 9.4, 18.3; 8192 tokens (1024 waves) cold 22.5,
+//    56.6 / 17.7, 42.4.  At rank 16 and less up to the line of rank 32: 18 700 tokens cold 24.1, 61.5 / 24.6, 63.4 / larger tiles 27.5, 70.2.
+//  * 32 (64 tokens x 32 columns) up to rank 64.  Rank 32, against the larger tiles, half of which is padding: 18 700 tokens (584 row
+//    tiles) hot 18.5, 44 / 18.6, 50, cold 29.4, 75 / 30.2, 78; three projections cold 48.4 / 48.2.  Rank 64, 32 / 64 / larger: 8192 tokens (512 patches of
+//    32 x 32) hot 10.9, 20.4 / 12.1, 22.4 / 16.0, 32.8, cold 17.7, 42.4 / 22.9, 50.1 / 22.0, 51.0.
+//  * 64 (64 x 64).  Rank 64, two projections, 64 / larger: 8192 tokens (1024 patches) hot - , 24.9 / 33.8, cold 53.6 / 53.1; 12 288 (1536)
+//    hot 40.9 / 39.7, cold 92 / 87.  Rank 128, whose larger tiles are four times as large: 8192 tokens hot 12.3, 24.3 / 28.7, 65.8,
+//    cold 22.4, 53.6 / 46.7, 110; 12 288, two by 5632 (3072 patches) hot 81 / 90, cold 128 / 131; 18 700, two (4672) 141 / 129, 181 / 162.
+//  * With codes, 16 / 32 (32 x 64) or 64 / larger: rank 64, 4700 tokens hot 15.2, 37 / 17.4, 37 / 32, 74, 8192 cold 29, 80 / 24, 57 / 39, 95,
+//    12 288 (768 patches) cold 35, 91 (32) / 42, 108, 18 700 hot 30, 108 (32) / 34, 99; rank 128, 1890 tokens hot 10.2, 22 / 18.3, 38 / 39, 95,
+//    8192 cold 41, 117 / 27, 70 / 50, 119, 12 288 (1536) 44, 115 (64) / 56, 135, 18 700 hot 37, 126 (64) / 45, 123.
+static int shrink_patch(const PlanView &pv, const LinearArgs &a, int n_proj, bool codes)
 {
     if (a.d_in % 64 || a.r > 128) return 0;
     const int64_t tiles = host_tiles(pv, 32), cus = compute_units();
+    const int64_t patches = tiles * ((a.r + 31) / 32) * n_proj;
     if (tiles * ((a.r + 15) / 16) * n_proj <= 2 * cus) return 16;
-    const int64_t waves = tiles * ((a.r + 31) / 32) * n_proj;
-    if ((a.r <= 32 ? tiles : a.r <= 64 ? waves : waves / 2) > 3 * cus) return 0;
-    return a.r <= 16 ? 16 : 32;
+    if (a.r > 64) return patches <= (codes ? 6 : 12) * cus ? 64 : 0;
+    if (codes) return patches <= 3 * cus ? 32 : 0;
+    if (a.r <= 32) return tiles > 3 * cus ? 0 : a.r <= 16 ? 16 : 32;
+    return patches <= 2 * cus ? 32 : patches <= 4 * cus ? 64 : 0;
 }
 
 // The prefill shrink and the MXFP8 quantisation of x in one pass over x (r >= 1,
@@ -612,9 +663,10 @@ hipError_t launch_prefill_shrink_quant(const PlanView &pv, const LinearArgs &a, 
 {
     if (pv.max_tiles <= 0) return hipSuccess;
     if (a.r <= 0 || a.d_in % 128) return hipErrorInvalidValue;
-    switch (shrink_wave_columns(pv, a, 1)) {
-    case 16: return launch_shrink_wave<1, 1>(pv, a, nullptr, stream, xq, xs);
-    case 32: return launch_shrink_wave<2, 2>(pv, a, nullptr, stream, xq, xs);
+    switch (shrink_patch(pv, a, 1, true)) {
+    case 16: return launch_shrink_patch<CfgPatch16, 1>(pv, a, nullptr, stream, xq, xs);
+    case 32: return launch_shrink_patch<CfgPatchWide, 4>(pv, a, nullptr, stream, xq, xs);
+    case 64: return launch_shrink_patch<CfgPatch64, 4>(pv, a, nullptr, stream, xq, xs);
     }
     if (a.r > 64 && a.r <= 128) return launch_shrink_as<CfgShrinkDeep, true>(pv, a, stream, xq, xs);
     return launch_shrink_as<CfgShrinkDeep64, true>(pv, a, stream, xq, xs);
@@ -623,9 +675,10 @@ hipError_t launch_prefill_shrink_quant(const PlanView &pv, const LinearArgs &a, 
 static hipError_t launch_prefill_shrink_any(const PlanView &pv, const LinearArgs &a, const SharedX *shared, hipStream_t stream)
 {
     if (a.r <= 0 || pv.max_tiles <= 0) return hipSuccess;
-    switch (shrink_wave_columns(pv, a, shared ? shared->n : 1)) {
-    case 16: return launch_shrink_wave<1>(pv, a, shared, stream);
-    case 32: return launch_shrink_wave<2>(pv, a, shared, stream);
+    switch (shrink_patch(pv, a, shared ? shared->n : 1, false)) {
+    case 16: return launch_shrink_patch<CfgPatch16>(pv, a, shared, stream);
+    case 32: return launch_shrink_patch<CfgPatch32>(pv, a, shared, stream);
+    case 64: return launch_shrink_patch<CfgPatch64>(pv, a, shared, stream);
     }
     if (a.d_in % 64 == 0 && a.r > 64 && a.r <= 128)
         return launch_shrink_as<CfgShrinkR128>(pv, a, stream, nullptr, nullptr, shared);

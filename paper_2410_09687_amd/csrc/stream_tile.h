@@ -17,14 +17,15 @@ struct HalfTiles {
     __device__ __forceinline__ HalfTiles(const int *tile_rows, const int *n_tiles_, int max_tiles)
     {
         const int lane = threadIdx.x & 63;
-        int rows[CHUNKS];
-#pragma unroll
-        for (int i = 0; i < CHUNKS; ++i) rows[i] = i * 64 + lane < max_tiles ? tile_rows[i * 64 + lane] : 0;
+        const int first = lane < max_tiles ? tile_rows[lane] : 0;   // (under way with the number of tiles)
         n_tiles = uniform(*n_tiles_);
-        count = n_tiles;
+        second[0] = __ballot(lane < n_tiles && first > TILE_M / 2);
+        count = n_tiles + __popcll(second[0]);
+        if (n_tiles <= 64) return;
 #pragma unroll
-        for (int i = 0; i < CHUNKS; ++i) {
-            second[i] = __ballot(i * 64 + lane < n_tiles && rows[i] > TILE_M / 2);
+        for (int i = 1; i < CHUNKS; ++i) {
+            const int rows = i * 64 + lane < min(n_tiles, max_tiles) ? tile_rows[i * 64 + lane] : 0;
+            second[i] = __ballot(rows > TILE_M / 2);
             count += __popcll(second[i]);
         }
         if (n_tiles > 64 * CHUNKS) count = 2 * n_tiles;
@@ -33,19 +34,24 @@ struct HalfTiles {
     __device__ __forceinline__ int find(int j) const
     {
         if (n_tiles > 64 * CHUNKS) return j;
-        const int lane = threadIdx.x & 63;
+        if (n_tiles <= 64) return find_in(0, j);
         int at = 0;
 #pragma unroll
         for (int i = 0; i < CHUNKS; ++i) {
-            const int n = min(max(n_tiles - i * 64, 0), 64), halves = n + __popcll(second[i]);
-            if (j >= 0 && j < halves) {
-                auto before = [&](int t) { return t + __popcll(second[i] & ((1ull << t) - 1)); };   // halves of the chunk's first t tiles
-                const int t = __popcll(__ballot(lane < n && before(lane) <= j)) - 1;
-                at = (i * 64 + t) * 2 + j - before(t);
-            }
+            const int halves = min(max(n_tiles - i * 64, 0), 64) + __popcll(second[i]);
+            if (j >= 0 && j < halves) at = find_in(i, j);
             j -= halves;
         }
-        return uniform(at);
+        return at;
+    }
+
+private:
+    __device__ __forceinline__ int find_in(int i, int j) const   // j: counted from the chunk's first half
+    {
+        const int lane = threadIdx.x & 63;
+        auto before = [&](int t) { return t + __popcll(second[i] & ((1ull << t) - 1)); };   // halves of the chunk's first t tiles
+        const int t = __popcll(__ballot(i * 64 + lane < n_tiles && before(lane) <= j)) - 1;
+        return uniform((i * 64 + t) * 2 + j - before(t));
     }
 };
 

@@ -105,11 +105,11 @@ def test_gathered(d_in, r, f32):
     _compare(y, _reference(inp, ids, [1] * S, None, r), d_in, max(r, 8))
 
 
-@pytest.mark.parametrize("d_in,r,times", [(64, 24, 10), (192, 32, 10), (320, 64, 10), (192, 72, 10), (704, 128, 10), (128, 136, 1)])
+@pytest.mark.parametrize("d_in,r,times", [(64, 24, 10), (192, 32, 10), (320, 64, 10), (192, 72, 14), (704, 128, 10), (128, 136, 1)])
 def test_shrink(d_in, r, times):
     lens, ids = LENS * times, np.tile(IDS, times)
     if r <= 128:
-        _beyond(lens, 32, 1 if r <= 32 else -(-r // 32) / (2 if r > 64 else 1), 3)
+        _beyond(lens, 32, 1 if r <= 32 else -(-r // 32), 3 if r <= 32 else 4 if r <= 64 else 12)
     inp = _inputs(lens, ids, d_in, 8, r, d_in + r)
     rk = _own_ranks(inp, r, True)
     print(f"[gpu] shrink of many row tiles d_in={d_in} r={r}", flush=True)
@@ -170,7 +170,7 @@ def test_quantised_gathered(d_in, r):
 def test_quantising_shrink(d_in, r, times):
     lens, ids, ctx = LENS * times, np.tile(IDS, times), gc.ctx()
     if r <= 128:
-        _beyond(lens, 32, -(-r // 32) / (2 if r > 64 else 1), 3)
+        _beyond(lens, 32, -(-r // 32), 6 if r > 64 else 3)
     T = sum(lens)
     inp = _inputs(lens, ids, d_in, 72, r, d_in + r)
     rk = _own_ranks(inp, r, True)

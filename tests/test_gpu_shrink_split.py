@@ -1,4 +1,5 @@
-"""The shrink of few row tiles, a wave per 32 tokens and 16 or (in the batches of 40 sequences) 32 columns: row counts around a
+"""The shrink of few row tiles, a wave per 32 tokens and 16 columns by itself or (in the batches of 30 and 40 sequences) in tiles of
+64 x 32 and 64 x 64, on a quantised base 32 x 64 and 64 x 64: row counts around a
 tile, fewer blocks of 64 than stages to many more, every width, ranks that end inside one, on a bf16 and (codes made on the
 way, and given) an MXFP8 base; against torch in fp64, and codes against the quantiser's."""
 import numpy as np
@@ -26,7 +27,8 @@ def _inputs(d_in, d_out, r, times=1):
 
 
 @pytest.mark.parametrize("d_in,r,ranked", [(64, 8, False), (128, 16, True), (192, 32, False), (320, 40, True), (704, 64, False),
-                                           (2048, 64, True), (256, 72, True), (1344, 96, False), (5632, 128, True)])
+                                           (2048, 64, True), (256, 72, True), (1344, 96, False), (5632, 128, True), (512, 16, False),
+                                           (576, 40, True)])
 def test_against_fp64(d_in, r, ranked):
     inp = _inputs(d_in, 72, r)
     rk = torch.tensor([r, 8, max(8, r - 8), 0, 8], dtype=torch.int32, device="cuda") if ranked else None
@@ -37,12 +39,13 @@ def test_against_fp64(d_in, r, ranked):
     _check(y, _reference(inp, IDS, LENS, rk, r), d_in, r)
 
 
-@pytest.mark.parametrize("d_in,r,ranked", [(64, 24, False), (192, 32, True), (256, 40, False), (320, 64, True), (704, 72, False),
-                                           (2048, 64, False), (1344, 128, True)])
-def test_wider_patches_against_fp64(d_in, r, ranked):
-    inp, ids, lens = _inputs(d_in, 72, r, 4), np.tile(IDS, 4), LENS * 4
+@pytest.mark.parametrize("d_in,r,ranked,times", [
+    (64, 24, False, 4), (192, 32, True, 4), (256, 40, False, 3), (320, 64, True, 3), (1408, 48, True, 3),
+    (128, 40, True, 4), (256, 64, False, 4), (704, 72, False, 4), (2048, 64, False, 4), (1344, 128, True, 4), (192, 96, True, 4)])
+def test_wider_patches_against_fp64(d_in, r, ranked, times):
+    inp, ids, lens = _inputs(d_in, 72, r, times), np.tile(IDS, times), LENS * times
     rk = torch.tensor([r, 8, max(8, r - 8), 0, 8], dtype=torch.int32, device="cuda") if ranked else None
-    print(f"[gpu] shrink, 32 columns a wave, d_in={d_in} r={r} ranked={ranked}", flush=True)
+    print(f"[gpu] shrink, tiles of several waves, d_in={d_in} r={r} ranked={ranked}", flush=True)
     y = moin.moin_lora_linear(gc.ctx(), inp.x, inp.seq_offsets, inp.expert_ids, inp.W, inp.A_stack, inp.B_stack, 2.0,
                               y_dtype=torch.float32, rank_of_expert=rk)
     gc.ctx().check()
