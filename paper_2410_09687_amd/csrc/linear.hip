@@ -282,8 +282,8 @@ __device__ __forceinline__ void quantise_rows(const ShrinkKParams &p, int row0, 
 // what the tiles fetch, x once for every tile of columns.  Here a wave holds 32 tokens x 16 or 32 columns, and the next
 // block's fragments come to registers under the products of the present one: 0.12 and 0.16 us a block, the wave's own stream of
 // requests, reads and products.  In the smallest batches a wave is a workgroup, with stages that nobody else waits for; in larger ones
-// two or four share a tile of 64 tokens, and a barrier a block.  (16 columns, us by 5632 of 1890 tokens with cold adapters: four stages 20, six
-// 18.2, eight 15.9, ten 17.1; the others are no faster with six or eight than with four.)
+// two or four share a tile of 64 tokens, and a barrier a block.  (16 columns, us by 5632 of 1890 tokens with adapters from HBM: six stages
+// 18.2, eight 15.9, ten 17.1; tiles of several waves are no faster with six than with four.)
 // With codes as well (QW): waves of their own make them, since a block's 32 x 64 values cost a wave 0.5 us.
 // The rule below gives times.
 template <int FN_, int WM_, int WN_, int NS_>
@@ -638,8 +638,8 @@ static hipError_t launch_shrink_patch(const PlanView &pv, const LinearArgs &a, c
 //  * 32 (64 tokens x 32 columns) up to rank 64.  Rank 32, against the larger tiles, half of which is padding: 18 700 tokens (584 row
 //    tiles) hot 18.5, 44 / 18.6, 50, cold 29.4, 75 / 30.2, 78; three projections cold 48.4 / 48.2.  Rank 64, 32 / 64 / larger: 8192 tokens (512 patches of
 //    32 x 32) hot 10.9, 20.4 / 12.1, 22.4 / 16.0, 32.8, cold 17.7, 42.4 / 22.9, 50.1 / 22.0, 51.0.
-//  * 64 (64 x 64).  Rank 64, two projections, 64 / larger: 8192 tokens (1024 patches) hot - , 24.9 / 33.8, cold 53.6 / 53.1; 12 288 (1536)
-//    hot 40.9 / 39.7, cold 92 / 87.  Rank 128, whose larger tiles are four times as large: 8192 tokens hot 12.3, 24.3 / 28.7, 65.8,
+//  * 64 (64 x 64).  Rank 64, two projections, 64 / larger: 8192 tokens by 5632 (1024 patches) hot 24.9 / 33.8, cold 53.6 / 53.1; 12 288
+//    (1536) hot 40.9 / 39.7, cold 92 / 87.  Rank 128, whose larger tiles are four times as large: 8192 tokens hot 12.3, 24.3 / 28.7, 65.8,
 //    cold 22.4, 53.6 / 46.7, 110; 12 288, two by 5632 (3072 patches) hot 81 / 90, cold 128 / 131; 18 700, two (4672) 141 / 129, 181 / 162.
 //  * With codes, 16 / 32 (32 x 64) or 64 / larger: rank 64, 4700 tokens hot 15.2, 37 / 17.4, 37 / 32, 74, 8192 cold 29, 80 / 24, 57 / 39, 95,
 //    12 288 (768 patches) cold 35, 91 (32) / 42, 108, 18 700 hot 30, 108 (32) / 34, 99; rank 128, 1890 tokens hot 10.2, 22 / 18.3, 38 / 39, 95,
