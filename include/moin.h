@@ -163,7 +163,9 @@ int moin_histogram(moin_ctx *ctx, const int32_t *ids, int64_t N, int32_t K,
  * fewer, down to one expert per token: "Future Works", per token adapters),
  * where a row tile per sequence would be mostly padding: their base product
  * runs over plain row tiles and the adapter term over the tokens gathered by
- * expert.
+ * expert.  Of these batches, calls with 320 tokens and more, 64 per sequence
+ * on average or more, go by d_in and r as well: the prefill path where that is
+ * the shorter one.
  */
 int moin_lora_linear(moin_ctx *ctx, const void *x, const int32_t *seq_offsets,
                      const int32_t *expert_ids, int32_t S, int64_t T,

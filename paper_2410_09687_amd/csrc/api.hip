@@ -210,7 +210,7 @@ int drain_spans(moin_ctx *ctx)
 struct PlanLayout {
     size_t tile_row0, tile_rows, tile_expert, tile_rank, n_tiles, tok_sorted, grp_meta,
         grp_start, grp_tmp, n_groups, keys, tmp, plain, total;
-    int max_tiles, max_groups, max_plain, decode;
+    int max_tiles, max_groups, max_plain, decode, tiles;
 };
 
 // upper_bound: sizes that hold the plan of ANY batch of at most S sequences and T tokens
@@ -226,6 +226,7 @@ PlanLayout plan_layout(int32_t S, int64_t T, int32_t E, bool upper_bound = false
             if (T > step) cut = std::max(cut, group_chunk_records(step));
     const int64_t groups = std::min<int64_t>(S, (int64_t)E + 1) + cut;
     L.decode = upper_bound || ((T <= DECODE_MAX_T || T <= (int64_t)GATHER_MAX_AVG_LEN * S) && groups <= 65535);
+    L.tiles = !L.decode || upper_bound || (T >= BOTH_MIN_T && T >= (int64_t)BOTH_MIN_AVG_LEN * S);
     L.max_tiles = (int)(T / TILE_M) + S + 1;
     L.max_groups = L.decode ? (int)std::min<int64_t>(groups, 65535) : 0;
     size_t npow2 = 1;
@@ -252,6 +253,33 @@ PlanLayout plan_layout(int32_t S, int64_t T, int32_t E, bool upper_bound = false
     L.plain = take(((size_t)4 * L.max_plain + 1) * 4);
     L.total = off;
     return L;
+}
+
+// Whether a call takes its tokens gathered by expert (the decode kernels) rather than in row tiles of a sequence each.  Only
+// where the plan has both is there a choice.  Row tiles: two kernels that fill their tiles, fp32 sums that never leave the
+// registers and, from a few hundred tokens on, matrix rates the gathered base product does not reach; but a chain of
+// d_in / 64 blocks in one workgroup, half-empty tiles under short sequences, and with low ranks the adapter term, which
+// costs the gathered kernels a pass over fp32 planes, is cheap there too.  So the line goes by d_in, rank, tokens and
+// tokens per sequence -- not by d_out: projections that share a call take the same way as calls of their own.
+// Us of a call, gathered / row tiles (S x tokens each):
+//  1024 -> 1416 rank 8 4 x 96 25 / 22, 8 x 64 25 / 22, 32 x 64 37 / 29, rank 128 4 x 250 34 / 22, 64 x 100 107 / 51; 256 -> 256
+//   rank 8 4 x 96 15 / 16, 14 x 96 27 / 16
+//  2048 -> 2048 rank 8 4 x 250 34 / 32, 32 x 64 45 / 48, 32 x 96 56 / 48, rank 64 4 x 96 25 / 28, 4 x 160 32 / 29, 32 x 64 51 / 47,
+//   rank 128 4 x 96 30 / 28, 8 x 120 41 / 30, 64 x 100 136 / 87
+//  2048 -> 5632 rank 8 4 x 250 58 / 43, 8 x 64 37 / 42, 32 x 64 78 / 105, 64 x 100 217 / 231, rank 128 4 x 160 58 / 41, 64 x 64 200 / 206
+//  5632 -> 2048 rank 32 4 x 250 63 / 62, 14 x 96 72 / 65, 64 x 100 176 / 199, rank 64 8 x 96 58 / 55, 4 x 160 47 / 55, 64 x 64 152 / 182,
+//   rank 128 4 x 160 58 / 56, 4 x 96 43 / 55
+//  a layer of seven projections, rank 16 8 x 80 181 / 187, 8 x 112 221 / 191, 14 x 80 315 / 238; rank 128 8 x 48 168 / 173, 4 x 96
+//   164 / 144, 1 x 640 227 / 155, 14 x 96 475 / 273; on an MXFP8 base rank 64 4 x 96 206 / 199, 32 x 64 391 / 383, 32 x 96 560 / 417
+bool gathered_pays(const PlanView &pv, int d_in, int r)
+{
+    if (!pv.decode || !pv.tiles || r <= 0 || r > 128) return pv.decode;
+    const int rank = r < 48 ? 0 : r < 96 ? 1 : 2, deep = d_in <= 1024 ? 0 : d_in <= 3072 ? 1 : 2;
+    static constexpr int min_tokens[3][3] = {{384, BOTH_MIN_T, BOTH_MIN_T}, {768, 512, 384}, {DECODE_MAX_T + 1, 768, 640}};
+    int min_len = rank == 0 ? (deep == 0 ? 80 : 96) : rank == 1 ? (deep == 0 ? BOTH_MIN_AVG_LEN : 72) : BOTH_MIN_AVG_LEN;
+    if (pv.T > DECODE_MAX_T && rank == 1 && deep > 0) min_len = 80;
+    if (pv.T > 4096 && rank == 0 && deep > 0) return true;   // (up to GATHER_MAX_AVG_LEN tokens a sequence)
+    return pv.T < min_tokens[deep][rank] || pv.T < (int64_t)min_len * pv.S;
 }
 
 // The plan's buffer, at least `bytes` large; same rules under stream capture as ensure_ws.
@@ -324,6 +352,7 @@ static int plan_prepare(moin_plan *plan, const int32_t *seq_offsets, const int32
     pv.max_tiles = L.max_tiles;
     pv.max_groups = L.max_groups;
     pv.decode = L.decode;
+    pv.tiles = L.tiles;
     pv.chunk = group_chunk(T);
     return 0;
 }
@@ -379,9 +408,10 @@ int linear_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, con
     a.d_in = d_in; a.d_out = d_out; a.r = adapters ? r : 0; a.scale = scale; a.act = ctx->act;
     a.u_hi = a.u_lo = nullptr;
 
-    a.ldu = pv.decode ? a.r : prefill_ldu(a);
+    const bool gathered = gathered_pays(pv, d_in, a.r);
+    a.ldu = gathered ? a.r : prefill_ldu(a);
     const size_t u_bytes = align_up((size_t)pv.T * (size_t)a.ldu * 2, 256);
-    if (!pv.decode) {
+    if (!gathered) {
         if (a.r > 0) {
             const int rc = ensure_ws(ctx, 2 * u_bytes, stream);
             if (rc != MOIN_OK) return rc;
@@ -487,12 +517,12 @@ int linear_mx_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, 
     m.plain_kb_per_split = 0;
     // decode-sized batches with adapters: the base product for all tokens at once as
     // fp32 partial planes, then the decode path's own shrink and expand kernels
-    const bool decode = pv.decode && a.r > 0;
+    const bool gathered = gathered_pays(pv, d_in, a.r), decode = gathered && a.r > 0;
     size_t yb_bytes = 0;
     if (decode) {
         mx_plain_shape(pv.T, d_in, d_out, &m.plain_splits, &m.plain_kb_per_split);
         yb_bytes = align_up((size_t)m.plain_splits * (size_t)pv.T * (size_t)d_out * 4, 256);
-    } else if (pv.decode) {
+    } else if (gathered) {
         m.plain_splits = 1;            // no adapters anywhere: the plain product writes y itself
         m.plain_kb_per_split = d_in / 128;
     }
@@ -506,7 +536,7 @@ int linear_mx_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, 
     m.Wq = Wq;
     m.Ws = Ws;
     // prefill with adapters: the shrink's pass over x writes the codes and scales as well
-    const bool fused_q = own_q && !pv.decode && a.r > 0;
+    const bool fused_q = own_q && !gathered && a.r > 0;
     if (own_q && !fused_q && timed(ctx, MOIN_K_MX_QUANT, stream, [&] {
             return launch_mx_quantize(x, pv.T, d_in, const_cast<void *>(m.xq), const_cast<void *>(m.xs), 1, stream);
         }) != hipSuccess)
@@ -532,7 +562,7 @@ int linear_mx_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, 
             return MOIN_EHIP;
         return MOIN_OK;
     }
-    if (a.r > 0 && !pv.decode && timed(ctx, MOIN_K_SHRINK, stream, [&] {
+    if (a.r > 0 && !gathered && timed(ctx, MOIN_K_SHRINK, stream, [&] {
             return fused_q ? launch_prefill_shrink_quant(pv, a, const_cast<void *>(m.xq),
                                                          const_cast<void *>(m.xs), stream)
                            : launch_prefill_shrink(pv, a, stream);
@@ -1031,7 +1061,8 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
                                         pv.E, d_in, d_out[i], r, scale, y[i], y_dt);
         if (vrc != MOIN_OK) return vrc;
     }
-    if (pv.decode && adapters && n > 1 && pv.max_plain == 0) {
+    const bool gathered = gathered_pays(pv, d_in, adapters ? r : 0);
+    if (gathered && adapters && n > 1 && pv.max_plain == 0) {
         // Decode-sized batch: the projections' base tiles and shrink slabs in one launch, their expand
         // blocks in another, where they agree in everything those launches share.
         DecodeArgs d[MAX_SHARED_X];
@@ -1066,7 +1097,7 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
             return MOIN_OK;
         }
     }
-    if (pv.decode || !adapters || n == 1) {
+    if (gathered || !adapters || n == 1) {
         // nothing to share on these paths: the projections one after the other
         for (int i = 0; i < n; ++i) {
             const int rc = linear_planned_impl(ctx, plan, x, W[i], adapters ? A_stack[i] : nullptr,

@@ -16,6 +16,9 @@ constexpr int TILE_M = 256;        // rows per plan tile (prefill)
 // where a row tile per sequence would be mostly padding.
 constexpr int DECODE_MAX_T = 1024;
 constexpr int GATHER_MAX_AVG_LEN = 128;
+// From here on (tokens, and tokens per sequence on average) such a batch is grouped both ways and each call takes the one
+// that suits its widths (gathered_pays in api.hip).
+constexpr int BOTH_MIN_T = 320, BOTH_MIN_AVG_LEN = 64;
 // Tokens per group record: a hot expert's tokens are spread over several.  The decode kernels walk a record's
 // tokens in blocks of 16, one trip to memory after the other, so a small batch has records of a single block (4 x 64
 // tokens on a 256-wide projection: 37 us in one record per expert, 11 us in four); large ones, which have records
@@ -63,6 +66,7 @@ struct PlanView {
     int64_t T;
     int E;
     int decode;  // grouping arrays valid
+    int tiles;   // prefill tiles valid (both: the call decides, gathered_pays)
     int chunk;   // tokens per group record at most
 };
 
@@ -75,6 +79,12 @@ inline int64_t host_tiles(const PlanView &pv, int rows)
 {
     const int64_t S = std::max<int64_t>(1, std::min<int64_t>(pv.S, pv.max_tiles)), len = (pv.T + S - 1) / S;
     return S * ((len + rows - 1) / rows);
+}
+
+// Rounds that a workgroup per compute unit needs for the call's TILE_M-row tiles by `cols` column tiles (>= 1).
+inline int64_t tile_rounds(const PlanView &pv, int64_t cols, int64_t n_cus)
+{
+    return std::max<int64_t>(1, (host_tiles(pv, TILE_M) * cols + n_cus - 1) / n_cus);
 }
 
 struct LinearArgs {
@@ -103,7 +113,8 @@ hipError_t launch_prefill_linear(const PlanView &pv, const LinearArgs &a, hipStr
 hipError_t launch_prefill_linear_shared(const PlanView &pv, const LinearArgs *a, int n, hipStream_t stream);
 // The 128 x 128 tiles of linear_mid.hip: whether they beat the larger ones for this call, and the call (a[0].ldu: columns
 // of u as stored, r or more).
-bool mid_kernel_pays(const PlanView &pv, const LinearArgs *a, int n, int n_cus);
+bool mid_kernel_pays(const PlanView &pv, const LinearArgs *a, int n, int n_cus);    // than the register-staged tiles
+bool mid_beats_stream(const PlanView &pv, const LinearArgs *a, int n, int n_cus);   // than the streaming kernel
 hipError_t launch_linear_mid(const PlanView &pv, const LinearArgs *a, int n, int n_cus, hipStream_t stream);
 // shapes the persistent streaming prefill kernel takes (anything else: linear_mid.hip or the tiled kernel)
 bool stream_kernel_fits(const LinearArgs &a);

@@ -285,6 +285,20 @@ bool mid_kernel_pays(const PlanView &pv, const LinearArgs *a, int n, int n_cus)
     return mid_tiles(pv, a, n) <= 2 * (int64_t)n_cus;
 }
 
+// Against the streaming kernel the same line holds for each round that its 256 x 256 tiles need (two of these tiles per
+// unit and round): with full row tiles, four of these in a large one, that is the first round's line alone, but where
+// sequences end in the first half of a row tile, or a last round would be nearly empty, it lies further out.  Us of the
+// kernel, 256 x 256 / these: 2048 -> 2048 64 sequences of 128 tokens (512 large tiles, 1024 of these) 109 / 71, 96 of 128
+// 160 / 106, 20 of 300 (320, 960) 94 / 66; 2048 -> 11264 8 of 112 98 / 58, 32 of 112 305 / 198, 64 of 128 599 / 517, 4 of
+// 300 (352, 1056: beyond the line) 98 / 85; 5632 -> 2048 64 of 128 244 / 158, 20 of 300 214 / 154; just beyond the line
+// about equal (32 of 300 109 / 101, 24 of 512 99 / 102), further out the large ones win (32 of 512 112 / 133).
+bool mid_beats_stream(const PlanView &pv, const LinearArgs *a, int n, int n_cus)
+{
+    int64_t tn = 0;
+    for (int i = 0; i < n; ++i) tn += (a[i].d_out + TILE_M - 1) / TILE_M;
+    return mid_tiles(pv, a, n) <= 2 * n_cus * tile_rounds(pv, tn, n_cus);
+}
+
 template <int NS>
 static hipError_t launch_mid(const stream::Params &p, unsigned grid, hipStream_t stream_)
 {

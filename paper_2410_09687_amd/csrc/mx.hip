@@ -727,8 +727,10 @@ bool mx_stream_kernel_fits(int d_in, int r) { return d_in % 128 == 0 && d_in >= 
 
 // 128 x 128 tiles as long as the chip holds all of them at a time, as in linear_mid.hip.  Us of the kernel, 256 x 256 tiles / these:
 // 2048 -> 2048 512 tiles 29.6 / 24.5, 544 29.8 / 33.6, 768 31.2 / 35.7; 5632 -> 2048 512 61 / 52, 544 61 / 76; 2048 -> 5632 528
-// 31.3 / 35.1.  (Beyond the larger tiles' first round about equal: 1152 56 / 52, 5632 outputs 1232 57 / 60.)
-static bool mx_mid_pays(int64_t tiles, int n_cus) { return tiles <= 2 * (int64_t)n_cus; }
+// 31.3 / 35.1.  (Beyond the larger tiles' first round about equal: 1152 56 / 52, 5632 outputs 1232 57 / 60.)  Per round of those, as
+// in linear_mid.hip, where row tiles are half empty or a round nearly so: 2048 -> 2048 64 sequences of 128 tokens 62 / 47, 20 of 300
+// 56 / 42; 2048 -> 5632 12 of 112 55 / 36, 64 of 128 172 / 134; 5632 -> 2048 64 of 128 133 / 95, 20 of 300 118 / 87.
+static bool mx_mid_pays(int64_t tiles, int64_t rounds, int n_cus) { return tiles <= 2 * n_cus * rounds; }
 
 // Parts of the contraction range for the plain (decode) base product: a workgroup of the 128 x 128 tiles per compute unit
 // (two per unit lost up to 3 %), at least two blocks per part, at most four parts (the decode expand kernel sums up to
@@ -774,7 +776,7 @@ hipError_t launch_linear_mx_stream(const PlanView &pv, const MxLinearArgs &a, in
     p.plane_bytes = (int64_t)pv.T * a.lin.d_out * (a.lin.y_f32 ? 4 : 2);
     const int64_t cols = (a.lin.d_out + mxm::BT - 1) / mxm::BT;
     const int64_t rows = p.plain ? (pv.T + mxm::BT - 1) / mxm::BT : host_tiles(pv, mxm::BT);
-    if (mx_mid_pays(rows * cols, n_cus)) {
+    if (mx_mid_pays(rows * cols, p.plain ? 1 : tile_rounds(pv, p.n_tiles_n, n_cus), n_cus)) {
         p.n_tiles_n = (int)cols;
         p.tiles_m = (int)rows;
         const int64_t work = (p.plain ? rows * p.k_splits : (int64_t)pv.max_tiles * (TILE_M / mxm::BT)) * cols;

@@ -219,7 +219,7 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
     uint16_t *head_at = L.idx[cur ^ 1];   // per group: its first sorted position
 
     // 3. tiles / tokens / groups before each sorted position, a run of positions per thread; emit.  (The decode
-    // kernels know no tiles, the prefill kernels no token order.)
+    // kernels know no tiles, the prefill kernels no token order; a batch that calls may take either way has both.)
     const int per = (S + PT - 1) / PT;
     const int p0 = min(tid * per, S), p1 = min(p0 + per, S);
     int v[3] = {0, 0, 0}, total[3];
@@ -231,12 +231,12 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
         v[2] += p == 0 || L.ekey[order[p - 1]] != L.ekey[s];
     }
     plan_scan<PT, 3>(v, total, L.sums);
-    if (tid == 0) *pv.n_tiles = pv.decode ? 0 : min(total[0], pv.max_tiles);
+    if (tid == 0) *pv.n_tiles = pv.tiles ? min(total[0], pv.max_tiles) : 0;
     for (int p = p0; p < p1; ++p) {
         const int s = order[p];
         const int lo = seq_offsets[s], len = seq_offsets[s + 1] - lo;
         const int e = (int)L.ekey[s] - 1;
-        if (!pv.decode) {
+        if (pv.tiles) {
             const int rk = plan_rank_of(e, rank_of_expert, err_word);
             for (int left = len, j = 0; left > 0 && v[0] < pv.max_tiles; ++j, ++v[0], left -= TILE_M) {
                 pv.tile_row0[v[0]] = lo + j * TILE_M;
@@ -244,7 +244,8 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
                 pv.tile_expert[v[0]] = e;
                 pv.tile_rank[v[0]] = rk;
             }
-        } else {
+        }
+        if (pv.decode) {
             L.tokbase[p] = v[1];
             if (p == 0 || L.ekey[order[p - 1]] != L.ekey[s]) head_at[v[2]++] = (uint16_t)p;
             if (len > 8) L.any_long = 1;
