@@ -747,6 +747,13 @@ constexpr int DECODE_BASE_TARGET_WGS = 512;
 constexpr int DECODE_BASE_MAX_SPLITS = 4;   // the expand kernel sums up to four parts
 constexpr int DECODE_BASE_MIN_BLOCKS = 4;   // BK blocks per part at least
 constexpr int DECODE_BASE_SPLIT_BLOCKS = 32;
+// One row of tiles, not mixed with slabs (33 to 128 tokens): a block of a tile's loop takes 0.36 us however many loads are in
+// flight (five stages instead of four change nothing) and the planes are small, so up to four parts wherever they have
+// this many blocks.  Us of the two launches, parts of 32 blocks / of 8 and more: 2048 -> 2048 rank 16 40 tokens 23 / 18, 128 25 / 21,
+// rank 128 64 tokens 29 / 24, 128 34 / 31; 2048 -> 2048, 256, 256 rank 128 111 tokens of one sequence 25 / 21, 128 single 42 / 43;
+// 1024 -> 1416 rank 64 64 24 / 17; twice 2048 -> 5632, which fills the chip with two parts, 40 28 / 28, 64 39 / 38, 128 51 / 54
+// (128 tokens more, rank 64: 62 / 69).
+constexpr int DECODE_BASE_SPLIT_BLOCKS_FEW = 8, DECODE_BASE_FEW_MIN = 33, DECODE_BASE_FEW_MAX = 128;
 
 template <class C>
 static void shape_for(int64_t T, int d_in, int d_out, bool may_split, DecodeBaseShape *sh)
@@ -759,7 +766,9 @@ static void shape_for(int64_t T, int d_in, int d_out, bool may_split, DecodeBase
     if (want > DECODE_BASE_MAX_SPLITS) want = DECODE_BASE_MAX_SPLITS;
     // every part costs a plane of fp32 partial sums written and read back: no more
     // parts than it takes to keep a tile's serial loop to about DECODE_BASE_SPLIT_BLOCKS blocks
-    const int by_len = (nkb + DECODE_BASE_SPLIT_BLOCKS - 1) / DECODE_BASE_SPLIT_BLOCKS;
+    const bool few = T >= DECODE_BASE_FEW_MIN && T <= DECODE_BASE_FEW_MAX;
+    const int blocks = few ? DECODE_BASE_SPLIT_BLOCKS_FEW : DECODE_BASE_SPLIT_BLOCKS;
+    const int by_len = (nkb + blocks - 1) / blocks;
     if (want > by_len) want = by_len;
     if (want > nkb / DECODE_BASE_MIN_BLOCKS) want = nkb / DECODE_BASE_MIN_BLOCKS;
     if (want < 1) want = 1;
