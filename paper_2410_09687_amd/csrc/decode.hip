@@ -128,9 +128,6 @@ __device__ __forceinline__ void store_u(const Partials &red, int lane, int pos0,
     }
 }
 
-// Barrier for data that goes through LDS: loads from memory stay in flight across it (__syncthreads waits for them).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // One (expert group g, 16-row slab of A_e) of a large batch's shrink; `red` is two buffers, used in turn (`flip`).
 // KS_HOLD > 0 (records of several blocks of 16 tokens): a wave's share of the slab is at
 // most KS_HOLD k-steps and stays in registers for all of the record's token

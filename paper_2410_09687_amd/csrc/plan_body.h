@@ -9,14 +9,19 @@ constexpr int PLAN_THREADS_MAX = 1024;   // large batches
 constexpr int PLAN_THREADS_SMALL = 256;  // up to PLAN_CAP_SMALL sequences: four waves meet at a barrier much faster than sixteen
 constexpr int PLAN_CAP_SMALL = 512;
 constexpr int PLAN_CAP_MAX = 12288;      // what one compute unit's LDS holds, at 12 bytes a sequence
-constexpr int PLAN_COUNT_S = 128;        // up to here a sequence's place is found by comparing it with all others
+// Up to here a sequence's place is found by comparing it with all others (200 sequences: 7.8 us, a radix sort 6.6).
+constexpr int PLAN_COUNT_S = 128;
 
 // (The arrays are always reached through the struct, never through a pointer that could also be a global one: for
 // such a generic pointer the compiler may form &array[-1] ahead of a loop, and below the start of LDS that is an
 // address outside every segment.)
 template <int PT, int CAP>
 struct PlanLds {
-    unsigned ekey[CAP];          // expert + 1 of each sequence (-1, no adapter, sorts first)
+    // What every sequence has in memory, where there is room for it: read once, on the way in.
+    static constexpr bool KEEPS = CAP <= PLAN_CAP_SMALL;
+    alignas(16) unsigned ekey[CAP];   // expert + 1 of each sequence (-1, no adapter, sorts first)
+    int off[KEEPS ? CAP + 1 : 1];     // sequence offsets
+    int rank[KEEPS ? CAP : 1];        // of the sequence's adapter
     int tokbase[CAP];            // per sorted position: tokens before it
     uint16_t idx[2][CAP];        // sequences in sorted order, and the buffer they are sorted through
     int hist[PT / 64][128];      // per wave: digit counts, then cursors
@@ -44,7 +49,7 @@ __device__ __forceinline__ void plan_scan(int (&v)[N], int (&total)[N], int (*su
     if (lane == 63)
 #pragma unroll
         for (int k = 0; k < N; ++k) sums[k][wave] = v[k];
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int k = 0; k < N; ++k) {
         int before = 0, all = 0;
@@ -57,7 +62,7 @@ __device__ __forceinline__ void plan_scan(int (&v)[N], int (&total)[N], int (*su
         v[k] += before - own[k];
         total[k] = all;
     }
-    __syncthreads();
+    lds_barrier();
 }
 
 // Rank of adapter slot e ("Future Works": adaptive rank per topic).  Multiples of 8,
@@ -112,40 +117,62 @@ __device__ __forceinline__ void plan_base_only(const PlanView &pv, int nt_thread
 // The whole grouping of a batch of at most CAP sequences, by ONE workgroup of PT threads (all of them must
 // call it), in LDS.  A device function so that the kernel that routes a request-sized batch can go on to group
 // it in the same launch; that kernel hands in LDS it has no more use for.
-// Bound by latency: trips to memory, barriers, dependent LDS reads.  The sort is stable and takes the digits
+// Bound by latency: trips to memory, barriers, dependent LDS reads.  Nothing written to memory is read back, so the
+// barriers wait for LDS alone (__syncthreads also waits until every store has arrived).  The sort is stable and takes the digits
 // of the expert alone: up to PLAN_COUNT_S sequences each finds its place by comparing itself with all others
 // (one barrier), beyond them a radix sort, 7 bits a pass, lanes of a wave that share a digit finding each other
 // with one ballot per bit.  (It was a bitonic sort of 64-bit keys: 36 barriers for 256 sequences, and above
 // 2048 through global memory: 8192 sequences took 230 us.)
-template <int PT, int CAP>
+// IDS_IN_LDS: the caller has left the experts in L.ekey and the offsets in L.off (thread t those of t, t + PT, ..., the last
+// offset whichever).
+template <int PT, int CAP, bool IDS_IN_LDS = false>
 __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_offsets, const int *expert_ids,
                                           const int *rank_of_expert, int *err_word, PlanLds<PT, CAP> &L)
 {
+    using Lds = PlanLds<PT, CAP>;
+    static_assert(!IDS_IN_LDS || Lds::KEEPS, "room for the offsets");
+    auto offset_of = [&](int s) __attribute__((always_inline)) { return Lds::KEEPS ? L.off[s] : seq_offsets[s]; };
+    auto rank_of = [&](int s, int e) __attribute__((always_inline)) {
+        return Lds::KEEPS ? L.rank[s] : plan_rank_of(e, rank_of_expert, err_word);
+    };
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int S = pv.S;
     const int T = (int)pv.T;
 
     // 1. validate, fetch the experts
     if (tid == 0) L.bad_offsets = L.any_long = 0;
-    __syncthreads();
+    lds_barrier();
     int err = 0;
-    if (tid == 0 && (seq_offsets[0] != 0 || seq_offsets[S] != T)) err |= ERR_BAD_OFFSETS;
+    if constexpr (!IDS_IN_LDS) {
+        if (tid == 0 && (seq_offsets[0] != 0 || seq_offsets[S] != T)) err |= ERR_BAD_OFFSETS;
+    } else if (tid == 0 && (L.off[0] != 0 || L.off[S] != T)) {   // (behind the barrier)
+        err |= ERR_BAD_OFFSETS;
+    }
     for (int s = tid; s < S; s += PT) {
-        const int lo = seq_offsets[s], hi = seq_offsets[s + 1];
-        int e = expert_ids[s];
+        const int lo = IDS_IN_LDS ? L.off[s] : seq_offsets[s], hi = IDS_IN_LDS ? L.off[s + 1] : seq_offsets[s + 1];
+        int e = IDS_IN_LDS ? (int)L.ekey[s] : expert_ids[s];
         if (lo < 0 || hi > T || hi < lo) err |= ERR_BAD_OFFSETS;
         if (e < -1 || e >= pv.E) {
             err |= ERR_BAD_EXPERT;
             e = -1;
         }
-        if (plan_rank_of(e, rank_of_expert, err_word) == 0) e = -1;   // rank 0: base model only
+        const int rk = plan_rank_of(e, rank_of_expert, err_word);
+        if (rk == 0) e = -1;   // rank 0: base model only
         L.ekey[s] = (unsigned)(e + 1);
         L.idx[0][s] = (uint16_t)s;
+        if constexpr (Lds::KEEPS) {
+            L.rank[s] = rk;
+            if constexpr (!IDS_IN_LDS) {
+                L.off[s] = lo;
+                if (s == S - 1) L.off[S] = hi;
+            }
+        }
     }
+    if (S <= PLAN_COUNT_S && tid < 16 && S + tid < (S + 15) / 16 * 16) L.ekey[S + tid] = ~0u;   // whole turns of the comparison
     if (err) atomicOr(err_word, err);
     if (err & ERR_BAD_OFFSETS) L.bad_offsets = 1;
     plan_plain_tiles(pv, PT);
-    __syncthreads();
+    lds_barrier();
     if (L.bad_offsets) {
         plan_base_only(pv, PT);
         return;
@@ -154,19 +181,25 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
     // 2. sort the sequences by expert, stably
     int cur = 0;
     if (S <= PLAN_COUNT_S) {
-        static_assert(PT >= PLAN_COUNT_S && CAP >= PLAN_COUNT_S, "a sequence per thread");
+        static_assert(PT >= PLAN_COUNT_S && CAP >= PLAN_COUNT_S && PLAN_COUNT_S % 16 == 0, "a sequence per thread");
         if (tid < S) {
+            // sixteen keys a turn, four per LDS read: one at a time their latency made it 2.1 us for 64 sequences, now 1.2
             const unsigned me = L.ekey[tid];
             int at = 0;
-#pragma unroll 4
-            for (int j = 0; j < S; ++j) {
-                const unsigned o = L.ekey[j];
-                at += (o < me || (o == me && j < tid)) ? 1 : 0;
+            for (int j = 0; j < S; j += 16) {
+                uint4 o[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) o[q] = *reinterpret_cast<const uint4 *>(&L.ekey[j + 4 * q]);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int d = tid - (j + 4 * q);   // key k of the four comes first if it is smaller, or equal and k < d
+                    at += (o[q].x < me + (0 < d)) + (o[q].y < me + (1 < d)) + (o[q].z < me + (2 < d)) + (o[q].w < me + (3 < d));
+                }
             }
             L.idx[1][at] = (uint16_t)tid;
         }
         cur = 1;
-        __syncthreads();
+        lds_barrier();
     } else {
         constexpr int NW = PT / 64;
         const int per_wave = ((S + NW - 1) / NW + 63) / 64 * 64;
@@ -176,7 +209,7 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
             for (int d = lane; d < 128; d += 64) L.hist[wave][d] = 0;
             for (int i = w0 + lane; i < w1; i += 64)   // (a wave's own row: its LDS operations stay in order)
                 atomicAdd(&L.hist[wave][(L.ekey[L.idx[cur][i]] >> shift) & 127], 1);
-            __syncthreads();
+            lds_barrier();
             // cursors: digits in order, the waves of a digit in order
             constexpr int PER = 128 * NW / PT;   // 2
             int c[PER], v[1] = {0}, total[1];
@@ -193,7 +226,7 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
                 L.hist[f % NW][f / NW] = v[0];
                 v[0] += c[q];
             }
-            __syncthreads();
+            lds_barrier();
             for (int i = w0 + lane; i - lane < w1; i += 64) {
                 const bool ok = i < w1;
                 const int s = ok ? L.idx[cur][i] : 0;
@@ -212,7 +245,7 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
                 }
             }
             cur ^= 1;
-            __syncthreads();
+            lds_barrier();
         }
     }
     const uint16_t *order = L.idx[cur];
@@ -225,7 +258,7 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
     int v[3] = {0, 0, 0}, total[3];
     for (int p = p0; p < p1; ++p) {
         const int s = order[p];
-        const int len = seq_offsets[s + 1] - seq_offsets[s];
+        const int len = offset_of(s + 1) - offset_of(s);
         v[0] += (len + TILE_M - 1) / TILE_M;
         v[1] += len;
         v[2] += p == 0 || L.ekey[order[p - 1]] != L.ekey[s];
@@ -234,10 +267,10 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
     if (tid == 0) *pv.n_tiles = pv.tiles ? min(total[0], pv.max_tiles) : 0;
     for (int p = p0; p < p1; ++p) {
         const int s = order[p];
-        const int lo = seq_offsets[s], len = seq_offsets[s + 1] - lo;
+        const int lo = offset_of(s), len = offset_of(s + 1) - lo;
         const int e = (int)L.ekey[s] - 1;
         if (pv.tiles) {
-            const int rk = plan_rank_of(e, rank_of_expert, err_word);
+            const int rk = e < 0 ? 0 : rank_of(s, e);   // (a sequence of rank 0 has become one without an adapter)
             for (int left = len, j = 0; left > 0 && v[0] < pv.max_tiles; ++j, ++v[0], left -= TILE_M) {
                 pv.tile_row0[v[0]] = lo + j * TILE_M;
                 pv.tile_rows[v[0]] = min(left, TILE_M);
@@ -255,22 +288,26 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
         }
     }
     if (!pv.decode) return;
-    __syncthreads();
+    lds_barrier();
     const int n_tok = min(total[1], T), n_groups = total[2];
     if (L.any_long) {
-        // The longer sequences, one wave each: a wave fetches what it needs of 64 of them at once and then writes
-        // them out one after the other.  (With a binary search per token the grouping of 64 sequences of 128 tokens took 24 us, now 13.)
-        constexpr int NW = PT / 64;
-        for (int c = 0; c < S; c += 64 * NW) {
-            const int p = c + lane * NW + wave;
+        // The longer sequences: eight lanes each, whole waves for the very long ones.  (A wave for each took 0.11 us a
+        // sequence: 500 sequences of up to 24 tokens 26 us for the kernel, now 15.)
+        constexpr int NW = PT / 64, WAVE_LEN = 256;
+        for (int c = wave * 8; c < S; c += 8 * NW) {
+            const int p = c + (lane >> 3);
             const int s = p < S ? order[p] : 0;
-            const int lo = p < S ? seq_offsets[s] : 0, len = p < S ? seq_offsets[s + 1] - lo : 0;
+            const int lo = p < S ? offset_of(s) : 0, len = p < S ? offset_of(s + 1) - lo : 0;
             const int base = p < S ? L.tokbase[p] : 0;
-            for (uint64_t left = __ballot(len > 8); left != 0; left &= left - 1) {
+            if (len > 8 && len <= WAVE_LEN) {
+                const int n = min(len, n_tok - base);
+                for (int j = lane & 7; j < n; j += 8) pv.tok_sorted[base + j] = lo + j;
+            }
+            for (uint64_t left = __ballot(len > WAVE_LEN && (lane & 7) == 0); left != 0; left &= left - 1) {
                 const int q = __builtin_ctzll(left);
-                const int qlo = __builtin_amdgcn_readlane(lo, q), qlen = __builtin_amdgcn_readlane(len, q);
-                const int qbase = __builtin_amdgcn_readlane(base, q);
-                for (int j = lane; j < qlen && qbase + j < n_tok; j += 64) pv.tok_sorted[qbase + j] = qlo + j;
+                const int qlo = __builtin_amdgcn_readlane(lo, q), qbase = __builtin_amdgcn_readlane(base, q);
+                const int qn = min(__builtin_amdgcn_readlane(len, q), n_tok - qbase);
+                for (int j = lane; j < qn; j += 64) pv.tok_sorted[qbase + j] = qlo + j;
             }
         }
     }
@@ -286,14 +323,32 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
     }
     plan_scan<PT, 1>(n, n_rec, L.sums);
     int base_only = 0;
-    for (int g = g0; g < g1; ++g) {
-        const int p = head_at[g];
-        const int gs = L.tokbase[p], ge = g + 1 < n_groups ? L.tokbase[head_at[g + 1]] : n_tok;
-        const int e = (int)L.ekey[order[p]] - 1;
-        const int rk = plan_rank_of(e, rank_of_expert, err_word);
-        for (int t = gs; t < ge && n[0] < pv.max_groups; t += pv.chunk, ++n[0])
-            pv.grp_meta[n[0]] = make_int4(e, t, min(t + pv.chunk, ge), rk);
-        if (e < 0) base_only = n[0];   // (the first group, if any)
+    for (int k = 0; k < gper; ++k) {   // (the same number of turns for the whole wave)
+        const int g = g0 + k;
+        int e = -1, rk = 0, gs = 0, ge = 0;
+        if (g < g1) {
+            const int p = head_at[g], s = order[p];
+            gs = L.tokbase[p];
+            ge = g + 1 < n_groups ? L.tokbase[head_at[g + 1]] : n_tok;
+            e = (int)L.ekey[s] - 1;
+            if (e >= 0) rk = rank_of(s, e);   // (a sequence of rank 0 has become one without an adapter)
+        }
+        // A group of many records is written by the whole wave: by its own thread the 95 of 6000 base-only tokens took 4 us.
+        const int recs = (ge - gs + pv.chunk - 1) / pv.chunk, first = n[0];
+        constexpr int OWN = 4;
+        if (recs <= OWN)
+            for (int j = 0; j < recs && first + j < pv.max_groups; ++j)
+                pv.grp_meta[first + j] = make_int4(e, gs + j * pv.chunk, min(gs + (j + 1) * pv.chunk, ge), rk);
+        for (uint64_t left = __ballot(recs > OWN); left != 0; left &= left - 1) {
+            const int q = __builtin_ctzll(left);
+            const int qe = __builtin_amdgcn_readlane(e, q), qrk = __builtin_amdgcn_readlane(rk, q);
+            const int qs = __builtin_amdgcn_readlane(gs, q), qend = __builtin_amdgcn_readlane(ge, q);
+            const int qfirst = __builtin_amdgcn_readlane(first, q), qn = __builtin_amdgcn_readlane(recs, q);
+            for (int j = lane; j < qn && qfirst + j < pv.max_groups; j += 64)
+                pv.grp_meta[qfirst + j] = make_int4(qe, qs + j * pv.chunk, min(qs + (j + 1) * pv.chunk, qend), qrk);
+        }
+        n[0] = min(first + recs, max(first, pv.max_groups));
+        if (g < g1 && e < 0) base_only = n[0];   // (the first group, if any)
     }
     const int n_out = min(n_rec[0], pv.max_groups);
     if (tid == 0) {

@@ -62,6 +62,17 @@ __device__ __forceinline__ void route_finish(const RouteKParams &p, char *smem)
         __syncthreads();
     }
     if (p.self_clean && threadIdx.x <= ARRIVAL_FAN) p.arrivals[threadIdx.x * ARRIVAL_STRIDE] = 0;
+    // The grouping's own inputs: the offsets on their way beside the winners, the experts handed over in LDS.
+    constexpr bool MAY_PLAN = NT == PLAN_THREADS_SMALL;
+    PlanLdsSmall &L = *reinterpret_cast<PlanLdsSmall *>(smem);
+    constexpr int OFFS = PLAN_CAP_SMALL / PLAN_THREADS_SMALL + 1;
+    int off[OFFS];
+    if constexpr (MAY_PLAN) {
+        if (p.with_plan) {
+#pragma unroll
+            for (int u = 0; u < OFFS; ++u) off[u] = p.seq_offsets[min((int)threadIdx.x + u * NT, (int)p.N)];
+        }
+    }
     constexpr int UNR = 4;   // the loads of several queries in flight: each is a trip to memory
     for (int q0 = threadIdx.x; q0 < (int)p.N; q0 += NT * UNR) {
         int bi[UNR];
@@ -81,20 +92,21 @@ __device__ __forceinline__ void route_finish(const RouteKParams &p, char *smem)
             if (q >= (int)p.N) break;
             if (p.cid) p.cid[q] = bi[u];
             if (p.expert_ids) p.expert_ids[q] = e[u];
+            if constexpr (MAY_PLAN)
+                if (p.with_plan) L.ekey[q] = (unsigned)e[u];   // (at most PLAN_CAP_SMALL queries)
             if (p.counts) atomicAdd(&p.counts[bi[u]], 1);
         }
     }
     if (p.self_clean) {   // ready for the next call (every thread its own queries, read above; lanes past the end read the last)
-        __syncthreads();
+        lds_barrier();
         for (int q = threadIdx.x; q < (int)p.N; q += NT) p.best[q] = ~0ull;
     }
-    if constexpr (NT == PLAN_THREADS_SMALL) {
+    if constexpr (MAY_PLAN) {
         if (p.with_plan) {
-            // the ids this workgroup has just written are the plan's input
-            __threadfence_block();
-            __syncthreads();
-            plan_body<PLAN_THREADS_SMALL, PLAN_CAP_SMALL>(p.plan, p.seq_offsets, p.expert_ids, p.rank_of_expert, p.err_word,
-                                          *reinterpret_cast<PlanLdsSmall *>(smem));
+#pragma unroll
+            for (int u = 0; u < OFFS; ++u)
+                if ((int)threadIdx.x + u * NT <= (int)p.N) L.off[threadIdx.x + u * NT] = off[u];
+            plan_body<PLAN_THREADS_SMALL, PLAN_CAP_SMALL, true>(p.plan, nullptr, nullptr, p.rank_of_expert, p.err_word, L);
         }
     }
 }
