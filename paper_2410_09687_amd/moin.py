@@ -1,4 +1,5 @@
-"""Thin ctypes binding of ``libmoin.so`` -- argument marshalling only.
+"""Thin binding of ``libmoin.so`` -- argument marshalling only, natively (``csrc/binding.cpp``) for the calls made per
+request or per layer, through ctypes for the others.
 
 Every function takes torch tensors that already live on the GPU, passes their
 device pointers and the current torch stream across the C ABI declared in
@@ -16,6 +17,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmoin.so")
+BINDING_PATH = os.path.join(_HERE, "_moin_binding.so")
 
 MOIN_F32, MOIN_BF16 = 0, 1
 MOIN_MX_X_INTERNAL, MOIN_MX_X_EMIT, MOIN_MX_X_GIVEN = 0, 1, 2
@@ -44,6 +46,7 @@ ACTIVATIONS = {None: 0, "none": 0, "relu": 1, "silu": 2, "gelu": 3}
 CACHE_STATS = ["batches", "seq_hits", "seq_misses", "loads", "evictions", "overflows", "bytes"]
 
 _lib = None
+_native = None   # the module of csrc/binding.cpp, once load() has run
 
 
 class MoinError(RuntimeError):
@@ -55,13 +58,14 @@ class MoinError(RuntimeError):
 def load() -> ctypes.CDLL:
     """Opens libmoin.so; a missing library is a hard error (build it with
     ``python -m paper_2410_09687_amd.build``)."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise FileNotFoundError(
-            f"{LIB_PATH} not found: build it with `python -m paper_2410_09687_amd.build`; "
-            "there is no fallback path")
+    for path in (LIB_PATH, BINDING_PATH):
+        if not os.path.exists(path):
+            raise FileNotFoundError(
+                f"{path} not found: build it with `python -m paper_2410_09687_amd.build`; "
+                "there is no fallback path")
     lib = ctypes.CDLL(LIB_PATH)
     c = ctypes
     vp, i32, i64, u32 = c.c_void_p, c.c_int32, c.c_int64, c.c_uint32
@@ -124,6 +128,9 @@ def load() -> ctypes.CDLL:
                         "moin_probe_out_len", "moin_workspace_bytes"):
             getattr(lib, name).restype = c.c_int
     lib.moin_workspace_bytes.restype = c.c_int64
+    from . import _moin_binding   # (finds libmoin.so beside itself, the one opened above)
+    _moin_binding.set_error(MoinError)
+    _native = _moin_binding
     _lib = lib
     return lib
 
@@ -151,7 +158,7 @@ def _dev_ptr(t: Optional[torch.Tensor], name: str, dtype=None):
 
 def _stream_ptr(stream=None):
     if stream is not None:
-        return ctypes.c_void_p(stream.cuda_stream)
+        return stream.cuda_stream
     # The current stream's handle without the Stream object around it: 0.2 us instead of 2.9, of the 15 that a call of
     # two launches costs the host (the five calls of a layer of 8 tokens take it as long as their kernels take the GPU).
     if not torch.cuda.is_initialized():
@@ -217,59 +224,20 @@ def moin_route(ctx: Context, emb: torch.Tensor, centroids: torch.Tensor,
     triple preallocated by the caller.  ``static``: through ``moin_route_static``, the entry point that
     allocates no device memory (N <= 65536, K <= 16384).  ``same_centroids``: the caller vouches that
     the table is unchanged since the previous call on this context (``MOIN_ROUTE_SAME_CENTROIDS``)."""
-    if emb.dim() != 2 or centroids.dim() != 2 or emb.shape[1] != centroids.shape[1]:
-        raise ValueError("emb [N,D] and centroids [K,D] expected")
-    if emb.dtype != centroids.dtype or emb.dtype not in (torch.float32, torch.bfloat16):
-        raise TypeError("emb/centroids must both be float32 or both bfloat16")
-    N, D = emb.shape
-    K = centroids.shape[0]
-    dt = MOIN_BF16 if emb.dtype == torch.bfloat16 else MOIN_F32
-    dev = centroids.device
-    if out is not None:
-        expert_ids, cids, counts = out
-        for t, n in ((expert_ids, N), (cids, N), (counts, K)):
-            if t is not None and (t.dtype != torch.int32 or t.numel() != n):
-                raise ValueError("out: int32 tensors of N, N and K elements (or None) expected")
-    else:
-        expert_ids = torch.empty(N, dtype=torch.int32, device=dev)
-        cids = torch.empty(N, dtype=torch.int32, device=dev) if want_centroid_ids else None
-        counts = torch.empty(K, dtype=torch.int32, device=dev) if want_counts else None
-    fn = load().moin_route_static if static else load().moin_route
-    _ck(fn(ctx._h, _dev_ptr(emb, "emb") if N else None, _dev_ptr(centroids, "centroids"),
-                          N, K, D, dt, _dev_ptr(slot_of_centroid, "slot_of_centroid", torch.int32),
-                          (MOIN_ROUTE_RETAINED_ONLY if retained_only else 0)
-                          | (MOIN_ROUTE_SAME_CENTROIDS if same_centroids else 0),
-                          _dev_ptr(expert_ids, "expert_ids") if N else None,
-                          _dev_ptr(cids, "centroid_ids") if (cids is not None and N) else None,
-                          _dev_ptr(counts, "counts"), _stream_ptr(stream)),
-        "moin_route_static" if static else "moin_route")
-    return expert_ids, cids, counts
+    load()
+    return _native.route(ctx._h.value, emb, centroids, slot_of_centroid,
+                         (MOIN_ROUTE_RETAINED_ONLY if retained_only else 0)
+                         | (MOIN_ROUTE_SAME_CENTROIDS if same_centroids else 0),
+                         bool(want_centroid_ids), bool(want_counts), _stream_ptr(stream), out, bool(static))
 
 
 def moin_route_topk(ctx: Context, emb: torch.Tensor, centroids: torch.Tensor, k: int,
                     slot_of_centroid: Optional[torch.Tensor] = None, retained_only: bool = False, stream=None):
     """The ``k`` (1..8) nearest centroids of every query, nearest first: ``(expert_ids, centroid_ids, dist2)``,
     each ``[N, k]`` (int32, int32, float32); -1 / inf where fewer than ``k`` centroids took part."""
-    if emb.dim() != 2 or centroids.dim() != 2 or emb.shape[1] != centroids.shape[1]:
-        raise ValueError("emb [N,D] and centroids [K,D] expected")
-    if emb.dtype != centroids.dtype or emb.dtype not in (torch.float32, torch.bfloat16):
-        raise TypeError("emb/centroids must both be float32 or both bfloat16")
-    if not 1 <= int(k) <= 8:
-        raise ValueError("k must be 1..8")
-    N, D = emb.shape
-    K = centroids.shape[0]
-    dt = MOIN_BF16 if emb.dtype == torch.bfloat16 else MOIN_F32
-    dev = centroids.device
-    eids = torch.empty((N, k), dtype=torch.int32, device=dev)
-    cids = torch.empty((N, k), dtype=torch.int32, device=dev)
-    d2 = torch.empty((N, k), dtype=torch.float32, device=dev)
-    _ck(load().moin_route_topk(ctx._h, _dev_ptr(emb, "emb") if N else None, _dev_ptr(centroids, "centroids"),
-                               N, K, D, dt, _dev_ptr(slot_of_centroid, "slot_of_centroid", torch.int32),
-                               MOIN_ROUTE_RETAINED_ONLY if retained_only else 0, int(k),
-                               _dev_ptr(eids, "expert_ids") if N else None,
-                               _dev_ptr(cids, "centroid_ids") if N else None,
-                               _dev_ptr(d2, "dist2") if N else None, _stream_ptr(stream)), "moin_route_topk")
-    return eids, cids, d2
+    load()
+    return _native.route_topk(ctx._h.value, emb, centroids, int(k), slot_of_centroid,
+                              MOIN_ROUTE_RETAINED_ONLY if retained_only else 0, _stream_ptr(stream))
 
 
 def moin_merge_adapters(ctx: Context, A_stack: torch.Tensor, B_stack: torch.Tensor, ids: torch.Tensor,
@@ -277,22 +245,8 @@ def moin_merge_adapters(ctx: Context, A_stack: torch.Tensor, B_stack: torch.Tens
     """Writes into ``A_out [r_out, d_in]`` / ``B_out [d_out, r_out]`` (e.g. one slot of wider stacks) the adapter
     of rank ``len(ids) * r`` that stands for ``sum_m weights[m] * B[ids[m]] @ A[ids[m]]``; ``ids`` (int32) and
     ``weights`` (float32) live on the device."""
-    E, r, d_in = A_stack.shape
-    d_out = B_stack.shape[1]
-    if tuple(B_stack.shape) != (E, d_out, r):
-        raise ValueError("A_stack [E,r,d_in] / B_stack [E,d_out,r] shape mismatch")
-    n = ids.numel()
-    if weights.numel() != n:
-        raise ValueError("one weight per id expected")
-    r_out = A_out.shape[0]
-    if tuple(A_out.shape) != (r_out, d_in) or tuple(B_out.shape) != (d_out, r_out):
-        raise ValueError("A_out [r_out,d_in] / B_out [d_out,r_out] expected")
-    bf = torch.bfloat16
-    _ck(load().moin_merge_adapters(ctx._h, _dev_ptr(A_stack, "A_stack", bf), _dev_ptr(B_stack, "B_stack", bf), E, r,
-                                   d_in, d_out, _dev_ptr(ids, "ids", torch.int32),
-                                   _dev_ptr(weights, "weights", torch.float32), n, r_out,
-                                   _dev_ptr(A_out, "A_out", bf), _dev_ptr(B_out, "B_out", bf), _stream_ptr(stream)),
-        "moin_merge_adapters")
+    load()
+    _native.merge_adapters(ctx._h.value, A_stack, B_stack, ids, weights, A_out, B_out, _stream_ptr(stream))
 
 
 def moin_histogram(ctx: Context, ids: torch.Tensor, K: int, stream=None) -> torch.Tensor:
@@ -329,31 +283,9 @@ def moin_lora_linear(ctx: Context, x: torch.Tensor, seq_offsets: torch.Tensor,
                      out: Optional[torch.Tensor] = None, stream=None,
                      rank_of_expert: Optional[torch.Tensor] = None) -> torch.Tensor:
     """``rank_of_expert`` (int32 [E] on the device, optional): per-expert adapter rank."""
-    if x.dim() != 2 or W.dim() != 2 or x.shape[1] != W.shape[1]:
-        raise ValueError("x [T,d_in] and W [d_out,d_in] expected")
-    d_in, d_out, E, r = _stack_dims(W, A_stack, B_stack)
-    if rank_of_expert is not None and rank_of_expert.numel() != E:
-        raise ValueError("rank_of_expert must have E entries")
-    S = expert_ids.numel()
-    if seq_offsets.numel() != S + 1:
-        raise ValueError("seq_offsets must have S+1 entries")
-    T = x.shape[0]
-    y, ydt = _y_out(x, d_out, y_dtype, out)
-    bf = torch.bfloat16
-    if rank_of_expert is not None:
-        _ck(load().moin_lora_linear_ranked(
-            ctx._h, _dev_ptr(x, "x", bf) if T else None, _dev_ptr(seq_offsets, "seq_offsets", torch.int32),
-            _dev_ptr(expert_ids, "expert_ids", torch.int32) if S else None, S, T, _dev_ptr(W, "W", bf),
-            _dev_ptr(A_stack, "A_stack", bf), _dev_ptr(B_stack, "B_stack", bf), E, d_in, d_out, r,
-            _dev_ptr(rank_of_expert, "rank_of_expert", torch.int32), float(scale),
-            _dev_ptr(y, "y") if T else None, ydt, _stream_ptr(stream)), "moin_lora_linear_ranked")
-        return y
-    _ck(load().moin_lora_linear(
-        ctx._h, _dev_ptr(x, "x", bf) if T else None, _dev_ptr(seq_offsets, "seq_offsets", torch.int32),
-        _dev_ptr(expert_ids, "expert_ids", torch.int32) if S else None, S, T, _dev_ptr(W, "W", bf),
-        _dev_ptr(A_stack, "A_stack", bf), _dev_ptr(B_stack, "B_stack", bf), E, d_in, d_out, r,
-        float(scale), _dev_ptr(y, "y") if T else None, ydt, _stream_ptr(stream)), "moin_lora_linear")
-    return y
+    load()
+    return _native.lora_linear(ctx._h.value, x, seq_offsets, expert_ids, W, A_stack, B_stack, float(scale), y_dtype, out,
+                               _stream_ptr(stream), rank_of_expert)
 
 
 def moin_mx_quantize(ctx: Context, values: torch.Tensor, blocked: bool = False, stream=None):
@@ -417,15 +349,9 @@ class Plan:
 
     def build(self, seq_offsets: torch.Tensor, expert_ids: torch.Tensor, T: int, E: int, stream=None,
               rank_of_expert: Optional[torch.Tensor] = None):
-        S = expert_ids.numel()
-        if seq_offsets.numel() != S + 1:
-            raise ValueError("seq_offsets must have S+1 entries")
-        if rank_of_expert is not None and rank_of_expert.numel() != E:
-            raise ValueError("rank_of_expert must have E entries")
-        _ck(load().moin_plan_build_ranked(self.ctx._h, self._h, _dev_ptr(seq_offsets, "seq_offsets", torch.int32),
-                                          _dev_ptr(expert_ids, "expert_ids", torch.int32) if S else None,
-                                          S, T, E, _dev_ptr(rank_of_expert, "rank_of_expert", torch.int32),
-                                          _stream_ptr(stream)), "moin_plan_build_ranked")
+        load()
+        S = _native.plan_build(self.ctx._h.value, self._h.value, seq_offsets, expert_ids, T, E, rank_of_expert,
+                               _stream_ptr(stream))
         self.T, self.S, self.E = T, S, E
         return self
 
@@ -455,61 +381,22 @@ def moin_route_plan(ctx: Context, plan: Plan, emb: torch.Tensor, centroids: torc
     """``moin_route`` and ``Plan.build`` on its ids in one call (one launch for a request-sized batch): the
     ``N`` queries are the batch's sequences.  Returns ``(expert_ids, centroid_ids or None, counts or None)``;
     ``plan`` is rebuilt.  ``out``: the same triple preallocated by the caller (``expert_ids`` required)."""
-    if emb.dim() != 2 or centroids.dim() != 2 or emb.shape[1] != centroids.shape[1]:
-        raise ValueError("emb [N,D] and centroids [K,D] expected")
-    if emb.dtype != centroids.dtype or emb.dtype not in (torch.float32, torch.bfloat16):
-        raise TypeError("emb/centroids must both be float32 or both bfloat16")
-    N, D = emb.shape
-    K = centroids.shape[0]
-    if seq_offsets.numel() != N + 1:
-        raise ValueError("seq_offsets must have N+1 entries")
-    if rank_of_expert is not None and rank_of_expert.numel() != E:
-        raise ValueError("rank_of_expert must have E entries")
-    dt = MOIN_BF16 if emb.dtype == torch.bfloat16 else MOIN_F32
-    dev = centroids.device
-    if out is not None:
-        expert_ids, cids, counts = out
-        if expert_ids is None:
-            raise ValueError("out: expert_ids is required")
-        for t, n in ((expert_ids, N), (cids, N), (counts, K)):
-            if t is not None and (t.dtype != torch.int32 or t.numel() != n):
-                raise ValueError("out: int32 tensors of N, N and K elements (or None) expected")
-    else:
-        expert_ids = torch.empty(N, dtype=torch.int32, device=dev)
-        cids = torch.empty(N, dtype=torch.int32, device=dev) if want_centroid_ids else None
-        counts = torch.empty(K, dtype=torch.int32, device=dev) if want_counts else None
-    _ck(load().moin_route_plan(ctx._h, plan._h, _dev_ptr(emb, "emb") if N else None,
-                               _dev_ptr(centroids, "centroids"), N, K, D, dt,
-                               _dev_ptr(slot_of_centroid, "slot_of_centroid", torch.int32),
-                               (MOIN_ROUTE_RETAINED_ONLY if retained_only else 0)
-                               | (MOIN_ROUTE_SAME_CENTROIDS if same_centroids else 0),
-                               _dev_ptr(seq_offsets, "seq_offsets", torch.int32), int(T), int(E),
-                               _dev_ptr(rank_of_expert, "rank_of_expert", torch.int32),
-                               _dev_ptr(expert_ids, "expert_ids"),
-                               _dev_ptr(cids, "centroid_ids") if (cids is not None and N) else None,
-                               _dev_ptr(counts, "counts"), _stream_ptr(stream)), "moin_route_plan")
-    plan.T, plan.S, plan.E = int(T), N, int(E)
-    return expert_ids, cids, counts
+    load()
+    ids = _native.route_plan(ctx._h.value, plan._h.value, emb, centroids, slot_of_centroid,
+                             (MOIN_ROUTE_RETAINED_ONLY if retained_only else 0)
+                             | (MOIN_ROUTE_SAME_CENTROIDS if same_centroids else 0), seq_offsets, int(T), int(E),
+                             rank_of_expert, bool(want_centroid_ids), bool(want_counts), _stream_ptr(stream), out)
+    plan.T, plan.S, plan.E = int(T), emb.shape[0], int(E)
+    return ids
 
 
 def moin_lora_linear_planned(ctx: Context, plan: Plan, x: torch.Tensor, W: torch.Tensor,
                              A_stack: Optional[torch.Tensor], B_stack: Optional[torch.Tensor],
                              scale: float, y_dtype=torch.bfloat16, out: Optional[torch.Tensor] = None,
                              stream=None) -> torch.Tensor:
-    if x.dim() != 2 or W.dim() != 2 or x.shape[1] != W.shape[1] or x.shape[0] != plan.T:
-        raise ValueError("x [T,d_in] (T as planned) and W [d_out,d_in] expected")
-    d_in, d_out, E, r = _stack_dims(W, A_stack, B_stack)
-    if E and E != plan.E:
-        raise ValueError("stack holds a different number of experts than the plan was built for")
-    y, ydt = _y_out(x, d_out, y_dtype, out)
-    bf = torch.bfloat16
-    T = x.shape[0]
-    _ck(load().moin_lora_linear_planned(
-        ctx._h, plan._h, _dev_ptr(x, "x", bf) if T else None, _dev_ptr(W, "W", bf),
-        _dev_ptr(A_stack, "A_stack", bf), _dev_ptr(B_stack, "B_stack", bf), d_in, d_out, r,
-        float(scale), _dev_ptr(y, "y") if T else None, ydt, _stream_ptr(stream)),
-        "moin_lora_linear_planned")
-    return y
+    load()
+    return _native.lora_linear_planned(ctx._h.value, plan._h.value, plan.T, plan.E, x, W, A_stack, B_stack, float(scale),
+                                       y_dtype, out, _stream_ptr(stream))
 
 
 def moin_lora_linear_mx_planned(ctx: Context, plan: "Plan", x: torch.Tensor, Wq: torch.Tensor, Ws: torch.Tensor,
@@ -519,30 +406,9 @@ def moin_lora_linear_mx_planned(ctx: Context, plan: "Plan", x: torch.Tensor, Wq:
     """``moin_lora_linear_mx`` on a plan; ``xq``, ``xs`` let projections that share their input quantise it
     once: the first call fills them (``emit=True``; uint8 [T, d_in] and [d_in/128, T, 4]), the others read them
     (as they read what ``moin_mx_quantize(x, blocked=True)`` returns)."""
-    if x.dim() != 2 or Wq.dim() != 2 or x.shape[1] != Wq.shape[1] or x.shape[0] != plan.T:
-        raise ValueError("x [T,d_in] (T as planned) and Wq [d_out,d_in] expected")
-    if Wq.dtype != torch.uint8 or Ws.dtype != torch.uint8 or Wq.shape[1] % 128 or \
-            tuple(Ws.shape) != (Wq.shape[1] // 128, Wq.shape[0], 4):
-        raise ValueError("Wq [d_out,d_in] / Ws [d_in/128,d_out,4] (blocked layout) uint8 expected")
-    d_in, d_out, E, r = _stack_dims(Wq, A_stack, B_stack)
-    if E and E != plan.E:
-        raise ValueError("stack holds a different number of experts than the plan was built for")
-    T = x.shape[0]
-    if (xq is None) != (xs is None):
-        raise ValueError("xq and xs go together")
-    if xq is not None and (tuple(xq.shape) != (T, d_in) or tuple(xs.shape) != (d_in // 128, T, 4)):
-        raise ValueError("xq [T,d_in] / xs [d_in/128,T,4] (blocked layout) expected")
-    if emit and xq is None:
-        raise ValueError("emit=True needs xq and xs to write to")
-    mode = MOIN_MX_X_INTERNAL if xq is None else (MOIN_MX_X_EMIT if emit else MOIN_MX_X_GIVEN)
-    y, ydt = _y_out(x, d_out, y_dtype, out)
-    bf = torch.bfloat16
-    _ck(load().moin_lora_linear_mx_planned(
-        ctx._h, plan._h, _dev_ptr(x, "x", bf) if T else None, _dev_ptr(xq, "xq", torch.uint8),
-        _dev_ptr(xs, "xs", torch.uint8), mode, _dev_ptr(Wq, "Wq", torch.uint8), _dev_ptr(Ws, "Ws", torch.uint8),
-        _dev_ptr(A_stack, "A_stack", bf), _dev_ptr(B_stack, "B_stack", bf), d_in, d_out, r, float(scale),
-        _dev_ptr(y, "y") if T else None, ydt, _stream_ptr(stream)), "moin_lora_linear_mx_planned")
-    return y
+    load()
+    return _native.lora_linear_mx_planned(ctx._h.value, plan._h.value, plan.T, plan.E, x, Wq, Ws, A_stack, B_stack,
+                                          float(scale), xq, xs, bool(emit), y_dtype, out, _stream_ptr(stream))
 
 
 def moin_lora_linear_planned_shared(ctx: Context, plan: "Plan", x: torch.Tensor, Ws, A_stacks, B_stacks, scale: float,
@@ -550,38 +416,9 @@ def moin_lora_linear_planned_shared(ctx: Context, plan: "Plan", x: torch.Tensor,
     """``moin_lora_linear_planned`` for up to four projections that read the same ``x`` (q, k, v; gate, up):
     lists of weights ``Ws[i] [d_out_i, d_in]`` and of stacks (or ``None`` for both lists); returns the list
     of outputs.  On the prefill path the adapters' first products come out of one pass over ``x``."""
-    n = len(Ws)
-    if not 1 <= n <= 4:
-        raise ValueError("1 to 4 projections expected")
-    if (A_stacks is None) != (B_stacks is None):
-        raise ValueError("A_stacks and B_stacks go together")
-    if A_stacks is not None and (len(A_stacks) != n or len(B_stacks) != n):
-        raise ValueError("one A_stack and one B_stack per weight expected")
-    dims = [_stack_dims(Ws[i], None if A_stacks is None else A_stacks[i], None if B_stacks is None else B_stacks[i])
-            for i in range(n)]
-    d_in, E, r = dims[0][0], dims[0][2], dims[0][3]
-    if any(d[0] != d_in or d[2] != E or d[3] != r for d in dims):
-        raise ValueError("the projections must agree in d_in, E and r")
-    if x.dim() != 2 or x.shape[1] != d_in or x.shape[0] != plan.T:
-        raise ValueError("x [T,d_in] (T as planned) expected")
-    if E and E != plan.E:
-        raise ValueError("stacks hold a different number of experts than the plan was built for")
-    T = x.shape[0]
-    ys, ydt = [], None
-    for i in range(n):
-        y, ydt = _y_out(x, dims[i][1], y_dtype, None if outs is None else outs[i])
-        ys.append(y)
-    bf = torch.bfloat16
-    vpa = ctypes.c_void_p * n
-    def ptrs(ts, name, dtype=None):
-        return vpa(*[_dev_ptr(t, name, dtype) for t in ts])
-    _ck(load().moin_lora_linear_planned_shared(
-        ctx._h, plan._h, _dev_ptr(x, "x", bf) if T else None, n, ptrs(Ws, "W", bf),
-        ptrs(A_stacks, "A_stack", bf) if A_stacks is not None else None,
-        ptrs(B_stacks, "B_stack", bf) if B_stacks is not None else None, d_in,
-        (ctypes.c_int32 * n)(*[d[1] for d in dims]), r, float(scale), ptrs(ys, "y") if T else vpa(), ydt,
-        _stream_ptr(stream)), "moin_lora_linear_planned_shared")
-    return ys
+    load()
+    return _native.lora_linear_planned_shared(ctx._h.value, plan._h.value, plan.T, plan.E, x, Ws, A_stacks, B_stacks,
+                                              float(scale), y_dtype, outs, _stream_ptr(stream))
 
 
 def moin_probe_mfma_bf16(ctx: Context, operands: torch.Tensor, iters: int, stream=None):
