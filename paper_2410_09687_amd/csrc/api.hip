@@ -270,12 +270,13 @@ PlanLayout plan_layout(int32_t S, int64_t T, int32_t E, bool upper_bound = false
 //  5632 -> 2048 rank 32 4 x 250 63 / 62, 14 x 96 72 / 65, 64 x 100 176 / 199, rank 64 8 x 96 58 / 55, 4 x 160 47 / 55, 64 x 64 152 / 182,
 //   rank 128 4 x 160 58 / 56, 4 x 96 43 / 55
 //  a layer of seven projections, rank 16 8 x 80 181 / 187, 8 x 112 221 / 191, 14 x 80 315 / 238; rank 128 8 x 48 168 / 173, 4 x 96
-//   164 / 144, 1 x 640 227 / 155, 14 x 96 475 / 273; on an MXFP8 base rank 64 4 x 96 206 / 199, 32 x 64 391 / 383, 32 x 96 560 / 417
+//   164 / 144, 1 x 640 227 / 155, 14 x 96 475 / 273 (the line at 2048 lies where a layer gains that keeps its 5632-wide down
+//   projection gathered: 1 x 363 rank 128 155 / 126, 1 x 390 rank 64 148 / 126); on an MXFP8 base rank 64 4 x 96 206 / 199, 32 x 64 391 / 383, 32 x 96 560 / 417
 bool gathered_pays(const PlanView &pv, int d_in, int r)
 {
     if (!pv.decode || !pv.tiles || r <= 0 || r > 128) return pv.decode;
     const int rank = r < 48 ? 0 : r < 96 ? 1 : 2, deep = d_in <= 1024 ? 0 : d_in <= 3072 ? 1 : 2;
-    static constexpr int min_tokens[3][3] = {{384, BOTH_MIN_T, BOTH_MIN_T}, {768, 512, 384}, {DECODE_MAX_T + 1, 768, 640}};
+    static constexpr int min_tokens[3][3] = {{384, BOTH_MIN_T, BOTH_MIN_T}, {768, 384, BOTH_MIN_T}, {DECODE_MAX_T + 1, 768, 640}};
     int min_len = rank == 0 ? (deep == 0 ? 80 : 96) : rank == 1 ? (deep == 0 ? BOTH_MIN_AVG_LEN : 72) : BOTH_MIN_AVG_LEN;
     if (pv.T > DECODE_MAX_T && rank == 1 && deep > 0) min_len = 80;
     if (pv.T > 4096 && rank == 0 && deep > 0) return true;   // (up to GATHER_MAX_AVG_LEN tokens a sequence)

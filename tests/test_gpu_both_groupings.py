@@ -41,7 +41,7 @@ def _counted(ctx, call):
 @pytest.mark.parametrize("lens,d_in,r,tiles", [
     ([319], 64, 128, False), ([320], 64, 128, True), ([64] * 5, 1000, 64, True), ([64] * 5 + [63], 1024, 64, False),
     ([383], 1024, 8, False), ([384], 1024, 8, True), ([20, 140] * 5, 72, 40, True), ([19, 140] * 5, 72, 40, False),
-    ([300, 83], 2048, 128, False), ([300, 84], 2048, 128, True), ([72] * 7, 1032, 64, False), ([72] * 8, 1032, 64, True),
+    ([300, 19], 2048, 128, False), ([300, 20], 2048, 128, True), ([76] * 5, 1032, 64, False), ([77] * 5, 1032, 64, True),
     ([10, 134] * 7, 2048, 72, True), ([9, 134] * 7, 2048, 72, False), ([96] * 8, 2048, 16, True), ([95, 96] * 4, 2048, 16, False),
     ([639], 5632, 128, False), ([640], 5632, 128, True), ([1024], 5632, 16, False), ([1025], 5632, 16, True),
     ([80] * 13, 2048, 48, True), ([79] * 13, 2048, 48, False), ([127] * 33, 1032, 40, False), ([127] * 33, 1032, 48, True),
@@ -69,7 +69,7 @@ def test_both_sides_of_each_line(lens, d_in, r, tiles):
     plan.close()
 
 
-@pytest.mark.parametrize("lens,r,tiles", [([64] * 7, 64, False), ([72] * 8, 64, True), ([5, 379], 128, True), ([5, 378], 128, False)])
+@pytest.mark.parametrize("lens,r,tiles", [([64] * 7, 64, False), ([72] * 8, 64, True), ([5, 315], 128, True), ([5, 314], 128, False)])
 def test_quantised_base(lens, r, tiles):
     d_in, T, ctx = 1152, sum(lens), gc.ctx()
     inp, ids, _ = _batch(lens, d_in, 200, r, False)
