@@ -765,7 +765,7 @@ static int route_launches(moin_ctx *ctx, const void *emb, const void *centroids,
     a.cid = centroid_ids ? centroid_ids : (need_cid ? reinterpret_cast<int *>(w + L.cid) : nullptr);
     a.expert_ids = expert_ids;
     a.counts = counts;
-    a.self_clean = self_clean ? 1 : 0;   // 1: norms kernel + self-cleaning kernel, 2: the norms in w are current
+    a.self_clean = self_clean ? 1 : 0;   // 1: self-cleaning kernel, norms to be computed; 2: the norms in w are current
     if (fuse) {
         a.plan = fuse->pv;
         a.seq_offsets = fuse->seq_offsets;
@@ -778,7 +778,8 @@ static int route_launches(moin_ctx *ctx, const void *emb, const void *centroids,
     };
     const bool routed = N > 0 && (a.cid || a.expert_ids);
     if (routed) {
-        if (self_clean != 2 && !a.screen_ws &&
+        a.norms_here = self_clean == 1 && route_computes_norms(a);
+        if (self_clean != 2 && !a.norms_here && !a.screen_ws &&
             run(MOIN_K_ROUTE_AUX, [&] { return launch_centroid_norms(a, st); }) != hipSuccess)
             return MOIN_EHIP;
         if (run(MOIN_K_ROUTE, [&] { return launch_route(a, st); }) != hipSuccess) return MOIN_EHIP;

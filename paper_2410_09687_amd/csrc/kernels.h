@@ -174,6 +174,7 @@ struct RouteArgs {
     int group;                 // route_stream_group() of the call
     int self_clean = 0;        // small batches: best / arrivals are kept clean between calls by the kernel
                                // itself, counts are zeroed by its finishing workgroup (no reset launch)
+    int norms_here = 0;        // the routing launch computes the norms (route_computes_norms): none ahead of it
     // small batches, optional: the routed batch is grouped by expert in the same launch (the queries
     // are the batch's S = N sequences; expert_ids must be given)
     const PlanView *plan = nullptr;
@@ -195,6 +196,8 @@ constexpr int ROUTE_SMALL_MAX_N = 4096;  // up to here the K range is split acro
 // true for the batches that are routed, unpacked and tallied in one launch (N <= ROUTE_SMALL_MAX_N; bf16 with
 // D a multiple of 64, or fp32 with few enough pairs)
 bool route_small_batch(int64_t N, int K, int D, int is_bf16);
+// Batches whose routing launch can compute the centroids' norms on its way.
+bool route_computes_norms(const RouteArgs &a);
 // Workgroups that share one query tile in the large-batch bf16 kernel (1: none).
 int route_stream_group(int64_t N, int K, int D, int is_bf16);
 hipError_t launch_centroid_norms(const RouteArgs &a, hipStream_t stream);

@@ -16,6 +16,7 @@
 #include "gemm_core.h"
 #include "kernels.h"
 #include "route_finish.h"
+#include "wave_sums.h"
 
 namespace moin {
 
@@ -538,9 +539,15 @@ __global__ __launch_bounds__(256) void route_unpack_kernel(const unsigned long l
 // against 64 queries and merges its per-query minimum into best[] with a 64-bit
 // atomic min on (score key << 32 | index): exact, order-independent, and the
 // lowest index wins equal scores.  The workgroup that arrives last unpacks.
-template <class C>
+// NORMS: ||c||^2 is not in memory yet.  Every workgroup sums the squares of its 64 centroids from the blocks as they lie
+// in LDS, in the order and tree of centroid_norm_kernel (the same bits), and the first query tile's leave them in memory
+// for later calls, instead of a launch of 4.3 us ahead.  Us a call, ahead / here: 1 query x 50 x 64 10.2 / 6.3, 100 x 1000 x 256
+// 10.4 / 7.1, 64 x 500 x 768 11.2 / 10.4, 3000 x 100 x 768 18.9 / 17.7.  (One value a lane and row, 16 reads a block: no gain at 768.)
+template <class C, bool NORMS>
 __global__ __launch_bounds__(C::NT) void route_small_kernel(RouteKParams p, int nqt)
 {
+    static_assert(!NORMS || (C::BM == 64 && C::NT == 256 && C::BK == 64), "a wave sums 16 rows, a lane one value of a block");
+    __shared__ __align__(16) float own_norms[NORMS ? C::BM : 4];
     extern __shared__ __align__(16) char smem[];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -555,6 +562,14 @@ __global__ __launch_bounds__(C::NT) void route_small_kernel(RouteKParams p, int 
     const auto lc = C::template make_lanes<C::A_I>(nc);
     const auto lq = C::template make_lanes<C::B_I>(nq);
 
+    float sq[16];
+    int slot_of = 0;
+    const int norm_k = c0 + wave * 16 + (lane & 3) * 4 + (lane >> 4);   // the centroid whose norm this lane ends up with
+    if constexpr (NORMS) {
+#pragma unroll
+        for (int t = 0; t < 16; ++t) sq[t] = 0.f;
+        if (p.retained_only) slot_of = p.slot[min(norm_k, p.K - 1)];
+    }
     typename C::Acc acc;
     C::zero(acc);
 #pragma unroll
@@ -568,6 +583,18 @@ __global__ __launch_bounds__(C::NT) void route_small_kernel(RouteKParams p, int 
         const int ns = (st == 0) ? C::NS - 1 : st - 1;
         if (nb < nkb) C::issue(smem + ns * C::STAGE_BYTES, cb, ld, lc, qb, ld, lq, (uint32_t)nb * (C::BK * 2));
         C::compute_stage(smem + st * C::STAGE_BYTES, acc);
+        if constexpr (NORMS) {
+            // four rows a read, four values a lane: value 4 m + s of the block in lane m of its row's sixteen
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int row = wave * 16 + g * 4 + (lane >> 4);
+                const uint2 w = *reinterpret_cast<const uint2 *>(
+                    smem + st * C::STAGE_BYTES + row * C::ROWB + ((((lane & 15) >> 1) ^ C::swz(row)) * 16) + (lane & 1) * 8);
+                const float v[4] = {bits_f32(w.x << 16), bits_f32(w.x & 0xFFFF0000u), bits_f32(w.y << 16), bits_f32(w.y & 0xFFFF0000u)};
+#pragma unroll
+                for (int s = 0; s < 4; ++s) sq[s * 4 + g] = fmaf(v[s], v[s], sq[s * 4 + g]);
+            }
+        }
         st = (st + 1 == C::NS) ? 0 : st + 1;
     }
 
@@ -578,7 +605,36 @@ __global__ __launch_bounds__(C::NT) void route_small_kernel(RouteKParams p, int 
         bestv[j] = __builtin_inff();
         besti[j] = 0;
     }
-    fold_scores<C>(acc, p.cnorm + c0, c0, bestv, besti);
+    if constexpr (NORMS) {
+        // values 32, 16, 8 and 4 apart are in lanes 8, 4, 2 and 1 apart, those 2 and 1 apart beside each other in a lane:
+        // sums of four rows and four positions at once, then over the positions
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sq[j] = merge_x<8>(sq[j], sq[j + 8], lane);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sq[j] = merge_x<4>(sq[j], sq[j + 4], lane);
+        sq[0] = merge_x<2>(sq[0], sq[2], lane);
+        sq[1] = merge_x<2>(sq[1], sq[3], lane);
+        float s = merge_x<1>(sq[0], sq[1], lane);
+        s += __shfl_xor(s, 8);
+        s += __shfl_xor(s, 4);
+        const float norm = norm_k < p.K && slot_of >= 0 ? s : __builtin_inff();
+        if ((lane & 12) == 0) {
+            own_norms[norm_k - c0] = norm;
+            if (qt == 0) {
+                p.cnorm_out[norm_k] = norm;
+                p.cinit_out[norm_k] = -0.5f * norm;
+            }
+        }
+        if (qt == 0 && c0 + C::BM >= p.K)   // padding up to a multiple of 256
+            for (int k = c0 + C::BM + (int)threadIdx.x; k < (p.K + 255) / 256 * 256; k += C::NT) {
+                p.cnorm_out[k] = __builtin_inff();
+                p.cinit_out[k] = -__builtin_inff();
+            }
+        __syncthreads();
+        fold_scores<C>(acc, own_norms, c0, bestv, besti);
+    } else {
+        fold_scores<C>(acc, p.cnorm + c0, c0, bestv, besti);
+    }
 #pragma unroll
     for (int j = 0; j < C::FN; ++j) {
         const float ov = __shfl_xor(bestv[j], 32);
@@ -737,8 +793,9 @@ hipError_t prepare_route_kernels()
     if ((e = prepare_route_exact_kernels()) != hipSuccess) return e;
     if ((e = allow_lds(&route_kernel<CfgRoute>, CfgRoute::SMEM_BYTES)) != hipSuccess) return e;
     if ((e = allow_lds(&route_stream4_kernel, r4::SMEM_BYTES)) != hipSuccess) return e;
-    if ((e = allow_lds(&route_small_kernel<CfgRouteMid>, CfgRouteMid::SMEM_BYTES)) != hipSuccess) return e;
-    return allow_lds(&route_small_kernel<CfgRouteSmall>, CfgRouteSmall::SMEM_BYTES);
+    if ((e = allow_lds(&route_small_kernel<CfgRouteMid, false>, CfgRouteMid::SMEM_BYTES)) != hipSuccess) return e;
+    if ((e = allow_lds(&route_small_kernel<CfgRouteSmall, true>, CfgRouteSmall::SMEM_BYTES)) != hipSuccess) return e;
+    return allow_lds(&route_small_kernel<CfgRouteSmall, false>, CfgRouteSmall::SMEM_BYTES);
 }
 
 // (5000 centroids, 768 dimensions, us a call with 64 x 64 / 128 x 128 tiles: 256 queries 22 / -, 512: 28 / 22,
@@ -749,6 +806,17 @@ constexpr int64_t ROUTE_MID_MIN_TILES = 128;
 static bool whole_blocks(const RouteArgs &a) { return a.is_bf16 && (a.D % 64 == 0 || a.pad_ws); }
 
 static bool use_small_route(const RouteArgs &a) { return whole_blocks(a) && a.N <= ROUTE_SMALL_MAX_N; }
+
+static bool use_mid_route(const RouteArgs &a)
+{
+    using M = CfgRouteMid;
+    return ((a.N + M::BN - 1) / M::BN) * ((a.K + M::BM - 1) / M::BM) >= ROUTE_MID_MIN_TILES;
+}
+
+bool route_computes_norms(const RouteArgs &a)
+{
+    return use_small_route(a) && a.D % 64 == 0 && a.self_clean && !use_mid_route(a);
+}
 
 static bool use_stream_route(const RouteArgs &a) { return a.is_bf16 && a.D % 64 == 0 && !use_small_route(a); }
 
@@ -823,6 +891,8 @@ hipError_t launch_route(const RouteArgs &a, hipStream_t stream)
     p.finish = finishes_itself(a) ? 1 : 0;
     p.counts = p.finish ? a.counts : nullptr;
     p.N = a.N; p.K = a.K; p.D = a.D;
+    p.cnorm_out = a.cnorm; p.cinit_out = a.cinit; p.retained_only = a.retained_only;
+    if (a.norms_here && !route_computes_norms(a)) return hipErrorInvalidValue;
     p.group = a.group > 1 ? a.group : 1;
     p.n_virtual = 0;
     p.self_clean = p.finish ? a.self_clean : 0;
@@ -854,18 +924,18 @@ hipError_t launch_route(const RouteArgs &a, hipStream_t stream)
             p.cent = pad.cent_p;
             p.D = pad.Dp;
         }
-        auto launch = [&](auto cfg) {
+        auto launch = [&](auto cfg, auto norms) {
             using C = decltype(cfg);
             const int nqt = (int)((a.N + C::BN - 1) / C::BN);
             const int64_t grid = (int64_t)nqt * ((a.K + C::BM - 1) / C::BM);
             if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-            hipLaunchKernelGGL(route_small_kernel<C>, dim3((unsigned)grid), dim3(C::NT),
+            hipLaunchKernelGGL((route_small_kernel<C, decltype(norms)::value>), dim3((unsigned)grid), dim3(C::NT),
                                C::SMEM_BYTES, stream, p, nqt);
             return hipSuccess;
         };
-        using M = CfgRouteMid;
-        const int64_t mid_tiles = ((a.N + M::BN - 1) / M::BN) * ((a.K + M::BM - 1) / M::BM);
-        const hipError_t e = mid_tiles >= ROUTE_MID_MIN_TILES ? launch(M{}) : launch(CfgRouteSmall{});
+        const hipError_t e = use_mid_route(a) ? launch(CfgRouteMid{}, std::false_type{})
+                             : a.norms_here   ? launch(CfgRouteSmall{}, std::true_type{})
+                                              : launch(CfgRouteSmall{}, std::false_type{});
         if (e != hipSuccess) return e;
         if (!p.finish) unpack();
     } else {

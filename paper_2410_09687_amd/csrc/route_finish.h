@@ -19,6 +19,8 @@ struct RouteKParams {
     int *counts;          // batches with a finishing workgroup: tallied by it (zeroed beforehand)
     int64_t N;
     int K, D;
+    float *cnorm_out, *cinit_out;   // small batches: where a launch that computes the norms itself leaves them
+    int retained_only;
     int group;            // streaming kernel: workgroups that share one query tile
     int64_t n_virtual;    // streaming kernel: work items (query tiles rounded up to 8, times group)
     int finish;           // the workgroup that arrives last turns best[] into ids (route_finish)
