@@ -220,6 +220,118 @@ __global__ __launch_bounds__(64 * KM_SCATTER_WAVES) void km_scatter(KmeansArgs a
     }
 }
 
+// Steps 1 to 4 in one launch of one workgroup, for tables of so few points that the launches are what they take.  Each wave
+// has a run of the points and, per centre, a count of its own, which the prefix sum turns into its cursor: runs in order,
+// so that the sort is stable, and no wave waits for another.  Counts and ids take 16 bits: 96 + 10 KB of LDS at the limits.
+// Us of a fit, four launches / one: 1000 points x 16 centres one iteration 58 / 42, 1200 x 40 two 83 / 62, 3000 x 100 three 170 /
+// 143, 5000 x 600 two 179 / 170, but 8000 x 3000 160 / 162, 12 000 x 200 150 / 163, 16 384 x 5000 319 / 359.
+constexpr int KM_ONE_WAVES = 8, KM_ONE_MAX_K = 6144, KM_ONE_MAX_N = 5120;
+static bool km_sort_in_one(int64_t N, int K) { return N > 0 && N <= KM_ONE_MAX_N && K <= KM_ONE_MAX_K; }
+static size_t km_one_lds(int64_t N, int K) { return (size_t)K * KM_ONE_WAVES * 2 + ((size_t)N + 7) / 8 * 16; }
+__global__ __launch_bounds__(64 * KM_ONE_WAVES) void km_sort_one(KmeansArgs a, int id_bits)
+{
+    extern __shared__ __align__(16) unsigned km_cur[];   // [K][KM_ONE_WAVES] 16-bit counts, then cursors
+    constexpr int NW = KM_ONE_WAVES, NT = 64 * NW;
+    static_assert(KM_ONE_MAX_N < (1 << 16) && KM_ONE_MAX_K < 0xffff, "cursors and ids in 16 bits");
+    __shared__ int sums[2][NW];
+    uint16_t *cur = reinterpret_cast<uint16_t *>(km_cur);
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    const int K = a.K, N = (int)a.N;
+    for (int i = tid; i < K * (NW / 2); i += NT) km_cur[i] = 0;
+    lds_barrier();
+    const int run = ((N + NW - 1) / NW + 63) / 64 * 64;
+    const int i0 = min(wave * run, N), i1 = min(i0 + run, N);
+    bool bad = false;
+    uint16_t *ids = cur + K * NW;   // [N], 0xffff: out of range
+    for (int i = i0 + lane; i < i1; i += 256) {   // four ids of a lane on their way
+        int v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = a.ids[min(i + 64 * u, i1 - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (i + 64 * u >= i1) break;
+            const bool ok = (unsigned)v[u] < (unsigned)K;
+            if (ok) atomicAdd(&km_cur[(v[u] * NW + wave) >> 1], 1u << (16 * (wave & 1)));
+            bad = bad || !ok;
+            ids[i + 64 * u] = (uint16_t)(ok ? v[u] : 0xffff);
+        }
+    }
+    if (bad) atomicOr(a.err_word, ERR_BAD_ID);
+    lds_barrier();
+    // centres in order, a run of them per thread
+    const int per = (K + NT - 1) / NT;
+    const int k0 = min(tid * per, K), k1 = min(k0 + per, K);
+    auto count_of = [&](int k) __attribute__((always_inline)) {
+        const uint4 w = *reinterpret_cast<const uint4 *>(&km_cur[k * (NW / 2)]);
+        const unsigned t = (w.x & 0xffff) + (w.x >> 16) + (w.y & 0xffff) + (w.y >> 16) + (w.z & 0xffff) + (w.z >> 16) + (w.w & 0xffff) + (w.w >> 16);
+        return (int)t;
+    };
+    int cnt = 0, pcs = 0;
+    for (int k = k0; k < k1; ++k) {
+        const int c = count_of(k);
+        cnt += c;
+        pcs += (c + KM_PIECE - 1) / KM_PIECE;
+    }
+    int at_c = cnt, at_p = pcs;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int yc = __shfl_up(at_c, off), yp = __shfl_up(at_p, off);
+        at_c += lane >= off ? yc : 0;
+        at_p += lane >= off ? yp : 0;
+    }
+    if (lane == 63) {
+        sums[0][wave] = at_c;
+        sums[1][wave] = at_p;
+    }
+    lds_barrier();
+    at_c -= cnt;
+    at_p -= pcs;
+    int all_c = 0, all_p = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const int c = sums[0][w], q = sums[1][w];
+        at_c += w < wave ? c : 0;
+        at_p += w < wave ? q : 0;
+        all_c += c;
+        all_p += q;
+    }
+    for (int k = k0; k < k1; ++k) {
+        const int c = count_of(k);
+        a.counts[k] = c;
+        a.seg_start[k] = at_c;
+        a.piece_start[k] = at_p;
+        for (int f = 0; f < c; f += KM_PIECE) a.pieces[at_p++] = make_int4(k, at_c + f, at_c + min(f + KM_PIECE, c), 0);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const int n = cur[k * NW + w];
+            cur[k * NW + w] = (uint16_t)at_c;
+            at_c += n;
+        }
+    }
+    if (tid == 0) {
+        a.seg_start[K] = all_c;
+        a.piece_start[K] = all_p;
+        *a.n_pieces = all_p;
+    }
+    lds_barrier();
+    const uint64_t lt = lanemask_lt();
+    for (int i = i0 + lane; i - lane < i1; i += 64) {   // (a wave's LDS operations stay in order)
+        const int id = i < i1 ? ids[i] : 0xffff;
+        const bool ok = id < K;
+        uint64_t m = __ballot(ok);
+        for (int bit = 0; bit < id_bits; ++bit) {
+            const bool one = (id >> bit) & 1;
+            const uint64_t bal = __ballot(one);
+            m &= one ? bal : ~bal;
+        }
+        if (ok) {
+            const int at = id * NW + wave, rank = __popcll(m & lt), base = cur[at];
+            a.perm[base + rank] = i;
+            if (rank == 0) cur[at] = (uint16_t)(base + __popcll(m));   // (all of them have read it: one instruction for the wave)
+        }
+    }
+}
+
 // VPC values per 16-byte chunk: 8 (bf16) or 4 (fp32).
 template <int VPC>
 __device__ __forceinline__ void km_unpack(const uint4 &v, float (&f)[VPC])
@@ -394,6 +506,9 @@ hipError_t prepare_kmeans_kernels()
 {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&km_chunk_hist),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, KM_MAX_K * 4);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&km_sort_one), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)km_one_lds(KM_ONE_MAX_N, KM_ONE_MAX_K));
     if (e != hipSuccess) return e;
     return hipFuncSetAttribute(reinterpret_cast<const void *>(&km_scatter),
                                hipFuncAttributeMaxDynamicSharedMemorySize, KM_MAX_K * 4);
@@ -416,6 +531,12 @@ void kmeans_shape(int64_t N, int K, int D, int is_bf16, int *chunk, int *n_chunk
 // Steps 1-4: perm[] and the piece list.
 hipError_t launch_kmeans_sort(const KmeansArgs &a, hipStream_t stream)
 {
+    if (km_sort_in_one(a.N, a.K)) {
+        int id_bits = 1;
+        while ((a.K - 1) >> id_bits) ++id_bits;
+        hipLaunchKernelGGL(km_sort_one, dim3(1), dim3(64 * KM_ONE_WAVES), km_one_lds(a.N, a.K), stream, a, id_bits);
+        return hipGetLastError();
+    }
     const size_t lds = (size_t)a.K * 4;
     if (a.N > 0) hipLaunchKernelGGL(km_chunk_hist, dim3(a.n_chunks), dim3(256), lds, stream, a);
     hipLaunchKernelGGL(km_col_scan, dim3((a.K + 63) / 64), dim3(64 * KM_SCAN_WAVES), 0, stream, a);
