@@ -1,4 +1,4 @@
-// Prefill main kernel for calls of few tiles, and for contraction lengths that are not whole blocks (Section 3.2:
+// Prefill main kernels for calls of few tiles, and for contraction lengths that are not whole blocks (Section 3.2:
 // y = W x + W_b (W_a x), one adapter per sequence).
 //
 // The products of linear_stream.hip, k-step for k-step in the same order, so that its results are the same bits, on
@@ -28,36 +28,43 @@ using stream::BK;
 using stream::ROWB;
 constexpr int NW = 4, NT = NW * 64;
 
-constexpr int FP = 4, FQ = 4;          // 16 x 16 accumulators per wave: 64 outputs x 64 tokens
-constexpr int BT = 128;                // tile edge, both ways
-constexpr int SUB = TILE_M / BT;       // tiles per plan tile
+// BT_: tile edge, both ways
+template <int BT_>
+struct Shape {
+    static constexpr int BT = BT_;
+    static constexpr int FP = BT / 32, FQ = BT / 32;   // 16 x 16 accumulators per wave: half of the outputs x half of the tokens
+    static constexpr int SUB = TILE_M / BT;            // tiles per plan tile
+    static constexpr int P_BYTES = BT * ROWB, STAGE_BYTES = 2 * P_BYTES;
+    static constexpr int LOADS = FP + FQ;              // requests of a wave per block, 8 rows each
+    static constexpr int SCR_BYTES = 16 * FP * 16 * 4; // epilogue scratch of a wave: 16 tokens x its outputs, fp32
+    static_assert(NW * SCR_BYTES <= 2 * STAGE_BYTES, "the scratch takes the stages' place");
+};
+constexpr int BT = 128, SUB = TILE_M / BT;
 static_assert(SUB == 2, "HalfTiles");
-constexpr int P_BYTES = BT * ROWB, STAGE_BYTES = 2 * P_BYTES;
-constexpr int LOADS = FP + FQ;         // requests of a wave per block, 8 rows each
-constexpr int SCR_BYTES = 16 * FP * 16 * 4;   // epilogue scratch of a wave: 16 tokens x its outputs, fp32
-static_assert(NW * SCR_BYTES <= 2 * STAGE_BYTES, "the scratch takes the stages' place");
 
 // what the lanes past an operand row's end fetch
 __device__ __align__(16) const unsigned int zero16[4] = {0, 0, 0, 0};
 
 }  // namespace mid
 
-template <int NS, bool Y_F32, bool RAGGED>
-__global__ __launch_bounds__(mid::NT, NS == 2 ? 2 : 1) void linear_mid_kernel(stream::Params p)
+template <int NS, bool Y_F32, bool RAGGED, int BT>
+__device__ __forceinline__ void mid_tile(const stream::Params &p)
 {
     using namespace mid;
+    using S = Shape<BT>;
+    constexpr int FP = S::FP, FQ = S::FQ, P_BYTES = S::P_BYTES, STAGE_BYTES = S::STAGE_BYTES, LOADS = S::LOADS, SCR_BYTES = S::SCR_BYTES;
     extern __shared__ __align__(16) char smem[];
     const int lane = threadIdx.x & 63;
     const int wave = uniform(threadIdx.x >> 6);
     const int wp = wave >> 1, wq = wave & 1;
 
-    const HalfTiles halves(p.tile_rows, p.n_tiles, p.max_tiles);
-    const int ntm = halves.count;
+    const std::conditional_t<S::SUB == 2, HalfTiles, QuarterTiles> parts(p.tile_rows, p.n_tiles, p.max_tiles);
+    const int ntm = parts.count;
     const int id = xcd_band_id(blockIdx.x, ntm * p.n_tiles_n);
     if (id < 0) return;
     const int tm = p.by_columns ? id % ntm : id / p.n_tiles_n;
     const int tn = p.by_columns ? id / ntm : id % p.n_tiles_n;
-    const stream::Tile t = stream::load_tile<BT, BT>(p, halves.find(tm), tn);
+    const stream::Tile t = stream::load_tile<BT, BT>(p, parts.find(tm), tn);
     if (t.q_rows <= 0) return;
 
     const int nkb0 = (p.d_in + BK - 1) / BK;
@@ -119,7 +126,8 @@ __global__ __launch_bounds__(mid::NT, NS == 2 ? 2 : 1) void linear_mid_kernel(st
 
     const int total = t.total;
     constexpr int M = FP * FQ, R = FP + FQ;
-    static_assert(M >= 2 * R, "a gap for every read and every request");
+    static_assert(M >= 2 * R || M >= R, "a gap for every read and every request, or for the two together");
+    constexpr int GAP = M >= 2 * R ? 2 : 1;   // MFMAs per read (and request) of the second k-step
     // One block: k-step 0 with the reads of k-step 1, the barrier, k-step 1 with the reads of the next block's k-step 0
     // and (MORE) the requests of the block NS ahead into the stage that is now free.
     auto body = [&](int b, char *st_cur, const char *st_nxt, auto first_tag, auto more_tag) __attribute__((always_inline)) {
@@ -141,13 +149,13 @@ __global__ __launch_bounds__(mid::NT, NS == 2 ? 2 : 1) void linear_mid_kernel(st
 #pragma unroll
         for (int n = 0; n < M; ++n) {
             mfma(1, n / FQ, n % FQ);
-            if (n % 2 == 0 && n / 2 < R) {
-                read_one(st_nxt, lo0, 0, frag_at(n / 2));
+            if (n % GAP == 0 && n / GAP < R) {
+                read_one(st_nxt, lo0, 0, frag_at(n / GAP));
                 __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (MORE)
-                if (n % 2 == 1 && n / 2 < R) {
-                    issue_one(f, st_cur, n / 2);
+                if (n % GAP == GAP - 1 && n / GAP < R) {
+                    issue_one(f, st_cur, n / GAP);
                     __builtin_amdgcn_sched_barrier(0);
                 }
         }
@@ -236,8 +244,12 @@ __global__ __launch_bounds__(mid::NT, NS == 2 ? 2 : 1) void linear_mid_kernel(st
             };
 #pragma unroll
             for (int ps = 0; ps < NPS; ps += 2) {
-                const uint4 v0 = rd(ps), v1 = rd(ps + 1);
-                st_(ps, v0), st_(ps + 1, v1);
+                if constexpr (NPS == 1) {
+                    st_(ps, rd(ps));
+                } else {
+                    const uint4 v0 = rd(ps), v1 = rd(ps + 1);
+                    st_(ps, v0), st_(ps + 1, v1);
+                }
             }
             lds_order();
         }
@@ -245,32 +257,55 @@ __global__ __launch_bounds__(mid::NT, NS == 2 ? 2 : 1) void linear_mid_kernel(st
 }
 
 template <int NS, bool Y_F32, bool RAGGED>
-static hipError_t allow_lds()
+__global__ __launch_bounds__(mid::NT, NS == 2 ? 2 : 1) void linear_mid_kernel(stream::Params p)
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_mid_kernel<NS, Y_F32, RAGGED>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, NS * mid::STAGE_BYTES);
+    mid_tile<NS, Y_F32, RAGGED, mid::BT>(p);
 }
-template <int NS>
+
+// The same on 64 x 64 tiles, one per compute unit, eight stages: half the bytes through LDS per block and more blocks on
+// their way, for calls of so few tiles that most of the chip would stand idle under the larger ones.  Us of the kernel,
+// 128 x 128 / these: 500 tokens 2048 -> 2048 20 / 14, 330 2048 -> 2048, 256, 256 20 / 14, 4000 2048 -> 256 19 / 14, 640 1024 -> 1416
+// 14 / 10, 1200 256 -> 256 9 / 8.  Beyond a tile per unit, 640 2048 -> 2048, 20 / 22.
+constexpr int FINE_BT = 64, FINE_NS = 8;
+template <bool Y_F32, bool RAGGED>
+__global__ __launch_bounds__(mid::NT, 1) void linear_fine_kernel(stream::Params p)
+{
+    mid_tile<FINE_NS, Y_F32, RAGGED, FINE_BT>(p);
+}
+
+// The kernel for NS stages of BT x BT tiles.
+template <int NS, int BT>
+static auto mid_kernel(bool y_f32, bool ragged)
+{
+    if constexpr (BT == FINE_BT)
+        return y_f32 ? (ragged ? &linear_fine_kernel<true, true> : &linear_fine_kernel<true, false>)
+                     : (ragged ? &linear_fine_kernel<false, true> : &linear_fine_kernel<false, false>);
+    else
+        return y_f32 ? (ragged ? &linear_mid_kernel<NS, true, true> : &linear_mid_kernel<NS, true, false>)
+                     : (ragged ? &linear_mid_kernel<NS, false, true> : &linear_mid_kernel<NS, false, false>);
+}
+template <int NS, int BT>
 static hipError_t allow_lds_all()
 {
-    hipError_t e = allow_lds<NS, false, false>();
-    if (e == hipSuccess) e = allow_lds<NS, true, false>();
-    if (e == hipSuccess) e = allow_lds<NS, false, true>();
-    if (e == hipSuccess) e = allow_lds<NS, true, true>();
+    hipError_t e = hipSuccess;
+    for (int v = 0; v < 4 && e == hipSuccess; ++v)
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(mid_kernel<NS, BT>(v & 1, v & 2)),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, NS * mid::Shape<BT>::STAGE_BYTES);
     return e;
 }
 
 hipError_t prepare_mid_kernels()
 {
-    const hipError_t e = allow_lds_all<2>();
-    return e == hipSuccess ? allow_lds_all<4>() : e;
+    hipError_t e = allow_lds_all<2, mid::BT>();
+    if (e == hipSuccess) e = allow_lds_all<4, mid::BT>();
+    return e == hipSuccess ? allow_lds_all<FINE_NS, FINE_BT>() : e;
 }
 
-static int64_t mid_tiles(const PlanView &pv, const LinearArgs *a, int n)
+static int64_t mid_tiles(const PlanView &pv, const LinearArgs *a, int n, int bt = mid::BT)
 {
     int64_t tn = 0;
-    for (int i = 0; i < n; ++i) tn += (a[i].d_out + mid::BT - 1) / mid::BT;
-    return host_tiles(pv, mid::BT) * tn;
+    for (int i = 0; i < n; ++i) tn += (a[i].d_out + bt - 1) / bt;
+    return host_tiles(pv, bt) * tn;
 }
 
 // Up to the tiles that the chip holds at a time.  Us of the kernel, 256 x 256 tiles / these: 2048 -> 2048 448 tiles 42 / 31, 512 45 /
@@ -299,33 +334,29 @@ bool mid_beats_stream(const PlanView &pv, const LinearArgs *a, int n, int n_cus)
     return mid_tiles(pv, a, n) <= 2 * n_cus * tile_rounds(pv, tn, n_cus);
 }
 
-template <int NS>
-static hipError_t launch_mid(const stream::Params &p, unsigned grid, hipStream_t stream_)
+template <int NS, int BT>
+static hipError_t launch_mid(const PlanView &pv, const LinearArgs *a, int n, hipStream_t stream_)
 {
-#define MOIN_MID(Y32, RAG) \
-    hipLaunchKernelGGL((linear_mid_kernel<NS, Y32, RAG>), dim3(grid), dim3(mid::NT), NS * mid::STAGE_BYTES, stream_, p)
+    using S = mid::Shape<BT>;
+    stream::Params p;
+    const int tn = stream::fill_params(&p, pv, a, n, BT);
+    // the larger operand's rows are dealt out over the XCDs, the smaller one is read by all of them
+    p.by_columns = (int64_t)tn * BT > pv.T;
+    const int64_t work = (int64_t)pv.max_tiles * S::SUB * tn;
+    if (work > 0x7ffffff0LL) return hipErrorInvalidValue;
+    const unsigned grid = (unsigned)((work + 7) / 8 * 8);
     const bool ragged = p.r % mid::BK != 0 || p.d_in % mid::BK != 0;
-    if (p.y_f32 && ragged) MOIN_MID(true, true);
-    else if (p.y_f32) MOIN_MID(true, false);
-    else if (ragged) MOIN_MID(false, true);
-    else MOIN_MID(false, false);
-#undef MOIN_MID
+    hipLaunchKernelGGL((mid_kernel<NS, BT>(p.y_f32, ragged)), dim3(grid), dim3(mid::NT), NS * S::STAGE_BYTES, stream_, p);
     return hipGetLastError();
 }
 
 hipError_t launch_linear_mid(const PlanView &pv, const LinearArgs *a, int n, int n_cus, hipStream_t stream_)
 {
     if (n < 1 || n > MAX_SHARED_X) return hipErrorInvalidValue;
-    stream::Params p;
-    const int tn = stream::fill_params(&p, pv, a, n, mid::BT);
-    // the larger operand's rows are dealt out over the XCDs, the smaller one is read by all of them
-    p.by_columns = (int64_t)tn * mid::BT > pv.T;
-    const int64_t work = (int64_t)pv.max_tiles * mid::SUB * tn;
-    if (work > 0x7ffffff0LL) return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)((work + 7) / 8 * 8);
+    if (pv.max_tiles <= QuarterTiles::MAX && mid_tiles(pv, a, n, FINE_BT) <= n_cus) return launch_mid<FINE_NS, FINE_BT>(pv, a, n, stream_);
     // (Us of the kernel, four stages / two: 240 tiles 20 / 25, 256 22 / 26, 268 37 / 29, 320 36 / 30.)
-    if (mid_tiles(pv, a, n) <= n_cus) return launch_mid<4>(p, grid, stream_);
-    return launch_mid<2>(p, grid, stream_);
+    if (mid_tiles(pv, a, n) <= n_cus) return launch_mid<4, mid::BT>(pv, a, n, stream_);
+    return launch_mid<2, mid::BT>(pv, a, n, stream_);
 }
 
 }  // namespace moin

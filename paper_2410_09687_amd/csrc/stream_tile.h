@@ -55,6 +55,37 @@ private:
     }
 };
 
+// The same with quarters of plan tiles, of calls of at most MAX plan tiles.
+struct QuarterTiles {
+    static constexpr int MAX = 64;
+    unsigned long long more[3];   // which plan tiles have tokens in their second, third, fourth quarter
+    int n_tiles, count;
+
+    __device__ __forceinline__ QuarterTiles(const int *tile_rows, const int *n_tiles_, int max_tiles)
+    {
+        const int lane = threadIdx.x & 63;
+        const int rows = lane < max_tiles ? tile_rows[lane] : 0;   // (under way with the number of tiles)
+        n_tiles = min(uniform(*n_tiles_), MAX);
+        count = n_tiles;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            more[q] = __ballot(lane < n_tiles && rows > (q + 1) * (TILE_M / 4));
+            count += __popcll(more[q]);
+        }
+    }
+    // Quarter number j (< count): its plan tile times four, plus its place there.
+    __device__ __forceinline__ int find(int j) const
+    {
+        const int lane = threadIdx.x & 63;
+        auto before = [&](int t) {   // quarters of the first t tiles
+            const unsigned long long m = (1ull << t) - 1;
+            return t + __popcll(more[0] & m) + __popcll(more[1] & m) + __popcll(more[2] & m);
+        };
+        const int t = __popcll(__ballot(lane < n_tiles && before(lane) <= j)) - 1;
+        return uniform(t * 4 + j - before(t));
+    }
+};
+
 namespace stream {
 
 constexpr int BK = 64;          // contraction steps of a block

@@ -42,7 +42,7 @@ def _counted(ctx, call):
     ([319], 64, 128, False), ([320], 64, 128, True), ([64] * 5, 1000, 64, True), ([64] * 5 + [63], 1024, 64, False),
     ([383], 1024, 8, False), ([384], 1024, 8, True), ([20, 140] * 5, 72, 40, True), ([19, 140] * 5, 72, 40, False),
     ([300, 19], 2048, 128, False), ([300, 20], 2048, 128, True), ([76] * 5, 1032, 64, False), ([77] * 5, 1032, 64, True),
-    ([10, 134] * 7, 2048, 72, True), ([9, 134] * 7, 2048, 72, False), ([96] * 8, 2048, 16, True), ([95, 96] * 4, 2048, 16, False),
+    ([10, 134] * 7, 2048, 72, True), ([9, 134] * 7, 2048, 72, False), ([96] * 8, 2048, 16, True), ([95, 96] * 4, 2048, 16, False), ([153] * 5, 2048, 32, False), ([154] * 5, 2048, 32, True),
     ([639], 5632, 128, False), ([640], 5632, 128, True), ([1024], 5632, 16, False), ([1025], 5632, 16, True),
     ([80] * 13, 2048, 48, True), ([79] * 13, 2048, 48, False), ([127] * 33, 1032, 40, False), ([127] * 33, 1032, 48, True),
     ([400] * 2, 2048, 136, False), ([1, 500, 0, 3, 150], 2048, 128, True)])
