@@ -32,6 +32,15 @@ using PlanLdsSmall = PlanLds<PLAN_THREADS_SMALL, PLAN_CAP_SMALL>;
 using PlanLdsMax = PlanLds<PLAN_THREADS_MAX, PLAN_CAP_MAX>;
 
 // Exclusive prefix sums of N values per thread over the workgroup, and the totals.
+// Barrier for what goes through LDS.  Nothing written to memory is read back, so four waves wait for LDS alone (__syncthreads also
+// waits until every store has arrived); sixteen waves are faster by __syncthreads (1024 sequences: 10.9 us for the kernel, 11.5).
+template <int PT>
+__device__ __forceinline__ void plan_meet()
+{
+    if constexpr (PT == PLAN_THREADS_SMALL) lds_barrier();
+    else __syncthreads();
+}
+
 template <int PT, int N>
 __device__ __forceinline__ void plan_scan(int (&v)[N], int (&total)[N], int (*sums)[PT / 64])
 {
@@ -49,7 +58,7 @@ __device__ __forceinline__ void plan_scan(int (&v)[N], int (&total)[N], int (*su
     if (lane == 63)
 #pragma unroll
         for (int k = 0; k < N; ++k) sums[k][wave] = v[k];
-    lds_barrier();
+    plan_meet<PT>();
 #pragma unroll
     for (int k = 0; k < N; ++k) {
         int before = 0, all = 0;
@@ -62,7 +71,7 @@ __device__ __forceinline__ void plan_scan(int (&v)[N], int (&total)[N], int (*su
         v[k] += before - own[k];
         total[k] = all;
     }
-    lds_barrier();
+    plan_meet<PT>();
 }
 
 // Rank of adapter slot e ("Future Works": adaptive rank per topic).  Multiples of 8,
@@ -117,8 +126,7 @@ __device__ __forceinline__ void plan_base_only(const PlanView &pv, int nt_thread
 // The whole grouping of a batch of at most CAP sequences, by ONE workgroup of PT threads (all of them must
 // call it), in LDS.  A device function so that the kernel that routes a request-sized batch can go on to group
 // it in the same launch; that kernel hands in LDS it has no more use for.
-// Bound by latency: trips to memory, barriers, dependent LDS reads.  Nothing written to memory is read back, so the
-// barriers wait for LDS alone (__syncthreads also waits until every store has arrived).  The sort is stable and takes the digits
+// Bound by latency: trips to memory, barriers, dependent LDS reads.  The sort is stable and takes the digits
 // of the expert alone: up to PLAN_COUNT_S sequences each finds its place by comparing itself with all others
 // (one barrier), beyond them a radix sort, 7 bits a pass, lanes of a wave that share a digit finding each other
 // with one ballot per bit.  (It was a bitonic sort of 64-bit keys: 36 barriers for 256 sequences, and above
@@ -135,13 +143,14 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
     auto rank_of = [&](int s, int e) __attribute__((always_inline)) {
         return Lds::KEEPS ? L.rank[s] : plan_rank_of(e, rank_of_expert, err_word);
     };
+    constexpr bool COMPARES = CAP <= PLAN_CAP_SMALL;   // (the larger instantiation gets no batch that small: less code to fetch, 0.3 us)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int S = pv.S;
     const int T = (int)pv.T;
 
     // 1. validate, fetch the experts
     if (tid == 0) L.bad_offsets = L.any_long = 0;
-    lds_barrier();
+    plan_meet<PT>();
     int err = 0;
     if constexpr (!IDS_IN_LDS) {
         if (tid == 0 && (seq_offsets[0] != 0 || seq_offsets[S] != T)) err |= ERR_BAD_OFFSETS;
@@ -168,11 +177,11 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
             }
         }
     }
-    if (S <= PLAN_COUNT_S && tid < 16 && S + tid < (S + 15) / 16 * 16) L.ekey[S + tid] = ~0u;   // whole turns of the comparison
+    if (COMPARES && S <= PLAN_COUNT_S && tid < 16 && S + tid < (S + 15) / 16 * 16) L.ekey[S + tid] = ~0u;   // whole turns of the comparison
     if (err) atomicOr(err_word, err);
     if (err & ERR_BAD_OFFSETS) L.bad_offsets = 1;
     plan_plain_tiles(pv, PT);
-    lds_barrier();
+    plan_meet<PT>();
     if (L.bad_offsets) {
         plan_base_only(pv, PT);
         return;
@@ -180,8 +189,8 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
 
     // 2. sort the sequences by expert, stably
     int cur = 0;
-    if (S <= PLAN_COUNT_S) {
-        static_assert(PT >= PLAN_COUNT_S && CAP >= PLAN_COUNT_S && PLAN_COUNT_S % 16 == 0, "a sequence per thread");
+    if (COMPARES && S <= PLAN_COUNT_S) {
+        static_assert(!COMPARES || (PT >= PLAN_COUNT_S && CAP >= PLAN_COUNT_S && PLAN_COUNT_S % 16 == 0), "a sequence per thread");
         if (tid < S) {
             // sixteen keys a turn, four per LDS read: one at a time their latency made it 2.1 us for 64 sequences, now 1.2
             const unsigned me = L.ekey[tid];
@@ -199,7 +208,7 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
             L.idx[1][at] = (uint16_t)tid;
         }
         cur = 1;
-        lds_barrier();
+        plan_meet<PT>();
     } else {
         constexpr int NW = PT / 64;
         const int per_wave = ((S + NW - 1) / NW + 63) / 64 * 64;
@@ -209,7 +218,7 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
             for (int d = lane; d < 128; d += 64) L.hist[wave][d] = 0;
             for (int i = w0 + lane; i < w1; i += 64)   // (a wave's own row: its LDS operations stay in order)
                 atomicAdd(&L.hist[wave][(L.ekey[L.idx[cur][i]] >> shift) & 127], 1);
-            lds_barrier();
+            plan_meet<PT>();
             // cursors: digits in order, the waves of a digit in order
             constexpr int PER = 128 * NW / PT;   // 2
             int c[PER], v[1] = {0}, total[1];
@@ -226,7 +235,7 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
                 L.hist[f % NW][f / NW] = v[0];
                 v[0] += c[q];
             }
-            lds_barrier();
+            plan_meet<PT>();
             for (int i = w0 + lane; i - lane < w1; i += 64) {
                 const bool ok = i < w1;
                 const int s = ok ? L.idx[cur][i] : 0;
@@ -245,7 +254,7 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
                 }
             }
             cur ^= 1;
-            lds_barrier();
+            plan_meet<PT>();
         }
     }
     const uint16_t *order = L.idx[cur];
@@ -288,7 +297,7 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
         }
     }
     if (!pv.decode) return;
-    lds_barrier();
+    plan_meet<PT>();
     const int n_tok = min(total[1], T), n_groups = total[2];
     if (L.any_long) {
         // The longer sequences: eight lanes each, whole waves for the very long ones.  (A wave for each took 0.11 us a
