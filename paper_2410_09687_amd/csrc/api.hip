@@ -155,6 +155,18 @@ int ensure_ws(moin_ctx *ctx, size_t bytes, hipStream_t st, bool exact = false)
     return MOIN_OK;
 }
 
+// The same for a call that needs `bytes` where a smaller batch of its kind may need more, up to `keep` (it takes the other
+// grouping, or its base product more parts): an eager call then sizes the workspace for both, so that the largest batch
+// prepares captured calls of all smaller ones.
+int ensure_ws_smaller(moin_ctx *ctx, size_t bytes, size_t keep, hipStream_t st)
+{
+    if (keep > bytes && keep > ctx->ws_bytes && !capturing(st)) {
+        const int rc = ensure_ws(ctx, keep, st);
+        if (rc != MOIN_ENOMEM) return rc;
+    }
+    return ensure_ws(ctx, bytes, st);
+}
+
 hipEvent_t take_event(moin_ctx *ctx)
 {
     if (!ctx->free_events.empty()) {
@@ -281,6 +293,13 @@ bool gathered_pays(const PlanView &pv, int d_in, int r)
     if (pv.T > DECODE_MAX_T && rank == 1 && deep > 0) min_len = 80;
     if (pv.T > 4096 && rank == 0 && deep > 0) return true;   // (up to GATHER_MAX_AVG_LEN tokens a sequence)
     return pv.T < min_tokens[deep][rank] || pv.T < (int64_t)min_len * pv.S;
+}
+
+// What gathered calls of the plan's size and smaller ones ask of the workspace, at most.
+size_t gathered_ws(const PlanView &pv, int d_in, int d_out, int r)
+{
+    const int64_t rows = pv.max_plain > 0 ? pv.T : decode_base_rows(pv.T, d_in, d_out);
+    return 2 * align_up((size_t)pv.T * (size_t)r * 2, 256) + align_up((size_t)rows * (size_t)d_out * 4, 256);
 }
 
 // The plan's buffer, at least `bytes` large; same rules under stream capture as ensure_ws.
@@ -414,7 +433,7 @@ int linear_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, con
     const size_t u_bytes = align_up((size_t)pv.T * (size_t)a.ldu * 2, 256);
     if (!gathered) {
         if (a.r > 0) {
-            const int rc = ensure_ws(ctx, 2 * u_bytes, stream);
+            const int rc = ensure_ws_smaller(ctx, 2 * u_bytes, pv.decode ? gathered_ws(pv, d_in, d_out, r) : 0, stream);
             if (rc != MOIN_OK) return rc;
             a.u_hi = ctx->ws;
             a.u_lo = static_cast<char *>(ctx->ws) + u_bytes;
@@ -455,7 +474,7 @@ int linear_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, con
     d.lin = a;
     d.k_splits = big ? 1 : decode_base_splits(pv.T, d_in, d_out);
     const size_t yb_bytes = align_up((size_t)d.k_splits * (size_t)pv.T * (size_t)d_out * 4, 256);
-    const int rc = ensure_ws(ctx, 2 * u_bytes + yb_bytes, stream);
+    const int rc = ensure_ws_smaller(ctx, 2 * u_bytes + yb_bytes, gathered_ws(pv, d_in, d_out, r), stream);
     if (rc != MOIN_OK) return rc;
     char *w = static_cast<char *>(ctx->ws);
     d.ug_hi = w;
@@ -519,7 +538,12 @@ int linear_mx_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, 
     // decode-sized batches with adapters: the base product for all tokens at once as
     // fp32 partial planes, then the decode path's own shrink and expand kernels
     const bool gathered = gathered_pays(pv, d_in, a.r), decode = gathered && a.r > 0;
-    size_t yb_bytes = 0;
+    size_t yb_bytes = 0, yb_smaller = 0;
+    if (pv.decode && !gathered) {
+        int parts = 0, per = 0;
+        mx_plain_shape(pv.T, d_in, d_out, &parts, &per);
+        yb_smaller = align_up((size_t)parts * (size_t)pv.T * (size_t)d_out * 4, 256);
+    }
     if (decode) {
         mx_plain_shape(pv.T, d_in, d_out, &m.plain_splits, &m.plain_kb_per_split);
         yb_bytes = align_up((size_t)m.plain_splits * (size_t)pv.T * (size_t)d_out * 4, 256);
@@ -527,7 +551,8 @@ int linear_mx_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, 
         m.plain_splits = 1;            // no adapters anywhere: the plain product writes y itself
         m.plain_kb_per_split = d_in / 128;
     }
-    const int rc = ensure_ws(ctx, 2 * u_bytes + xq_bytes + xs_bytes + yb_bytes, stream);
+    const size_t head_bytes = 2 * u_bytes + xq_bytes + xs_bytes;
+    const int rc = ensure_ws_smaller(ctx, head_bytes + yb_bytes, head_bytes + yb_smaller, stream);
     if (rc != MOIN_OK) return rc;
     char *w = static_cast<char *>(ctx->ws);
     a.u_hi = w;
@@ -1068,7 +1093,7 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
         // Decode-sized batch: the projections' base tiles and shrink slabs in one launch, their expand
         // blocks in another, where they agree in everything those launches share.
         DecodeArgs d[MAX_SHARED_X];
-        size_t off[MAX_SHARED_X], total = 0;
+        size_t off[MAX_SHARED_X], total = 0, smaller = 0;
         const size_t u_bytes = align_up((size_t)pv.T * (size_t)r * 2, 256);
         for (int i = 0; i < n; ++i) {
             LinearArgs &a = d[i].lin;
@@ -1080,9 +1105,10 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
             d[i].ybase_by_pos = 1;
             off[i] = total;
             total += 2 * u_bytes + align_up((size_t)d[i].k_splits * (size_t)pv.T * (size_t)d_out[i] * 4, 256);
+            smaller += gathered_ws(pv, d_in, d_out[i], r);
         }
         if (decode_shared_fits(pv, d, n)) {
-            const int rc = ensure_ws(ctx, total, st);
+            const int rc = ensure_ws_smaller(ctx, total, smaller, st);
             if (rc != MOIN_OK) return rc;
             for (int i = 0; i < n; ++i) {
                 char *w = static_cast<char *>(ctx->ws) + off[i];
@@ -1116,7 +1142,9 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
     a.d_in = d_in; a.d_out = 0; a.r = r; a.scale = scale; a.act = ctx->act;
     a.ldu = prefill_ldu(a);
     const size_t u_bytes = align_up((size_t)pv.T * (size_t)a.ldu * 2, 256);
-    const int rc = ensure_ws(ctx, (size_t)n * 2 * u_bytes, st);
+    size_t smaller = 0;
+    for (int i = 0; pv.decode && i < n; ++i) smaller += gathered_ws(pv, d_in, d_out[i], r);
+    const int rc = ensure_ws_smaller(ctx, (size_t)n * 2 * u_bytes, smaller, st);
     if (rc != MOIN_OK) return rc;
     void *u_hi[MAX_SHARED_X], *u_lo[MAX_SHARED_X];
     for (int i = 0; i < n; ++i) {

@@ -133,6 +133,8 @@ struct DecodeArgs {
 };
 // Number of k ranges the decode base GEMM is cut into for this shape (>= 1).
 int decode_base_splits(int64_t T, int d_in, int d_out);
+// Rows of partial sums, over all parts, that no batch of up to T tokens exceeds (fewer tokens may be cut into more parts).
+int64_t decode_base_rows(int64_t T, int d_in, int d_out);
 // ybase[s] = x[:, k range s] W[:, k range s]^T
 hipError_t launch_decode_base(const PlanView &pv, const DecodeArgs &a, hipStream_t stream);
 // ug = scale * A_e x per expert group

@@ -802,6 +802,13 @@ DecodeBaseShape decode_base_shape(int64_t T, int d_in, int d_out) { return base_
 
 int decode_base_splits(int64_t T, int d_in, int d_out) { return decode_base_shape(T, d_in, d_out).k_splits; }
 
+int64_t decode_base_rows(int64_t T, int d_in, int d_out)
+{
+    const int64_t few = T < DECODE_BASE_FEW_MAX ? T : DECODE_BASE_FEW_MAX;
+    const int64_t own = T * decode_base_splits(T, d_in, d_out), fewer = few * decode_base_splits(few, d_in, d_out);
+    return own > fewer ? own : fewer;
+}
+
 LinearKParams decode_base_params(const PlanView &pv, const LinearArgs &a, void *out, int out_f32,
                                  const DecodeBaseShape &sh, const int *gather)
 {

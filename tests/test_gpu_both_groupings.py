@@ -92,3 +92,30 @@ def test_quantised_base(lens, r, tiles):
     on_x = _reference(inp, ids, lens, None, r) - inp.x.double() @ inp.W.double().T   # the adapters' share
     _check(made, on_x + values(xq, xs) @ values(Wq, Ws).T, d_in, r)
     plan.close()
+
+
+@pytest.mark.parametrize("first,then,r", [([500], [300], 128), ([130], [128], 16), ([96] * 10, [80] * 10, 64)])
+@pytest.mark.parametrize("kind", ["plain", "shared", "mx"])
+def test_the_largest_batch_sizes_the_workspace_for_smaller_ones(first, then, r, kind):
+    if kind == "mx" and r % 64:
+        pytest.skip("not a rank of the quantised base")
+    ctx = moin.Context(0)
+    try:
+        sizes = []
+        for lens in (first, then):
+            inp, _, _ = _batch(lens, 2048, 2048, r, False)
+            plan = moin.Plan(ctx).build(inp.seq_offsets, inp.expert_ids, sum(lens), E)
+            if kind == "mx":
+                Wq, Ws = moin.moin_mx_quantize(ctx, inp.W, blocked=True)
+                moin.moin_lora_linear_mx_planned(ctx, plan, inp.x, Wq, Ws, inp.A_stack, inp.B_stack, 2.0)
+            elif kind == "shared":
+                moin.moin_lora_linear_planned_shared(ctx, plan, inp.x, [inp.W] * 2, [inp.A_stack] * 2, [inp.B_stack] * 2, 2.0)
+            else:
+                moin.moin_lora_linear_planned(ctx, plan, inp.x, inp.W, inp.A_stack, inp.B_stack, 2.0)
+            ctx.check()
+            sizes.append(ctx.workspace_bytes())
+            plan.close()
+        assert sizes[1] == sizes[0]
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
