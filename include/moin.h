@@ -201,7 +201,8 @@ int moin_lora_linear_planned(moin_ctx *ctx, const moin_plan *plan, const void *x
  * of n device pointers (stacks [E, r, d_in] / [E, d_out[i], r]; A_stack and B_stack
  * may be NULL when there are no adapters), d_out: host array of n widths; r and
  * scale are common.  The prefill path needs 2 n T r bf16 of workspace, r rounded up
- * to a multiple of 64 where d_in is one.  Errors as moin_lora_linear_planned; n
+ * to a multiple of 64 where d_in is one; an eager call also sizes it for smaller
+ * batches, which may need more ("HIP graphs" below).  Errors as moin_lora_linear_planned; n
  * outside 1..4: MOIN_EINVAL. */
 int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const void *x, int32_t n,
                                     const void *const *W, const void *const *A_stack,
@@ -233,7 +234,10 @@ int moin_route_plan(moin_ctx *ctx, moin_plan *plan, const void *emb, const void 
  * none) grow on demand (hipMalloc), which a stream under capture must not do.  A call
  * on a capturing stream that would have to grow any of them returns MOIN_ECAPTURE and
  * records nothing: make the first call with the largest shapes outside the capture, or
- * reserve beforehand.  What a captured call has used is kept until moin_destroy /
+ * reserve beforehand.  An eager linear call sizes the workspace for every batch of at
+ * most its sequences and its tokens through the same projections, also where a smaller
+ * one takes the other path or is cut into more parts and needs more than itself; where
+ * memory does not reach for that, it has what it needs itself.  What a captured call has used is kept until moin_destroy /
  * moin_plan_destroy even when a later, larger call replaces it, so replays of the
  * graph keep reading valid memory (results of a replay are then only defined if
  * no other call on the context runs concurrently, as for eager calls).

@@ -55,6 +55,7 @@ struct moin_ctx {
     int *err_word;
     void *ws;
     size_t ws_bytes;
+    size_t ws_refused;              // ensure_ws_smaller: there was no memory for this much
     int ws_pinned;                  // a captured graph may hold ws's address (see moin_plan::pinned)
     std::vector<void *> ws_retired;
     // small routing batches: centroid norms, packed minima and the arrival counter in a block of their
@@ -150,19 +151,22 @@ int ensure_ws(moin_ctx *ctx, size_t bytes, hipStream_t st, bool exact = false)
         ctx->ws = p;
         ctx->ws_bytes = want;
         ctx->ws_pinned = 0;
+        ctx->ws_refused = SIZE_MAX;
     }
     if (cap && bytes > 0) ctx->ws_pinned = 1;
     return MOIN_OK;
 }
 
-// The same for a call that needs `bytes` where a smaller batch of its kind may need more, up to `keep` (it takes the other
-// grouping, or its base product more parts): an eager call then sizes the workspace for both, so that the largest batch
-// prepares captured calls of all smaller ones.
+// The same for a call that needs `bytes` where a smaller batch may need more, up to `keep` (it takes the other grouping, or
+// its base product more parts): an eager call then sizes the workspace for both, so that the largest batch prepares
+// captured calls of all smaller ones.  Without memory for that the call has what it needs itself, and calls of its size do
+// not ask again until the workspace has grown otherwise.
 int ensure_ws_smaller(moin_ctx *ctx, size_t bytes, size_t keep, hipStream_t st)
 {
-    if (keep > bytes && keep > ctx->ws_bytes && !capturing(st)) {
+    if (keep > bytes && keep > ctx->ws_bytes && keep < ctx->ws_refused && !capturing(st)) {
         const int rc = ensure_ws(ctx, keep, st);
         if (rc != MOIN_ENOMEM) return rc;
+        ctx->ws_refused = keep;
     }
     return ensure_ws(ctx, bytes, st);
 }
@@ -295,11 +299,41 @@ bool gathered_pays(const PlanView &pv, int d_in, int r)
     return pv.T < min_tokens[deep][rank] || pv.T < (int64_t)min_len * pv.S;
 }
 
-// What gathered calls of the plan's size and smaller ones ask of the workspace, at most.
-size_t gathered_ws(const PlanView &pv, int d_in, int d_out, int r)
+// Tokens of the largest batch of up to the plan's sequences and tokens that is gathered.
+int64_t gathered_tokens(const PlanView &pv)
 {
-    const int64_t rows = pv.max_plain > 0 ? pv.T : decode_base_rows(pv.T, d_in, d_out);
-    return 2 * align_up((size_t)pv.T * (size_t)r * 2, 256) + align_up((size_t)rows * (size_t)d_out * 4, 256);
+    return std::min(pv.T, std::max<int64_t>(DECODE_MAX_T, (int64_t)GATHER_MAX_AVG_LEN * pv.S));
+}
+
+// Whether the base product of a gathered batch of more than DECODE_MAX_T tokens is cut into parts nevertheless (below): the
+// rows of up to this many tokens, 0 for none.
+int64_t large_parts_tokens(int d_in, int d_out)
+{
+    LinearArgs a;
+    a.d_in = d_in;
+    return stream_kernel_fits(a) ? 0 : compute_units() / 2 / ((d_out + 127) / 128) * 128;
+}
+
+// What a call of n projections asks of the workspace for the batch, of those of up to the plan's sequences and tokens, that
+// asks for the most.
+size_t linear_ws_most(const PlanView &pv, int n, int d_in, const int32_t *d_out, int r)
+{
+    auto bytes = [&](int64_t tokens, int64_t rows, int i) {
+        return 2 * align_up((size_t)tokens * (size_t)r * 2, 256) + align_up((size_t)rows * (size_t)d_out[i] * 4, 256);
+    };
+    LinearArgs a;
+    a.d_in = d_in;
+    a.r = r;
+    const int64_t T = gathered_tokens(pv), few = std::min<int64_t>(T, DECODE_MAX_T);
+    const size_t tiled = (size_t)n * 2 * align_up((size_t)pv.T * (size_t)prefill_ldu(a) * 2, 256);
+    size_t small = 0, large = 0;   // side by side up to DECODE_MAX_T tokens, one projection after the other beyond
+    for (int i = 0; i < n; ++i) {
+        small += bytes(few, decode_base_rows(few, d_in, d_out[i]), i);
+        if (T <= DECODE_MAX_T) continue;
+        const int64_t cut = std::min(T, large_parts_tokens(d_in, d_out[i]));
+        large = std::max(large, bytes(T, cut > DECODE_MAX_T ? std::max(T, decode_base_rows(cut, d_in, d_out[i])) : T, i));
+    }
+    return std::max({tiled, small, large});
 }
 
 // The plan's buffer, at least `bytes` large; same rules under stream capture as ensure_ws.
@@ -433,7 +467,7 @@ int linear_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, con
     const size_t u_bytes = align_up((size_t)pv.T * (size_t)a.ldu * 2, 256);
     if (!gathered) {
         if (a.r > 0) {
-            const int rc = ensure_ws_smaller(ctx, 2 * u_bytes, pv.decode ? gathered_ws(pv, d_in, d_out, r) : 0, stream);
+            const int rc = ensure_ws_smaller(ctx, 2 * u_bytes, linear_ws_most(pv, 1, d_in, &d_out, r), stream);
             if (rc != MOIN_OK) return rc;
             a.u_hi = ctx->ws;
             a.u_lo = static_cast<char *>(ctx->ws) + u_bytes;
@@ -454,8 +488,8 @@ int linear_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, con
     // 2056 -> 256 (64) 41 / 43, 2000 5640 -> 1000 (128) 71 / 76, but 1300 5640 -> 2048 (176) 113 / 79.
     LinearArgs ab = a;
     ab.r = 0;
-    const bool parts = a.r > 0 && !stream_kernel_fits(ab) && decode_base_splits(pv.T, d_in, d_out) > 1 &&
-                       (pv.T + 127) / 128 * ((d_out + 127) / 128) <= compute_units() / 2;
+    const bool parts = a.r > 0 && decode_base_splits(pv.T, d_in, d_out) > 1 &&
+                       pv.T <= large_parts_tokens(d_in, d_out);
     const bool big = pv.max_plain > 0 && !parts;
     PlanView pp = pv;
     pp.tile_row0 = pv.plain_row0; pp.tile_rows = pv.plain_rows; pp.tile_expert = pv.plain_expert;
@@ -474,7 +508,7 @@ int linear_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, con
     d.lin = a;
     d.k_splits = big ? 1 : decode_base_splits(pv.T, d_in, d_out);
     const size_t yb_bytes = align_up((size_t)d.k_splits * (size_t)pv.T * (size_t)d_out * 4, 256);
-    const int rc = ensure_ws_smaller(ctx, 2 * u_bytes + yb_bytes, gathered_ws(pv, d_in, d_out, r), stream);
+    const int rc = ensure_ws_smaller(ctx, 2 * u_bytes + yb_bytes, linear_ws_most(pv, 1, d_in, &d_out, r), stream);
     if (rc != MOIN_OK) return rc;
     char *w = static_cast<char *>(ctx->ws);
     d.ug_hi = w;
@@ -538,12 +572,7 @@ int linear_mx_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, 
     // decode-sized batches with adapters: the base product for all tokens at once as
     // fp32 partial planes, then the decode path's own shrink and expand kernels
     const bool gathered = gathered_pays(pv, d_in, a.r), decode = gathered && a.r > 0;
-    size_t yb_bytes = 0, yb_smaller = 0;
-    if (pv.decode && !gathered) {
-        int parts = 0, per = 0;
-        mx_plain_shape(pv.T, d_in, d_out, &parts, &per);
-        yb_smaller = align_up((size_t)parts * (size_t)pv.T * (size_t)d_out * 4, 256);
-    }
+    size_t yb_bytes = 0;
     if (decode) {
         mx_plain_shape(pv.T, d_in, d_out, &m.plain_splits, &m.plain_kb_per_split);
         yb_bytes = align_up((size_t)m.plain_splits * (size_t)pv.T * (size_t)d_out * 4, 256);
@@ -552,7 +581,8 @@ int linear_mx_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, 
         m.plain_kb_per_split = d_in / 128;
     }
     const size_t head_bytes = 2 * u_bytes + xq_bytes + xs_bytes;
-    const int rc = ensure_ws_smaller(ctx, head_bytes + yb_bytes, head_bytes + yb_smaller, stream);
+    const size_t yb_most = a.r > 0 ? align_up((size_t)mx_plain_rows(gathered_tokens(pv), d_in, d_out) * (size_t)d_out * 4, 256) : 0;
+    const int rc = ensure_ws_smaller(ctx, head_bytes + yb_bytes, head_bytes + yb_most, stream);
     if (rc != MOIN_OK) return rc;
     char *w = static_cast<char *>(ctx->ws);
     a.u_hi = w;
@@ -623,6 +653,7 @@ int moin_create(moin_ctx **out, int device)
     ctx->err_word = nullptr;
     ctx->ws = nullptr;
     ctx->ws_bytes = 0;
+    ctx->ws_refused = SIZE_MAX;
     ctx->ws_pinned = 0;
     ctx->route_buf = nullptr;
     ctx->route_bytes = 0;
@@ -1089,11 +1120,12 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
         if (vrc != MOIN_OK) return vrc;
     }
     const bool gathered = gathered_pays(pv, d_in, adapters ? r : 0);
+    const size_t most = adapters && n > 1 ? linear_ws_most(pv, n, d_in, d_out, r) : 0;
     if (gathered && adapters && n > 1 && pv.max_plain == 0) {
         // Decode-sized batch: the projections' base tiles and shrink slabs in one launch, their expand
         // blocks in another, where they agree in everything those launches share.
         DecodeArgs d[MAX_SHARED_X];
-        size_t off[MAX_SHARED_X], total = 0, smaller = 0;
+        size_t off[MAX_SHARED_X], total = 0;
         const size_t u_bytes = align_up((size_t)pv.T * (size_t)r * 2, 256);
         for (int i = 0; i < n; ++i) {
             LinearArgs &a = d[i].lin;
@@ -1105,10 +1137,9 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
             d[i].ybase_by_pos = 1;
             off[i] = total;
             total += 2 * u_bytes + align_up((size_t)d[i].k_splits * (size_t)pv.T * (size_t)d_out[i] * 4, 256);
-            smaller += gathered_ws(pv, d_in, d_out[i], r);
         }
         if (decode_shared_fits(pv, d, n)) {
-            const int rc = ensure_ws_smaller(ctx, total, smaller, st);
+            const int rc = ensure_ws_smaller(ctx, total, most, st);
             if (rc != MOIN_OK) return rc;
             for (int i = 0; i < n; ++i) {
                 char *w = static_cast<char *>(ctx->ws) + off[i];
@@ -1127,6 +1158,8 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
     }
     if (gathered || !adapters || n == 1) {
         // nothing to share on these paths: the projections one after the other
+        const int wrc = ensure_ws_smaller(ctx, 0, most, st);
+        if (wrc != MOIN_OK) return wrc;
         for (int i = 0; i < n; ++i) {
             const int rc = linear_planned_impl(ctx, plan, x, W[i], adapters ? A_stack[i] : nullptr,
                                                adapters ? B_stack[i] : nullptr, d_in, d_out[i], r, scale, y[i],
@@ -1142,9 +1175,7 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
     a.d_in = d_in; a.d_out = 0; a.r = r; a.scale = scale; a.act = ctx->act;
     a.ldu = prefill_ldu(a);
     const size_t u_bytes = align_up((size_t)pv.T * (size_t)a.ldu * 2, 256);
-    size_t smaller = 0;
-    for (int i = 0; pv.decode && i < n; ++i) smaller += gathered_ws(pv, d_in, d_out[i], r);
-    const int rc = ensure_ws_smaller(ctx, (size_t)n * 2 * u_bytes, smaller, st);
+    const int rc = ensure_ws_smaller(ctx, (size_t)n * 2 * u_bytes, most, st);
     if (rc != MOIN_OK) return rc;
     void *u_hi[MAX_SHARED_X], *u_lo[MAX_SHARED_X];
     for (int i = 0; i < n; ++i) {

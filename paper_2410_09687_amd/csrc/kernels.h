@@ -133,7 +133,7 @@ struct DecodeArgs {
 };
 // Number of k ranges the decode base GEMM is cut into for this shape (>= 1).
 int decode_base_splits(int64_t T, int d_in, int d_out);
-// Rows of partial sums, over all parts, that no batch of up to T tokens exceeds (fewer tokens may be cut into more parts).
+// Rows of partial sums, over all parts, of the batch of up to T tokens that has the most (fewer tokens may be cut into more parts).
 int64_t decode_base_rows(int64_t T, int d_in, int d_out);
 // ybase[s] = x[:, k range s] W[:, k range s]^T
 hipError_t launch_decode_base(const PlanView &pv, const DecodeArgs &a, hipStream_t stream);
@@ -263,6 +263,7 @@ struct MxLinearArgs {
     int plain_splits, plain_kb_per_split;
 };
 void mx_plain_shape(int64_t T, int d_in, int d_out, int *k_splits, int *kb_per_split);
+int64_t mx_plain_rows(int64_t T, int d_in, int d_out);   // as decode_base_rows
 // codes / scales of rows x cols bf16 values (cols a multiple of 32); scales row-major
 // [rows, cols / 32] or, blocked (cols a multiple of 128), [cols / 128, rows, 4]
 hipError_t launch_mx_quantize(const void *src, int64_t rows, int64_t cols, void *codes, void *scales,

@@ -804,9 +804,17 @@ int decode_base_splits(int64_t T, int d_in, int d_out) { return decode_base_shap
 
 int64_t decode_base_rows(int64_t T, int d_in, int d_out)
 {
-    const int64_t few = T < DECODE_BASE_FEW_MAX ? T : DECODE_BASE_FEW_MAX;
-    const int64_t own = T * decode_base_splits(T, d_in, d_out), fewer = few * decode_base_splits(few, d_in, d_out);
-    return own > fewer ? own : fewer;
+    // The parts fall as the row tiles become more (shape_for), and where the rule for few tokens ends: the most rows are those
+    // of T tokens, of the last batch of few, or of the last that leaves room for two, three or four parts.
+    const bool dma = d_in % 64 == 0;
+    const int64_t bm = dma ? CfgDecodeBase::BM : CfgThin::BM, bn = dma ? CfgDecodeBase::BN : CfgThin::BN, cols = (d_out + bn - 1) / bn;
+    int64_t most = T * decode_base_splits(T, d_in, d_out);
+    auto try_ = [&](int64_t t) {
+        if (t > 0 && t < T) most = std::max(most, t * decode_base_splits(t, d_in, d_out));
+    };
+    try_(DECODE_BASE_FEW_MAX);
+    for (int parts = 2; parts <= DECODE_BASE_MAX_SPLITS; ++parts) try_((DECODE_BASE_TARGET_WGS - 1) / (parts - 1) / cols * bm);
+    return most;
 }
 
 LinearKParams decode_base_params(const PlanView &pv, const LinearArgs &a, void *out, int out_f32,

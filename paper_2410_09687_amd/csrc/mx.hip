@@ -754,6 +754,21 @@ void mx_plain_shape(int64_t T, int d_in, int d_out, int *k_splits, int *kb_per_s
     }
 }
 
+int64_t mx_plain_rows(int64_t T, int d_in, int d_out)
+{
+    // (the parts fall as the tiles become more: the most rows are those of the last batch of each number of parts)
+    const int64_t cols = (d_out + mxm::BT - 1) / mxm::BT;
+    int64_t most = 0;
+    for (int want = 1; want <= 4; ++want) {
+        const int64_t t = want == 1 ? T : std::min<int64_t>(T, compute_units() / want / cols * mxm::BT);
+        if (t <= 0) continue;
+        int parts = 0, per = 0;
+        mx_plain_shape(t, d_in, d_out, &parts, &per);
+        most = std::max(most, t * parts);
+    }
+    return most;
+}
+
 hipError_t launch_linear_mx_stream(const PlanView &pv, const MxLinearArgs &a, int n_cus, hipStream_t stream_)
 {
     mxs::Params p;
