@@ -261,14 +261,16 @@ __global__ __launch_bounds__(64 * KM_ONE_WAVES) void km_sort_one(KmeansArgs a, i
     // centres in order, a run of them per thread
     const int per = (K + NT - 1) / NT;
     const int k0 = min(tid * per, K), k1 = min(k0 + per, K);
-    auto count_of = [&](int k) __attribute__((always_inline)) {
-        const uint4 w = *reinterpret_cast<const uint4 *>(&km_cur[k * (NW / 2)]);
+    // (counts and cursors of a centre, eight times 16 bits, are read and written as one uint4 throughout: the same bytes as two
+    // types between two barriers are nothing the compiler has to keep in order)
+    auto counts_of = [&](int k) __attribute__((always_inline)) -> uint4 & { return *reinterpret_cast<uint4 *>(&km_cur[k * (NW / 2)]); };
+    auto sum_of = [](const uint4 &w) __attribute__((always_inline)) {
         const unsigned t = (w.x & 0xffff) + (w.x >> 16) + (w.y & 0xffff) + (w.y >> 16) + (w.z & 0xffff) + (w.z >> 16) + (w.w & 0xffff) + (w.w >> 16);
         return (int)t;
     };
     int cnt = 0, pcs = 0;
     for (int k = k0; k < k1; ++k) {
-        const int c = count_of(k);
+        const int c = sum_of(counts_of(k));
         cnt += c;
         pcs += (c + KM_PIECE - 1) / KM_PIECE;
     }
@@ -296,17 +298,24 @@ __global__ __launch_bounds__(64 * KM_ONE_WAVES) void km_sort_one(KmeansArgs a, i
         all_p += q;
     }
     for (int k = k0; k < k1; ++k) {
-        const int c = count_of(k);
+        const uint4 w = counts_of(k);
+        const int c = sum_of(w);
         a.counts[k] = c;
         a.seg_start[k] = at_c;
         a.piece_start[k] = at_p;
         for (int f = 0; f < c; f += KM_PIECE) a.pieces[at_p++] = make_int4(k, at_c + f, at_c + min(f + KM_PIECE, c), 0);
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const int n = cur[k * NW + w];
-            cur[k * NW + w] = (uint16_t)at_c;
-            at_c += n;
-        }
+        static_assert(NW == 8, "a uint4");
+        auto cursors = [&](unsigned two) __attribute__((always_inline)) {
+            const unsigned first = (unsigned)at_c, second = first + (two & 0xffff);
+            at_c = (int)(second + (two >> 16));
+            return first | second << 16;
+        };
+        uint4 at;
+        at.x = cursors(w.x);
+        at.y = cursors(w.y);
+        at.z = cursors(w.z);
+        at.w = cursors(w.w);
+        counts_of(k) = at;
     }
     if (tid == 0) {
         a.seg_start[K] = all_c;
