@@ -117,14 +117,22 @@ void check(int code, const char *what)
     }
     throw Raised{};
 }
-// The library's call without the interpreter's lock.
+// The interpreter's lock, given back for the time of a call into the library and held again however that ends: what unwinds an
+// exception drops references and sets Python's error.
+struct Unlocked {
+    PyThreadState *state = PyEval_SaveThread();
+    Unlocked() = default;
+    Unlocked(const Unlocked &) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
 template <class F>
 void call(const char *what, F &&f)
 {
     int code;
-    Py_BEGIN_ALLOW_THREADS
-    code = f();
-    Py_END_ALLOW_THREADS
+    {
+        const Unlocked free;
+        code = f();
+    }
     check(code, what);
 }
 
