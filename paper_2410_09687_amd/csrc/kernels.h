@@ -113,8 +113,7 @@ hipError_t launch_prefill_linear(const PlanView &pv, const LinearArgs &a, hipStr
 hipError_t launch_prefill_linear_shared(const PlanView &pv, const LinearArgs *a, int n, hipStream_t stream);
 // The 128 x 128 tiles of linear_mid.hip: whether they beat the larger ones for this call, and the call (a[0].ldu: columns
 // of u as stored, r or more).
-bool mid_kernel_pays(const PlanView &pv, const LinearArgs *a, int n, int n_cus);    // than the register-staged tiles
-bool mid_beats_stream(const PlanView &pv, const LinearArgs *a, int n, int n_cus);   // than the streaming kernel
+bool mid_kernel_pays(const PlanView &pv, const LinearArgs *a, int n, int n_cus);
 hipError_t launch_linear_mid(const PlanView &pv, const LinearArgs *a, int n, int n_cus, hipStream_t stream);
 // shapes the persistent streaming prefill kernel takes (anything else: linear_mid.hip or the tiled kernel)
 bool stream_kernel_fits(const LinearArgs &a);

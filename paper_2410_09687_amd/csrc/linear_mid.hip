@@ -308,26 +308,23 @@ static int64_t mid_tiles(const PlanView &pv, const LinearArgs *a, int n, int bt 
     return host_tiles(pv, bt) * tn;
 }
 
-// Up to the tiles that the chip holds at a time.  Us of the kernel, 256 x 256 tiles / these: 2048 -> 2048 448 tiles 42 / 31, 512 45 /
+// Up to the tiles that the chip holds at a time, for each round that the 256 x 256 tiles need (two of these tiles per unit and
+// round): with full row tiles, four of these in a large one, that is the first round's line alone, but where sequences end
+// in the first half of a row tile, or a last round would be nearly empty, it lies further out.
+// Us of the kernel, the streaming kernel's 256 x 256 tiles / these: 2048 -> 2048 448 tiles 42 / 31, 512 45 /
 // 34, 544 45 / 52, 768 47 / 56, 1024 55 / 64 (one round of the larger tiles until then); beyond their first round 1152 89 / 84,
 // 1280 90 / 87, but 1280 with 5632 outputs a call 106 / 113, so the line stays here; 5632 -> 2048 512 tiles 100 / 81,
 // 544 101 / 132; 2048 -> 2048, 256, 256 480 tiles 46 / 33, 560 48 / 52; 528 tiles 2048 -> 5632 47 / 52.  Uneven sequences can
 // make more tiles than the host takes them to: 16 of 60 to 430 tokens 560 instead of 512, 46 / 53 (were the line lower, as
-// many even ones would lose 11).  1000 -> 2048 against tiles that go through registers, us of a call: 256 tiles 50 / 30,
-// 1024 59 / 62, 1416 -> 5632 at 11264 654 / 776.
+// many even ones would lose 11).  Half-empty row tiles: 2048 -> 2048 64 sequences of 128 tokens (512 large tiles, 1024 of
+// these) 109 / 71, 96 of 128 160 / 106, 20 of 300 (320, 960) 94 / 66; 2048 -> 11264 8 of 112 98 / 58, 32 of 112 305 / 198, 64 of
+// 128 599 / 517, 4 of 300 (352, 1056: beyond the line) 98 / 85; 5632 -> 2048 64 of 128 244 / 158, 20 of 300 214 / 154; just
+// beyond the line about equal (32 of 300 109 / 101, 24 of 512 99 / 102), further out the large ones win (32 of 512 112 / 133).
+// Against tiles that go through registers (rows that are not whole blocks), us of a call: 1000 -> 2048 256 tiles 50 / 30,
+// 1024 59 / 62, 1416 -> 5632 at 11264 654 / 776; half-empty ones 1000 -> 2048 40 sequences of 80 tokens 83 / 51, 64 of 64 at
+// rank 64 92 / 59, 128 of 64 169 / 100; 1000 -> 5632 12 of 96 85 / 49, 64 of 80 246 / 139; sequences of 129 to 1000
+// tokens the same within what runs differ.
 bool mid_kernel_pays(const PlanView &pv, const LinearArgs *a, int n, int n_cus)
-{
-    return mid_tiles(pv, a, n) <= 2 * (int64_t)n_cus;
-}
-
-// Against the streaming kernel the same line holds for each round that its 256 x 256 tiles need (two of these tiles per
-// unit and round): with full row tiles, four of these in a large one, that is the first round's line alone, but where
-// sequences end in the first half of a row tile, or a last round would be nearly empty, it lies further out.  Us of the
-// kernel, 256 x 256 / these: 2048 -> 2048 64 sequences of 128 tokens (512 large tiles, 1024 of these) 109 / 71, 96 of 128
-// 160 / 106, 20 of 300 (320, 960) 94 / 66; 2048 -> 11264 8 of 112 98 / 58, 32 of 112 305 / 198, 64 of 128 599 / 517, 4 of
-// 300 (352, 1056: beyond the line) 98 / 85; 5632 -> 2048 64 of 128 244 / 158, 20 of 300 214 / 154; just beyond the line
-// about equal (32 of 300 109 / 101, 24 of 512 99 / 102), further out the large ones win (32 of 512 112 / 133).
-bool mid_beats_stream(const PlanView &pv, const LinearArgs *a, int n, int n_cus)
 {
     int64_t tn = 0;
     for (int i = 0; i < n; ++i) tn += (a[i].d_out + TILE_M - 1) / TILE_M;

@@ -367,7 +367,7 @@ int prefill_ldu(const LinearArgs &a) { return stream_kernel_fits(a) ? (a.r + 63)
 hipError_t launch_linear_stream_shared(const PlanView &pv, const LinearArgs *a, int n, int n_cus, hipStream_t stream_)
 {
     if (n < 1 || n > MAX_SHARED_X) return hipErrorInvalidValue;
-    if (mid_beats_stream(pv, a, n, n_cus)) return launch_linear_mid(pv, a, n, n_cus, stream_);
+    if (mid_kernel_pays(pv, a, n, n_cus)) return launch_linear_mid(pv, a, n, n_cus, stream_);
     stream::Params p;
     stream::fill_params(&p, pv, a, n, stream::BT);
     // one workgroup per compute unit (the LDS footprint allows no more), fewer
