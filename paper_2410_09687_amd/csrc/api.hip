@@ -276,27 +276,51 @@ PlanLayout plan_layout(int32_t S, int64_t T, int32_t E, bool upper_bound = false
 // registers and, from a few hundred tokens on, matrix rates the gathered base product does not reach; but a chain of
 // d_in / 64 blocks in one workgroup, half-empty tiles under short sequences, and with low ranks the adapter term, which
 // costs the gathered kernels a pass over fp32 planes, is cheap there too.  So the line goes by d_in, rank, tokens and
-// tokens per sequence -- not by d_out: projections that share a call take the same way as calls of their own.
+// tokens per sequence -- not by d_out: projections that share a call take the same way as calls of their own.  It is drawn
+// for a layer, whose seven projections in four calls are nowhere longer by it: 183 layers of 6 to 96 sequences of 64 to 112 tokens at
+// ranks 16, 64 and 128, 2048 wide, take 0.49 to 1.02 of the gathered ones' time, 0.80 in the middle.  A single projection may lose just beyond it,
+// where its tiles begin another round of the chip: the worst are marked *.
 // Us of a call, gathered / row tiles (S x tokens each):
-//  1024 -> 1416 rank 8 4 x 96 25 / 22, 8 x 64 25 / 22, 32 x 64 37 / 29, rank 128 4 x 250 34 / 22, 64 x 100 107 / 51; 256 -> 256
-//   rank 8 4 x 96 15 / 16, 14 x 96 27 / 16
-//  2048 -> 2048 rank 8 4 x 250 34 / 32, 32 x 64 45 / 48, 32 x 96 56 / 48, rank 64 4 x 96 25 / 28, 4 x 160 32 / 29, 32 x 64 51 / 47,
-//   rank 128 4 x 96 30 / 28, 8 x 120 41 / 30, 64 x 100 136 / 87
-//  2048 -> 5632 rank 8 4 x 250 58 / 43, 8 x 64 37 / 42, 32 x 64 78 / 105, 64 x 100 217 / 231, rank 128 4 x 160 58 / 41, 64 x 64 200 / 206
-//  5632 -> 2048 rank 32 4 x 250 63 / 62, 14 x 96 72 / 65, 64 x 100 176 / 199, rank 64 8 x 96 58 / 55, 4 x 160 47 / 55, 64 x 64 152 / 182,
-//   rank 128 4 x 160 58 / 56, 4 x 96 43 / 55
-//  a layer of seven projections, rank 16 8 x 80 181 / 187, 8 x 112 221 / 191, 14 x 80 315 / 238; rank 128 8 x 48 168 / 173, 4 x 96
-//   164 / 144, 1 x 640 227 / 155, 14 x 96 475 / 273 (the line at 2048 lies where a layer gains that keeps its 5632-wide down
-//   projection gathered: 1 x 363 rank 128 155 / 126, 1 x 390 rank 64 148 / 126); on an MXFP8 base rank 64 4 x 96 206 / 199, 32 x 64 391 / 383, 32 x 96 560 / 417
+//  256 -> 256 rank 8 4 x 96 11 / 10, 14 x 96 18 / 10; 1024 -> 1416 rank 8 4 x 80 20 / 15, 32 x 64 31 / 26, 64 x 64 41 / 41, 64 x 100 59 / 42, rank
+//   128 4 x 250 31 / 18, 64 x 100 105 / 49
+//  2048 -> 2048 rank 8 4 x 96 21 / 22, 1 x 640 25 / 27, 4 x 250 30 / 29, 14 x 80 35 / 30, 32 x 64 40 / 43, 32 x 96 50 / 44, 40 x 96* 55 / 65, 64 x 100
+//   86 / 79, rank 64
+//   4 x 80 21 / 19, 4 x 160 29 / 25, 32 x 64 45 / 44, rank 128 4 x 80 25 / 20, 8 x 120 37 / 27, 64 x 100 133 / 88
+//  2048 -> 5632 rank 8 4 x 80 32 / 29, 8 x 64 34 / 38, 1 x 640 40 / 31, 4 x 250 55 / 40, 14 x 96 66 / 64, 24 x 96* 77 / 92, 32 x 64 75 / 103, 64 x 100 211 / 228,
+//   rank 128 4 x 160 55 / 39, 64 x 64 196 / 202, 128 x 64* 340 / 440
+//  5632 -> 2048 rank 32 4 x 96 30 / 47, 4 x 250 59 / 59, 14 x 96 68 / 61, 40 x 96* 117 / 160, 64 x 100 171 / 203, rank 64 4 x 160 43 / 52, 8 x 96 55 / 51, 32 x 64
+//   84 / 102, 64 x 64 148 / 182, rank 128 4 x 96 39 / 39, 8 x 64 42 / 40, 1 x 640 52 / 52
+// Some calls short of the line are a little shorter in row tiles as well (it lies where a layer of 1 x 363 tokens at rank 128,
+// that keeps its 5632-wide down projection gathered, gains).  Ranks above 128 stay gathered, where they always were;
+// that is the shorter way for deep rows alone: rank 136 5632 -> 2048 4 x 96 46 / 66, 1 x 640 65 / 77, 8 x 120 88 / 79, but 2048 -> 2048 4 x 96
+// 31 / 31, 8 x 120 45 / 37, 2048 -> 5632 1 x 640 66 / 38, 1024 -> 1416 32 x 96 79 / 34, rank 256 5632 -> 2048 1 x 640 86 / 72.
+enum RankClass { RANK_LOW, RANK_MID, RANK_HIGH };    // below 48, below 96
+enum DepthClass { SHALLOW, MEDIUM, DEEP };           // contraction of up to 1024, up to 3072
+RankClass rank_class(int r) { return r < 48 ? RANK_LOW : r < 96 ? RANK_MID : RANK_HIGH; }
+DepthClass depth_class(int d_in) { return d_in <= 1024 ? SHALLOW : d_in <= 3072 ? MEDIUM : DEEP; }
 bool gathered_pays(const PlanView &pv, int d_in, int r)
 {
     if (!pv.decode || !pv.tiles || r <= 0 || r > 128) return pv.decode;
-    const int rank = r < 48 ? 0 : r < 96 ? 1 : 2, deep = d_in <= 1024 ? 0 : d_in <= 3072 ? 1 : 2;
+    const RankClass rank = rank_class(r);
+    const DepthClass deep = depth_class(d_in);
     static constexpr int min_tokens[3][3] = {{384, BOTH_MIN_T, BOTH_MIN_T}, {768, 384, BOTH_MIN_T}, {DECODE_MAX_T + 1, 768, 640}};
-    int min_len = rank == 0 ? (deep == 0 ? 80 : 96) : rank == 1 ? (deep == 0 ? BOTH_MIN_AVG_LEN : 72) : BOTH_MIN_AVG_LEN;
-    if (pv.T > DECODE_MAX_T && rank == 1 && deep > 0) min_len = 80;
-    if (pv.T > 4096 && rank == 0 && deep > 0) return true;   // (up to GATHER_MAX_AVG_LEN tokens a sequence)
+    int min_len = rank == RANK_LOW ? (deep == SHALLOW ? 80 : 96) : rank == RANK_MID ? (deep == SHALLOW ? BOTH_MIN_AVG_LEN : 72) : BOTH_MIN_AVG_LEN;
+    if (pv.T > DECODE_MAX_T && rank == RANK_MID && deep != SHALLOW) min_len = 80;
+    if (pv.T > 4096 && rank == RANK_LOW && deep != SHALLOW) return true;   // (up to GATHER_MAX_AVG_LEN tokens a sequence)
     return pv.T < min_tokens[deep][rank] || pv.T < (int64_t)min_len * pv.S;
+}
+
+// The same on an MXFP8 base (calls of one projection each): beyond the line, up to 1024 tokens, a deep contraction stays gathered at
+// ranks of 48 to 95, and one of 16 blocks and more where the row tiles are few.  Us of a call, gathered / row tiles:
+// 5632 -> 2048 rank 64 1 x 768 46 / 55, 1 x 1024 48 / 56, 12 x 96 71 / 57; 2048 -> 256 rank 64 1 x 512 21 / 23, 1 x 700 22 / 24, 10 x 80 24 / 24, rank
+// 128 1 x 363 20 / 23, 1 x 512 21 / 23, 8 x 80 26 / 23.  (2048 -> 11008 rank 128 64 x 64 276 / 296 takes row tiles.)
+bool gathered_pays_mx(const PlanView &pv, int d_in, int d_out, int r)
+{
+    if (gathered_pays(pv, d_in, r)) return true;
+    if (!pv.decode || pv.T > DECODE_MAX_T) return false;
+    const RankClass rank = rank_class(r);
+    if (depth_class(d_in) == DEEP && rank == RANK_MID) return true;
+    return d_in >= 2048 && host_tiles(pv, 128) * ((d_out + 127) / 128) <= 16 && pv.T < (rank == RANK_HIGH ? 528 : 704);
 }
 
 // Tokens of the largest batch of up to the plan's sequences and tokens that is gathered.
@@ -571,7 +595,7 @@ int linear_mx_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, 
     m.plain_kb_per_split = 0;
     // decode-sized batches with adapters: the base product for all tokens at once as
     // fp32 partial planes, then the decode path's own shrink and expand kernels
-    const bool gathered = gathered_pays(pv, d_in, a.r), decode = gathered && a.r > 0;
+    const bool gathered = gathered_pays_mx(pv, d_in, d_out, a.r), decode = gathered && a.r > 0;
     size_t yb_bytes = 0;
     if (decode) {
         mx_plain_shape(pv.T, d_in, d_out, &m.plain_splits, &m.plain_kb_per_split);
