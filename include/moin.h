@@ -195,9 +195,9 @@ int moin_lora_linear_planned(moin_ctx *ctx, const moin_plan *plan, const void *x
  * each projection's main product runs as in moin_lora_linear_planned (in one launch
  * where all of them fit the streaming kernel); on the decode path the projections'
  * work shares the call's two launches (base products and first adapter products,
- * then second adapter products) where those whose base product is cut into tiles
- * agree in the number of its parts, else they run one after the other.  The results
- * are, bit for bit, those of n single calls.  W, A_stack, B_stack, y: host arrays
+ * then second adapter products) up to 128 tokens, and beyond where those whose base
+ * product is cut into tiles agree in the number of its parts, else they run one after
+ * the other.  The results are, bit for bit, those of n single calls.  W, A_stack, B_stack, y: host arrays
  * of n device pointers (stacks [E, r, d_in] / [E, d_out[i], r]; A_stack and B_stack
  * may be NULL when there are no adapters), d_out: host array of n widths; r and
  * scale are common.  The prefill path needs 2 n T r bf16 of workspace, r rounded up

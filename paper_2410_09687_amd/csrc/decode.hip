@@ -192,9 +192,8 @@ __device__ __forceinline__ void decode_shrink_slab(const ShrinkDParams &p, int s
 }
 
 // What differs between the projections of one call that read the same x (gate, up; q, k, v): they
-// share the token groups, d_in, r, the scale and the number of base parts, so their base tiles, their
-// shrink slabs and their expand blocks stand side by side in the call's two launches and the
-// launches' ramp and tail are paid once.  Entry 0 repeats what the plain parameter blocks hold.
+// share the token groups, d_in, r and the scale, so their base tiles, their shrink slabs and their expand
+// blocks stand side by side in the call's two launches and the launches' ramp and tail are paid once.  Entry 0 repeats what the plain parameter blocks hold.
 struct DecodeMore {
     int n;                          // projections of the call (1..MAX_SHARED_X)
     int tile_first[MAX_SHARED_X];   // first base tile of each (multiples of 8; the next one's where it has none)
@@ -483,6 +482,8 @@ __global__ __launch_bounds__(SHRINK_WAVES * 64, 4) void decode_base_shrink_kerne
             q.y = reinterpret_cast<char *>(args->m.ybase[i]);
             q.d_out = args->m.d_out[i];
             q.n_tiles_n = args->m.n_tiles_n[i];
+            q.k_splits = args->m.k_splits[i];
+            q.kb_per_split = (q.d_in / CfgDecodeBase::BK + q.k_splits - 1) / q.k_splits;   // as decode_base_shape has it
             linear_tile<CfgDecodeBase, PACED>(q, b - args->m.tile_first[i], smem);
             __syncthreads();   // (the tile's epilogue has left LDS)
         }
@@ -646,7 +647,7 @@ __device__ __forceinline__ void expand_item(const ExpandKParams &p, int slab, in
 
 // Items of (record, EXPAND_WAVES * RB * 16 rows of B_e), the row blocks of one record neighbours; with several
 // projections in the call (`m`) a record's items are the row blocks of all of them (n_xb).
-// MIXED: projections with fewer parts of the base product than NSPLIT among them (slabs of W beside tiles).
+// MIXED: projections with fewer parts of the base product than NSPLIT among them.
 template <int KS_HOLD, int NSPLIT, bool BY_POS, int RB, bool MIXED>
 __global__ __launch_bounds__(EXPAND_WAVES * 64) void decode_expand_kernel(ExpandKParams p, DecodeMore m, int n_xb)
 {
@@ -996,7 +997,10 @@ hipError_t prepare_decode_kernels()
 }
 
 // True when the n projections of a call that share x can share its two launches: the same input, contraction length,
-// rank, scale, activation, output type and -- those whose base product is cut into tiles -- number of its parts.
+// rank, scale, activation, output type and -- those whose base product is cut into tiles, beyond MIX_MAX_T tokens -- number
+// of its parts.  (Up to there the parts go by the projection's width: linear.hip's rule for few tokens.)
+constexpr int MIX_MAX_T = 128;
+static_assert(MIX_MAX_T <= DECODE_MAX_T, "records of 16 tokens, which the streaming expand takes");
 bool decode_shared_fits(const PlanView &pv, const DecodeArgs *d, int n)
 {
     if (n < 1 || n > MAX_SHARED_X) return false;
@@ -1005,7 +1009,7 @@ bool decode_shared_fits(const PlanView &pv, const DecodeArgs *d, int n)
         if (!decode_base_shrink_fits(pv, d[i])) return false;
         const LinearArgs &a = d[i].lin, &a0 = d[0].lin;
         if (decode_base_shape(pv.T, a.d_in, a.d_out).slab_blocks == 0) {
-            if (tile_splits != 0 && d[i].k_splits != tile_splits) return false;
+            if (tile_splits != 0 && d[i].k_splits != tile_splits && pv.T > MIX_MAX_T) return false;
             tile_splits = d[i].k_splits;
         }
         if (a.x != a0.x || a.d_in != a0.d_in || a.r != a0.r || a.scale != a0.scale || a.act != a0.act ||
@@ -1039,7 +1043,7 @@ hipError_t launch_decode_base_shrink_shared(const PlanView &pv, const DecodeArgs
     DecodeMore m = decode_more(d, n);
     int64_t n_tiles = 0, n_w = 0;
     LinearKParams lp{};
-    int tile_blocks = 0;   // of a tile's part of the contraction
+    int tile_blocks = 0;   // of a tile's part of the contraction, at most
     for (int i = 0; i < n; ++i) {
         const DecodeBaseShape sh = decode_base_shape(pv.T, a.d_in, d[i].lin.d_out);
         if (!(sh.dma || sh.slab_blocks) || sh.k_splits != d[i].k_splits) return hipErrorInvalidValue;
@@ -1050,7 +1054,8 @@ hipError_t launch_decode_base_shrink_shared(const PlanView &pv, const DecodeArgs
             n_w += sh.grid;
         } else {
             n_tiles += sh.grid;   // (a multiple of 8, every projection's tiles keep their place in the XCD rotation)
-            tile_blocks = sh.kb_per_split;
+            if (sh.kb_per_split != (a.d_in / CfgDecodeBase::BK + sh.k_splits - 1) / sh.k_splits) return hipErrorInvalidValue;
+            tile_blocks = std::max(tile_blocks, sh.kb_per_split);
         }
         if (i == 0 || sh.slab_blocks == 0)   // (what the slabs need of it is the batch's size)
             lp = decode_base_params(pv, a, d[i].ybase, 1, sh, pv.tok_sorted);   // rows in by-expert order
@@ -1088,7 +1093,7 @@ hipError_t launch_decode_expand_shared(const PlanView &pv, const DecodeArgs *d, 
     if (n < 1 || n > MAX_SHARED_X) return hipErrorInvalidValue;
     if (pv.max_groups <= 0) return hipSuccess;
     const LinearArgs &a = d[0].lin;
-    int k_splits = d[0].k_splits;   // of the kernel; a projection with fewer parts (slabs beside tiles) adds its own
+    int k_splits = d[0].k_splits;   // of the kernel; a projection with fewer parts adds its own
     for (int i = 1; i < n; ++i) {
         if (d[i].lin.r != a.r || d[i].lin.y_f32 != a.y_f32 || d[i].ybase_by_pos != d[0].ybase_by_pos)
             return hipErrorInvalidValue;
@@ -1118,10 +1123,10 @@ hipError_t launch_decode_expand_shared(const PlanView &pv, const DecodeArgs *d, 
     const int64_t stream_wgs = (std::max(items, base_only) + EXPAND_WAVES - 1) / EXPAND_WAVES;
     const dim3 grid((unsigned)(streams ? persistent_grid(expand_stream_wgs(ks, k_splits, stream_rb), stream_wgs)
                                        : persistent_grid(HELD_WGS, items)));
-    // parts that differ come from slabs (one) beside tiles of up to 64 blocks (two): decode_base_shape
+    // parts that differ: slabs (one) beside tiles, or tiles of up to MIX_MAX_T tokens (decode_shared_fits)
     bool mixed = false;
     for (int i = 1; i < n; ++i) mixed = mixed || d[i].k_splits != d[0].k_splits;
-    if (mixed && !(k_splits == 2 && d[0].ybase_by_pos)) return hipErrorInvalidValue;
+    if (mixed && (!d[0].ybase_by_pos || pv.T > MIX_MAX_T || (nks <= 4 && !streams))) return hipErrorInvalidValue;
 #define MOIN_EXPAND_STREAM(KS, NS, BP, SRB, MIX)                                                                          \
     hipLaunchKernelGGL((decode_expand_stream_kernel<(KS > 0 ? KS : 1), NS, BP, SRB, MIX>), grid, dim3(EXPAND_WAVES * 64), \
                        EXPAND_WAVES * expand_stage(KS, SRB), stream, ExpandStreamArgs{p, m, (int)xb, pv.max_groups})
@@ -1129,7 +1134,7 @@ hipError_t launch_decode_expand_shared(const PlanView &pv, const DecodeArgs *d, 
     hipLaunchKernelGGL((decode_expand_kernel<KS, NS, BP, RB, MIX>), grid, dim3(EXPAND_WAVES * 64), 0, stream, p, m, (int)xb)
 #define MOIN_EXPAND_R(KS, NS, BP)                                                                                      \
     do {                                                                                                               \
-        constexpr bool may_mix = NS == 2 && BP;                                                                        \
+        constexpr bool may_mix = NS >= 2 && BP;                                                                        \
         if (KS > 0 && streams && NS == 1 && !BP && large) MOIN_EXPAND_STREAM(KS, 1, false, 4, false);                  \
         else if (KS > 0 && streams && mixed) MOIN_EXPAND_STREAM(KS, NS, BP, (expand_stream_rb(KS, false)), may_mix);   \
         else if (KS > 0 && streams) MOIN_EXPAND_STREAM(KS, NS, BP, (expand_stream_rb(KS, false)), false);              \

@@ -748,12 +748,22 @@ constexpr int DECODE_BASE_MAX_SPLITS = 4;   // the expand kernel sums up to four
 constexpr int DECODE_BASE_MIN_BLOCKS = 4;   // BK blocks per part at least
 constexpr int DECODE_BASE_SPLIT_BLOCKS = 32;
 // One row of tiles, not mixed with slabs (33 to 128 tokens): a block of a tile's loop takes 0.36 us however many loads are in
-// flight (five stages instead of four change nothing) and the planes are small, so up to four parts wherever they have
-// this many blocks.  Us of the two launches, parts of 32 blocks / of 8 and more: 2048 -> 2048 rank 16 40 tokens 23 / 18, 128 25 / 21,
-// rank 128 64 tokens 29 / 24, 128 34 / 31; 2048 -> 2048, 256, 256 rank 128 111 tokens of one sequence 25 / 21, 128 single 42 / 43;
-// 1024 -> 1416 rank 64 64 24 / 17; twice 2048 -> 5632, which fills the chip with two parts, 40 28 / 28, 64 39 / 38, 128 51 / 54
-// (128 tokens more, rank 64: 62 / 69).
+// flight (five stages instead of four change nothing), so up to four parts wherever they have this many blocks -- as long
+// as the planes, which the expand reads back, are small.  By the projection's own width, not the call's: projections that
+// share a call have the bits of calls of their own.  Us of a call, parts of 32 blocks / of 8 and more: 2048 -> 2048 rank 16 40
+// tokens 19 / 15, 128 20 / 16, rank 128 64 of one sequence 20 / 15, 128 single 30 / 26; 1024 -> 1416 rank 64 64 21 / 15; 2048 -> 5632
+// rank 16 40 22 / 19, 128 26 / 25, rank 128 128 43.5 / 42; 2048 -> 8192 rank 16 40 single 23 / 21, 80 27 / 26; beyond the line
+// 128 of one sequence 23 / 25, 2048 -> 11008 rank 16 64 single 29 / 30, 2048 -> 22016 43 / 48.  What it costs: several wide projections in a call fill the chip
+// with fewer parts, twice 2048 -> 5632 rank 16 40 26.0 / 27.2, rank 128 64 single 59 / 63, 64 of one sequence 25.2 / 25.0, twice 1024 -> 2816
+// rank 64 128 single 30 / 33; in layers of 33 to 128 tokens, ranks 16 to 128, the others outweigh that (0.90 to 0.99 of the
+// time; 64 to 128 single tokens at rank 128 1.01).
 constexpr int DECODE_BASE_SPLIT_BLOCKS_FEW = 8, DECODE_BASE_FEW_MIN = 33, DECODE_BASE_FEW_MAX = 128;
+constexpr int DECODE_BASE_FEW_OUT = 8192, DECODE_BASE_FEW_PLANE = DECODE_BASE_FEW_MAX * 5632;   // outputs; values of a plane
+// Tokens up to which the rule for few takes this many outputs.
+static int64_t few_tokens(int d_out)
+{
+    return d_out > DECODE_BASE_FEW_OUT ? 0 : std::min(DECODE_BASE_FEW_MAX, DECODE_BASE_FEW_PLANE / d_out);
+}
 
 template <class C>
 static void shape_for(int64_t T, int d_in, int d_out, bool may_split, DecodeBaseShape *sh)
@@ -766,7 +776,7 @@ static void shape_for(int64_t T, int d_in, int d_out, bool may_split, DecodeBase
     if (want > DECODE_BASE_MAX_SPLITS) want = DECODE_BASE_MAX_SPLITS;
     // every part costs a plane of fp32 partial sums written and read back: no more
     // parts than it takes to keep a tile's serial loop to about DECODE_BASE_SPLIT_BLOCKS blocks
-    const bool few = T >= DECODE_BASE_FEW_MIN && T <= DECODE_BASE_FEW_MAX;
+    const bool few = T >= DECODE_BASE_FEW_MIN && T <= few_tokens(d_out);
     const int blocks = few ? DECODE_BASE_SPLIT_BLOCKS_FEW : DECODE_BASE_SPLIT_BLOCKS;
     const int by_len = (nkb + blocks - 1) / blocks;
     if (want > by_len) want = by_len;
@@ -812,7 +822,7 @@ int64_t decode_base_rows(int64_t T, int d_in, int d_out)
     auto try_ = [&](int64_t t) {
         if (t > 0 && t < T) most = std::max(most, t * decode_base_splits(t, d_in, d_out));
     };
-    try_(DECODE_BASE_FEW_MAX);
+    try_(few_tokens(d_out));
     for (int parts = 2; parts <= DECODE_BASE_MAX_SPLITS; ++parts) try_((DECODE_BASE_TARGET_WGS - 1) / (parts - 1) / cols * bm);
     return most;
 }
