@@ -17,21 +17,21 @@ constexpr int PLAN_COUNT_S = 128;
 // address outside every segment.)
 template <int PT, int CAP>
 struct PlanLds {
-    // What every sequence has in memory, where there is room for it: read once, on the way in.
     static constexpr bool KEEPS = CAP <= PLAN_CAP_SMALL;
-    alignas(16) unsigned ekey[CAP];   // expert + 1 of each sequence (-1, no adapter, sorts first)
-    int off[KEEPS ? CAP + 1 : 1];     // sequence offsets
-    int rank[KEEPS ? CAP : 1];        // of the sequence's adapter
+    alignas(KEEPS ? 16 : 4) unsigned ekey[CAP];   // expert + 1 of each sequence (-1, no adapter, sorts first)
     int tokbase[CAP];            // per sorted position: tokens before it
     uint16_t idx[2][CAP];        // sequences in sorted order, and the buffer they are sorted through
     int hist[PT / 64][128];      // per wave: digit counts, then cursors
     int sums[3][PT / 64];
     int bad_offsets, any_long;
+    // What every sequence has in memory, where there is room for it: read once, on the way in.  (At the end: two words ahead of
+    // the other arrays cost the large kernel 0.6 us of 8.4.)
+    int off[KEEPS ? CAP + 1 : 1];     // sequence offsets
+    int rank[KEEPS ? CAP : 1];        // of the sequence's adapter
 };
 using PlanLdsSmall = PlanLds<PLAN_THREADS_SMALL, PLAN_CAP_SMALL>;
 using PlanLdsMax = PlanLds<PLAN_THREADS_MAX, PLAN_CAP_MAX>;
 
-// Exclusive prefix sums of N values per thread over the workgroup, and the totals.
 // Barrier for what goes through LDS.  Nothing written to memory is read back, so four waves wait for LDS alone (__syncthreads also
 // waits until every store has arrived); sixteen waves are faster by __syncthreads (1024 sequences: 10.9 us for the kernel, 11.5).
 template <int PT>
@@ -41,6 +41,7 @@ __device__ __forceinline__ void plan_meet()
     else __syncthreads();
 }
 
+// Exclusive prefix sums of N values per thread over the workgroup, and the totals.
 template <int PT, int N>
 __device__ __forceinline__ void plan_scan(int (&v)[N], int (&total)[N], int (*sums)[PT / 64])
 {
@@ -192,17 +193,24 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
     if (COMPARES && S <= PLAN_COUNT_S) {
         static_assert(!COMPARES || (PT >= PLAN_COUNT_S && CAP >= PLAN_COUNT_S && PLAN_COUNT_S % 16 == 0), "a sequence per thread");
         if (tid < S) {
-            // sixteen keys a turn, four per LDS read: one at a time their latency made it 2.1 us for 64 sequences, now 1.2
+            // sixteen keys a turn, four per LDS read: one at a time their latency made it 2.1 us for 64 sequences, now 1.2; of up to
+            // eight sequences four a turn (one sequence: 0.15 us less for the kernel)
             const unsigned me = L.ekey[tid];
             int at = 0;
-            for (int j = 0; j < S; j += 16) {
-                uint4 o[4];
+            auto before_me = [&](const uint4 &o, int j) __attribute__((always_inline)) {   // (key k of the four comes first if it is smaller, or equal and k < d)
+                const int d = tid - j;
+                return (o.x < me + (0 < d)) + (o.y < me + (1 < d)) + (o.z < me + (2 < d)) + (o.w < me + (3 < d));
+            };
+            auto keys = [&](int j) __attribute__((always_inline)) { return *reinterpret_cast<const uint4 *>(&L.ekey[j]); };
+            if (S <= 8) {
+                for (int j = 0; j < S; j += 4) at += before_me(keys(j), j);
+            } else {
+                for (int j = 0; j < S; j += 16) {
+                    uint4 o[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) o[q] = *reinterpret_cast<const uint4 *>(&L.ekey[j + 4 * q]);
+                    for (int q = 0; q < 4; ++q) o[q] = keys(j + 4 * q);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int d = tid - (j + 4 * q);   // key k of the four comes first if it is smaller, or equal and k < d
-                    at += (o[q].x < me + (0 < d)) + (o[q].y < me + (1 < d)) + (o[q].z < me + (2 < d)) + (o[q].w < me + (3 < d));
+                    for (int q = 0; q < 4; ++q) at += before_me(o[q], j + 4 * q);
                 }
             }
             L.idx[1][at] = (uint16_t)tid;
@@ -323,41 +331,57 @@ __device__ __forceinline__ void plan_body(const PlanView &pv, const int *seq_off
     // 4. A group ends where the next one starts.  It is cut into records of at most pv.chunk tokens: the
     // decode kernels hand a record to one column of workgroups, and a hot expert's tokens must not all queue
     // behind one column.
+    const int chunk_bits = __builtin_ctz((unsigned)pv.chunk), chunk_m1 = pv.chunk - 1;   // (a power of two: group_chunk)
     const int gper = (n_groups + PT - 1) / PT;
     const int g0 = min(tid * gper, n_groups), g1 = min(g0 + gper, n_groups);
     int n[1] = {0}, n_rec[1];
     for (int g = g0; g < g1; ++g) {
         const int gs = L.tokbase[head_at[g]], ge = g + 1 < n_groups ? L.tokbase[head_at[g + 1]] : n_tok;
-        n[0] += (ge - gs + pv.chunk - 1) / pv.chunk;
+        n[0] += (ge - gs + chunk_m1) >> chunk_bits;
     }
     plan_scan<PT, 1>(n, n_rec, L.sums);
     int base_only = 0;
-    for (int k = 0; k < gper; ++k) {   // (the same number of turns for the whole wave)
-        const int g = g0 + k;
-        int e = -1, rk = 0, gs = 0, ge = 0;
-        if (g < g1) {
+    // Where groups have more than a few records, those of many are written by the whole wave, unless a wave has many such
+    // groups: by its own thread the 95 of 6000 base-only tokens took 4 us, but a group for each turn of the wave 64 groups of 8
+    // records 8 (600 x 100 tokens: 23.5 us for the kernel, now 15).
+    constexpr int FEW_MORE = 8, OWN = 4, SHARED_GROUPS = 8, OWN_MOST = 64;
+    if (n_rec[0] - n_groups <= FEW_MORE) {
+        for (int g = g0; g < g1; ++g) {
             const int p = head_at[g], s = order[p];
-            gs = L.tokbase[p];
-            ge = g + 1 < n_groups ? L.tokbase[head_at[g + 1]] : n_tok;
-            e = (int)L.ekey[s] - 1;
-            if (e >= 0) rk = rank_of(s, e);   // (a sequence of rank 0 has become one without an adapter)
+            const int gs = L.tokbase[p], ge = g + 1 < n_groups ? L.tokbase[head_at[g + 1]] : n_tok;
+            const int e = (int)L.ekey[s] - 1;
+            const int rk = e >= 0 ? rank_of(s, e) : 0;   // (a sequence of rank 0 has become one without an adapter)
+            for (int t = gs; t < ge && n[0] < pv.max_groups; t += pv.chunk, ++n[0])
+                pv.grp_meta[n[0]] = make_int4(e, t, min(t + pv.chunk, ge), rk);
+            if (e < 0) base_only = n[0];   // (the first group, if any)
         }
-        // A group of many records is written by the whole wave: by its own thread the 95 of 6000 base-only tokens took 4 us.
-        const int recs = (ge - gs + pv.chunk - 1) / pv.chunk, first = n[0];
-        constexpr int OWN = 4;
-        if (recs <= OWN)
-            for (int j = 0; j < recs && first + j < pv.max_groups; ++j)
-                pv.grp_meta[first + j] = make_int4(e, gs + j * pv.chunk, min(gs + (j + 1) * pv.chunk, ge), rk);
-        for (uint64_t left = __ballot(recs > OWN); left != 0; left &= left - 1) {
-            const int q = __builtin_ctzll(left);
-            const int qe = __builtin_amdgcn_readlane(e, q), qrk = __builtin_amdgcn_readlane(rk, q);
-            const int qs = __builtin_amdgcn_readlane(gs, q), qend = __builtin_amdgcn_readlane(ge, q);
-            const int qfirst = __builtin_amdgcn_readlane(first, q), qn = __builtin_amdgcn_readlane(recs, q);
-            for (int j = lane; j < qn && qfirst + j < pv.max_groups; j += 64)
-                pv.grp_meta[qfirst + j] = make_int4(qe, qs + j * pv.chunk, min(qs + (j + 1) * pv.chunk, qend), qrk);
+    } else {
+        for (int k = 0; k < gper; ++k) {   // (the same number of turns for the whole wave)
+            const int g = g0 + k;
+            int e = -1, rk = 0, gs = 0, ge = 0;
+            if (g < g1) {
+                const int p = head_at[g], s = order[p];
+                gs = L.tokbase[p];
+                ge = g + 1 < n_groups ? L.tokbase[head_at[g + 1]] : n_tok;
+                e = (int)L.ekey[s] - 1;
+                if (e >= 0) rk = rank_of(s, e);
+            }
+            const int recs = (ge - gs + chunk_m1) >> chunk_bits, first = n[0];
+            const int own = __popcll(__ballot(recs > OWN)) <= SHARED_GROUPS ? OWN : OWN_MOST;
+            if (recs <= own)
+                for (int j = 0; j < recs && first + j < pv.max_groups; ++j)
+                    pv.grp_meta[first + j] = make_int4(e, gs + (j << chunk_bits), min(gs + ((j + 1) << chunk_bits), ge), rk);
+            for (uint64_t left = __ballot(recs > own); left != 0; left &= left - 1) {
+                const int q = __builtin_ctzll(left);
+                const int qe = __builtin_amdgcn_readlane(e, q), qrk = __builtin_amdgcn_readlane(rk, q);
+                const int qs = __builtin_amdgcn_readlane(gs, q), qend = __builtin_amdgcn_readlane(ge, q);
+                const int qfirst = __builtin_amdgcn_readlane(first, q), qn = __builtin_amdgcn_readlane(recs, q);
+                for (int j = lane; j < qn && qfirst + j < pv.max_groups; j += 64)
+                    pv.grp_meta[qfirst + j] = make_int4(qe, qs + (j << chunk_bits), min(qs + ((j + 1) << chunk_bits), qend), qrk);
+            }
+            n[0] = min(first + recs, max(first, pv.max_groups));
+            if (g < g1 && e < 0) base_only = n[0];
         }
-        n[0] = min(first + recs, max(first, pv.max_groups));
-        if (g < g1 && e < 0) base_only = n[0];   // (the first group, if any)
     }
     const int n_out = min(n_rec[0], pv.max_groups);
     if (tid == 0) {

@@ -6,7 +6,9 @@ import pytest
 import torch
 
 from paper_2410_09687_amd import moin
+from paper_2410_09687_amd import workloads as wl
 from tests import gpu_common as gc
+from tests.test_gpu_decode_stream import _check, _reference
 from tests.test_gpu_plan_sizes import _run
 
 pytestmark = pytest.mark.gpu
@@ -53,3 +55,25 @@ def test_behind_the_routing(S):
         ref[at] += 2.0 * (x[at].double() @ A[e, :k].double().T) @ B[e, :, :k].double().T
     # sums of 128 + 16 products in fp32 and u as a bf16 pair: 2e-5 of the largest output holds
     assert float((ys[0].double() - ref).abs().max()) <= 2e-5 * float(ref.abs().max())
+
+
+# Tokens per expert, cut into records of 16 (up to 1024 tokens) or 128 (beyond 16 384): eight and nine records more than groups;
+# eight and nine groups of five; more than eight groups, one of 64 and one of 65; lengths of a sequence.
+@pytest.mark.parametrize("groups,length", [([144, 1, 1], 9), ([145, 1, 1], 9), ([80] * 8, 5), ([80] * 9, 5), ([16] * 8 + [33], 1), ([7], 1),
+                                           ([8192] * 9 + [8193], 48), ([8192, 8193, 600], 30), ([70] * 12, 1)])
+def test_records_of_few_and_many_groups(groups, length):
+    lens, ids = [], []
+    for e, n in enumerate(groups):
+        cut = [length] * (n // length) + ([n % length] if n % length else [])
+        lens += cut
+        ids += [e - 1] * len(cut)          # (the first group without an adapter)
+    at = np.random.default_rng(len(lens)).permutation(len(lens))
+    lens, ids = [lens[i] for i in at], np.array(ids, dtype=np.int32)[at]
+    d_in, r, E = 128, 16, len(groups)
+    inp = wl.make_linear_inputs(wl.LinearWorkload("records", d_in, 72, r, E, lens, "uniform", scale=2.0, seed=len(lens)), "cuda",
+                                expert_ids=ids)
+    print(f"[gpu] records of {len(groups)} groups, S={len(lens)} T={sum(lens)}", flush=True)
+    y = moin.moin_lora_linear(gc.ctx(), inp.x, inp.seq_offsets, inp.expert_ids, inp.W, inp.A_stack, inp.B_stack, 2.0,
+                              y_dtype=torch.float32)
+    gc.ctx().check()
+    _check(y, _reference(inp, ids, lens, None, r), d_in, r)
