@@ -405,7 +405,9 @@ static int plan_prepare(moin_plan *plan, const int32_t *seq_offsets, const int32
     }
     if (!seq_offsets || !expert_ids) return MOIN_EINVAL;
     const PlanLayout L = plan_layout(S, T, E);
-    const int grc = plan_grow(plan, L.total, stream);
+    // (an eager call's buffer holds the plan of any smaller batch as well, which may have more records or the other grouping)
+    const bool grows = L.total > plan->bytes && !capturing(stream);
+    const int grc = plan_grow(plan, grows ? plan_layout(S, T, E, true).total : L.total, stream);
     if (grc != MOIN_OK) return grc;
     char *b = static_cast<char *>(plan->buf);
     PlanView &pv = plan->pv;

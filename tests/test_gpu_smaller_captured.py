@@ -69,3 +69,34 @@ def test_captured_after_the_largest_eager_call(first, then, d_in, d_out, r, kind
     finally:
         torch.cuda.synchronize()
         ctx.close()
+
+
+@pytest.mark.parametrize("first,then", [([68] * 16 + [12], [62] * 16), ([300] * 4, [100] * 4), ([9000], [128]), ([1] * 4100, [1] * 4096),
+                                        ([2048, 2048, 300], [1023, 1])])
+def test_smaller_batches_are_grouped_under_capture(first, then):
+    ctx, other = moin.Context(0), gc.ctx()
+    try:
+        plan = moin.Plan(ctx)
+        inp, _, _ = _batch(first, 128, 72, 16, False)
+        plan.build(inp.seq_offsets, inp.expert_ids, sum(first), E)
+        _call(ctx, "plain", plan, inp)
+        inp, _, _ = _batch(then, 128, 72, 16, False)
+        eager = _call(other, "plain", moin.Plan(other).build(inp.seq_offsets, inp.expert_ids, sum(then), E), inp)[0]
+        out = torch.empty_like(eager)
+        print(f"[gpu] captured grouping of {len(then)} sequences, {sum(then)} tokens after {sum(first)}", flush=True)
+        ctx.check()
+        other.check()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            plan.build(inp.seq_offsets, inp.expert_ids, sum(then), E)
+            _call(ctx, "plain", plan, inp, [out])
+        for _ in range(2):
+            out.fill_(float("nan"))
+            graph.replay()
+            ctx.check()
+            assert torch.equal(out.view(torch.int16), eager.view(torch.int16))
+        del graph
+        plan.close()
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
