@@ -62,8 +62,7 @@ def test_both_sides_of_each_line(lens, d_in, r, tiles):
     one = moin.moin_lora_linear_planned(ctx, plan, inp.x, W2, A2, B2, 2.0, y_dtype=torch.float32)
     base = moin.moin_lora_linear_planned(ctx, plan, inp.x, inp.W, None, None, 2.0, y_dtype=torch.float32)
     ctx.check()
-    if tiles:   # (the decode path's sums also go by the call's projections)
-        assert torch.equal(two[0], y) and torch.equal(two[1], one)
+    assert torch.equal(two[0], y) and torch.equal(two[1], one)
     _check(two[1], y[:, :72].double(), d_in, r)
     _check(base, inp.x.double() @ inp.W.double().T, d_in, r)
     plan.close()
