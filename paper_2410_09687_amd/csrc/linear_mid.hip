@@ -126,7 +126,7 @@ __device__ __forceinline__ void mid_tile(const stream::Params &p)
 
     const int total = t.total;
     constexpr int M = FP * FQ, R = FP + FQ;
-    static_assert(M >= 2 * R || M >= R, "a gap for every read and every request, or for the two together");
+    static_assert(M >= R, "a gap for every read and every request, or for the two together");
     constexpr int GAP = M >= 2 * R ? 2 : 1;   // MFMAs per read (and request) of the second k-step
     // One block: k-step 0 with the reads of k-step 1, the barrier, k-step 1 with the reads of the next block's k-step 0
     // and (MORE) the requests of the block NS ahead into the stage that is now free.

@@ -67,6 +67,8 @@ def load() -> ctypes.CDLL:
                 f"{path} not found: build it with `python -m paper_2410_09687_amd.build`; "
                 "there is no fallback path")
     lib = ctypes.CDLL(LIB_PATH)
+    # (of every entry point, also those that this module calls natively: for programs that call the library through load(),
+    # whose pointers ctypes would pass as 32 bits otherwise)
     c = ctypes
     vp, i32, i64, u32 = c.c_void_p, c.c_int32, c.c_int64, c.c_uint32
     lib.moin_create.argtypes = [c.POINTER(vp), c.c_int]
