@@ -813,9 +813,14 @@ static bool use_mid_route(const RouteArgs &a)
     return ((a.N + M::BN - 1) / M::BN) * ((a.K + M::BM - 1) / M::BM) >= ROUTE_MID_MIN_TILES;
 }
 
+// Where a workgroup sums them once and the sums are short: its waits for a block's squares let no load of the next blocks
+// stay in flight, and each query tile sums them again.  Us a call, a launch ahead / here: 256 tiles of 768 dimensions (1000 x 1000) 14.5 /
+// 13.4, 376 (3000 x 500) of 384 21.7 / 21.7, of 768 25.4 / 28.0, of 1024 28.7 / 32.9, 316 (200 x 5000) of 1024 26.6 / 29.7.
 bool route_computes_norms(const RouteArgs &a)
 {
-    return use_small_route(a) && a.D % 64 == 0 && a.self_clean && !use_mid_route(a);
+    using S = CfgRouteSmall;
+    return use_small_route(a) && a.D % 64 == 0 && a.self_clean && !use_mid_route(a) &&
+           (a.D <= 384 || ((a.N + S::BN - 1) / S::BN) * ((a.K + S::BM - 1) / S::BM) <= compute_units());
 }
 
 static bool use_stream_route(const RouteArgs &a) { return a.is_bf16 && a.D % 64 == 0 && !use_small_route(a); }

@@ -88,3 +88,8 @@ def test_the_norms_to_the_last_bit(K, D, N, large):
         slot[int(k)] = -1
     ctx.check()
     assert got[0] == got[1] == got[2] == want.tolist()
+
+
+@pytest.mark.parametrize("N,K,D", [(1024, 1024, 448), (1025, 1024, 448), (1025, 1024, 384)])
+def test_either_side_of_the_line_for_long_sums(N, K, D):   # a tile per compute unit, more, more of short sums
+    test_same_ids_and_norms(N, K, D, True)
