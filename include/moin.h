@@ -234,11 +234,14 @@ int moin_route_plan(moin_ctx *ctx, moin_plan *plan, const void *emb, const void 
  * none) grow on demand (hipMalloc), which a stream under capture must not do.  A call
  * on a capturing stream that would have to grow any of them returns MOIN_ECAPTURE and
  * records nothing: make the first call with the largest shapes outside the capture, or
- * reserve beforehand.  An eager grouping or linear call sizes the plan's buffer or the
- * workspace for every batch of at most its sequences, tokens and experts (through the
- * same projections), also where a smaller one takes the other path or is cut into more
- * parts and needs more than itself; where memory does not reach for the workspace of
- * those, it has what the call needs itself.  What a captured call has used is kept until moin_destroy /
+ * reserve beforehand.  An eager grouping sizes the plan's buffer for every batch of at
+ * most its sequences, tokens and experts.  An eager linear call sizes the workspace for
+ * every batch of at most its sequences and tokens through the same projections, also
+ * where a smaller one takes the other path or is cut into more parts and needs more --
+ * but those of up to 1024 tokens, or up to 128 per sequence on average, only if it is
+ * such a batch itself; a prefill of long sequences does not prepare decode batches.
+ * Where memory does not reach for smaller batches, it has what the call needs itself.
+ * What a captured call has used is kept until moin_destroy /
  * moin_plan_destroy even when a later, larger call replaces it, so replays of the
  * graph keep reading valid memory (results of a replay are then only defined if
  * no other call on the context runs concurrently, as for eager calls).

@@ -55,7 +55,7 @@ struct moin_ctx {
     int *err_word;
     void *ws;
     size_t ws_bytes;
-    size_t ws_refused;              // ensure_ws_smaller: there was no memory for this much
+    size_t ws_refused;              // ensure_ws: there was no memory to keep this much
     int ws_pinned;                  // a captured graph may hold ws's address (see moin_plan::pinned)
     std::vector<void *> ws_retired;
     // small routing batches: centroid norms, packed minima and the arrival counter in a block of their
@@ -129,16 +129,31 @@ bool capturing(hipStream_t st)
 // workspace holds fails with MOIN_ECAPTURE and records nothing.  A workspace that a
 // captured call has used is never freed before moin_destroy -- a graph replays with
 // the addresses it recorded -- so growing it later keeps the old block aside.
-int ensure_ws(moin_ctx *ctx, size_t bytes, hipStream_t st, bool exact = false)
+// An eager call may ask for `keep` as well, which smaller batches than its own need (they take the other grouping, or their base
+// product more parts), so that the largest batch prepares captured calls of smaller ones.  Without memory for that the
+// call has what it needs itself, and calls of its size do not ask again until the workspace has grown otherwise.
+int ensure_ws(moin_ctx *ctx, size_t bytes, hipStream_t st, bool exact = false, size_t keep = 0)
 {
     const bool cap = capturing(st);
-    if (bytes > ctx->ws_bytes) {
+    const bool keeps = !cap && keep > ctx->ws_bytes && keep < ctx->ws_refused;
+    if (bytes > ctx->ws_bytes || keeps) {
         if (cap) return MOIN_ECAPTURE;
-        const size_t want = exact ? align_up(bytes, 256) : align_up(bytes + bytes / 4, 1 << 20);
+        const size_t own = exact ? align_up(bytes, 256) : align_up(bytes + bytes / 4, 1 << 20);
+        // (a bound needs little room to grow; blocks of 64 MB and more take 0.2 ms to free)
+        size_t want = keeps ? std::max(own, align_up(keep + keep / 16, 1 << 20)) : own;
         void *p = nullptr;
         if (hipMalloc(&p, want) != hipSuccess) {
             (void)hipGetLastError();
-            return MOIN_ENOMEM;
+            if (keeps) ctx->ws_refused = keep;
+            if (bytes <= ctx->ws_bytes) return MOIN_OK;   // (it was for keep alone)
+            if (want == own) return MOIN_ENOMEM;
+            want = own;
+            if (hipMalloc(&p, want) != hipSuccess) {
+                (void)hipGetLastError();
+                return MOIN_ENOMEM;
+            }
+        } else {
+            ctx->ws_refused = SIZE_MAX;
         }
         if (ctx->ws) {
             if (ctx->ws_pinned) {
@@ -151,24 +166,9 @@ int ensure_ws(moin_ctx *ctx, size_t bytes, hipStream_t st, bool exact = false)
         ctx->ws = p;
         ctx->ws_bytes = want;
         ctx->ws_pinned = 0;
-        ctx->ws_refused = SIZE_MAX;
     }
     if (cap && bytes > 0) ctx->ws_pinned = 1;
     return MOIN_OK;
-}
-
-// The same for a call that needs `bytes` where a smaller batch may need more, up to `keep` (it takes the other grouping, or
-// its base product more parts): an eager call then sizes the workspace for both, so that the largest batch prepares
-// captured calls of all smaller ones.  Without memory for that the call has what it needs itself, and calls of its size do
-// not ask again until the workspace has grown otherwise.
-int ensure_ws_smaller(moin_ctx *ctx, size_t bytes, size_t keep, hipStream_t st)
-{
-    if (keep > bytes && keep > ctx->ws_bytes && keep < ctx->ws_refused && !capturing(st)) {
-        const int rc = ensure_ws(ctx, keep, st);
-        if (rc != MOIN_ENOMEM) return rc;
-        ctx->ws_refused = keep;
-    }
-    return ensure_ws(ctx, bytes, st);
 }
 
 hipEvent_t take_event(moin_ctx *ctx)
@@ -323,12 +323,6 @@ bool gathered_pays_mx(const PlanView &pv, int d_in, int d_out, int r)
     return d_in >= 2048 && host_tiles(pv, 128) * ((d_out + 127) / 128) <= 16 && pv.T < (rank == RANK_HIGH ? 528 : 704);
 }
 
-// Tokens of the largest batch of up to the plan's sequences and tokens that is gathered.
-int64_t gathered_tokens(const PlanView &pv)
-{
-    return std::min(pv.T, std::max<int64_t>(DECODE_MAX_T, (int64_t)GATHER_MAX_AVG_LEN * pv.S));
-}
-
 // Whether the base product of a gathered batch of more than DECODE_MAX_T tokens is cut into parts nevertheless (below): the
 // rows of up to this many tokens, 0 for none.
 int64_t large_parts_tokens(int d_in, int d_out)
@@ -339,7 +333,9 @@ int64_t large_parts_tokens(int d_in, int d_out)
 }
 
 // What a call of n projections asks of the workspace for the batch, of those of up to the plan's sequences and tokens, that
-// asks for the most.
+// asks for the most; gathered ones only where the plan's batch could be gathered itself.  (Planes are as large as two
+// outputs: kept for after every prefill as well, they made the first call of 64 x 512 tokens 2048 -> 2048 60 us longer, a layer's on an
+// MXFP8 base 250.)
 size_t linear_ws_most(const PlanView &pv, int n, int d_in, const int32_t *d_out, int r)
 {
     auto bytes = [&](int64_t tokens, int64_t rows, int i) {
@@ -348,8 +344,9 @@ size_t linear_ws_most(const PlanView &pv, int n, int d_in, const int32_t *d_out,
     LinearArgs a;
     a.d_in = d_in;
     a.r = r;
-    const int64_t T = gathered_tokens(pv), few = std::min<int64_t>(T, DECODE_MAX_T);
-    const size_t tiled = (size_t)n * 2 * align_up((size_t)pv.T * (size_t)prefill_ldu(a) * 2, 256);
+    const int64_t T = pv.T, few = std::min<int64_t>(T, DECODE_MAX_T);
+    const size_t tiled = (size_t)n * 2 * align_up((size_t)T * (size_t)prefill_ldu(a) * 2, 256);
+    if (!pv.decode) return tiled;
     size_t small = 0, large = 0;   // side by side up to DECODE_MAX_T tokens, one projection after the other beyond
     for (int i = 0; i < n; ++i) {
         small += bytes(few, decode_base_rows(few, d_in, d_out[i]), i);
@@ -493,7 +490,7 @@ int linear_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, con
     const size_t u_bytes = align_up((size_t)pv.T * (size_t)a.ldu * 2, 256);
     if (!gathered) {
         if (a.r > 0) {
-            const int rc = ensure_ws_smaller(ctx, 2 * u_bytes, linear_ws_most(pv, 1, d_in, &d_out, r), stream);
+            const int rc = ensure_ws(ctx, 2 * u_bytes, stream, false, linear_ws_most(pv, 1, d_in, &d_out, r));
             if (rc != MOIN_OK) return rc;
             a.u_hi = ctx->ws;
             a.u_lo = static_cast<char *>(ctx->ws) + u_bytes;
@@ -534,7 +531,7 @@ int linear_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, con
     d.lin = a;
     d.k_splits = big ? 1 : decode_base_splits(pv.T, d_in, d_out);
     const size_t yb_bytes = align_up((size_t)d.k_splits * (size_t)pv.T * (size_t)d_out * 4, 256);
-    const int rc = ensure_ws_smaller(ctx, 2 * u_bytes + yb_bytes, linear_ws_most(pv, 1, d_in, &d_out, r), stream);
+    const int rc = ensure_ws(ctx, 2 * u_bytes + yb_bytes, stream, false, linear_ws_most(pv, 1, d_in, &d_out, r));
     if (rc != MOIN_OK) return rc;
     char *w = static_cast<char *>(ctx->ws);
     d.ug_hi = w;
@@ -607,8 +604,8 @@ int linear_mx_planned_impl(moin_ctx *ctx, const moin_plan *plan, const void *x, 
         m.plain_kb_per_split = d_in / 128;
     }
     const size_t head_bytes = 2 * u_bytes + xq_bytes + xs_bytes;
-    const size_t yb_most = a.r > 0 ? align_up((size_t)mx_plain_rows(gathered_tokens(pv), d_in, d_out) * (size_t)d_out * 4, 256) : 0;
-    const int rc = ensure_ws_smaller(ctx, head_bytes + yb_bytes, head_bytes + yb_most, stream);
+    const size_t yb_most = pv.decode && a.r > 0 ? align_up((size_t)mx_plain_rows(pv.T, d_in, d_out) * (size_t)d_out * 4, 256) : 0;
+    const int rc = ensure_ws(ctx, head_bytes + yb_bytes, stream, false, head_bytes + yb_most);
     if (rc != MOIN_OK) return rc;
     char *w = static_cast<char *>(ctx->ws);
     a.u_hi = w;
@@ -1165,7 +1162,7 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
             total += 2 * u_bytes + align_up((size_t)d[i].k_splits * (size_t)pv.T * (size_t)d_out[i] * 4, 256);
         }
         if (decode_shared_fits(pv, d, n)) {
-            const int rc = ensure_ws_smaller(ctx, total, most, st);
+            const int rc = ensure_ws(ctx, total, st, false, most);
             if (rc != MOIN_OK) return rc;
             for (int i = 0; i < n; ++i) {
                 char *w = static_cast<char *>(ctx->ws) + off[i];
@@ -1184,7 +1181,7 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
     }
     if (gathered || !adapters || n == 1) {
         // nothing to share on these paths: the projections one after the other
-        const int wrc = ensure_ws_smaller(ctx, 0, most, st);
+        const int wrc = ensure_ws(ctx, 0, st, false, most);
         if (wrc != MOIN_OK) return wrc;
         for (int i = 0; i < n; ++i) {
             const int rc = linear_planned_impl(ctx, plan, x, W[i], adapters ? A_stack[i] : nullptr,
@@ -1201,7 +1198,7 @@ int moin_lora_linear_planned_shared(moin_ctx *ctx, const moin_plan *plan, const 
     a.d_in = d_in; a.d_out = 0; a.r = r; a.scale = scale; a.act = ctx->act;
     a.ldu = prefill_ldu(a);
     const size_t u_bytes = align_up((size_t)pv.T * (size_t)a.ldu * 2, 256);
-    const int rc = ensure_ws_smaller(ctx, (size_t)n * 2 * u_bytes, most, st);
+    const int rc = ensure_ws(ctx, (size_t)n * 2 * u_bytes, st, false, most);
     if (rc != MOIN_OK) return rc;
     void *u_hi[MAX_SHARED_X], *u_lo[MAX_SHARED_X];
     for (int i = 0; i < n; ++i) {

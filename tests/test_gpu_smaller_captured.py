@@ -1,4 +1,4 @@
-"""An eager call with the largest batch prepares the captured calls of all batches of no more sequences and tokens: those that
+"""An eager call with the largest batch prepares the captured calls of batches of no more sequences and tokens: those that
 take the other grouping, whose base product is cut into more parts, or whose projections share their launches."""
 import pytest
 import torch
@@ -22,8 +22,9 @@ def _call(ctx, kind, plan, inp, outs=None):
 
 @pytest.mark.parametrize("first,then,d_in,d_out,r", [
     ([1] * 1100, [1] * 1000, 5632, 2048, 128),     # plain row tiles / four parts
-    ([300] * 4, [100] * 4, 2048, 2048, 16),        # not gathered at all / gathered
-    ([1100], [300], 2048, 2048, 64),
+    ([128] * 9, [330], 2048, 2048, 16),            # row tiles or gathered by the call
+    ([500, 524], [300], 2048, 2048, 64),
+    ([1100, 900], [700, 500], 2048, 264, 64),      # row tiles both
     ([897], [896], 4096, 4096, 16),                # two parts / three
     ([1] * 1024, [1] * 896, 2048, 8192, 64),       # one part / two
     ([1] * 9000, [1] * 8000, 1000, 256, 32),       # whole / parts of rows that are not whole blocks
@@ -79,7 +80,7 @@ def test_smaller_batches_are_grouped_under_capture(first, then):
         plan = moin.Plan(ctx)
         inp, _, _ = _batch(first, 128, 72, 16, False)
         plan.build(inp.seq_offsets, inp.expert_ids, sum(first), E)
-        _call(ctx, "plain", plan, inp)
+        ctx.reserve_workspace(8 << 20)
         inp, _, _ = _batch(then, 128, 72, 16, False)
         eager = _call(other, "plain", moin.Plan(other).build(inp.seq_offsets, inp.expert_ids, sum(then), E), inp)[0]
         out = torch.empty_like(eager)
