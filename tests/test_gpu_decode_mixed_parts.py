@@ -1,4 +1,4 @@
-"""Calls of 33 to 128 tokens whose projections' base products are cut into different numbers of parts: two launches, the bits of
+"""Calls of up to 128 tokens whose projections' base products are cut into different numbers of parts: two launches, the bits of
 single calls; widths on both sides of the rule for few tokens, ranks in every form of the expand, own ranks, base-only
 sequences; against torch in fp64."""
 import numpy as np
@@ -17,7 +17,7 @@ E = 6
     (33, 2048, (8200, 264), 16, False), (88, 2048, (8192, 1024, 1024), 64, True), (89, 2048, (8192, 1024, 1024), 128, False),
     (80, 2048, (2048, 8208), 40, True), (128, 2048, (72, 8200, 2048, 8), 128, True), (128, 1024, (8208, 264), 136, False),
     (64, 1088, (264, 8264), 24, False), (100, 2112, (8264, 16), 200, True), (128, 512, (264, 8456), 32, False),
-    (129, 2048, (8192, 1024), 64, False)])
+    (129, 2048, (8192, 1024), 64, False), (20, 4224, (22016, 264), 32, True)])
 def test_projections_of_different_parts_share_their_launches(T, d_in, d_outs, r, ranked):
     lens = [T // 3, 1, T - T // 3 - 12, 4, 7]
     ids = np.array([1, -1, 3, 0, 1], dtype=np.int32)
